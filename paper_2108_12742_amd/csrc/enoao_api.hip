@@ -86,6 +86,13 @@ inline double *member_buffer(double *m, size_t cells, int i) { return m + (size_
 // below nx = ny = 512 or 624).  Caller-owned states (plans, batches) keep pitch nx.
 inline int padded_pitch(int nx) { return (nx + 15) / 16 * 16; }
 
+// most bytes of a member's list of row segments (2D)
+size_t fix_list_bytes(const enoao_problem *p)
+{
+    const size_t c = strip_cells(p->order);
+    return p->equation == EULER2D ? (p->nx + c - 1) / c * p->ny * fix_places(p->nx) * FIX_ENTRY_BYTES : 0;
+}
+
 // device bytes of one member: w1, w2 (+ Lx for 2D) and the selection record
 size_t member_bytes(const enoao_problem *p)
 {
@@ -97,7 +104,7 @@ size_t member_bytes(const enoao_problem *p)
     return b;
 }
 
-size_t member_fixed_bytes() { return sizeof(Inst) + sizeof(Ctrl) + AMAX_SLOTS * AMAX_VALS * 8 + 256; }
+size_t member_fixed_bytes() { return sizeof(Inst) + sizeof(Ctrl) + AMAX_SLOTS * amax_slot_words(EULER2D) * 8 + 256; }
 
 #define HIP_TRY(x)                                    \
     do {                                              \
@@ -124,6 +131,8 @@ struct Runtime {
     Inst *d_inst = nullptr;
     Ctrl *d_ctrl = nullptr;
     unsigned long long *d_amax = nullptr;
+    unsigned *d_fix_count = nullptr;           // 2D: list counters (FIX_SETS sets)
+    unsigned long long *d_fix_list = nullptr;  // 2D: lists of row segments that need a selection
     int *d_res_order = nullptr;  // LDS-resident launches: members by decreasing size
     Ctrl *h_ctrl = nullptr;    // pinned mirror
     // captured step graphs (k steps of control + stages), one per step count k
@@ -132,14 +141,14 @@ struct Runtime {
     // one event per stream the object's work was enqueued on: destroy waits for
     // them instead of the whole device
     std::vector<std::pair<hipStream_t, hipEvent_t>> marks;
-    int grid_x[4] = {0, 0, 0, 0}, grid_y[4] = {0, 0, 0, 0}, grid_m = 0;
+    int grid_x[4] = {0, 0, 0, 0}, grid_2d[4] = {0, 0, 0, 0}, grid_fix = 0, grid_m = 0;
     // pools: the fewest workgroups that share a tile list (the kernel's occupancy)
-    int gmin_x[4] = {0, 0, 0, 0}, gmin_y[4] = {0, 0, 0, 0}, gmin_m = 0;
+    int gmin_x[4] = {0, 0, 0, 0}, gmin_m = 0;
     int wg_per_cu = 0;  // resident workgroups per CU of the persistent sweeps (0: occupancy)
     // per kernel kind (x-sweep stages 1..3, y-sweep stages 1..3): workgroups per
     // CU of that launch (0: wg_per_cu)
     int wg_kind[6] = {0, 0, 0, 0, 0, 0};
-    int yw = 8;  // columns per wave strip of the y-sweep tiles (4 or 8); set from the order at creation
+    bool short_units = false;  // 2D: half as many rows per unit (enoao_plan_set_tiles with 4)
     // every member 1D and small enough for the LDS-resident solver; controlled
     // steps then run there, one launch per LDS size class (below)
     bool resident = false;
@@ -216,6 +225,8 @@ struct Runtime {
         if (failed) (void)hipGetLastError();  // a pair without a reading is skipped, not left as an error
     }
 
+    size_t amax_words() const { return (size_t)AMAX_SLOTS * amax_slot_words(eq); }  // per member
+
     KParams params(int r_in, int r_out, int r_zero, int sel_slot = 0) const
     {
         KParams p{};
@@ -230,6 +241,10 @@ struct Runtime {
         p.r_zero = r_zero;
         p.flags = kflags;
         p.res_order = d_res_order;
+        if (n_cap == 1 && !dynamic) {
+            p.lone_ctrl = d_ctrl;
+            p.lone_amax = d_amax;
+        }
         return p;
     }
 
@@ -268,7 +283,6 @@ struct Runtime {
         }
         eq = ps[0].equation;
         order = ps[0].order;
-        yw = yw_default(order);
         nc = ncomp_of(eq);
         n = count;
         n_cap = count;
@@ -290,9 +304,13 @@ struct Runtime {
         const size_t o_hdr = take(sizeof(BatchHdr));
         const size_t o_inst = take(sizeof(Inst) * count);
         const size_t o_ctrl = take(sizeof(Ctrl) * count);
-        const size_t o_amax = take(8ull * AMAX_SLOTS * AMAX_VALS * count);
+        const size_t o_amax = take(8ull * amax_words() * count);
         const size_t o_order = take(sizeof(int) * count);
         const size_t o_bar = take(2 * sizeof(unsigned));
+        const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * sizeof(unsigned));
+        size_t fix_bytes = 0;
+        for (int i = 0; i < count; ++i) fix_bytes += fix_list_bytes(&ps[i]);
+        const size_t o_fix = take(fix_bytes);
         std::vector<size_t> o_mem(count);
         for (int i = 0; i < count; ++i) o_mem[i] = take(member_bytes(&ps[i]));
         if (hipMalloc(&d_block, off) != hipSuccess) {
@@ -306,24 +324,30 @@ struct Runtime {
         d_amax = (unsigned long long *)(base + o_amax);
         d_res_order = (int *)(base + o_order);
         d_bar = (unsigned *)(base + o_bar);
+        if (eq == EULER2D) {
+            d_fix_count = (unsigned *)(base + o_fixc);
+            d_fix_list = (unsigned long long *)(base + o_fix);
+        }
         if (hipHostMalloc((void **)&h_ctrl, sizeof(Ctrl) * count, hipHostMallocDefault) != hipSuccess) {
             h_ctrl = nullptr;
             return ENOAO_ENOMEM;
         }
 
         h_inst.resize(count);
-        long long xt = 0, yt = 0;
+        wg_per_cu = g_wg_per_cu;
+        choose_rows(ps, count);
+        long long xt = 0, ut = 0;
         for (int i = 0; i < count; ++i) {
             double *m = (double *)(base + o_mem[i]);
             const size_t cells = (size_t)nc * ps[i].nx * ps[i].ny;
             fill_inst(h_inst[i], ps[i], nullptr, member_buffer(m, cells, 0), member_buffer(m, cells, 1),
                       eq == EULER2D ? member_buffer(m, cells, 2) : nullptr,
                       rec ? (uint8_t *)member_buffer(m, cells, eq == EULER2D ? 3 : 2) : nullptr,
-                      d_amax + (size_t)i * AMAX_SLOTS * AMAX_VALS, d_ctrl + i, xt, yt);
+                      d_amax + (size_t)i * amax_words(), d_ctrl + i, xt, ut);
         }
         h_hdr.n_inst = count;
         h_hdr.xtiles_total = xt;
-        h_hdr.ytiles_total = yt;
+        h_hdr.units_total = ut;
         HIP_TRY(hipMemcpyAsync(d_hdr, &h_hdr, sizeof(BatchHdr), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipMemcpyAsync(d_inst, h_inst.data(), sizeof(Inst) * count, hipMemcpyHostToDevice, stream));
         std::vector<Ctrl> c0(count);
@@ -346,7 +370,6 @@ struct Runtime {
         HIP_TRY(hipMemcpyAsync(d_res_order, order_h.data(), sizeof(int) * count, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
 
-        wg_per_cu = g_wg_per_cu;
         set_grids();
         if (eq != EULER2D && !rec) {
             if (enoao_status e = plan_resident(ps, order_h)) return e;
@@ -443,7 +466,7 @@ struct Runtime {
 
     // descriptor of one member; advances the running tile offsets
     void fill_inst(Inst &I, const enoao_problem &p, double *u, double *w1, double *w2, double *lx, uint8_t *sel,
-                   unsigned long long *amax, Ctrl *ctrl, long long &xt, long long &yt, int pitch = 0) const
+                   unsigned long long *amax, Ctrl *ctrl, long long &xt, long long &ut, int pitch = 0)
     {
         std::memset(&I, 0, sizeof(I));
         I.u = u;
@@ -462,28 +485,77 @@ struct Runtime {
         I.dy = eq == EULER2D ? (p.y_hi - p.y_lo) / p.ny : 1.0;
         I.adv = p.adv_speed;
         I.segs_per_row = (p.nx + XW_CELLS - 1) / XW_CELLS;
-        I.ytiles_per_row = (p.ny + yt_cells(yw) - 1) / yt_cells(yw);
-        I.ycol_groups = (p.nx + yt_cols(yw) - 1) / yt_cols(yw);
         I.xtile0 = xt;
         I.xtiles = ((long long)p.ny * I.segs_per_row + XW_SEGS - 1) / XW_SEGS;
-        I.ytile0 = yt;
-        I.ytiles = eq == EULER2D ? (long long)I.ytiles_per_row * I.ycol_groups : 0;
         xt += I.xtiles;
-        yt += I.ytiles;
+        set_units(I, ut);
+    }
+
+    // 2D: the member's units of `rows` rows of a strip each
+    long long list_places = 0;  // of the members set so far
+    void set_units(Inst &I, long long &ut)
+    {
+        if (eq != EULER2D) return;
+        if (ut == 0) list_places = 0;
+        I.strips = strips_of(I.nx);
+        I.row_blocks = (I.ny + rows - 1) / rows;
+        I.unit0 = ut;
+        I.units = (long long)I.strips * I.row_blocks;
+        ut += I.units;
+        I.list0 = list_places;
+        list_places += (long long)I.strips * I.ny * fix_places(I.nx);
+    }
+    int strips_of(int nx) const { return (nx + strip_cells(order) - 1) / strip_cells(order); }
+
+    // Rows per unit: as many units as the launch has waves resident, so every wave
+    // takes one (the rows above a unit's first face are read and their fluxes formed
+    // again, about one row's time; a second round of units would wait for the first).
+    int rows = 1;
+    bool wide = false;  // a plane of 4 GiB or more: the recording kernels' 64-bit offsets
+    void choose_rows(const enoao_problem *ps, int count)
+    {
+        if (eq != EULER2D) return;
+        const int per_cu = wg_per_cu > 0 ? wg_per_cu : occupancy_2d(order, M_S2, false, ch);
+        const long long waves = (long long)cus * per_cu * (BLOCK / 64);
+        long long total = 0;
+        int most = 1;
+        if (!dynamic) wide = false;  // (a pool's captured graphs outlive its members)
+        for (int i = 0; i < count; ++i) {
+            if (8ll * padded_pitch(ps[i].nx) * ps[i].ny >= 1ll << 32) wide = true;
+            total += (long long)strips_of(ps[i].nx) * ps[i].ny;
+            most = std::max(most, ps[i].ny);
+        }
+        auto units = [&](long long r) {
+            long long n = 0;
+            for (int i = 0; i < count; ++i) n += strips_of(ps[i].nx) * ((ps[i].ny + r - 1) / r);
+            return n;
+        };
+        most = std::min(most, 1 << 15);  // (a row within a unit is 16 bits of a list entry)
+        long long r = std::max<long long>(1, (total + waves - 1) / waves);
+        while (r < most && units(r) > waves) r += std::max<long long>(1, r / 32);
+        r = std::min<long long>(r, most);
+        rows = (int)(short_units ? std::max<long long>(1, r / 2) : r);
     }
 
     void set_grids()
     {
-        const long long xt = h_hdr.xtiles_total, yt = h_hdr.ytiles_total;
+        const long long xt = h_hdr.xtiles_total;
+        if (eq == EULER2D) {
+            // a workgroup per listed row at most (a pool's rows change between steps)
+            long long most = 0;
+            for (const Inst &I : h_inst) most += (long long)I.strips * I.ny;
+            if (dynamic || h_inst.empty()) most = 1ll << 30;
+            grid_fix = (int)std::min<long long>(most, (long long)cus * occupancy_fix_2d(order, M_S2, false, ch));
+        }
         for (int m = 0; m < 4; ++m) {
+            if (eq == EULER2D) {
+                grid_2d[m] = grid_for((h_hdr.units_total + BLOCK / 64 - 1) / (BLOCK / 64),
+                                      occupancy_2d(order, m, false, ch), m >= 1 ? wg_kind[2 + m] : 0);
+                continue;
+            }
             const int ox = occupancy_x(eq, order, m, false, ch);
             grid_x[m] = grid_for(xt, ox, m >= 1 ? wg_kind[m - 1] : 0);
             gmin_x[m] = std::min(grid_x[m], cus * ox);
-            if (eq == EULER2D) {
-                const int oy = occupancy_y(order, m, false, ch, yw);
-                grid_y[m] = grid_for(yt, oy, m >= 1 ? wg_kind[2 + m] : 0);
-                gmin_y[m] = std::min(grid_y[m], cus * oy);
-            }
         }
         grid_m = grid_for(xt, occupancy_maxima(eq));
         gmin_m = std::min(grid_m, cus * occupancy_maxima(eq));
@@ -529,22 +601,17 @@ struct Runtime {
         for (auto &m : marks) (void)hipEventSynchronize(m.second);
     }
 
-    // new y tile width: the members' y tile lists rebuilt and uploaded, grids
-    // recomputed, the captured graph dropped
-    enoao_status set_ytiles(int w, hipStream_t s)
+    // 2D units of full or half height: the members' unit lists rebuilt and uploaded,
+    // grids recomputed, the captured graphs dropped
+    enoao_status set_short_units(bool on, hipStream_t s)
     {
-        if (w == yw) return ENOAO_OK;
-        yw = w;
-        long long yt = 0;
-        for (int i = 0; i < n; ++i) {
-            Inst &I = h_inst[i];
-            I.ytiles_per_row = (I.ny + yt_cells(yw) - 1) / yt_cells(yw);
-            I.ycol_groups = (I.nx + yt_cols(yw) - 1) / yt_cols(yw);
-            I.ytile0 = yt;
-            I.ytiles = eq == EULER2D ? (long long)I.ytiles_per_row * I.ycol_groups : 0;
-            yt += I.ytiles;
-        }
-        h_hdr.ytiles_total = yt;
+        if (on == short_units) return ENOAO_OK;
+        short_units = on;
+        if (eq != EULER2D) return ENOAO_OK;
+        choose_rows(probs.data(), n);
+        long long ut = 0;
+        for (int i = 0; i < n; ++i) set_units(h_inst[i], ut);
+        h_hdr.units_total = ut;
         HIP_TRY(hipMemcpyAsync(d_inst, h_inst.data(), sizeof(Inst) * n, hipMemcpyHostToDevice, s));
         HIP_TRY(hipMemcpyAsync(d_hdr, &h_hdr, sizeof(BatchHdr), hipMemcpyHostToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));  // the host copies are reused
@@ -574,21 +641,31 @@ struct Runtime {
     }
 
     // ---- building blocks, all enqueued on stream s ----
-    enoao_status set_pointers(int k, const double *u, double *lx, hipStream_t s)
+    enoao_status maxima(hipStream_t s)
     {
-        // patch the member's u (and L output) in the device descriptor
-        HIP_TRY(launch_patch_inst(d_inst, k, u, lx, lx != nullptr, s));
+        int slot;
+        HIP_TRY(prof_begin(PROF_MAXIMA, s, slot));
+        HIP_TRY(launch_state_maxima(eq, chunked(params(-1, 0, -1), gmin_m), grid_m, s));
+        HIP_TRY(prof_end(slot, s));
         return ENOAO_OK;
     }
 
     enoao_status reset_and_maxima(hipStream_t s)
     {
-        int slot;
-        HIP_TRY(launch_reset_maxima(params(0, 0, -1), n_cap, s));
-        HIP_TRY(prof_begin(PROF_MAXIMA, s, slot));
-        HIP_TRY(launch_state_maxima(eq, chunked(params(-1, 0, -1), gmin_m), grid_m, s));
-        HIP_TRY(prof_end(slot, s));
-        return ENOAO_OK;
+        KParams p = params(0, 0, -1);
+        p.fix_count = d_fix_count;
+        HIP_TRY(launch_reset_maxima(eq, p, n_cap, s));
+        return maxima(s);
+    }
+
+    // a plan's member: caller pointers (lx may be null) and control block (launch_begin_lone)
+    // set, the maxima of its state taken unless the solver of the steps takes its own
+    enoao_status begin(const double *u, double *lx, const Ctrl &v, int mode, bool own_maxima, hipStream_t s)
+    {
+        KParams p = params(0, 0, -1);
+        p.fix_count = d_fix_count;
+        HIP_TRY(launch_begin_lone(eq, p, d_inst, u, lx, d_ctrl, v, mode, s));
+        return own_maxima ? ENOAO_OK : maxima(s);
     }
 
     // one Runge-Kutta stage (1..3); slots: stage s reads s-1, writes s%3, clears (s+1)%3
@@ -597,26 +674,31 @@ struct Runtime {
         const int r_in = (s - 1) % 3, r_out = s % 3, r_zero = (s + 1) % 3;
         const int mode = s;  // M_S1..M_S3
         int slot;
-        HIP_TRY(prof_begin(PROF_X1 + s - 1, st, slot));
-        const KParams px = chunked(params(r_in, eq == EULER2D ? -1 : r_out, r_zero, s - 1), gmin_x[mode]);
-        HIP_TRY(launch_sweep_x(eq, order, mode, record, ch, px, grid_x[mode], st));
+        HIP_TRY(prof_begin((eq == EULER2D ? PROF_Y1 : PROF_X1) + s - 1, st, slot));
+        KParams p = params(r_in, r_out, r_zero, s - 1);
+        // stage s counts its lists with set s mod 3 and zeroes the next stage's
+        set_list(p, s % 3, (s + 1) % 3);
+        if (eq == EULER2D) HIP_TRY(launch_stage_2d(order, mode, record || wide, ch, p, grid_2d[mode], grid_fix, st));
+        else HIP_TRY(launch_sweep_x(eq, order, mode, record, ch, chunked(p, gmin_x[mode]), grid_x[mode], st));
         HIP_TRY(prof_end(slot, st));
-        if (eq == EULER2D) {
-            HIP_TRY(prof_begin(PROF_Y1 + s - 1, st, slot));
-            const KParams py = chunked(params(r_in, r_out, -1, s - 1), gmin_y[mode]);
-            HIP_TRY(launch_sweep_y(order, mode, record, ch, yw, py, grid_y[mode], st));
-            HIP_TRY(prof_end(slot, st));
-        }
         if (record) last_sel = s - 1;
         return ENOAO_OK;
     }
 
+    void set_list(KParams &p, int counter, int zero) const
+    {
+        if (eq != EULER2D) return;
+        p.fix_list = d_fix_list;
+        p.fix_count = d_fix_count + counter * FIX_SET_WORDS;
+        p.fix_zero = zero >= 0 ? d_fix_count + zero * FIX_SET_WORDS : nullptr;
+    }
+
     enoao_status rhs(hipStream_t s)
     {
-        HIP_TRY(launch_sweep_x(eq, order, M_RHS, rec, ch, chunked(params(0, -1, -1), gmin_x[M_RHS]), grid_x[M_RHS], s));
-        if (eq == EULER2D)
-            HIP_TRY(launch_sweep_y(order, M_RHS, rec, ch, yw, chunked(params(0, -1, -1), gmin_y[M_RHS]), grid_y[M_RHS],
-                                   s));
+        KParams p = params(0, -1, -1);
+        set_list(p, 3, -1);  // (zeroed with the maxima before it)
+        if (eq == EULER2D) HIP_TRY(launch_stage_2d(order, M_RHS, rec || wide, ch, p, grid_2d[M_RHS], grid_fix, s));
+        else HIP_TRY(launch_sweep_x(eq, order, M_RHS, rec, ch, chunked(p, gmin_x[M_RHS]), grid_x[M_RHS], s));
         last_sel = 0;
         return ENOAO_OK;
     }
@@ -725,7 +807,6 @@ struct Runtime {
 
 struct enoao_plan {
     Runtime rt;
-    double *ws_lx = nullptr;  // 2D: Lx workspace (inside the runtime allocation)
 };
 
 // ---------------------------------------------------------------------------
@@ -736,7 +817,10 @@ struct enoao_plan {
 // per device with hipGetSymbolAddress and kept in noalloc_ptr.
 namespace {
 
-__device__ __align__(256) unsigned char scratch[ENOAO_NOALLOC_SCRATCH_BYTES];
+// (the list counters and the maxima ring follow the stated bytes)
+constexpr size_t NA_FIX = ENOAO_NOALLOC_SCRATCH_BYTES, NA_AMAX = NA_FIX + FIX_SETS * FIX_SET_WORDS * sizeof(unsigned);
+constexpr size_t NA_END = NA_AMAX + AMAX_SLOTS * amax_slot_words(EULER2D) * 8;
+__device__ __align__(256) unsigned char scratch[NA_END];
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
 std::mutex noalloc_mutex;
@@ -755,10 +839,9 @@ void *noalloc_scratch(int device)
     return noalloc_ptr[device];
 }
 
-// scratch layout: header, descriptor, control, maxima ring, then the stage buffers
-constexpr size_t NA_HDR = 0, NA_INST = 256, NA_CTRL = 512, NA_AMAX = 768, NA_MEM = 1024;
-static_assert(sizeof(BatchHdr) <= 256 && sizeof(Inst) <= 256 && sizeof(Ctrl) <= 256 &&
-                  AMAX_SLOTS * AMAX_VALS * 8 <= 256, "scratch header slots");
+// scratch layout: header, descriptor, control, then the stage buffers (NA_FIX, NA_AMAX: above)
+constexpr size_t NA_HDR = 0, NA_INST = 256, NA_CTRL = 512, NA_MEM = 1024;
+static_assert(sizeof(BatchHdr) <= 256 && sizeof(Inst) <= 256 && sizeof(Ctrl) <= 256, "scratch header slots");
 
 size_t noalloc_bytes(const enoao_problem *p)
 {
@@ -858,7 +941,11 @@ struct enoao_pool {
     {
         Runtime &r = rt;
         r.h_inst.clear();
-        long long xt = 0, yt = 0;
+        std::vector<enoao_problem> live;
+        for (const Slot &sl : slots)
+            if (sl.used) live.push_back(sl.prob);
+        r.choose_rows(live.data(), (int)live.size());
+        long long xt = 0, ut = 0;
         for (int k = 0; k < max_members; ++k) {
             if (!slots[k].used) continue;
             const enoao_problem &p = slots[k].prob;
@@ -868,13 +955,13 @@ struct enoao_pool {
             Inst I;
             r.fill_inst(I, p, member_buffer(m, cells, 0), member_buffer(m, cells, 1), member_buffer(m, cells, 2),
                         r.eq == EULER2D ? member_buffer(m, cells, 3) : nullptr, nullptr,
-                        r.d_amax + (size_t)k * AMAX_SLOTS * AMAX_VALS, r.d_ctrl + k, xt, yt, pitch);
+                        r.d_amax + (size_t)k * r.amax_words(), r.d_ctrl + k, xt, ut, pitch);
             r.h_inst.push_back(I);
         }
         r.n = (int)r.h_inst.size();
         r.h_hdr.n_inst = r.n;
         r.h_hdr.xtiles_total = xt;
-        r.h_hdr.ytiles_total = yt;
+        r.h_hdr.units_total = ut;
         pin_cur ^= 1;
         HIP_TRY(hipEventSynchronize(ev_pin[pin_cur]));  // this buffer's previous upload
         char *h = h_pin[pin_cur];
@@ -993,13 +1080,13 @@ enoao_status enoao_batch_set_launch_kinds(enoao_batch *batch, const int32_t *wor
 enoao_status enoao_plan_set_tiles(enoao_plan *plan, int32_t y_strip_columns, void *stream)
 {
     if (!plan || (y_strip_columns != 0 && y_strip_columns != 4 && y_strip_columns != 8)) return ENOAO_EINVAL;
-    return plan->rt.set_ytiles(y_strip_columns ? y_strip_columns : yw_default(plan->rt.order), (hipStream_t)stream);
+    return plan->rt.set_short_units(y_strip_columns == 4, (hipStream_t)stream);
 }
 
 enoao_status enoao_batch_set_tiles(enoao_batch *batch, int32_t y_strip_columns, void *stream)
 {
     if (!batch || (y_strip_columns != 0 && y_strip_columns != 4 && y_strip_columns != 8)) return ENOAO_EINVAL;
-    return batch->rt.set_ytiles(y_strip_columns ? y_strip_columns : yw_default(batch->rt.order), (hipStream_t)stream);
+    return batch->rt.set_short_units(y_strip_columns == 4, (hipStream_t)stream);
 }
 
 enoao_status enoao_set_resident(int32_t enable)
@@ -1050,7 +1137,6 @@ enoao_status enoao_plan_create(const enoao_problem *prob, void *stream, enoao_pl
         delete p;
         return e;
     }
-    p->ws_lx = p->rt.h_inst[0].lx;
     *out = p;
     return ENOAO_OK;
 }
@@ -1068,13 +1154,9 @@ enoao_status enoao_rhs(enoao_plan *plan, const double *u, double *L, void *strea
     if (!plan || !u || !L || (const double *)L == u) return ENOAO_EINVAL;
     Runtime &rt = plan->rt;
     hipStream_t s = (hipStream_t)stream;
-    if (enoao_status e = rt.set_pointers(0, u, L, s)) return e;
-    HIP_TRY(launch_clear_done(rt.params(0, -1, -1), 1, s));
-    if (enoao_status e = rt.reset_and_maxima(s)) return e;
+    Ctrl none{};
+    if (enoao_status e = rt.begin(u, L, none, 0, false, s)) return e;
     if (enoao_status e = rt.rhs(s)) return e;
-    // restore the workspace Lx pointer for later steps
-    if (rt.eq == EULER2D)
-        if (enoao_status e = rt.set_pointers(0, u, plan->ws_lx, s)) return e;
     HIP_TRY(rt.mark(s));
     return ENOAO_OK;
 }
@@ -1084,9 +1166,9 @@ enoao_status enoao_step(enoao_plan *plan, double *u, double dt, void *stream)
     if (!plan || !u || !(dt > 0.0) || !std::isfinite(dt)) return ENOAO_EINVAL;
     Runtime &rt = plan->rt;
     hipStream_t s = (hipStream_t)stream;
-    if (enoao_status e = rt.set_pointers(0, u, plan->ws_lx, s)) return e;
-    if (enoao_status e = rt.reset_and_maxima(s)) return e;
-    HIP_TRY(launch_set_dt(rt.params(0, -1, -1), 1, dt, s));
+    Ctrl c{};
+    c.dt = dt;
+    if (enoao_status e = rt.begin(u, nullptr, c, 1, false, s)) return e;
     if (enoao_status e = rt.steps(1, false, s)) return e;
     HIP_TRY(rt.mark(s));
     return ENOAO_OK;
@@ -1099,16 +1181,15 @@ enoao_status enoao_solve(enoao_plan *plan, double *u, double t_final, double cfl
     if (!(dt_fixed > 0.0) && !(cfl > 0.0)) return ENOAO_EINVAL;
     Runtime &rt = plan->rt;
     hipStream_t s = (hipStream_t)stream;
-    if (enoao_status e = rt.set_pointers(0, u, plan->ws_lx, s)) return e;
-    std::vector<Ctrl> c(1);
-    std::memset(c.data(), 0, sizeof(Ctrl));
-    c[0].t = 0.0;
-    c[0].t_final = t_final;
-    c[0].cfl = cfl;
-    c[0].dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
-    c[0].max_steps = max_steps;
-    if (enoao_status e = upload_ctrl(rt, c, s)) return e;
-    if (enoao_status e = rt.reset_and_maxima(s)) return e;
+    Ctrl c{};
+    c.t = 0.0;
+    c.t_final = t_final;
+    c.cfl = cfl;
+    c.dt_fixed = dt_fixed > 0.0 ? dt_fixed : 0.0;
+    c.max_steps = max_steps;
+    // (the resident and cooperative solvers take the maxima of the state themselves)
+    if (enoao_status e = rt.begin(u, nullptr, c, 2, rt.use_resident() || rt.use_coop(), s)) return e;
+    rt.h_ctrl[0] = c;  // (what is reported when no step is asked for)
 
     // steps per graph replay: a guess of the total, bounded
     auto steps_per_launch = [&]() {
@@ -1171,7 +1252,6 @@ enoao_status enoao_step_noalloc(const enoao_problem *prob, double *u, double dt,
     Runtime rt;
     rt.eq = prob->equation;
     rt.order = prob->order;
-    rt.yw = yw_default(rt.order);
     rt.nc = ncomp_of(rt.eq);
     rt.n = rt.n_cap = 1;
     rt.gamma = prob->gamma;
@@ -1185,25 +1265,32 @@ enoao_status enoao_step_noalloc(const enoao_problem *prob, double *u, double dt,
     rt.d_ctrl = (Ctrl *)(base + NA_CTRL);
     rt.d_amax = (unsigned long long *)(base + NA_AMAX);
     rt.d_res_order = nullptr;
+    if (rt.eq == EULER2D) {
+        // the third state buffer holds the lists (at most a place per cell)
+        rt.d_fix_count = (unsigned *)(base + NA_FIX);
+        rt.d_fix_list = (unsigned long long *)member_buffer((double *)(base + NA_MEM),
+                                                            (size_t)rt.nc * prob->nx * prob->ny, 2);
+    }
     double *m = (double *)(base + NA_MEM);
     const size_t cells = (size_t)rt.nc * prob->nx * prob->ny;
     Inst I;
-    long long xt = 0, yt = 0;
+    rt.wg_per_cu = g_wg_per_cu;
+    rt.choose_rows(prob, 1);
+    long long xt = 0, ut = 0;
     rt.fill_inst(I, *prob, u, member_buffer(m, cells, 0), member_buffer(m, cells, 1),
-                 rt.eq == EULER2D ? member_buffer(m, cells, 2) : nullptr, nullptr, rt.d_amax, rt.d_ctrl, xt, yt);
+                 rt.eq == EULER2D ? member_buffer(m, cells, 2) : nullptr, nullptr, rt.d_amax, rt.d_ctrl, xt, ut);
     rt.h_hdr.n_inst = 1;
     rt.h_hdr.xtiles_total = xt;
-    rt.h_hdr.ytiles_total = yt;
-    rt.wg_per_cu = g_wg_per_cu;
+    rt.h_hdr.units_total = ut;
     rt.set_grids();
     Ctrl c;
     std::memset(&c, 0, sizeof(Ctrl));
     c.t_final = INFINITY;
-    // the same launches as enoao_step: descriptors, maxima of u, the step size, three stages
+    c.dt = dt;
+    // the same launches as enoao_step: descriptors, maxima of u, three stages
     hipLaunchKernelGGL(noalloc_init, dim3(1), dim3(64), 0, s, rt.h_hdr, I, c, rt.d_hdr, rt.d_inst, rt.d_ctrl);
     HIP_TRY(hipGetLastError());
     if (enoao_status e = rt.reset_and_maxima(s)) return e;
-    HIP_TRY(launch_set_dt(rt.params(0, -1, -1), 1, dt, s));
     return rt.steps(1, false, s);
 }
 
@@ -1425,7 +1512,6 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     };
     r.eq = like->equation;
     r.order = like->order;
-    r.yw = yw_default(r.order);
     r.nc = ncomp_of(r.eq);
     r.gamma = like->gamma;
     r.delta = like->delta;
@@ -1435,6 +1521,7 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     r.n = 0;
     r.n_cap = max_members;
     r.probs.assign(1, *like);
+    r.wide = r.eq == EULER2D && arena_bytes >= 16ull << 32;  // (four buffers of four planes of 4 GiB)
     if (hipGetDevice(&r.device) != hipSuccess ||
         hipDeviceGetAttribute(&r.cus, hipDeviceAttributeMultiprocessorCount, r.device) != hipSuccess)
         return fail(ENOAO_EDEVICE);
@@ -1447,7 +1534,11 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     const size_t o_hdr = take(sizeof(BatchHdr));
     const size_t o_inst = take(sizeof(Inst) * max_members);
     const size_t o_ctrl = take(sizeof(Ctrl) * max_members);
-    const size_t o_amax = take(8ull * AMAX_SLOTS * AMAX_VALS * max_members);
+    const size_t o_amax = take(8ull * r.amax_words() * max_members);
+    const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * sizeof(unsigned));
+    // (a member of ny rows and s strips holds at least 128 ny max(16, 54 (s - 1)) bytes of
+    // the arena, and its list at most 128 s ny)
+    const size_t o_fix = take(r.eq == EULER2D ? arena_bytes / 16 + 256 : 0);
     const size_t o_arena = take(arena_bytes);
     if (hipMalloc(&r.d_block, off) != hipSuccess) {
         r.d_block = nullptr;
@@ -1458,6 +1549,10 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     r.d_inst = (Inst *)(base + o_inst);
     r.d_ctrl = (Ctrl *)(base + o_ctrl);
     r.d_amax = (unsigned long long *)(base + o_amax);
+    if (r.eq == EULER2D) {
+        r.d_fix_count = (unsigned *)(base + o_fixc);
+        r.d_fix_list = (unsigned long long *)(base + o_fix);
+    }
     pl->arena = base + o_arena;
     pl->arena_bytes = arena_bytes / 256 * 256;
     pl->free_list.push_back({0, pl->arena_bytes});
@@ -1484,7 +1579,7 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     }
     if (hipMemcpyAsync(r.d_ctrl, c0.data(), sizeof(Ctrl) * max_members, hipMemcpyHostToDevice, s) != hipSuccess)
         return fail(ENOAO_EDEVICE);
-    r.wg_per_cu = Runtime::POOL_WG_PER_CU;
+    r.wg_per_cu = r.eq == EULER2D ? 0 : Runtime::POOL_WG_PER_CU;
     r.set_grids();
     if (pl->rebuild(s)) return fail(ENOAO_EDEVICE);
     *out = pl;

@@ -18,15 +18,23 @@ enum Bc : int { BC_PERIODIC = 0, BC_TRANSMISSIVE = 1 };
 constexpr int XW_FACES = 64;
 constexpr int XW_CELLS = XW_FACES - 1;
 constexpr int XW_SEGS = 4;
-// y-sweep tiles: each of the 4 waves of a workgroup owns a strip of w columns
-// (w = 4 or 8, chosen per plan or batch) and w * 64/w = 64 lanes; a tile is
-// 4w columns x 64/w cell rows.
-// Default strip width per order (measured on the 2048^2 Euler workloads: 8 for
-// order 5; 4 for order 7, whose wider strips stage more halo rows per face
-// than its one wave per SIMD can hide).
-constexpr int yw_default(int order) { return order == 7 ? 4 : 8; }
-constexpr int yt_cells(int w) { return 64 / w; }
-constexpr int yt_cols(int w) { return 4 * w; }
+// 2D stages: a wave owns a strip of columns, one lane per column, the outer ones
+// the halo of 4 (order 7: 5) nodes on either side that an x-face reads.  A strip's
+// rows are cut into blocks of equal height to within one; a unit of work is one
+// block of one strip.
+constexpr int strip_cells(int order) { return order == 7 ? 54 : 56; }
+// Row segments whose faces need a selection are listed for a second kernel: one entry
+// per strip and row, or one per FIX_SPLIT cells where there are more than
+// FIX_FACES faces to select (a segment along a shock holds up to 169, eleven passes of
+// the wave that takes it, and the launch waited for those).  The units are cut into FIX_RANGES ranges with a list
+// and a counter each, the counters a cache line apart: the waves that end a launch
+// together take their places at once, and an atomic on one line takes 20 ns.  Four
+// sets of counters, three used in turn by the stages of a step, the fourth by an
+// evaluation of L.
+constexpr int FIX_SPLIT = 14, FIX_FACES = 48;
+constexpr int fix_places(int nx) { return nx > 3 * FIX_SPLIT ? 4 : (nx + FIX_SPLIT - 1) / FIX_SPLIT; }  // per strip and row
+constexpr int FIX_ENTRY_BYTES = 32, FIX_RANGES = 32, FIX_COUNTER_STRIDE = 16;
+constexpr int FIX_SET_WORDS = FIX_RANGES * FIX_COUNTER_STRIDE, FIX_SETS = 4;
 constexpr int BLOCK = 256;
 
 // per-field maxima kept per instance: three ring slots of 8 values each
@@ -34,8 +42,13 @@ constexpr int BLOCK = 256;
 // integer max is the floating-point max):
 //   [0..2] max |u-c|, |u|, |u+c| along x    [3..5] same along y (v)
 //   [6]    max (|u|+c)/dx + (|v|+c)/dy (2D time step)
+// A 2D slot has eight copies, a cache line each, that the workgroups share in turn
+// and its readers fold: hundreds of workgroups end a launch together, and their
+// atomics on one line took 5 us of a 20 us stage.
 constexpr int AMAX_VALS = 8;
 constexpr int AMAX_SLOTS = 3;
+constexpr int amax_copies(int eq) { return eq == EULER2D ? 8 : 1; }
+constexpr int amax_slot_words(int eq) { return AMAX_VALS * amax_copies(eq); }
 
 // Time-loop control of one instance (device memory).
 struct Ctrl {
@@ -56,7 +69,7 @@ struct Inst {
     double *u;                  // u^n: caller state, updated in place by stage 3
     double *w1, *w2;            // stage-1 and stage-2 states
     double *lx;                 // 2D: x-part of L; rhs: the L output
-    unsigned long long *amax;   // AMAX_SLOTS x AMAX_VALS
+    unsigned long long *amax;   // AMAX_SLOTS x amax_copies x AMAX_VALS
     Ctrl *ctrl;
     uint8_t *sel;               // selection record or nullptr
     int nx, ny;
@@ -64,11 +77,12 @@ struct Inst {
     double dx, dy;
     double adv;                 // advection speed
     int segs_per_row;           // ceil(nx / XW_CELLS)
-    int ytiles_per_row;         // ceil(ny / yt_cells(w)) tiles per column group (w: y strip width)
-    int ycol_groups;            // ceil(nx / yt_cols(w))
+    int strips;                 // 2D: ceil(nx / strip_cells(order))
+    int row_blocks;             // 2D: blocks of rows per strip
     int pitch;                  // row pitch of every state buffer, elements (>= nx; planes pitch * ny apart)
-    long long xtile0, ytile0;   // first x / y tile of this instance in the batch lists
-    long long xtiles, ytiles;   // number of x / y tiles
+    long long xtile0, unit0;    // first x tile / 2D unit of this instance in the batch lists
+    long long xtiles, units;    // number of x tiles / 2D units
+    long long list0;            // 2D: list places of the instances before this one
 };
 
 // LDS-resident solver of small 1D members: one workgroup of RES_BLOCK threads
@@ -92,7 +106,7 @@ constexpr unsigned long long resident_lds_bytes(int nc, int nq, int g, long long
 struct BatchHdr {
     int n_inst;
     int pad;
-    long long xtiles_total, ytiles_total;
+    long long xtiles_total, units_total;
 };
 
 }  // namespace enoao

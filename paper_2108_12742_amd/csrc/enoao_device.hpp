@@ -111,7 +111,12 @@ template <int ORDER> struct Recon {
     //     h6 = h5 + e1/60, h7 = h5 + e2/60, h8 = h6 + g1/105,
     // (a, b, c, ... the 1st, 2nd, 3rd ... undivided differences, index = first
     // node).
-    __device__ __forceinline__ static double select(const double (&f)[W], double delta, double is_top, int &sel)
+    // The same with the top candidate's indicator taken from the window itself;
+    // top: the top candidate's value.
+    __device__ __forceinline__ static double select_top(const double (&f)[W], double delta, int &sel, double &top);
+
+    __device__ __forceinline__ static double select(const double (&f)[W], double delta, double is_top, int &sel,
+                                                    double *top = nullptr)
     {
         if constexpr (ORDER == 5) {
             const double a0 = f[1] - f[0], a1 = f[2] - f[1], a2 = f[3] - f[2];
@@ -134,6 +139,7 @@ template <int ORDER> struct Recon {
             is[3] = fmin(fabs(d0), ad1);                                   // S_{j-2}^{j+1}
             is[4] = fmin(ad1, fabs(d2));                                   // S_{j-1}^{j+2}
             is[5] = is_top;                                                // S_{j-2}^{j+2}
+            if (top) *top = h[5];
             return select_candidate<6>(is, h, delta, sel);
         } else {
             double a[8], b[7], c[6], d[5], e[4], g[3];
@@ -170,6 +176,7 @@ template <int ORDER> struct Recon {
             is[6] = fmin(fabs(g[0]), ag1);                                         // S_{j-3}^{j+2}
             is[7] = fmin(ag1, fabs(g[2]));                                         // S_{j-2}^{j+3}
             is[8] = is_top;                                                        // S_{j-3}^{j+3}
+            if (top) *top = h[8];
             return select_candidate<9>(is, h, delta, sel);
         }
     }
@@ -209,20 +216,30 @@ template <int ORDER> struct TopStencil {
         }
     }
     // S over a face's nodes, x[0] = node 0
-    __device__ __forceinline__ static double sym(const double *x, int ns)
+    __device__ __forceinline__ static double sym(const double *x, int ns) { return sym1(x + ns, ns); }
+    // the same, x[0] = node 1 (the first that S reads)
+    __device__ __forceinline__ static double sym1(const double *x, int ns)
     {
-        const double s0 = x[H * ns] + x[(H + 1) * ns], s1 = x[(H - 1) * ns] + x[(H + 2) * ns];
-        const double s2 = x[(H - 2) * ns] + x[(H + 3) * ns];
+        const double s0 = x[(H - 1) * ns] + x[H * ns], s1 = x[(H - 2) * ns] + x[(H + 1) * ns];
+        const double s2 = x[(H - 3) * ns] + x[(H + 2) * ns];
         if constexpr (ORDER == 5) {
             return fma(1.0 / 30.0, s2 - s1, fma(-7.0 / 30.0, s1 - s0, s0));
         } else {
-            const double s3 = x[(H - 3) * ns] + x[(H + 4) * ns];
+            const double s3 = x[(H - 4) * ns] + x[(H + 3) * ns];
             double r = fma(-113.0 / 420.0, s1 - s0, s0);
             r = fma(13.0 / 210.0, s2 - s1, r);
             return fma(-1.0 / 140.0, s3 - s2, r);
         }
     }
 };
+
+template <int ORDER>
+__device__ __forceinline__ double Recon<ORDER>::select_top(const double (&f)[Recon<ORDER>::W], double delta, int &sel,
+                                                           double &top)
+{
+    const double is_top = fmin(fabs(TopStencil<ORDER>::diff(f, 1)), fabs(TopStencil<ORDER>::diff(f + 1, 1)));
+    return select(f, delta, is_top, sel, &top);
+}
 
 // ---------------------------------------------------------------------------
 // Per-node quantities staged in LDS (computed once per node by the lane that
@@ -262,6 +279,25 @@ __device__ __forceinline__ double sqrt_nr(double x)
     y = fma(d, h, y);
     d = fma(-y, y, x);
     return fma(d, h, y);
+}
+
+// sqrt(x) as above and its reciprocal, from the same iteration: h is 1/(2 sqrt(x))
+// to within rounding, one Newton step against the root settles it.
+__device__ __forceinline__ void sqrt_rcp_nr(double x, double &root, double &inv)
+{
+    const double r = __builtin_amdgcn_rsq(x);
+    double y = x * r;
+    double h = 0.5 * r;
+    const double e = fma(-h, y, 0.5);
+    y = fma(y, e, y);
+    h = fma(h, e, h);
+    double d = fma(-y, y, x);
+    y = fma(d, h, y);
+    d = fma(-y, y, x);
+    y = fma(d, h, y);
+    const double i = h + h;
+    root = y;
+    inv = fma(i, fma(-y, i, 1.0), i);
 }
 
 template <int EQ> struct NodeTraits;
@@ -315,8 +351,7 @@ __device__ __forceinline__ RoeState roe_state(double sL, double uL, double vL, d
     r.H = fma(wL, HL, wR * HR);
     r.q2h = 0.5 * fma(r.u, r.u, r.v * r.v);
     const double c2 = gm1 * (r.H - r.q2h);
-    r.c = sqrt_nr(c2);
-    r.ic = rcp_nr(r.c);
+    sqrt_rcp_nr(c2, r.c, r.ic);
     r.b1 = gm1 * r.ic * r.ic;
     r.b2 = r.q2h * r.b1;
     return r;

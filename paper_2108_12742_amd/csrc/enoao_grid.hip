@@ -1,0 +1,931 @@
+// enoao_grid.hip -- the 2D Runge-Kutta stage (gfx950): one kernel for both
+// directions, and one for the faces whose flux is not the top candidate's.
+//
+// stage_2d.  A wave owns a strip of columns, one lane per column, and marches along
+// y.  Per row it loads U once and keeps, in registers, the last rows' U and y-flux
+// for the y-faces; the x-faces of a row come from the neighbouring lanes (through a
+// row buffer in LDS private to the wave); L = L_x + L_y, the stage combine and the
+// maxima of the new state follow at once.  The state is read once and written once
+// per stage and nothing else goes through memory: the split sweeps this replaces
+// wrote L_x, read it back and read the stage input twice (544 bytes a cell-update
+// against 256), and staged 12 quantities and 8 differences per node in LDS for 108
+// LDS instructions a face against 60 for both faces of a cell.  Waves never
+// synchronise with one another.
+//
+// What a face costs.  Where the window is smooth every field takes its top
+// candidate on both sides, and the flux is linear in the window: Fhat = S F / 2 +
+// R (kappa alpha L D_1 U) / 2 (TopStencil; R L = I, so the central part needs no
+// projection).  That it is so follows, for nearly all such faces, from one bound on
+// the indicators: |l.(D F +- alpha D U)| <= |l|_1 max_c(|D F_c| + alpha |D U_c|),
+// formed with D_1, which both sides share, and compared with delta over a bound of
+// the left eigenvectors' row sums.  (On developed flows the bound leaves 11% of the
+// 64-face rows, the exact indicators 10%.)
+//
+// fix_2d.  The faces that the bound leaves are few (2 to 7%) but each costs ten
+// others, and they lie along shocks, so a wave that met them in its strip worked
+// several times as long as its neighbours: selecting inside stage_2d took 0.10 ms
+// of a 0.23 ms stage for 15% more instructions, and the selection's registers
+// spilled the row loop's.  stage_2d therefore lists the row segments that hold such
+// faces and gives every cell the top flux; fix_2d spreads the listed rows over the
+// machine, selects, one lane per face and field, and adds the difference to the
+// cells: U += c dt dL, with dL zero where the top candidate is chosen after all, so
+// no result depends on what the bound leaves.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "enoao_common.hpp"
+#include "enoao_device.hpp"
+#include "enoao_kernels.hpp"
+#include "enoao_wave.hpp"
+
+namespace enoao {
+
+// Waves per SIMD of stage_2d.  Order 5 fits two (243 registers).  Order 7 holds a third
+// more rows: at two it spills 38 registers in stages 2 and 3 (0.217 ms on a smooth
+// 2048^2 grid against 0.174 at one; stage 1 0.142 against 0.156).
+constexpr int stage_waves(int order) { return order == 7 ? 1 : 2; }
+// Waves per SIMD of fix_2d: as many as its LDS lets a CU hold (39 KB a workgroup at
+// order 5, 43 KB at order 7).
+constexpr int fix_waves(int order) { return order == 7 ? 3 : 4; }
+
+// p at a byte offset.  Offsets within a plane below 4 GiB take one 32-bit register
+// (unsigned) beside a wave-uniform address; larger planes take 64-bit offsets, in the
+// recording instantiations, which also serve members that large without a record.
+template <class Off> __device__ __forceinline__ double row_load(const GMEM double *p, Off off)
+{
+    return *(const GMEM double *)((const GMEM char *)p + off);
+}
+template <class Off> __device__ __forceinline__ void row_store(GMEM double *p, Off off, double x)
+{
+    *(GMEM double *)((GMEM char *)p + off) = x;
+}
+
+// value of the neighbouring lane (lane 0 / 63 keep their own)
+template <int CTRL> __device__ __forceinline__ double dpp_move(double x)
+{
+    union { double d; int w[2]; } a, b;
+    a.d = x;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) b.w[i] = __builtin_amdgcn_update_dpp(a.w[i], a.w[i], CTRL, 0xf, 0xf, false);
+    return b.d;
+}
+__device__ __forceinline__ double lane_prev(double x) { return dpp_move<0x138>(x); }  // wave_shr:1
+__device__ __forceinline__ double lane_next(double x) { return dpp_move<0x130>(x); }  // wave_shl:1
+
+// lane i's value, in scalar registers
+__device__ __forceinline__ double lane_value(double x, int i)
+{
+    union { double d; int w[2]; } a;
+    a.d = x;
+    a.w[0] = __builtin_amdgcn_readlane(a.w[0], i);
+    a.w[1] = __builtin_amdgcn_readlane(a.w[1], i);
+    return a.d;
+}
+
+__device__ __forceinline__ unsigned long long lane_bits(unsigned long long x, int i)
+{
+    return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, i) |
+           (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), i) << 32;
+}
+
+// maximum over the wave's lanes
+__device__ __forceinline__ double wave_max(double x)
+{
+    x = fmax(x, dpp_move<0xb1>(x));   // quad_perm 1, 0, 3, 2
+    x = fmax(x, dpp_move<0x4e>(x));   // quad_perm 2, 3, 0, 1
+    x = fmax(x, dpp_move<0x141>(x));  // row_half_mirror
+    x = fmax(x, dpp_move<0x140>(x));  // row_mirror: each lane its row's maximum
+    x = fmax(x, dpp_move<0x142>(x));  // row_bcast:15 into the next row
+    x = fmax(x, dpp_move<0x143>(x));  // row_bcast:31 into rows 2 and 3
+    return lane_value(x, 63);
+}
+
+// sum over the four lanes of a quad, the same in each
+__device__ __forceinline__ double quad_sum(double x)
+{
+    const double y = x + dpp_move<0xb1>(x);  // quad_perm 1, 0, 3, 2
+    return y + dpp_move<0x4e>(y);            // quad_perm 2, 3, 0, 1
+}
+
+// a launch's values of one member
+struct GridView {
+    long long u0, u1;  // its units in the list
+    int k, nx, ny, pitch, bcx, bcy, strips, blocks;
+    int active;
+    const GMEM double *in;
+    GMEM double *out;
+    const GMEM double *base;
+    GMEM uint8_t *sel;
+    GMEM unsigned long long *amax;
+    GMEM Ctrl *ctrl;
+    double idx, idy, dt;
+    double ax[4], ay[4];  // kappa alpha / 2 per field along x and along y
+    double mx, my;        // the largest alpha along x and along y
+    double rx[3], ry[3];  // alpha of the fields u-c, u, u+c (component-wise: one for all)
+};
+
+template <int ORDER, bool CH>
+__device__ __forceinline__ GridView grid_view(const KParams &P, int n_inst, long long unit)
+{
+    GridView v;
+    // (a lone member's control block and maxima are kernel arguments, so their loads do
+    // not wait for the descriptor's)
+    v.k = P.lone_ctrl ? 0 : uniform(find_inst<false>(P.inst, n_inst, unit));
+    const Inst &I = P.inst[v.k];
+    v.ctrl = gmem(P.lone_ctrl ? P.lone_ctrl : uniform(I.ctrl));
+    v.amax = gmem(P.lone_ctrl ? P.lone_amax : uniform(I.amax));
+    // one lane per value and copy of the stage input's maxima
+    const int lane = threadIdx.x & 63;
+    double am = as_double(v.amax[P.r_in * amax_slot_words(EULER2D) + lane]);
+    const int done = v.ctrl->done;
+    const double dt = v.ctrl->dt;
+    v.u0 = uniform(I.unit0);
+    v.u1 = v.u0 + uniform(I.units);
+    v.nx = uniform(I.nx);
+    v.ny = uniform(I.ny);
+    v.pitch = uniform(I.pitch);
+    v.bcx = uniform(I.bcx);
+    v.bcy = uniform(I.bcy);
+    v.strips = uniform(I.strips);
+    v.blocks = uniform(I.row_blocks);
+    v.active = uniform(done) == 0;
+    v.dt = uniform(dt);
+    v.in = gmem(uniform(P.mode == M_S2 ? I.w1 : (P.mode == M_S3 ? I.w2 : I.u)));
+    v.out = gmem(uniform(P.mode == M_RHS ? I.lx : (P.mode == M_S1 ? I.w1 : (P.mode == M_S2 ? I.w2 : I.u))));
+    v.base = gmem(uniform(I.u));
+    v.sel = gmem(uniform(I.sel));
+    if (v.sel && P.sel_slot > 0) {
+        // records of one evaluation: x block [4][2][ny][nx+1], then the y block [4][2][ny+1][nx]
+        v.sel += (long long)P.sel_slot * 8ll * ((long long)v.ny * (v.nx + 1) + (long long)(v.ny + 1) * v.nx);
+    }
+    v.idx = uniform(1.0 / I.dx);
+    v.idy = uniform(1.0 / I.dy);
+#pragma unroll
+    for (int o = AMAX_VALS; o < 64; o *= 2) am = fmax(am, __shfl_xor(am, o, 64));
+    double ax[3], ay[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        ax[i] = lane_value(am, i);
+        ay[i] = lane_value(am, 3 + i);
+    }
+    if constexpr (!CH) {
+        // one alpha for all components: max(|u| + c) = max(max|u - c|, max|u + c|)
+        ax[0] = ax[1] = ax[2] = fmax(ax[0], ax[2]);
+        ay[0] = ay[1] = ay[2] = fmax(ay[0], ay[2]);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int i = s == 0 ? 0 : (s == 3 ? 2 : 1);
+        v.ax[s] = uniform(ax[i] * (TopStencil<ORDER>::kappa * 0.5 / fscale<4, CH>(s)));
+        v.ay[s] = uniform(ay[i] * (TopStencil<ORDER>::kappa * 0.5 / fscale<4, CH>(s)));
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        v.rx[i] = uniform(ax[i]);
+        v.ry[i] = uniform(ay[i]);
+    }
+    v.mx = uniform(fmax(ax[0], fmax(ax[1], ax[2])));
+    v.my = uniform(fmax(ay[0], fmax(ay[1], ay[2])));
+    return v;
+}
+
+// Stage combine (Shu-Osher form): base u^n + y (in + dt L).  The stages of a step share
+// one instantiation: launched in turn they would otherwise each fetch 17 KB of code
+// that the last one evicted, a good part of a small problem's time.
+struct RkWeights {
+    double base, y;
+};
+__device__ __forceinline__ RkWeights rk_weights(int mode)
+{
+    if (mode == M_S2) return RkWeights{0.75, 0.25};
+    if (mode == M_S3) return RkWeights{1.0 / 3.0, 2.0 / 3.0};
+    return RkWeights{0.0, 1.0};
+}
+
+// columns from x0, rows y0 .. y1 - 1 of a unit: strips along a row follow one another
+struct UnitBox {
+    int x0, y0, y1;
+};
+__device__ __forceinline__ UnitBox unit_box(const GridView &v, long long unit, int cells)
+{
+    const unsigned lu = (unsigned)(unit - v.u0), b = lu / (unsigned)v.strips;
+    UnitBox u;
+    u.x0 = (int)(lu - b * (unsigned)v.strips) * cells;
+    const unsigned low = (unsigned)v.ny / (unsigned)v.blocks, extra = (unsigned)v.ny - low * (unsigned)v.blocks;
+    u.y0 = (int)(b * low + min(b, extra));
+    u.y1 = u.y0 + (int)(low + (b < extra ? 1u : 0u));
+    return u;
+}
+
+// A wave's running maxima live in LDS, one column per lane (non-negative doubles
+// as bit patterns: integer max): seven registers pairs fewer across the row loop.
+struct WaveMax {
+    unsigned long long v[7][64];
+};
+
+// U in the natural component order: maxima of the wave speeds, non-physical flag
+__device__ __forceinline__ bool wave_max_add(WaveMax &M, int lane, const double (&U)[4], double gamma, double idx,
+                                             double idy)
+{
+    Maxima<EULER2D> m;
+    m.reset();
+    m.add(U, gamma, idx, idy);
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+        __hip_atomic_fetch_max(&M.v[i][lane], as_bits(m.v[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    return m.bad != 0;
+}
+
+// The maxima of the n lanes' columns M[0 .. n-1] into the member's slot, one atomic
+// per value, by one wave; the columns start again at zero.
+__device__ __forceinline__ void wave_flush(WaveMax *M, int n, unsigned long long bad, GMEM unsigned long long *amax,
+                                           GMEM Ctrl *ctrl, int slot)
+{
+    const int lane = threadIdx.x & 63;
+    double mine = 0.0;
+    wave_sync();
+#pragma unroll 1
+    for (int i = 0; i < 7; ++i) {
+        unsigned long long m = 0ull;
+        for (int k = 0; k < n; ++k) {
+            m = max(m, M[k].v[i][lane]);
+            M[k].v[i][lane] = 0ull;
+        }
+        const double x = wave_max(as_double(m));
+        if (lane == i) mine = x;
+    }
+    if (slot >= 0 && lane < 7)
+        __hip_atomic_fetch_max(&amax[slot * amax_slot_words(EULER2D) + blockIdx.x % amax_copies(EULER2D) * AMAX_VALS + lane],
+                               as_bits(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (bad && lane == 0) __hip_atomic_fetch_or(&ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// sqrt(rho), velocities, total enthalpy and pressure of a node
+struct NodePrim {
+    double s, u, v, H, p;
+};
+__device__ __forceinline__ double node_pressure(double rho, double u, double v, double E, double gm1)
+{
+    return gm1 * fma(-0.5 * rho, fma(u, u, v * v), E);
+}
+__device__ __forceinline__ NodePrim node_prim(double rho, double m, double n, double E, double gm1)
+{
+    NodePrim q;
+    const double ir = rcp_nr(rho);
+    q.u = m * ir;
+    q.v = n * ir;
+    q.p = node_pressure(rho, q.u, q.v, E, gm1);
+    q.s = sqrt_nr(rho);
+    q.H = (E + q.p) * ir;
+    return q;
+}
+
+// Bound of the left eigenvectors' scaled row sums of a face (acoustic rows halved
+// to the window scale of the others), so that every indicator of the face is at
+// most this times the node bound.  Component-wise variables: 1.
+template <bool CH> __device__ __forceinline__ double row_bound(const RoeState &r)
+{
+    if constexpr (!CH) return 1.0;
+    const double au = 1.0 + fabs(r.u), av = fabs(r.v);
+    const double x = fma(r.b1, au + av, r.b2);
+    return fmax(fmax(1.0 + x, 0.5 * fma(r.ic, au, x)), 1.0 + av);
+}
+
+// Node bound max_c(|D F_c| + alpha |D U_c|); F_0 is U_1.
+__device__ __forceinline__ double node_bound(const double (&dU)[4], const double (&dF)[3], double amax)
+{
+    double b = fma(amax, fabs(dU[0]), fabs(dU[1]));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b = fmax(b, fma(amax, fabs(dU[k + 1]), fabs(dF[k])));
+    return b;
+}
+
+// Flux of a face whose fields all take the top candidate on both sides:
+// S F / 2 + R (kappa alpha L D_1 U) / 2; ka: kappa alpha / 2 per field.
+template <bool CH>
+__device__ __forceinline__ void top_flux(const RoeState &r, const double (&sF)[4], const double (&dU)[4],
+                                         const double (&ka)[4], double (&Fh)[4])
+{
+    double w[4];
+    to_fields<4, CH>(r, dU, w);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) w[s] *= ka[s];
+    from_fields<4, CH>(r, w, Fh);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Fh[c] = fma(0.5, sF[c], Fh[c]);
+}
+
+// units per range of the lists (a launch has fewer than 2^32)
+__device__ __forceinline__ unsigned fix_range_units(long long units)
+{
+    return max(1u, ((unsigned)units + FIX_RANGES - 1) / FIX_RANGES);
+}
+
+// first entry of the list of the units from `unit` on: every strip row before it has its places
+__device__ __forceinline__ long long fix_list_start(const KParams &P, int n_inst, long long unit)
+{
+    const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst<false>(P.inst, n_inst, unit)];
+    const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
+    const unsigned low = (unsigned)I.ny / (unsigned)I.row_blocks, extra = (unsigned)I.ny - low * (unsigned)I.row_blocks;
+    const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);
+    return I.list0 + fix_places(I.nx) * ((long long)I.strips * y0 + (long long)s * rows);
+}
+
+// A listed row segment: unit << 28 | row within the unit << 12 | first lane of its
+// cells << 6 | last, and the lanes whose faces need a selection: right of the lane's
+// column, below and above the row.
+struct FixEntry {
+    unsigned long long where, x, below, above;
+};
+static_assert(sizeof(FixEntry) == FIX_ENTRY_BYTES, "list sizes");
+
+template <int ORDER, bool STEP, bool REC, bool CH>
+__global__ __launch_bounds__(BLOCK)
+__attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P)
+{
+    using T = TopStencil<ORDER>;
+    using Off = std::conditional_t<REC, long long, unsigned>;
+    constexpr int H = ReconTraits<ORDER>::H, G = H + 1, K = ReconTraits<ORDER>::K;
+    constexpr int NS = 2 * H;                  // rows (columns) a difference or central stencil spans
+    constexpr int CELLS = strip_cells(ORDER);  // columns a wave updates
+    constexpr int ROW = 64 + 2 * G;            // row buffer: lane l's node at l + H
+    static_assert(CELLS == 64 - 2 * G, "a lane per column, halo included");
+    constexpr int NWV = BLOCK / 64, PENDING = 16;
+    __shared__ double rows[NWV][7][ROW];
+    __shared__ WaveMax maxima[STEP ? NWV : 1];
+    __shared__ FixEntry pending[NWV][PENDING];
+
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double(&rb)[7][ROW] = rows[wv];
+    const int n_inst = P.hdr->n_inst;
+    const long long units = P.hdr->units_total;
+    if (P.fix_zero && blockIdx.x == 0 && threadIdx.x < FIX_RANGES) gmem(P.fix_zero)[FIX_COUNTER_STRIDE * threadIdx.x] = 0u;
+    // Consecutive units (neighbouring strips of the same rows, which share their halo
+    // columns) go to one XCD's L2: workgroups are dealt to the eight XCDs in turn.
+    const unsigned g = gridDim.x;
+    const unsigned blk = g % 8 == 0 ? (blockIdx.x % 8) * (g / 8) + blockIdx.x / 8 : blockIdx.x;
+    const long long stride = (long long)g * NWV;
+    // threshold of the bound (it and the indicators differ by rounding); delta = 0
+    // leaves every face to the selection
+    const double thr = P.delta > 0.0 && !(P.flags & KF_FULL_SELECTION) ? 2.0 * P.delta * (1.0 - 1.0 / 1024.0) : -1.0;
+
+    const RkWeights rk = rk_weights(P.mode);
+    WaveMax &M = maxima[STEP ? wv : 0];
+    unsigned long long bad = 0;
+    if (STEP) {
+#pragma unroll
+        for (int i = 0; i < 7; ++i) M.v[i][lane] = 0ull;
+    }
+    // the pending entries of a unit to its range's list
+    unsigned npend = 0;
+    const unsigned per_range = fix_range_units(units);
+    auto flush_pending = [&](long long unit) {
+        if (npend == 0) return;
+        wave_sync();
+        const unsigned range = (unsigned)unit / per_range;
+        unsigned at = 0;
+        if (lane == 0)
+            at = __hip_atomic_fetch_add(gmem(P.fix_count) + range * FIX_COUNTER_STRIDE, npend, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+        const long long base = fix_list_start(P, n_inst, (long long)range * per_range);
+        if ((unsigned)lane < 4 * npend) {
+            const unsigned long long *src = &pending[wv][0].where;
+            gmem(P.fix_list)[4 * (base + uniform(at)) + lane] = src[lane];
+        }
+        wave_sync();
+        npend = 0;
+    };
+    GridView v;
+    v.u0 = 0;
+    v.u1 = -1;
+    bool have = false;
+    for (long long unit = (long long)blk * NWV + wv; unit < units; unit += stride) {
+        if (unit >= v.u1) {
+            if (STEP && have) wave_flush(&M, 1, bad, v.amax, v.ctrl, P.r_out);
+            bad = 0;
+            v = grid_view<ORDER, CH>(P, n_inst, unit);
+            have = v.active != 0;
+        }
+        if (!have) continue;
+        static_assert(amax_slot_words(EULER2D) == 64, "a lane per word of a slot");
+        if (STEP && P.r_zero >= 0 && unit == v.u0) v.amax[P.r_zero * 64 + lane] = 0ull;
+        const int nx = v.nx, ny = v.ny;
+        const long long plane = (long long)v.pitch * ny;
+        const UnitBox box = unit_box(v, unit, CELLS);
+        const int x0 = box.x0, y0 = box.y0, y1 = box.y1;
+        const int xn = x0 - G + lane;
+        const Off xc = 8 * (Off)bc_map(xn, nx, v.bcx);  // byte offset along a row
+        const bool cell = lane >= G && lane < 64 - G && xn < nx;
+        const bool face = lane >= H && lane < 64 - G && xn < nx;
+        // rows y0 - H .. y1 - 1 + H, the newest r; w[.][NS-1] is row r.  Quantities: rho,
+        // n, m, E (n the momentum along y) and the y-fluxes of n, m, E.  Row r completes
+        // the y-face between rows r - H and r - H + 1 and with it the cells of row r - H.
+        double w[7][NS];
+        double pre[4];
+        NodePrim pl;                      // row r - H
+        double Gm[4];                     // y-flux below row r - H
+        unsigned long long fail_b = 0;    // its faces that need a selection
+        auto load_row = [&](int r) {
+            const int y = r < 0 || r >= ny ? bc_map(r, ny, v.bcy) : r;
+            const GMEM double *p = v.in + (long long)y * v.pitch;
+            pre[0] = row_load(p, xc);
+            pre[1] = row_load(p + 2 * plane, xc);
+            pre[2] = row_load(p + plane, xc);
+            pre[3] = row_load(p + 3 * plane, xc);
+        };
+        auto flux_row = [&](int t) {
+            const double rho = w[0][t], n = w[1][t], m = w[2][t], E = w[3][t];
+            const double ir = rcp_nr(rho), u = m * ir, vv = n * ir;
+            const double p = node_pressure(rho, u, vv, E, P.gm1);
+            w[4][t] = fma(n, vv, p);
+            w[5][t] = n * u;
+            w[6][t] = (E + p) * vv;
+        };
+        const int rend = y1 + H;
+        // the rows above the unit's first face, their loads in flight together
+#pragma unroll
+        for (int t = 1; t < NS; ++t) {
+            load_row(y0 - H + t - 1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[q][t] = pre[q];
+        }
+        load_row(y0 + H - 1);
+#pragma unroll
+        for (int t = 1; t < NS; ++t) flux_row(t);
+        pl = node_prim(w[0][H], w[2][H], w[1][H], w[3][H], P.gm1);  // row y0 - 1
+#pragma unroll 1
+        for (int r = y0 + H - 1; r < rend; ++r) {
+            const int j = r - H;  // row updated in this pass
+#pragma unroll
+            for (int q = 0; q < 7; ++q)
+#pragma unroll
+                for (int t = 0; t + 1 < NS; ++t) w[q][t] = w[q][t + 1];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[q][NS - 1] = pre[q];
+            if (r + 1 < rend) load_row(r + 1);
+            flux_row(NS - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j >= y0) {
+                // row j for its x-faces below (written early: the y-face's arithmetic covers
+                // the exchange)
+                const double m = w[2][H - 1], E = w[3][H - 1];
+                rb[0][lane + H] = w[0][H - 1];
+                rb[1][lane + H] = m;
+                rb[2][lane + H] = w[1][H - 1];
+                rb[3][lane + H] = E;
+                rb[4][lane + H] = fma(m, pl.u, pl.p);
+                rb[5][lane + H] = m * pl.v;
+                rb[6][lane + H] = (E + pl.p) * pl.u;
+            }
+            const NodePrim pr = node_prim(w[0][H], w[2][H], w[1][H], w[3][H], P.gm1);  // row r - H + 1
+            double Fy[4];
+            unsigned long long fail_t;
+            {
+                // y-face j + 1/2
+                double sF[4], dU[4], dF[3];
+                sF[0] = T::sym1(w[1], 1);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    sF[k + 1] = T::sym1(w[4 + k], 1);
+                    dF[k] = T::diff(w[4 + k], 1);
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) dU[c] = T::diff(w[c], 1);
+                __builtin_amdgcn_sched_barrier(0);
+                RoeState ro{};
+                if constexpr (CH) ro = roe_state(pl.s, pl.v, pl.u, pl.H, pr.s, pr.v, pr.u, pr.H, P.gm1);
+                top_flux<CH>(ro, sF, dU, v.ay, Fy);
+                const bool ok = row_bound<CH>(ro) * node_bound(dU, dF, v.my) <= thr;
+                fail_t = __builtin_amdgcn_ballot_w64(!ok && cell);
+            }
+            if (REC && v.sel && cell && !((fail_t >> lane) & 1)) {
+                const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    v.sel[8 * xb + i * yb + (long long)(j + 1) * nx + xn] = (uint8_t)(K - 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (j >= y0) {
+                double ub[4] = {0.0, 0.0, 0.0, 0.0};
+                if (STEP && P.mode != M_S1) {
+                    const GMEM double *p = v.base + (long long)j * v.pitch;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) ub[c] = row_load(p + c * plane, xc);
+                }
+                // x-faces of row j: lane l's face is between columns l and l + 1
+                wave_sync();
+                double sx[4], dx[4], df[3];
+#pragma unroll
+                for (int i = 0; i < 7; ++i) {
+                    double win[NS];
+#pragma unroll
+                    for (int t = 0; t < NS; ++t) win[t] = i < 4 && t == H - 1 ? w[i == 1 ? 2 : (i == 2 ? 1 : i)][H - 1] : rb[i][lane + 1 + t];
+                    if (i == 1) sx[0] = T::sym1(win, 1);
+                    if (i >= 4) sx[i - 3] = T::sym1(win, 1);
+                    if (i < 4) dx[i] = T::diff(win, 1);
+                    else df[i - 4] = T::diff(win, 1);
+                    if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                RoeState ro{};
+                if constexpr (CH)
+                    ro = roe_state(pl.s, pl.u, pl.v, pl.H, lane_next(pl.s), lane_next(pl.u), lane_next(pl.v),
+                                   lane_next(pl.H), P.gm1);
+                double Fx[4];
+                top_flux<CH>(ro, sx, dx, v.ax, Fx);
+                const bool ok = row_bound<CH>(ro) * node_bound(dx, df, v.mx) <= thr;
+                const unsigned long long fail_x = __builtin_amdgcn_ballot_w64(!ok && face);
+                if (REC && v.sel && face && !((fail_x >> lane) & 1)) {
+                    const long long xb = (long long)ny * (nx + 1);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        v.sel[i * xb + (long long)j * (nx + 1) + xn + 1] = (uint8_t)(K - 1);
+                }
+                // cells with a face that needs a selection: their maxima are fix_2d's
+                const unsigned long long fixed = fail_x | (fail_x << 1) | fail_b | fail_t;
+                if (fixed) {
+                    const unsigned long long where = (unsigned long long)unit << 28 | (unsigned)(j - y0) << 12;
+                    auto push = [&](int lo, int hi, unsigned long long x, unsigned long long b, unsigned long long t) {
+                        if (!(x | b | t)) return;
+                        if (lane == 0) pending[wv][npend] = FixEntry{where | (unsigned)(lo << 6 | hi), x, b, t};
+                        ++npend;
+                    };
+                    if (__popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t) <= FIX_FACES) {
+                        push(G, 63 - G, fail_x, fail_b, fail_t);
+                    } else {
+#pragma unroll 1
+                        for (int lo = G; lo < min(64 - G, nx - x0 + G); lo += FIX_SPLIT) {  // (pieces with cells: the list's places)
+                            const unsigned long long m = ((1ull << FIX_SPLIT) - 1) << lo;
+                            push(lo, min(lo + FIX_SPLIT, 64 - G) - 1, fail_x & (m | m >> 1), fail_b & m, fail_t & m);
+                        }
+                    }
+                    if (npend > PENDING - 4) flush_pending(unit);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                const int perm[4] = {0, 2, 1, 3};
+                double L[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const double lx = -(Fx[c] - lane_prev(Fx[c])) * v.idx;
+                    L[c] = lx - (Fy[perm[c]] - Gm[perm[c]]) * v.idy;
+                }
+                bool b = false;
+                if (cell) {
+                    const long long o = (long long)j * v.pitch;
+                    if constexpr (!STEP) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) row_store(v.out + o + c * plane, xc, L[c]);
+                    } else {
+                        double Un[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            Un[c] = fma(rk.base, ub[c], rk.y * fma(v.dt, L[c], w[perm[c]][H - 1]));
+                            row_store(v.out + o + c * plane, xc, Un[c]);
+                        }
+                        if (!((fixed >> lane) & 1)) b = wave_max_add(M, lane, Un, P.gamma, v.idx, v.idy);
+                    }
+                }
+                if (STEP) bad |= __builtin_amdgcn_ballot_w64(b);
+                wave_sync();
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Gm[c] = Fy[c];
+            fail_b = fail_t;
+            pl = pr;
+        }
+        flush_pending(unit);
+    }
+    if constexpr (STEP) {
+        // The waves of a workgroup that end in one member (mostly all) flush together:
+        // every wave's atomics go to the member's one cache line (with 1800 waves doing
+        // so by themselves a stage of 504 x 400 nodes took 28 us against 17.5 without).
+        __shared__ int last[NWV];
+        if (lane == 0) last[wv] = have ? v.k : -1;
+        if (bad && lane == 0) __hip_atomic_fetch_or(&v.ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        bool same = have;
+#pragma unroll
+        for (int k = 0; k < NWV; ++k) same = same && (last[k] == v.k || last[k] < 0);
+        if (same) {
+            // the first wave with work; the others' columns are its, or zero
+            int k0 = 0;
+#pragma unroll
+            for (int k = NWV - 1; k >= 0; --k) k0 = last[k] >= 0 ? k : k0;
+            if (wv == k0) wave_flush(maxima, NWV, 0ull, v.amax, v.ctrl, P.r_out);
+        } else if (have) {
+            wave_flush(&M, 1, 0ull, v.amax, v.ctrl, P.r_out);
+        }
+    }
+}
+
+// Scratch of a wave of fix_2d (LDS).  A row segment has at most 57 x-faces and 56
+// y-faces on either side.
+template <int NW> struct FixScratch {
+    double dF[3][4][58];       // flux corrections by set (x, below, above) and lane from H on
+    double exchange[NW][64];   // window values by node and (face, field)
+    unsigned char face[176];   // set << 6 | lane of each face
+};
+
+// A face's line along x or y: window node t is pos + t on it
+template <class Off> struct FixLine {
+    bool x;
+    int pos, row, col;
+    // nodes t0 .. t0 + N - 1 (the last node for those past it) of a window of NW
+    template <int NW, int N>
+    __device__ __forceinline__ void load(const GridView &v, long long plane, int t0, double (&U)[N][4]) const
+    {
+        const int n = x ? v.nx : v.ny;
+        const bool off = pos < 0 || pos + NW > n;  // the window crosses the boundary
+        const bool any = __builtin_amdgcn_ballot_w64(off) != 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            int k = pos + min(t0 + i, NW - 1);
+            if (any) k = k < 0 || k >= n ? bc_map(k, n, x ? v.bcx : v.bcy) : k;
+            const Off o = 8 * (x ? (Off)row * v.pitch + k : (Off)k * v.pitch + col);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) U[i][c] = row_load(v.in + c * plane, o);
+        }
+    }
+};
+
+// A wave takes one listed row segment at a time (handing them out from a counter took
+// longer than the imbalance it removed, 20 ns each).  Where the
+// list is short the four waves of a
+// workgroup share each segment instead.  One lane per face and field for the
+// selection, one lane per cell for the update.  stage_2d gave the fields' top values;
+// a field that chooses another candidate on either side contributes the difference.
+template <int ORDER, bool STEP, bool REC, bool CH>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves(ORDER)))) void fix_2d(KParams P)
+{
+    using R = Recon<ORDER>;
+    using Off = std::conditional_t<REC, long long, unsigned>;
+    constexpr int H = R::H, G = H + 1, NW = 2 * H + 2, K = R::K, CELLS = strip_cells(ORDER), NWV = BLOCK / 64;
+    __shared__ FixScratch<NW> scratch[NWV];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_inst = P.hdr->n_inst;
+    // lane c: list c's first entry, and the entries of the lists up to it
+    const long long units = P.hdr->units_total;
+    const unsigned per_range = fix_range_units(units);
+    unsigned upto = lane < FIX_RANGES ? gmem(P.fix_count)[lane * FIX_COUNTER_STRIDE] : 0u;
+    const unsigned mine_n = upto;
+    const long long list0 = upto ? fix_list_start(P, n_inst, (long long)lane * per_range) : 0ll;
+#pragma unroll
+    for (int o = 1; o < FIX_RANGES; o *= 2) {
+        const unsigned x = __shfl_up(upto, o, 64);
+        upto += lane >= o ? x : 0u;
+    }
+    const unsigned count = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1);
+    if (count == 0) return;
+    const long long list_skew = list0 - (long long)(upto - mine_n);  // entry i of all is at i + list_skew
+    const bool team = count <= gridDim.x;
+    const unsigned stride = team ? gridDim.x : gridDim.x * NWV;
+    unsigned at = team ? blockIdx.x : blockIdx.x * NWV + wv, next_at = at + stride;
+    FixScratch<NW> &S = scratch[team ? 0 : wv];
+    const int start = team ? 64 * wv : 0, step = team ? BLOCK : 64;
+    auto sync = [&]() {
+        if (team) __syncthreads();
+        else wave_sync();
+    };
+    auto load_entry = [&](unsigned i) {
+        if (i >= count) return 0ull;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(lane < FIX_RANGES && upto <= i));
+        const long long e = i + (long long)lane_bits((unsigned long long)list_skew, c);
+        return lane < 4 ? gmem(P.fix_list)[4 * e + lane] : 0ull;
+    };
+    const RkWeights rk = rk_weights(P.mode);
+    unsigned long long bad = 0, next = load_entry(at);
+    double mine = 0.0;  // lane i: the wave's maximum of value i
+    const int ld = min(max(lane - H, 0), 57);  // (lanes outside repeat the first and last)
+    GridView v;
+    v.u0 = 0;
+    v.u1 = -1;
+    auto flush = [&]() {
+        if (lane < 7)
+            __hip_atomic_fetch_max(&v.amax[P.r_out * amax_slot_words(EULER2D) + blockIdx.x % amax_copies(EULER2D) * AMAX_VALS + lane],
+                                   as_bits(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (bad && lane == 0) __hip_atomic_fetch_or(&v.ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mine = 0.0;
+        bad = 0;
+    };
+    while (at < count) {
+        {
+            const unsigned long long where = lane_bits(next, 0), fx = lane_bits(next, 1), fb = lane_bits(next, 2),
+                                     ft = lane_bits(next, 3);
+            next = load_entry(next_at);  // on its way while this one is worked on
+            const long long unit = (long long)(where >> 28);
+            const int lo = (int)(where >> 6) & 63, hi = (int)where & 63;  // lanes of its cells
+            if (unit < v.u0 || unit >= v.u1) {
+                if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();
+                v = grid_view<ORDER, CH>(P, n_inst, unit);
+            }
+            const int nx = v.nx, ny = v.ny;
+            const long long plane = (long long)v.pitch * ny;
+            const UnitBox box = unit_box(v, unit, CELLS);
+            const int x0 = box.x0, j = box.y0 + (int)((where >> 12) & 0xffff);
+            // the faces: x, below, above
+            int nf = 0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const unsigned long long m = k == 0 ? fx : (k == 1 ? fb : ft);
+                if (!team || wv == k) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) S.dF[k][c][ld] = 0.0;
+                    if ((m >> lane) & 1)
+                        S.face[nf + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] =
+                            (unsigned char)(k << 6 | lane);
+                }
+                nf += __popcll(m);
+            }
+            // the cells, their top values on the way while the faces are selected
+            const unsigned long long fixed = fx | (fx << 1) | fb | ft;
+            const int xn = x0 - G + lane;
+            const bool cell = (!team || wv == 0) && ((fixed >> lane) & 1) && lane >= lo && lane <= hi && xn < nx;
+            GMEM double *out = v.out + (long long)j * v.pitch + xn;
+            double Uc[4] = {0.0, 0.0, 0.0, 0.0};
+            if (cell) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) Uc[c] = out[c * plane];
+            }
+            sync();
+            auto line = [&](unsigned f) {
+                const int col = x0 - G + (int)(f & 63u);
+                return FixLine<Off>{f < 64u, f < 64u ? col - H : (f < 128u ? j - 1 : j) - H, j, col};
+            };
+            auto alpha = [&](bool x, int s) {
+                const double a0 = x ? v.rx[0] : v.ry[0], a1 = x ? v.rx[1] : v.ry[1], a2 = x ? v.rx[2] : v.ry[2];
+                return s == 0 ? a0 : (s == 3 ? a2 : a1);
+            };
+#pragma unroll 1
+            for (int k0 = start; k0 < 4 * nf; k0 += step) {
+            const bool valid = k0 + lane < 4 * nf;
+            const int k = min(k0 + lane, 4 * nf - 1), s = k & 3;
+            const unsigned f = S.face[k >> 2], set = f >> 6;
+            const bool acoustic = CH && (s == 0 || s == 3);
+            const FixLine<Off> l = line(f);
+            const double a = alpha(l.x, s);
+            // The four lanes of a face share its window: each loads a quarter of the nodes
+            // and projects them on all fields, and takes its field of the others' from LDS
+            // (every lane loading the whole window took twice as long, half of it in the
+            // loads).
+            constexpr int NPL = (NW + 3) / 4;
+            double Q[NPL][4];
+            l.template load<NW, NPL>(v, plane, s * NPL, Q);
+            double U[NPL][4], F[NPL][4], hh[NPL];
+#pragma unroll
+            for (int i = 0; i < NPL; ++i) {
+                const double rho = Q[i][0], m = l.x ? Q[i][1] : Q[i][2], n = l.x ? Q[i][2] : Q[i][1], E = Q[i][3];
+                const double ir = rcp_nr(rho), u = m * ir, w = n * ir;
+                const double p = node_pressure(rho, u, w, E, P.gm1);
+                U[i][0] = rho;
+                U[i][1] = m;
+                U[i][2] = n;
+                U[i][3] = E;
+                F[i][0] = m;
+                F[i][1] = fma(m, u, p);
+                F[i][2] = m * w;
+                F[i][3] = (E + p) * u;
+                hh[i] = (E + p) * ir;
+                Q[i][1] = u;
+                Q[i][2] = w;
+            }
+            RoeState ro{};
+            if constexpr (CH) {
+                // nodes H and H + 1 from the lanes that hold them
+                constexpr int iL = H % NPL, iR = (H + 1) % NPL;
+                constexpr int fromL = 0x55 * (H / NPL), fromR = 0x55 * ((H + 1) / NPL);  // quad_perm broadcasts
+                ro = roe_state(sqrt_nr(dpp_move<fromL>(Q[iL][0])), dpp_move<fromL>(Q[iL][1]), dpp_move<fromL>(Q[iL][2]),
+                               dpp_move<fromL>(hh[iL]), sqrt_nr(dpp_move<fromR>(Q[iR][0])), dpp_move<fromR>(Q[iR][1]),
+                               dpp_move<fromR>(Q[iR][2]), dpp_move<fromR>(hh[iR]), P.gm1);
+            }
+            // windows g+ and g- = P F +- a P U; a lane's columns are rotated by its place in
+            // the quad, so the four writes of an instruction fall in different banks
+            double pu[NW], gp[2 * H + 1], gm[2 * H + 1];
+            double(&X)[NW][64] = scratch[wv].exchange;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int i = 0; i < NPL; ++i) {
+                    double w[4];
+                    to_fields<4, CH>(ro, h == 0 ? U[i] : F[i], w);
+                    const int t = s * NPL + i;
+                    if (4 * NPL == NW || t < NW) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) X[t][(lane & 60) + ((c + s) & 3)] = w[c];
+                    }
+                }
+                wave_sync();
+#pragma unroll
+                for (int t = 0; t < NW; ++t) {
+                    const double x = X[t][(lane & 60) + ((s + t / NPL) & 3)];
+                    if (h == 0) {
+                        pu[t] = x;
+                    } else {
+                        if (t <= 2 * H) gp[t] = fma(a, pu[t], x);
+                        if (t >= 1) gm[2 * H + 1 - t] = fma(-a, pu[t], x);
+                    }
+                }
+                wave_sync();
+            }
+            const double sd = (acoustic ? 4.0 : 2.0) * P.delta;
+            int sp, sm;
+            double tp, tm;
+            const double hp = R::select_top(gp, sd, sp, tp);
+            __builtin_amdgcn_sched_barrier(0);
+            const double hm = R::select_top(gm, sd, sm, tm);
+            if (REC && v.sel && valid) {
+                const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
+                const long long o = l.x ? 2 * s * xb + (long long)l.row * (nx + 1) + l.col + 1
+                                        : 8 * xb + 2 * s * yb + (long long)(set == 1u ? l.row : l.row + 1) * nx + l.col;
+                v.sel[o] = (uint8_t)sp;
+                v.sel[o + (l.x ? xb : yb)] = (uint8_t)sm;
+            }
+            // R de, summed over the face's four lanes; lane s stores component s
+            const double es = sp == K - 1 && sm == K - 1 ? 0.0 : ((hp - tp) + (hm - tm)) * (acoustic ? 0.25 : 0.5);
+            double d = es;
+            if constexpr (CH) {
+                const double e[4] = {s == 0 ? es : 0.0, s == 1 ? es : 0.0, s == 2 ? es : 0.0, s == 3 ? es : 0.0};
+                double r[4];
+                back_project<4>(ro, e, r);
+                const double d0 = quad_sum(r[0]), d1 = quad_sum(r[1]), d2 = quad_sum(r[2]), d3 = quad_sum(r[3]);
+                d = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
+            }
+            if (valid) S.dF[set][s][(f & 63u) - H] = d;
+        }
+            sync();
+            bool b = false;
+            Maxima<EULER2D> m;
+            m.reset();
+            if (cell) {
+                const int perm[4] = {0, 2, 1, 3};
+                double U[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const double lx = -(S.dF[0][c][ld] - S.dF[0][c][ld - 1]) * v.idx;
+                    const double dL = lx - (S.dF[2][perm[c]][ld] - S.dF[1][perm[c]][ld]) * v.idy;
+                    U[c] = STEP ? fma(rk.y * v.dt, dL, Uc[c]) : Uc[c] + dL;
+                    out[c * plane] = U[c];
+                }
+                if (STEP) m.add(U, P.gamma, v.idx, v.idy);
+                b = m.bad != 0;
+            }
+            if (STEP && (!team || wv == 0)) {
+                bad |= __builtin_amdgcn_ballot_w64(b);
+#pragma unroll
+                for (int i = 0; i < 7; ++i) {
+                    const double x = wave_max(m.v[i]);
+                    if (lane == i) mine = fmax(mine, x);
+                }
+            }
+            sync();
+            at = next_at;
+            next_at = at + stride;
+        }
+    }
+    if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();
+}
+
+// ---------------------------------------------------------------------------
+using KFn = void (*)(KParams);
+
+template <bool FIX, int ORDER, bool REC, bool CH> static KFn pick_step(int mode)
+{
+    if (mode == M_RHS) return FIX ? fix_2d<ORDER, false, REC, CH> : stage_2d<ORDER, false, REC, CH>;
+    return FIX ? fix_2d<ORDER, true, REC, CH> : stage_2d<ORDER, true, REC, CH>;
+}
+template <bool FIX, bool CH> static KFn pick_order(int order, int mode, bool rec)
+{
+    if (order == 7) return rec ? pick_step<FIX, 7, true, CH>(mode) : pick_step<FIX, 7, false, CH>(mode);
+    return rec ? pick_step<FIX, 5, true, CH>(mode) : pick_step<FIX, 5, false, CH>(mode);
+}
+template <bool FIX> static KFn pick(int order, int mode, bool rec, bool ch)
+{
+    return ch ? pick_order<FIX, true>(order, mode, rec) : pick_order<FIX, false>(order, mode, rec);
+}
+
+hipError_t launch_stage_2d(int order, int mode, bool rec, bool ch, const KParams &p, int grid, int fix_grid, hipStream_t s)
+{
+    KParams copy = p;
+    copy.mode = mode;
+    void *args[] = {&copy};
+    const hipError_t e = hipLaunchKernel((const void *)pick<false>(order, mode, rec, ch), dim3(grid > 0 ? grid : 1),
+                                         dim3(BLOCK), args, 0, s);
+    if (e != hipSuccess) return e;
+    return hipLaunchKernel((const void *)pick<true>(order, mode, rec, ch), dim3(fix_grid > 0 ? fix_grid : 1), dim3(BLOCK),
+                           args, 0, s);
+}
+
+static int occupancy(KFn fn)
+{
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)fn, BLOCK, 0) != hipSuccess || n < 1) n = 1;
+    return n;
+}
+
+int occupancy_2d(int order, int mode, bool rec, bool ch) { return occupancy(pick<false>(order, mode, rec, ch)); }
+int occupancy_fix_2d(int order, int mode, bool rec, bool ch) { return occupancy(pick<true>(order, mode, rec, ch)); }
+
+}  // namespace enoao

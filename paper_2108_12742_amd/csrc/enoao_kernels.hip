@@ -1,27 +1,26 @@
 // enoao_kernels.hip -- gfx950 kernels of the ENO-AO path.
 //
-// Per Runge-Kutta stage (Section 2: conservative finite differences, global
-// Lax-Friedrichs splitting, third-order TVD Runge-Kutta; Section 3: ENO-AO
-// reconstruction; Section 4: Roe characteristic decomposition):
-//   1D:  sweep_x<STAGE s>   tile load + BC -> per-node flux and Roe inputs in
-//        LDS -> one lane per face: projection, split, indicators, selection,
-//        candidate flux, back-projection -> flux difference -> RK stage
-//        combine -> per-field maxima of the new state for the next stage.
-//   2D:  sweep_x<STAGE s> writes the x-part of L; sweep_y<STAGE s> adds the
-//        y-part (dimension by dimension, both on the same stage state) and
-//        does the RK combine and the maxima.
-// Kernels are persistent: a grid of (CUs x occupancy) workgroups walks a
-// contiguous chunk of the flattened tile list of all instances of a batch.
-// Every face takes each field's top candidate in conserved-variable form and
-// runs the full selection only for the fields of a wave that need it (the
-// x-sweeps stage the top differences per node pair in LDS; the y-sweep and the
-// LDS-resident solver form them per face, which their LDS budgets require).
+// Per Runge-Kutta stage of a 1D problem (Section 2: conservative finite
+// differences, global Lax-Friedrichs splitting, third-order TVD Runge-Kutta;
+// Section 3: ENO-AO reconstruction; Section 4: Roe characteristic decomposition):
+//   sweep_x<STAGE s>   tile load + BC -> per-node flux and Roe inputs in LDS ->
+//        one lane per face: projection, split, indicators, selection, candidate
+//        flux, back-projection -> flux difference -> RK stage combine ->
+//        per-field maxima of the new state for the next stage.
+// (2D stages: enoao_grid.hip.)  Kernels are persistent: a grid of (CUs x
+// occupancy) workgroups walks a contiguous chunk of the flattened tile list of
+// all instances of a batch.  Every face takes each field's top candidate in
+// conserved-variable form and runs the full selection only for the fields of a
+// wave that need it (the sweeps stage the top differences per node pair in LDS;
+// the LDS-resident solver forms them per face).  The time-loop control and the
+// maxima of an input state, in 1D and 2D, are here too.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "enoao_common.hpp"
 #include "enoao_device.hpp"
 #include "enoao_kernels.hpp"
+#include "enoao_wave.hpp"
 
 // Tuning switches (defaults are the measured best on gfx950).
 #ifndef ENOAO_NODE_PREFETCH
@@ -33,140 +32,6 @@
 
 namespace enoao {
 
-// Workgroups sharing a persistent launch's tile list of T tiles: the whole
-// grid, or for a pool as many as give P.tiles_per_wg tiles each (at least
-// P.grid_min, at most the grid).  A pool's grid covers the machine several
-// times over; many small chunks let the workgroups that finish early take
-// more of them, which evens out members of uneven cost, while a pool holding
-// few tiles keeps chunks long enough for the y walks' row reuse.
-__device__ __forceinline__ long long chunk_groups(const KParams &P, long long T)
-{
-    const long long g = gridDim.x;
-    if (P.tiles_per_wg <= 0) return g;
-    return min(g, max((long long)P.grid_min, T / P.tiles_per_wg));
-}
-
-__device__ __forceinline__ int bc_map(int k, int n, int bc)
-{
-    if (bc == BC_PERIODIC) {
-        int r = k % n;
-        return r < 0 ? r + n : r;
-    }
-    return k < 0 ? 0 : (k >= n ? n - 1 : k);
-}
-
-// Device-memory pointers.  The state and control pointers reach a kernel through
-// the instance table in memory, so the compiler cannot tell that they address
-// global memory and would emit flat instructions for them.  Flat loads and
-// stores count against the LDS counter too, so every wait for an LDS read would
-// also wait for the next tile's global prefetch in flight (and for the previous
-// tile's stores).  Typed as global they compile to global instructions.
-#define GMEM __attribute__((address_space(1)))
-template <typename T> __device__ __forceinline__ GMEM T *gmem(T *p) { return (GMEM T *)p; }
-
-// wave-uniform copy of a value (scalar registers)
-template <typename T> __device__ __forceinline__ T uniform(T x)
-{
-    static_assert(sizeof(T) % 4 == 0, "32-bit multiple");
-    union { T v; int w[sizeof(T) / 4]; } a;
-    a.v = x;
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) a.w[i] = __builtin_amdgcn_readfirstlane(a.w[i]);
-    return a.v;
-}
-
-__device__ __forceinline__ double as_double(unsigned long long b) { return __longlong_as_double((long long)b); }
-__device__ __forceinline__ unsigned long long as_bits(double d) { return (unsigned long long)__double_as_longlong(d); }
-
-template <bool X>
-__device__ __forceinline__ int find_inst(const Inst *inst, int n, long long tile)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        const long long t0 = X ? inst[mid].xtile0 : inst[mid].ytile0;
-        if (t0 <= tile) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// ---------------------------------------------------------------------------
-// Maxima of the per-field wave speeds of a state (for alpha of the next
-// evaluation and for the CFL step), and the non-physical flag.
-template <int EQ> struct Maxima {
-    static constexpr int NV = EQ == EULER2D ? 7 : (EQ == EULER1D ? 3 : 0);  // values in use
-    double v[7];
-    int bad;
-    __device__ void reset()
-    {
-#pragma unroll
-        for (int i = 0; i < 7; ++i) v[i] = 0.0;
-        bad = 0;
-    }
-    // U in the natural component order; idx, idy = 1/dx, 1/dy
-    __device__ void add(const double *U, double gamma, double idx, double idy)
-    {
-        if constexpr (EQ == ADVECTION) {
-            bad |= !(U[0] == U[0]);
-        } else if constexpr (EQ == EULER1D) {
-            const double rho = U[0], ir = rcp_nr(rho), u = U[1] * ir;
-            const double p = (gamma - 1.0) * fma(-0.5 * rho, u * u, U[2]);
-            const double c = sqrt_nr(gamma * p * ir);
-            bad |= !(rho > 0.0 && p > 0.0);
-            v[0] = fmax(v[0], fabs(u - c));
-            v[1] = fmax(v[1], fabs(u));
-            v[2] = fmax(v[2], fabs(u + c));
-        } else {
-            const double rho = U[0], ir = rcp_nr(rho), u = U[1] * ir, w = U[2] * ir;
-            const double p = (gamma - 1.0) * fma(-0.5 * rho, fma(u, u, w * w), U[3]);
-            const double c = sqrt_nr(gamma * p * ir);
-            bad |= !(rho > 0.0 && p > 0.0);
-            v[0] = fmax(v[0], fabs(u - c));
-            v[1] = fmax(v[1], fabs(u));
-            v[2] = fmax(v[2], fabs(u + c));
-            v[3] = fmax(v[3], fabs(w - c));
-            v[4] = fmax(v[4], fabs(w));
-            v[5] = fmax(v[5], fabs(w + c));
-            v[6] = fmax(v[6], fma(fabs(u) + c, idx, (fabs(w) + c) * idy));
-        }
-    }
-    // workgroup reduction, then one atomic per value into the instance's slot
-    __device__ void flush(GMEM unsigned long long *amax, GMEM Ctrl *ctrl, int slot, double *red)
-    {
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            double x = v[i];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-            v[i] = x;
-        }
-        int b = bad;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) b |= __shfl_xor(b, o, 64);
-        if (lane == 0) {
-#pragma unroll
-            for (int i = 0; i < NV; ++i) red[wave * 8 + i] = v[i];
-            red[wave * 8 + 7] = (double)b;
-        }
-        __syncthreads();
-        if (threadIdx.x < NV || threadIdx.x == 7) {
-            double x = red[threadIdx.x];
-            for (int w = 1; w < BLOCK / 64; ++w) x = fmax(x, red[w * 8 + threadIdx.x]);
-            if (threadIdx.x < NV) {
-                if (slot >= 0)
-                    __hip_atomic_fetch_max(&amax[slot * AMAX_VALS + threadIdx.x], as_bits(x), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-            } else if (x != 0.0) {
-                __hip_atomic_fetch_or(&ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        __syncthreads();
-        reset();
-    }
-};
-
 // ---------------------------------------------------------------------------
 // One face: window node t (t = 0 .. 2G-1) of face j+1/2 is node j-H+t; the
 // plus side reads nodes j-H .. j+H, the minus side the mirror j+1+H .. j+1-H.
@@ -176,37 +41,6 @@ template <int EQ> struct Maxima {
 // projected symmetric stencil of F give both sides' top indicators and the sum
 // of both sides' top values, on the window scale 2 field_scale (the windows
 // below are g = P F +/- alpha P U with the scaled projection P).
-// Reconstruction variables.  CH: the characteristic fields of the face's Roe
-// state (Section 4), with the scaled projection and the field scales above;
-// otherwise the conserved components themselves (identity projection, scale 1,
-// and one alpha for all of them).
-template <int NC, bool CH>
-__device__ __forceinline__ void to_fields(const RoeState &r, const double (&x)[NC], double (&w)[NC])
-{
-    if constexpr (CH) {
-        project<NC>(r, x, w);
-    } else {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) w[c] = x[c];
-    }
-}
-
-template <int NC, bool CH>
-__device__ __forceinline__ void from_fields(const RoeState &r, const double (&w)[NC], double (&F)[NC])
-{
-    if constexpr (CH) {
-        back_project<NC>(r, w, F);
-    } else {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) F[c] = w[c];
-    }
-}
-
-template <int NC, bool CH> __device__ __forceinline__ constexpr double fscale(int s)
-{
-    return CH ? field_scale<NC>(s) : 1.0;
-}
-
 template <int NC> struct TopForm {
     double is[NC][2];  // IS_top of the plus and minus side
     double hs[NC];     // plus + minus top value
@@ -439,20 +273,6 @@ __device__ __forceinline__ void stage_diff2(const double *x, int qs, int ns, dou
     }
 }
 
-// RK stage combine (Shu-Osher form): s = 1: in + dt L; s = 2: 3/4 base +
-// 1/4 (in + dt L); s = 3: 1/3 base + 2/3 (in + dt L).
-template <int MODE>
-__device__ __forceinline__ double rk_combine(double in, double base, double dt, double L)
-{
-    const double y = fma(dt, L, in);
-    if constexpr (MODE == M_S1) return y;
-    else if constexpr (MODE == M_S2) return fma(0.75, base, 0.25 * y);
-    else return fma(1.0 / 3.0, base, (2.0 / 3.0) * y);
-}
-
-// 2D stages: the x-sweep writes its part of L, the y-sweep adds its own and
-// applies the combine to L = L_x + L_y.
-
 // Per-instance values of one sweep launch.  A workgroup walks a contiguous
 // chunk of the tile list, so it reloads them only when the walk crosses into
 // another instance; within an instance no tile reads a descriptor.
@@ -476,28 +296,27 @@ template <int EQ, int MODE> struct View {
 // (-1 at the start of a chunk: binary search); the tile lists are ordered by
 // instance, so after the first the walk just moves on to the next instance
 // that has tiles left.
-template <int EQ, int MODE, bool Y, bool CH>
+template <int EQ, int MODE, bool CH>
 __device__ __forceinline__ View<EQ, MODE> load_view(const KParams &P, int n_inst, long long tile, int prev)
 {
     constexpr int NC = NodeTraits<EQ>::NC;
     View<EQ, MODE> v;
     int k;
     if (prev < 0) {
-        k = find_inst<!Y>(P.inst, n_inst, tile);
+        k = find_inst<true>(P.inst, n_inst, tile);
     } else {
         k = prev + 1;
-        while (k < n_inst - 1 && tile >= (Y ? P.inst[k].ytile0 + P.inst[k].ytiles : P.inst[k].xtile0 + P.inst[k].xtiles))
-            ++k;
+        while (k < n_inst - 1 && tile >= P.inst[k].xtile0 + P.inst[k].xtiles) ++k;
     }
     v.k = uniform(k);
     const Inst &I = P.inst[v.k];
-    v.t0 = uniform(Y ? I.ytile0 : I.xtile0);
-    v.t1 = v.t0 + uniform(Y ? I.ytiles : I.xtiles);
+    v.t0 = uniform(I.xtile0);
+    v.t1 = v.t0 + uniform(I.xtiles);
     v.nx = uniform(I.nx);
     v.ny = uniform(I.ny);
     v.pitch = uniform(I.pitch);
-    v.per_row = uniform(Y ? I.ytiles_per_row : I.segs_per_row);
-    v.bc = uniform(Y ? I.bcy : I.bcx);
+    v.per_row = uniform(I.segs_per_row);
+    v.bc = uniform(I.bcx);
     v.ctrl = gmem(uniform(I.ctrl));
     v.active = uniform(v.ctrl->done) == 0;
     v.dt = uniform(v.ctrl->dt);
@@ -507,9 +326,8 @@ __device__ __forceinline__ View<EQ, MODE> load_view(const KParams &P, int n_inst
     v.lx = gmem(uniform(I.lx));
     v.sel = gmem(uniform(I.sel));
     if (v.sel && P.sel_slot > 0) {
-        // records of one evaluation: x block [NC][2][ny][nx+1], then in 2D the y block [NC][2][ny+1][nx]
-        const long long rec = (long long)NC * 2 * v.ny * (v.nx + 1) +
-                              (EQ == EULER2D ? (long long)NC * 2 * (v.ny + 1) * v.nx : 0ll);
+        // records of one evaluation: [NC][2][nx+1]
+        const long long rec = (long long)NC * 2 * v.ny * (v.nx + 1);
         v.sel += (long long)P.sel_slot * rec;
     }
     v.amax = gmem(uniform(I.amax));
@@ -519,7 +337,7 @@ __device__ __forceinline__ View<EQ, MODE> load_view(const KParams &P, int n_inst
     if constexpr (EQ == ADVECTION) {
         v.al[0] = fabs(v.adv);
     } else {
-        const GMEM unsigned long long *a = v.amax + P.r_in * AMAX_VALS + (Y ? 3 : 0);
+        const GMEM unsigned long long *a = v.amax + P.r_in * AMAX_VALS;
         const double m0 = uniform(as_double(a[0])), m1 = uniform(as_double(a[1])), m2 = uniform(as_double(a[2]));
         if constexpr (CH) {
             v.al[0] = m0;
@@ -543,23 +361,14 @@ __device__ __forceinline__ View<EQ, MODE> load_view(const KParams &P, int n_inst
 // Tiles are software-pipelined: the global operands of tile t+1 are loaded into
 // registers while tile t is reconstructed, so the memory latency hides behind
 // the face arithmetic.  Waves per SIMD the register allocation must allow
-// (measured: three for the x-sweep, whose LDS fits three workgroups per CU,
-// except order 7, which spills at three; two for the y-sweep, whose LDS fits
-// two, except order 7, which spills to scratch at two and runs faster at one
-// with its whole working set in registers).
+// (measured: three, the LDS fits three workgroups per CU, except order 7, which
+// spills at three).
 #ifndef ENOAO_X_WAVES_PER_EU
 #define ENOAO_X_WAVES_PER_EU 3
 #endif
 #ifndef ENOAO_X7_WAVES_PER_EU
 #define ENOAO_X7_WAVES_PER_EU 2  // order 7 (spills at three)
 #endif
-#ifndef ENOAO_Y_WAVES_PER_EU
-#define ENOAO_Y_WAVES_PER_EU 2
-#endif
-#ifndef ENOAO_Y7_WAVES_PER_EU
-#define ENOAO_Y7_WAVES_PER_EU 1  // order 7 (spills at two)
-#endif
-
 // a wave's segment within its instance: grid line and segment index along it
 struct XCur {
     int row, segx;
@@ -593,16 +402,6 @@ __device__ __forceinline__ XCur x_next(XCur c, int per_row)
     return c;
 }
 
-// LDS exchange among the lanes of one wave: the wave's LDS operations are
-// performed in order, so a wavefront-scope fence pair around a wave barrier
-// orders each lane's writes before every lane's later reads.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // a lane's global operands of one x tile: the nodes it stages (segment
 // positions lane and lane + 64; for a segment that continues the wave's
 // previous one along its line only the 63 new nodes, positions 2G + lane) and,
@@ -632,7 +431,7 @@ __device__ __forceinline__ void x_prefetch(const View<EQ, MODE> &v, XCur c, bool
 #pragma unroll
         for (int q = 0; q < NC; ++q) pre.U[j][q] = rowp[q * plane + x];
     }
-    if constexpr ((MODE == M_S2 || MODE == M_S3) && EQ != EULER2D) {
+    if constexpr (MODE == M_S2 || MODE == M_S3) {
         const int x = min(sx + lane, nx - 1);
         const GMEM double *b = v.base + (long long)row * v.pitch + x;
 #pragma unroll
@@ -650,7 +449,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 
     constexpr int NNP = NN + 1;
     constexpr int ND = EQ == ADVECTION ? 1 : 2 * NC;  // staged top differences per node
     constexpr int NDN = XW_FACES + 2;                  // nodes with a staged difference
-    constexpr bool FULL = (EQ != EULER2D) && (MODE != M_RHS);  // 1D stage: combine + maxima here
+    constexpr bool FULL = MODE != M_RHS;  // a stage: combine + maxima here
     __shared__ double lds[NQ * XW_SEGS * NNP];
     __shared__ double dif[ND * XW_SEGS * NDN];
     __shared__ double fh[NC * XW_SEGS * XW_FACES];
@@ -676,7 +475,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 
     // waves together).
     int prev = -1;
     for (long long tile = t0; tile < t1;) {
-        const View<EQ, MODE> v = load_view<EQ, MODE, false, CH>(P, n_inst, tile, prev);
+        const View<EQ, MODE> v = load_view<EQ, MODE, CH>(P, n_inst, tile, prev);
         prev = v.k;
         const long long tend = v.t1 < t1 ? v.t1 : t1;
         if (!v.active) {
@@ -764,7 +563,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 
 #pragma unroll
                 for (int q = 0; q < NC; ++q)
                     Lc[q] = -(fh[(q * XW_SEGS + wseg) * XW_FACES + lane + 1] - fh[(q * XW_SEGS + wseg) * XW_FACES + lane]) * v.idx;
-                if constexpr (!FULL) {  // L (rhs) or, in 2D, its x-part
+                if constexpr (!FULL) {  // L
 #pragma unroll
                     for (int q = 0; q < NC; ++q) v.lx[q * plane + o] = Lc[q];
                 } else {
@@ -784,246 +583,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 
         }
         tile = tend;
         if (FULL) mx.flush(v.amax, v.ctrl, P.r_out, red);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// y-sweep (2D).  A workgroup tile is 4 YW columns x 64/YW cell rows; each wave
-// owns a strip of YW columns (lane = YW * row + column) and walks its tiles
-// down the strip.  Successive tiles of a walk share node rows
-// and one face row, so a walk keeps a rolling buffer: after its first tile, a
-// tile copies the 2G-1 node rows it shares with the previous one, stages only
-// 64/YW new rows, reuses the previous tile's last face row, and computes
-// 64/YW new face rows -- one face and one staged node per lane and tile,
-// and every face of the walk is computed once.  Each wave exchanges data only
-// among its own lanes, so the tile loop has no workgroup barrier.  Momentum
-// components are exchanged on load so the x-direction formulas apply.  The
-// next tile's global operands are prefetched into registers.
-// a tile's position within its instance: tile row along y, column group
-struct YCur {
-    int ty, cg;
-};
-
-__device__ __forceinline__ YCur y_cursor(long long tile, long long t0, int per_row)
-{
-    // (tile counts of an instance fit 32 bits)
-    const unsigned tl = (unsigned)(tile - t0), cg = tl / (unsigned)per_row;
-    return YCur{(int)(tl - cg * (unsigned)per_row), (int)cg};
-}
-
-__device__ __forceinline__ YCur y_advance(YCur c, int per_row)
-{
-    if (++c.ty == per_row) {
-        c.ty = 0;
-        ++c.cg;
-    }
-    return c;
-}
-
-// buffer rows of a walk: row b holds node row sy - G + b (sy = first cell row
-// of the tile); face row k (k = 0..64/YW, the face below cell row sy + k)
-// reads buffer rows k .. k + 2G - 1
-template <int G, int YW> struct YBuf {
-    static constexpr int CELLS = yt_cells(YW), COLS = yt_cols(YW);
-    static constexpr int ROWS = CELLS + 2 * G;
-    static constexpr int NODES = ROWS * YW;                // staged by a walk's first tile
-    static constexpr int J = (NODES + 63) / 64;            // nodes per lane then
-    static constexpr int FRESH = 2 * G;                    // first row a later tile stages
-};
-
-template <int G, int YW> struct YPre {
-    double U[YBuf<G, YW>::J][4];
-    double lx[4];    // x-part of L at the lane's cell
-    double base[4];  // u^n at the lane's cell (stages 2 and 3)
-};
-
-// a lane's global operands of one y tile: the strip nodes it stages (all rows
-// for the first tile of a walk, rows FRESH.. for the others), the x-part of L
-// and, for stages 2 and 3, u^n at its cell (lanes past the grid's edge read a
-// clamped, in-bounds address whose value goes unused).
-template <int MODE, int G, int YW>
-__device__ __forceinline__ void y_prefetch(const View<EULER2D, MODE> &v, YCur c, bool first, int wv, int lane,
-                                           YPre<G, YW> &pre)
-{
-    using B = YBuf<G, YW>;
-    const int perm[4] = {0, 2, 1, 3};
-    const int nx = v.nx, ny = v.ny;
-    const long long plane = (long long)v.pitch * ny;
-    const int sy = c.ty * B::CELLS, cbase = c.cg * B::COLS + wv * YW;
-    const int b0 = first ? 0 : B::FRESH;
-#pragma unroll
-    for (int j = 0; j < B::J; ++j) {
-        const int i = b0 * YW + lane + 64 * j;
-        if (i < B::NODES && (first || j == 0)) {
-            const int r = i / YW, c0 = i % YW;
-            const int y = bc_map(sy - G + r, ny, v.bc);
-            const int x = min(cbase + c0, nx - 1);
-            const GMEM double *p = v.in + (long long)y * v.pitch + x;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pre.U[j][q] = p[perm[q] * plane];
-        }
-    }
-    const int fl = lane / YW, y = min(sy + fl, ny - 1), col = min(cbase + (lane % YW), nx - 1);
-    const long long o = (long long)y * v.pitch + col;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) pre.lx[q] = v.lx[q * plane + o];
-    if constexpr (MODE == M_S2 || MODE == M_S3) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) pre.base[q] = v.base[q * plane + o];
-    }
-}
-
-// one face of a y strip into the face buffer (and the selection record)
-template <int ORDER, bool REC, int MODE, int YW, bool CH>
-__device__ __forceinline__ void y_face(const View<EULER2D, MODE> &v, const KParams &P, const double *W, int QS,
-                                       double *WF, int k, int cc, int col, int f)
-{
-    constexpr int NC = 4, CELLS = yt_cells(YW);
-    double Fh[NC];
-    int sel[2 * NC];
-    face_flux<EULER2D, ORDER, false, CH>(W + k * YW + cc, QS, YW, nullptr, 0, 0, v.al, P.gm1, P.delta, 0.0,
-                                     (P.flags & KF_FULL_SELECTION) == 0, Fh, sel);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) WF[(q * (CELLS + 1) + k) * YW + cc] = Fh[q];
-    if (REC && v.sel && col < v.nx && f <= v.ny) {
-        const long long xblock = (long long)v.ny * (v.nx + 1), yblock = (long long)(v.ny + 1) * v.nx;
-        const long long ybase = (long long)NC * 2 * xblock;
-#pragma unroll
-        for (int s = 0; s < NC; ++s) {
-            const long long o = ybase + (long long)(2 * s) * yblock + (long long)f * v.nx + col;
-            v.sel[o] = (uint8_t)sel[2 * s];
-            v.sel[o + yblock] = (uint8_t)sel[2 * s + 1];
-        }
-    }
-}
-
-template <int ORDER, int MODE, bool REC, int YW, bool CH>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 7 ? ENOAO_Y7_WAVES_PER_EU
-                                                                  : ENOAO_Y_WAVES_PER_EU))) void sweep_y(KParams P)
-{
-    constexpr int NC = 4, NQ = 12, NW = BLOCK / 64;
-    constexpr int H = ReconTraits<ORDER>::H, G = H + 1;
-    using B = YBuf<G, YW>;
-    constexpr int CELLS = B::CELLS, COLS = B::COLS;
-    constexpr int QS = B::NODES;  // a wave's LDS stride between quantities
-    __shared__ double lds[NW * NQ * QS];
-    __shared__ double fh[NW * NC * (CELLS + 1) * YW];
-    __shared__ double red[NW * 8];
-    // epilogue operands of the tile (x-part of L; u^n for stages 2 and 3),
-    // staged from the prefetch registers so they are not held through the face
-    // arithmetic
-    constexpr bool BASE = MODE == M_S2 || MODE == M_S3;
-    __shared__ double elx[NC * BLOCK];
-    __shared__ double ebase[BASE ? NC * BLOCK : 1];
-    const int perm[4] = {0, 2, 1, 3};
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cc = lane % YW, fl = lane / YW;
-    double *W = lds + wv * NQ * QS;
-    double *WF = fh + wv * NC * (CELLS + 1) * YW;
-    const int n_inst = P.hdr->n_inst;
-    const long long T = P.hdr->ytiles_total;
-    const long long NG = chunk_groups(P, T);
-    if (blockIdx.x >= NG) return;
-    const long long t0 = (long long)blockIdx.x * T / NG, t1 = (long long)(blockIdx.x + 1) * T / NG;
-    Maxima<EULER2D> mx;
-    mx.reset();
-    YPre<G, YW> pre;
-
-    // one outer iteration per instance met by the workgroup's chunk (uniform
-    // over the workgroup: the maxima flush is reached by all waves together)
-    int prev = -1;
-    for (long long tile = t0; tile < t1;) {
-        const View<EULER2D, MODE> v = load_view<EULER2D, MODE, true, CH>(P, n_inst, tile, prev);
-        prev = v.k;
-        const long long tend = v.t1 < t1 ? v.t1 : t1;
-        if (!v.active) {
-            tile = tend;
-            continue;
-        }
-        const int nx = v.nx, ny = v.ny;
-        const long long plane = (long long)v.pitch * ny;
-        YCur c = y_cursor(tile, v.t0, v.per_row);
-        bool first = true;  // the tile starts a walk
-        y_prefetch<MODE, G, YW>(v, c, true, wv, lane, pre);
-        for (; tile < tend; ++tile) {
-            if (!first) {
-                // rows shared with the previous tile move up by 64/YW
-                for (int i = YW + lane; i < B::FRESH * YW; i += 64) {
-#pragma unroll
-                    for (int m = 0; m < NQ; ++m) W[m * QS + i] = W[m * QS + i + CELLS * YW];
-                }
-                wave_sync();  // the new rows below overwrite rows other lanes just read
-            }
-#pragma unroll
-            for (int j = 0; j < B::J; ++j) {
-                const int i = (first ? 0 : B::FRESH * YW) + lane + 64 * j;
-                if (i < B::NODES && (first || j == 0)) {
-                    double q[NQ];
-                    node_quantities<EULER2D>(pre.U[j], P.gm1, q);
-#pragma unroll
-                    for (int m = 0; m < NQ; ++m) W[m * QS + i] = q[m];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < NC; ++q) elx[q * BLOCK + tid] = pre.lx[q];
-            if constexpr (BASE) {
-#pragma unroll
-                for (int q = 0; q < NC; ++q) ebase[q * BLOCK + tid] = pre.base[q];
-            }
-            const YCur cn = y_advance(c, v.per_row);
-            const bool next_first = cn.ty == 0;
-            if (tile + 1 < tend) y_prefetch<MODE, G, YW>(v, cn, next_first, wv, lane, pre);
-            wave_sync();
-
-            const int sy = c.ty * CELLS;
-            const int col = c.cg * COLS + wv * YW + cc;
-            // a walk's first tile also computes face row 0 (one call site, so the
-            // face code is instantiated once)
-#pragma unroll 1
-            for (int pass = first ? 0 : 1; pass < 2; ++pass) {
-                const int k = pass == 0 ? 0 : fl + 1;
-                if (pass == 1 || lane < YW) y_face<ORDER, REC, MODE, YW, CH>(v, P, W, QS, WF, k, cc, col, sy + k);
-            }
-            wave_sync();
-
-            const int y = sy + fl;
-            if (y < ny && col < nx) {
-                const long long o = (long long)y * v.pitch + col;
-                double Ly[NC];  // natural component order
-#pragma unroll
-                for (int q = 0; q < NC; ++q)
-                    Ly[perm[q]] = -(WF[(q * (CELLS + 1) + fl + 1) * YW + cc] - WF[(q * (CELLS + 1) + fl) * YW + cc]) *
-                                  v.idy;
-                if constexpr (MODE == M_RHS) {
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) v.lx[q * plane + o] = elx[q * BLOCK + tid] + Ly[q];
-                } else {
-                    // stage input at the cell: buffer row fl + G (quantity perm[q]
-                    // holds natural component q)
-                    double Un[NC];
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) {
-                        const double uin = W[perm[q] * QS + (fl + G) * YW + cc];
-                        const double base = BASE ? ebase[q * BLOCK + tid] : 0.0;
-                        Un[q] = rk_combine<MODE>(uin, base, v.dt, elx[q * BLOCK + tid] + Ly[q]);
-                        v.out[q * plane + o] = Un[q];
-                    }
-                    mx.add(Un, P.gamma, v.idx, v.idy);
-                }
-            }
-            wave_sync();
-            // the last face row is the next tile's first
-            if (lane < YW) {
-#pragma unroll
-                for (int q = 0; q < NC; ++q) WF[(q * (CELLS + 1)) * YW + lane] = WF[(q * (CELLS + 1) + CELLS) * YW + lane];
-            }
-            wave_sync();
-            c = cn;
-            first = next_first;
-        }
-        if (MODE != M_RHS) mx.flush(v.amax, v.ctrl, P.r_out, red);
     }
 }
 
@@ -1078,15 +637,37 @@ __global__ __launch_bounds__(BLOCK) void state_maxima(KParams P)
     if (cur >= 0) mx.flush(gmem(P.inst[cur].amax), gmem(P.inst[cur].ctrl), P.r_out, red);
 }
 
-// zero all maxima slots and the status of every instance
-__global__ void reset_maxima(KParams P)
+// zero all maxima slots (words each) of every instance and the list counters
+__global__ void reset_maxima(KParams P, int words)
 {
     const int n = P.hdr->n_inst;
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n * AMAX_SLOTS * AMAX_VALS;
-         k += gridDim.x * blockDim.x) {
-        const int i = k / (AMAX_SLOTS * AMAX_VALS), j = k % (AMAX_SLOTS * AMAX_VALS);
-        gmem(P.inst[i].amax)[j] = 0ull;
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n * words; k += gridDim.x * blockDim.x)
+        gmem(P.inst[k / words].amax)[k % words] = 0ull;
+    if (P.fix_count && blockIdx.x == 0)
+        for (int k = threadIdx.x; k < FIX_SETS * FIX_RANGES; k += blockDim.x) gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = 0u;
+}
+
+// What precedes the maxima of a lone member's state, in one launch: the caller's
+// pointers into the descriptor, the control block (mode 0: cleared to run an
+// evaluation of L; 1: that and a given step size; 2: replaced), maxima slots (words in
+// all) and list counters zeroed.  Kernel arguments are captured at launch, so the
+// host values need not outlive the call.
+__global__ void begin_lone(KParams P, Inst *inst, const double *u, double *lx, Ctrl *c, Ctrl v, int mode, int words)
+{
+    const int t = threadIdx.x;
+    if (t == 0) {
+        inst->u = const_cast<double *>(u);
+        if (lx) inst->lx = lx;
+        if (mode == 2) {
+            *c = v;
+        } else {
+            c->done = 0;
+            if (mode == 1) c->dt = v.dt;
+        }
     }
+    for (int k = t; k < words; k += blockDim.x) gmem(P.lone_amax)[k] = 0ull;
+    if (P.fix_count)
+        for (int k = t; k < FIX_SETS * FIX_RANGES; k += blockDim.x) gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = 0u;
 }
 
 // Time-step control of one instance: CFL (or fixed) step from the maxima m of
@@ -1131,7 +712,10 @@ __global__ void step_control(KParams P)
     if (k >= P.hdr->n_inst) return;
     const Inst &I = P.inst[k];
     const unsigned long long *a = I.amax;
-    control_update<EQ>(*I.ctrl, as_double(a[0]), as_double(a[2]), as_double(a[6]), I.dx, I.adv);
+    unsigned long long m6 = a[6];
+#pragma unroll
+    for (int i = 1; i < amax_copies(EQ); ++i) m6 = max(m6, a[i * AMAX_VALS + 6]);
+    control_update<EQ>(*I.ctrl, as_double(a[0]), as_double(a[2]), as_double(m6), I.dx, I.adv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1489,23 +1073,6 @@ __global__ void coop_reset(unsigned long long *amax, unsigned *bar)
     if (t < 2) bar[t] = 0u;
 }
 
-// bind caller pointers into a member's descriptor (kernel arguments are
-// captured at launch, so the host values need not outlive the call)
-__global__ void patch_inst(Inst *inst, int k, const double *u, double *lx, int set_lx)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        inst[k].u = const_cast<double *>(u);
-        if (set_lx) inst[k].lx = lx;
-    }
-}
-
-// clear the done flag of every member (before an evaluation outside the time loop)
-__global__ void clear_done(KParams P)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < P.hdr->n_inst) P.inst[k].ctrl->done = 0;
-}
-
 // replace a member's control block (pool admission and retirement); info, if
 // given, receives the old block's done flag, status, step count and time
 __global__ void set_ctrl(Ctrl *c, Ctrl v, double *info)
@@ -1527,16 +1094,6 @@ __global__ void copy_pitched(const double *src, long long sp, double *dst, long 
     for (long long r = blockIdx.y; r < rows; r += gridDim.y)
         for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < width; x += gridDim.x * blockDim.x)
             dst[(long long)r * dp + x] = src[(long long)r * sp + x];
-}
-
-// host-given step size for a single step (all instances)
-__global__ void set_dt(KParams P, double dt)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= P.hdr->n_inst) return;
-    Ctrl &C = *P.inst[k].ctrl;
-    C.dt = dt;
-    C.done = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1565,27 +1122,7 @@ template <int EQ, bool CH> static KFn pick_x_rec(int order, int mode, bool rec)
 static KFn pick_x(int eq, int order, int mode, bool rec, bool ch)
 {
     if (eq == ADVECTION) return pick_x_rec<ADVECTION, true>(order, mode, rec);
-    if (eq == EULER1D) return ch ? pick_x_rec<EULER1D, true>(order, mode, rec) : pick_x_rec<EULER1D, false>(order, mode, rec);
-    return ch ? pick_x_rec<EULER2D, true>(order, mode, rec) : pick_x_rec<EULER2D, false>(order, mode, rec);
-}
-template <int ORDER, bool REC, int YW, bool CH> static KFn pick_y_mode(int mode)
-{
-    switch (mode) {
-    case M_RHS: return sweep_y<ORDER, M_RHS, REC, YW, CH>;
-    case M_S1: return sweep_y<ORDER, M_S1, REC, YW, CH>;
-    case M_S2: return sweep_y<ORDER, M_S2, REC, YW, CH>;
-    default: return sweep_y<ORDER, M_S3, REC, YW, CH>;
-    }
-}
-template <int YW, bool CH> static KFn pick_y_w(int order, int mode, bool rec)
-{
-    if (order == 7) return rec ? pick_y_mode<7, true, YW, CH>(mode) : pick_y_mode<7, false, YW, CH>(mode);
-    return rec ? pick_y_mode<5, true, YW, CH>(mode) : pick_y_mode<5, false, YW, CH>(mode);
-}
-static KFn pick_y(int order, int mode, bool rec, int yw, bool ch)
-{
-    if (ch) return yw == 4 ? pick_y_w<4, true>(order, mode, rec) : pick_y_w<8, true>(order, mode, rec);
-    return yw == 4 ? pick_y_w<4, false>(order, mode, rec) : pick_y_w<8, false>(order, mode, rec);
+    return ch ? pick_x_rec<EULER1D, true>(order, mode, rec) : pick_x_rec<EULER1D, false>(order, mode, rec);
 }
 static KFn pick_maxima(int eq)
 {
@@ -1615,44 +1152,32 @@ hipError_t launch_sweep_x(int eq, int order, int mode, bool rec, bool ch, const 
     return launch(pick_x(eq, order, mode, rec, ch), grid, BLOCK, p, s);
 }
 
-hipError_t launch_sweep_y(int order, int mode, bool rec, bool ch, int yw, const KParams &p, int grid, hipStream_t s)
-{
-    return launch(pick_y(order, mode, rec, yw, ch), grid, BLOCK, p, s);
-}
-
 hipError_t launch_state_maxima(int eq, const KParams &p, int grid, hipStream_t s)
 {
     return launch(pick_maxima(eq), grid, BLOCK, p, s);
 }
 
-hipError_t launch_reset_maxima(const KParams &p, int n_inst, hipStream_t s)
+hipError_t launch_reset_maxima(int eq, const KParams &p, int n_inst, hipStream_t s)
 {
-    const int total = n_inst * AMAX_SLOTS * AMAX_VALS;
-    return launch(reset_maxima, (total + BLOCK - 1) / BLOCK, BLOCK, p, s);
+    KParams copy = p;
+    int words = AMAX_SLOTS * amax_slot_words(eq);
+    void *args[] = {&copy, &words};
+    return hipLaunchKernel((const void *)reset_maxima, dim3((n_inst * words + BLOCK - 1) / BLOCK), dim3(BLOCK), args, 0, s);
+}
+
+hipError_t launch_begin_lone(int eq, const KParams &p, Inst *inst, const double *u, double *lx, Ctrl *c, const Ctrl &v,
+                             int mode, hipStream_t s)
+{
+    KParams copy = p;
+    Ctrl cv = v;
+    int words = AMAX_SLOTS * amax_slot_words(eq);
+    void *args[] = {&copy, &inst, &u, &lx, &c, &cv, &mode, &words};
+    return hipLaunchKernel((const void *)begin_lone, dim3(1), dim3(BLOCK), args, 0, s);
 }
 
 hipError_t launch_step_control(int eq, const KParams &p, int n_inst, hipStream_t s)
 {
     return launch(pick_control(eq), (n_inst + 63) / 64, 64, p, s);
-}
-
-hipError_t launch_set_dt(const KParams &p, int n_inst, double dt, hipStream_t s)
-{
-    KParams copy = p;
-    void *args[] = {&copy, &dt};
-    return hipLaunchKernel((const void *)set_dt, dim3((n_inst + 63) / 64), dim3(64), args, 0, s);
-}
-
-hipError_t launch_patch_inst(Inst *inst, int k, const double *u, double *lx, bool set_lx, hipStream_t s)
-{
-    int flag = set_lx ? 1 : 0;
-    void *args[] = {&inst, &k, &u, &lx, &flag};
-    return hipLaunchKernel((const void *)patch_inst, dim3(1), dim3(64), args, 0, s);
-}
-
-hipError_t launch_clear_done(const KParams &p, int n_inst, hipStream_t s)
-{
-    return launch(clear_done, (n_inst + 63) / 64, 64, p, s);
 }
 
 hipError_t launch_set_ctrl(Ctrl *c, const Ctrl &v, double *info, hipStream_t s)
@@ -1750,10 +1275,6 @@ int resident_groups_per_cu(int eq, int order, bool ch)
 }
 
 int occupancy_x(int eq, int order, int mode, bool rec, bool ch) { return occupancy(pick_x(eq, order, mode, rec, ch)); }
-int occupancy_y(int order, int mode, bool rec, bool ch, int yw)
-{
-    return occupancy(pick_y(order, mode, rec, yw, ch));
-}
 int occupancy_maxima(int eq) { return occupancy(pick_maxima(eq)); }
 
 }  // namespace enoao

@@ -7,9 +7,9 @@
 
 namespace enoao {
 
-// what a sweep kernel does with the flux difference
+// what a stage kernel does with the flux difference
 enum Mode : int {
-    M_RHS = 0,  // evaluate L of the caller state (1D: write L; 2D: x writes Lx, y adds Ly)
+    M_RHS = 0,  // evaluate and write L of the caller state
     M_S1 = 1,   // Runge-Kutta stage 1: input u^n, output w1
     M_S2 = 2,   // stage 2: input w1, output w2
     M_S3 = 3    // stage 3: input w2, output u^{n+1} (in place)
@@ -23,6 +23,7 @@ struct KParams {
     int r_out;   // slot receiving the maxima of the stage output (-1: none)
     int r_zero;  // slot cleared by the first kernel of the stage (-1: none)
     int flags;   // KF_* below
+    int mode;      // 2D stages: what to do with L (Mode)
     int sel_slot;  // selection record a recording launch writes (0..2: the stage's record)
     // LDS-resident launches: member run by workgroup b (members by decreasing
     // size, so the small ones fill the machine behind the large; null: member b)
@@ -33,6 +34,13 @@ struct KParams {
     // tiles each, at least grid_min (0: the whole grid shares it).
     int tiles_per_wg;
     int grid_min;
+    // a lone member's control block and maxima (null: per descriptor)
+    Ctrl *lone_ctrl;
+    unsigned long long *lone_amax;
+    // 2D stages: the lists of row segments that need a selection, their counters (zero
+    // at launch) and the set zeroed for a later launch (null: none)
+    unsigned long long *fix_list;
+    unsigned *fix_count, *fix_zero;
 };
 
 // every face takes the full selection (no wave-uniform shortcut); results are
@@ -42,15 +50,16 @@ constexpr int KF_FULL_SELECTION = 1;
 // ch: reconstruct in the characteristic fields of the Roe state (false: in the
 // conserved components; advection ignores it)
 hipError_t launch_sweep_x(int eq, int order, int mode, bool rec, bool ch, const KParams &p, int grid, hipStream_t s);
-// yw: columns per wave strip of the y tiles (4 or 8; the members' y tile lists
-// must have been built for the same width)
-hipError_t launch_sweep_y(int order, int mode, bool rec, bool ch, int yw, const KParams &p, int grid, hipStream_t s);
+// one 2D stage (or M_RHS: L), both directions: the stage kernel and the selections
+hipError_t launch_stage_2d(int order, int mode, bool rec, bool ch, const KParams &p, int grid, int fix_grid, hipStream_t s);
 hipError_t launch_state_maxima(int eq, const KParams &p, int grid, hipStream_t s);
-hipError_t launch_reset_maxima(const KParams &p, int n_inst, hipStream_t s);
+// (also zeroes the list counters from p.fix_count on, if not null)
+hipError_t launch_reset_maxima(int eq, const KParams &p, int n_inst, hipStream_t s);
+// a lone member before the maxima of its state: pointers (lx may be null: kept),
+// control block (mode 0: cleared to run; 1: and v.dt; 2: = v), maxima and list counters zeroed
+hipError_t launch_begin_lone(int eq, const KParams &p, Inst *inst, const double *u, double *lx, Ctrl *c, const Ctrl &v,
+                             int mode, hipStream_t s);
 hipError_t launch_step_control(int eq, const KParams &p, int n_inst, hipStream_t s);
-hipError_t launch_set_dt(const KParams &p, int n_inst, double dt, hipStream_t s);
-hipError_t launch_patch_inst(Inst *inst, int k, const double *u, double *lx, bool set_lx, hipStream_t s);
-hipError_t launch_clear_done(const KParams &p, int n_inst, hipStream_t s);
 // *c = v on the stream (v passed by value: no host buffer outlives the call);
 // info (device, 4 doubles, may be null) receives the old done, status, steps, t
 hipError_t launch_set_ctrl(Ctrl *c, const Ctrl &v, double *info, hipStream_t s);
@@ -81,7 +90,8 @@ hipError_t launch_coop(int eq, int order, bool ch, int groups, const KParams &p,
 
 // resident workgroups per CU of each kernel (for persistent grid sizes)
 int occupancy_x(int eq, int order, int mode, bool rec, bool ch);
-int occupancy_y(int order, int mode, bool rec, bool ch, int yw);
+int occupancy_2d(int order, int mode, bool rec, bool ch);
+int occupancy_fix_2d(int order, int mode, bool rec, bool ch);
 int occupancy_maxima(int eq);
 
 }  // namespace enoao

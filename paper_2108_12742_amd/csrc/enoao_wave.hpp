@@ -1,0 +1,201 @@
+// enoao_wave.hpp -- helpers shared by the kernel sources: device-memory pointers,
+// boundary mapping, member lookup, maxima, stage combine, wave-level exchange.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "enoao_common.hpp"
+#include "enoao_device.hpp"
+#include "enoao_kernels.hpp"
+
+namespace enoao {
+
+// Workgroups sharing a persistent launch's tile list of T tiles: the whole
+// grid, or for a pool as many as give P.tiles_per_wg tiles each (at least
+// P.grid_min, at most the grid).  A pool's grid covers the machine several
+// times over; many small chunks let the workgroups that finish early take
+// more of them, which evens out members of uneven cost, while a pool holding
+// few tiles keeps chunks long enough for the y walks' row reuse.
+__device__ __forceinline__ long long chunk_groups(const KParams &P, long long T)
+{
+    const long long g = gridDim.x;
+    if (P.tiles_per_wg <= 0) return g;
+    return min(g, max((long long)P.grid_min, T / P.tiles_per_wg));
+}
+
+__device__ __forceinline__ int bc_map(int k, int n, int bc)
+{
+    if (bc == BC_PERIODIC) {
+        int r = k % n;
+        return r < 0 ? r + n : r;
+    }
+    return k < 0 ? 0 : (k >= n ? n - 1 : k);
+}
+
+// Device-memory pointers.  The state and control pointers reach a kernel through
+// the instance table in memory, so the compiler cannot tell that they address
+// global memory and would emit flat instructions for them.  Flat loads and
+// stores count against the LDS counter too, so every wait for an LDS read would
+// also wait for the next tile's global prefetch in flight (and for the previous
+// tile's stores).  Typed as global they compile to global instructions.
+#define GMEM __attribute__((address_space(1)))
+template <typename T> __device__ __forceinline__ GMEM T *gmem(T *p) { return (GMEM T *)p; }
+
+// wave-uniform copy of a value (scalar registers)
+template <typename T> __device__ __forceinline__ T uniform(T x)
+{
+    static_assert(sizeof(T) % 4 == 0, "32-bit multiple");
+    union { T v; int w[sizeof(T) / 4]; } a;
+    a.v = x;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) a.w[i] = __builtin_amdgcn_readfirstlane(a.w[i]);
+    return a.v;
+}
+
+__device__ __forceinline__ double as_double(unsigned long long b) { return __longlong_as_double((long long)b); }
+__device__ __forceinline__ unsigned long long as_bits(double d) { return (unsigned long long)__double_as_longlong(d); }
+
+template <bool X>
+__device__ __forceinline__ int find_inst(const Inst *inst, int n, long long tile)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        const long long t0 = X ? inst[mid].xtile0 : inst[mid].unit0;
+        if (t0 <= tile) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// ---------------------------------------------------------------------------
+// Maxima of the per-field wave speeds of a state (for alpha of the next
+// evaluation and for the CFL step), and the non-physical flag.
+template <int EQ> struct Maxima {
+    static constexpr int NV = EQ == EULER2D ? 7 : (EQ == EULER1D ? 3 : 0);  // values in use
+    double v[7];
+    int bad;
+    __device__ void reset()
+    {
+#pragma unroll
+        for (int i = 0; i < 7; ++i) v[i] = 0.0;
+        bad = 0;
+    }
+    // U in the natural component order; idx, idy = 1/dx, 1/dy
+    __device__ void add(const double *U, double gamma, double idx, double idy)
+    {
+        if constexpr (EQ == ADVECTION) {
+            bad |= !(U[0] == U[0]);
+        } else if constexpr (EQ == EULER1D) {
+            const double rho = U[0], ir = rcp_nr(rho), u = U[1] * ir;
+            const double p = (gamma - 1.0) * fma(-0.5 * rho, u * u, U[2]);
+            const double c = sqrt_nr(gamma * p * ir);
+            bad |= !(rho > 0.0 && p > 0.0);
+            v[0] = fmax(v[0], fabs(u - c));
+            v[1] = fmax(v[1], fabs(u));
+            v[2] = fmax(v[2], fabs(u + c));
+        } else {
+            const double rho = U[0], ir = rcp_nr(rho), u = U[1] * ir, w = U[2] * ir;
+            const double p = (gamma - 1.0) * fma(-0.5 * rho, fma(u, u, w * w), U[3]);
+            const double c = sqrt_nr(gamma * p * ir);
+            bad |= !(rho > 0.0 && p > 0.0);
+            v[0] = fmax(v[0], fabs(u - c));
+            v[1] = fmax(v[1], fabs(u));
+            v[2] = fmax(v[2], fabs(u + c));
+            v[3] = fmax(v[3], fabs(w - c));
+            v[4] = fmax(v[4], fabs(w));
+            v[5] = fmax(v[5], fabs(w + c));
+            v[6] = fmax(v[6], fma(fabs(u) + c, idx, (fabs(w) + c) * idy));
+        }
+    }
+    // workgroup reduction, then one atomic per value into the instance's slot
+    __device__ void flush(GMEM unsigned long long *amax, GMEM Ctrl *ctrl, int slot, double *red)
+    {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            double x = v[i];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
+            v[i] = x;
+        }
+        int b = bad;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) b |= __shfl_xor(b, o, 64);
+        if (lane == 0) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) red[wave * 8 + i] = v[i];
+            red[wave * 8 + 7] = (double)b;
+        }
+        __syncthreads();
+        if (threadIdx.x < NV || threadIdx.x == 7) {
+            double x = red[threadIdx.x];
+            for (int w = 1; w < BLOCK / 64; ++w) x = fmax(x, red[w * 8 + threadIdx.x]);
+            if (threadIdx.x < NV) {
+                if (slot >= 0)
+                    __hip_atomic_fetch_max(&amax[slot * amax_slot_words(EQ) + blockIdx.x % amax_copies(EQ) * AMAX_VALS + threadIdx.x],
+                                           as_bits(x), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            } else if (x != 0.0) {
+                __hip_atomic_fetch_or(&ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        __syncthreads();
+        reset();
+    }
+};
+
+// Reconstruction variables.  CH: the characteristic fields of the face's Roe
+// state (Section 4), with the scaled projection and the field scales above;
+// otherwise the conserved components themselves (identity projection, scale 1,
+// and one alpha for all of them).
+template <int NC, bool CH>
+__device__ __forceinline__ void to_fields(const RoeState &r, const double (&x)[NC], double (&w)[NC])
+{
+    if constexpr (CH) {
+        project<NC>(r, x, w);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) w[c] = x[c];
+    }
+}
+
+template <int NC, bool CH>
+__device__ __forceinline__ void from_fields(const RoeState &r, const double (&w)[NC], double (&F)[NC])
+{
+    if constexpr (CH) {
+        back_project<NC>(r, w, F);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) F[c] = w[c];
+    }
+}
+
+template <int NC, bool CH> __device__ __forceinline__ constexpr double fscale(int s)
+{
+    return CH ? field_scale<NC>(s) : 1.0;
+}
+
+// RK stage combine (Shu-Osher form): s = 1: in + dt L; s = 2: 3/4 base +
+// 1/4 (in + dt L); s = 3: 1/3 base + 2/3 (in + dt L).
+template <int MODE>
+__device__ __forceinline__ double rk_combine(double in, double base, double dt, double L)
+{
+    const double y = fma(dt, L, in);
+    if constexpr (MODE == M_S1) return y;
+    else if constexpr (MODE == M_S2) return fma(0.75, base, 0.25 * y);
+    else return fma(1.0 / 3.0, base, (2.0 / 3.0) * y);
+}
+
+// LDS exchange among the lanes of one wave: the wave's LDS operations are
+// performed in order, so a wavefront-scope fence pair around a wave barrier
+// orders each lane's writes before every lane's later reads.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+}  // namespace enoao
