@@ -2,11 +2,9 @@
 
 hipcc cross-compiles for gfx950 without a GPU.  Every HIP source is compiled
 with packed FP32 instructions disabled (-Xclang -target-feature -Xclang
--packed-fp32-ops); the kernels are FP64 throughout.  The sweeps are bound by
-issue latency at their register-limited occupancy, and the machine scheduler's
-iterative ILP strategy (-mllvm -amdgpu-sched-strategy=iterative-ilp) measured
-1-2% faster on them than the default (instruction order only: results are
-bitwise the same).
+-packed-fp32-ops); the kernels are FP64 throughout.  The
+compiler's default scheduling strategy is used throughout (its iterative ILP
+strategy gave 1-2% on earlier forms of the sweeps and spills on these).
 """
 import os
 import subprocess
@@ -23,13 +21,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include")]
-FILE_FLAGS = {"enoao_kernels.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]}
 
 
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(CSRC, "_build", src + ".o")
     os.makedirs(os.path.dirname(obj), exist_ok=True)
-    cmd = [HIPCC] + FLAGS + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -398,7 +398,7 @@ struct Runtime {
     // CU) for the mid-sized members measured 13% slower.
     enoao_status plan_resident(const enoao_problem *ps, const std::vector<int> &sorted)
     {
-        const int nq = eq == ADVECTION ? 1 : 9, g = order == 5 ? 4 : 5;
+        const int nq = eq == ADVECTION ? 1 : 8, g = order == 5 ? 4 : 5;
         const size_t limit = resident_lds_limit();
         int per_cu = 0;
         if (hipDeviceGetAttribute(&per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device) != hipSuccess ||
@@ -456,7 +456,10 @@ struct Runtime {
             if (c > 0) HIP_TRY(hipStreamWaitEvent(st, res_events[0], 0));
             KParams p = params(0, -1, -1);
             p.res_first = rc.first;
-            HIP_TRY(launch_resident(eq, order, ch, rc.block, p, rc.count, k, rc.lds, st));
+            // with a CU to each member its latency counts, and the waves share the selections
+            // (128 nodes: 5.1 us a stage alone, 4.5 shared); with more, the barriers of the
+            // sharing cost more than it saves (512 members: 479 us alone, 537 shared)
+            HIP_TRY(launch_resident(eq, order, ch, n <= cus, rc.block, p, rc.count, k, rc.lds, st));
             if (c > 0) HIP_TRY(hipEventRecord(res_events[c], st));
         }
         for (size_t c = 1; c < res_classes.size(); ++c) HIP_TRY(hipStreamWaitEvent(s, res_events[c], 0));

@@ -93,12 +93,12 @@ constexpr int RES_BLOCK = 256;
 
 // dynamic LDS bytes of a resident member of n nodes (nc components, nq staged
 // quantities per node, halo width g, block threads): u^n and the two stage
-// states, each wave's segment staging (nodes and face fluxes), two parities of
-// per-wave maxima
+// states, each wave's segment staging (nodes, face fluxes and, for the Euler
+// equations, 64 bytes of listed faces), two parities of per-wave maxima
 constexpr unsigned long long resident_lds_bytes(int nc, int nq, int g, long long n, int block = RES_BLOCK)
 {
     const long long nnp = 64 + 2 * g, waves = block / 64;
-    return 8ull * (unsigned long long)(3 * nc * n + waves * (nq * nnp + nc * 64) + 2 * waves * 8);
+    return 8ull * (unsigned long long)(3 * nc * n + waves * (nq * nnp + nc * 64 + (nc > 1 ? 8 : 0)) + 2 * waves * 8);
 }
 
 // Batch header (device memory): kernels read the instance count and the tile

@@ -245,7 +245,7 @@ __device__ __forceinline__ double Recon<ORDER>::select_top(const double (&f)[Rec
 // Per-node quantities staged in LDS (computed once per node by the lane that
 // loads it; faces read them from LDS).
 //   advection: u
-//   Euler 1D : rho, m, E | F0..F2 | sqrt(rho), u, H
+//   Euler 1D : rho, m, E | F1, F2 | sqrt(rho), u, H   (F0 = m)
 //   Euler 2D : rho, m, n, E | F0..F3 | sqrt(rho), u, v, H
 // (for a y-sweep the two momentum components arrive exchanged, so the same
 //  x-direction formulas give the y-flux in exchanged order).
@@ -302,7 +302,7 @@ __device__ __forceinline__ void sqrt_rcp_nr(double x, double &root, double &inv)
 
 template <int EQ> struct NodeTraits;
 template <> struct NodeTraits<ADVECTION> { static constexpr int NC = 1, NQ = 1; };
-template <> struct NodeTraits<EULER1D> { static constexpr int NC = 3, NQ = 9; };
+template <> struct NodeTraits<EULER1D> { static constexpr int NC = 3, NQ = 8; };
 template <> struct NodeTraits<EULER2D> { static constexpr int NC = 4, NQ = 12; };
 
 // Returns false for a non-physical node (rho <= 0, p <= 0 or NaN).
@@ -319,8 +319,8 @@ __device__ __forceinline__ bool node_quantities(const double (&U)[NodeTraits<EQ>
         const double u = m * ir;
         const double p = gm1 * fma(-0.5 * rho, u * u, E);
         q[0] = rho; q[1] = m; q[2] = E;
-        q[3] = m; q[4] = fma(m, u, p); q[5] = (E + p) * u;
-        q[6] = sqrt_nr(rho); q[7] = u; q[8] = (E + p) * ir;
+        q[3] = fma(m, u, p); q[4] = (E + p) * u;  // (F_0 is m)
+        q[5] = sqrt_nr(rho); q[6] = u; q[7] = (E + p) * ir;
         return rho > 0.0 && p > 0.0;
     } else {
         const double rho = U[0], m = U[1], n = U[2], E = U[3];

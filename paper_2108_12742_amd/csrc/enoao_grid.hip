@@ -62,51 +62,10 @@ template <class Off> __device__ __forceinline__ void row_store(GMEM double *p, O
     *(GMEM double *)((GMEM char *)p + off) = x;
 }
 
-// value of the neighbouring lane (lane 0 / 63 keep their own)
-template <int CTRL> __device__ __forceinline__ double dpp_move(double x)
-{
-    union { double d; int w[2]; } a, b;
-    a.d = x;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) b.w[i] = __builtin_amdgcn_update_dpp(a.w[i], a.w[i], CTRL, 0xf, 0xf, false);
-    return b.d;
-}
-__device__ __forceinline__ double lane_prev(double x) { return dpp_move<0x138>(x); }  // wave_shr:1
-__device__ __forceinline__ double lane_next(double x) { return dpp_move<0x130>(x); }  // wave_shl:1
-
-// lane i's value, in scalar registers
-__device__ __forceinline__ double lane_value(double x, int i)
-{
-    union { double d; int w[2]; } a;
-    a.d = x;
-    a.w[0] = __builtin_amdgcn_readlane(a.w[0], i);
-    a.w[1] = __builtin_amdgcn_readlane(a.w[1], i);
-    return a.d;
-}
-
 __device__ __forceinline__ unsigned long long lane_bits(unsigned long long x, int i)
 {
     return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, i) |
            (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), i) << 32;
-}
-
-// maximum over the wave's lanes
-__device__ __forceinline__ double wave_max(double x)
-{
-    x = fmax(x, dpp_move<0xb1>(x));   // quad_perm 1, 0, 3, 2
-    x = fmax(x, dpp_move<0x4e>(x));   // quad_perm 2, 3, 0, 1
-    x = fmax(x, dpp_move<0x141>(x));  // row_half_mirror
-    x = fmax(x, dpp_move<0x140>(x));  // row_mirror: each lane its row's maximum
-    x = fmax(x, dpp_move<0x142>(x));  // row_bcast:15 into the next row
-    x = fmax(x, dpp_move<0x143>(x));  // row_bcast:31 into rows 2 and 3
-    return lane_value(x, 63);
-}
-
-// sum over the four lanes of a quad, the same in each
-__device__ __forceinline__ double quad_sum(double x)
-{
-    const double y = x + dpp_move<0xb1>(x);  // quad_perm 1, 0, 3, 2
-    return y + dpp_move<0x4e>(y);            // quad_perm 2, 3, 0, 1
 }
 
 // a launch's values of one member

@@ -22,255 +22,228 @@
 #include "enoao_kernels.hpp"
 #include "enoao_wave.hpp"
 
-// Tuning switches (defaults are the measured best on gfx950).
-#ifndef ENOAO_NODE_PREFETCH
-#define ENOAO_NODE_PREFETCH 1  // stencil nodes whose LDS reads are in flight ahead of use
-#endif
-#ifndef ENOAO_NODE_SCHED
-#define ENOAO_NODE_SCHED 1     // stencil nodes between scheduling fences (0: none; bounds register use)
-#endif
-
 namespace enoao {
 
 // ---------------------------------------------------------------------------
 // One face: window node t (t = 0 .. 2G-1) of face j+1/2 is node j-H+t; the
 // plus side reads nodes j-H .. j+H, the minus side the mirror j+1+H .. j+1-H.
 
-// Top candidate of every field of an Euler face in conserved-variable form
-// (TopStencil): the projected differences D_0, D_1, D_2 of U and F and the
-// projected symmetric stencil of F give both sides' top indicators and the sum
-// of both sides' top values, on the window scale 2 field_scale (the windows
-// below are g = P F +/- alpha P U with the scaled projection P).
-template <int NC> struct TopForm {
-    double is[NC][2];  // IS_top of the plus and minus side
-    double hs[NC];     // plus + minus top value
-};
-
-// Staged differences (DSTAGED): d0 points at D_0 of quantity 0 of the face,
-// quantities (U then F) dqs apart, positions dns apart.  Otherwise they are
-// formed here from the window nodes.
-template <int NC, int ORDER, bool DSTAGED, bool CH>
-__device__ __forceinline__ void top_form(const double *w0, int qs, int ns, const double *d0, int dqs, int dns,
-                                         const RoeState &r, const double *al, double delta, TopForm<NC> &tf)
+// Numerical flux of one advection face from its 2G window nodes (w0: node 0) and its
+// staged differences D_0, D_1, D_2 (DSTAGED; otherwise formed here).  f^(+/-) =
+// (a u +/- alpha u)/2 is reconstructed as 2 f^(+/-); the differences and the symmetric
+// stencil of f = a u are a times those of u.  shortcut = false: the full selection
+// everywhere (the result is the same).
+template <int ORDER, bool DSTAGED>
+__device__ __forceinline__ double advection_flux(const double *w0, const double *d0, double a, double adv, double delta,
+                                                 bool shortcut, int (&sel)[2])
 {
     using T = TopStencil<ORDER>;
-    constexpr int G = ReconTraits<ORDER>::H + 1;
-    double dv[3][2][NC], sf[NC];
-    if constexpr (DSTAGED) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int c = 0; c < NC; ++c) dv[p][v][c] = d0[(v * NC + c) * dqs + p * dns];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) sf[c] = T::sym(w0 + (NC + c) * qs, ns);
-    } else {
-        // one quantity's window at a time (bounds the live registers)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                double xw[2 * G];
-#pragma unroll
-                for (int t = 0; t < 2 * G; ++t) xw[t] = w0[(v * NC + c) * qs + t * ns];
-#pragma unroll
-                for (int p = 0; p < 3; ++p) dv[p][v][c] = T::diff(xw + p, 1);
-                if (v == 1) sf[c] = T::sym(xw, 1);
-                if (ENOAO_NODE_SCHED > 0 && c % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-    double pd[3][2][NC], psf[NC];
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) to_fields<NC, CH>(r, dv[p][v], pd[p][v]);
-    to_fields<NC, CH>(r, sf, psf);
-#pragma unroll
-    for (int s = 0; s < NC; ++s) {
-        const double a = al[s];
-        tf.is[s][0] = fmin(fabs(fma(a, pd[0][0][s], pd[0][1][s])), fabs(fma(a, pd[1][0][s], pd[1][1][s])));
-        tf.is[s][1] = fmin(fabs(fma(-a, pd[2][0][s], pd[2][1][s])), fabs(fma(-a, pd[1][0][s], pd[1][1][s])));
-        tf.hs[s] = fma(a * T::kappa, pd[1][0][s], psf[s]);
-    }
-}
-
-// every lane of the wave has IS_top <= delta on both sides of field s
-template <int NC, bool CH>
-__device__ __forceinline__ bool top_wave_ok(const TopForm<NC> &tf, int s, double delta, bool shortcut)
-{
-    const double sd = 2.0 * fscale<NC, CH>(s) * delta;
-    return wave_all(tf.is[s][0] <= sd && tf.is[s][1] <= sd) & shortcut;
-}
-
-// Full selection of the characteristic fields F0 (and F1 >= 0) of an Euler
-// face: project U and F of every stencil node (the compiler drops the rows not
-// used by these fields), split, select on both sides.  A field whose top
-// candidate is within delta on every lane (bit s of okmask) keeps the top
-// value; a lane whose selection takes the top candidate on both sides takes
-// the same value, tf (the face's top form, formed once).  Taking the fields in
-// two passes halves the live window registers.
-template <int NC, int ORDER, int F0, int F1, bool CH>
-__device__ __forceinline__ void field_pass(const double *w0, int qs, int ns, const RoeState &r, const double *al,
-                                           double delta, int okmask, const TopForm<NC> &tf, double (&wh)[NC],
-                                           int (&sel)[2 * NC])
-{
     constexpr int H = ReconTraits<ORDER>::H, G = H + 1, W = 2 * H + 1, K = ReconTraits<ORDER>::K;
-    constexpr int NF = F1 >= 0 ? 2 : 1;
-    constexpr int fs[2] = {F0, F1 >= 0 ? F1 : F0};
-    constexpr int pmask = (1 << F0) | (F1 >= 0 ? 1 << F1 : 0);
-    double gp[NF][W], gm[NF][W];
-    if ((okmask & pmask) != pmask) {
-        // node t's LDS reads go out NODE_PREFETCH nodes ahead of its arithmetic
-        constexpr int D = ENOAO_NODE_PREFETCH;
-        double Uq[2 * G][NC], Fq[2 * G][NC];
+    double du[3];
 #pragma unroll
-        for (int t = 0; t < D && t < 2 * G; ++t) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                Uq[t][c] = w0[c * qs + t * ns];
-                Fq[t][c] = w0[(NC + c) * qs + t * ns];
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 2 * G; ++t) {
-            if (t + D < 2 * G) {
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    Uq[t + D][c] = w0[c * qs + (t + D) * ns];
-                    Fq[t + D][c] = w0[(NC + c) * qs + (t + D) * ns];
-                }
-            }
-            double PU[NC], PF[NC];
-            to_fields<NC, CH>(r, Uq[t], PU);
-            to_fields<NC, CH>(r, Fq[t], PF);
-#pragma unroll
-            for (int i = 0; i < NF; ++i) {
-                const int s = fs[i];
-                if (t < W) gp[i][t] = fma(al[s], PU[s], PF[s]);
-                if (t >= 1) gm[i][2 * H + 1 - t] = fma(-al[s], PU[s], PF[s]);
-            }
-            // bound the live ranges: a scheduling fence every NODE_SCHED nodes
-            if (ENOAO_NODE_SCHED > 0 && t % ENOAO_NODE_SCHED == ENOAO_NODE_SCHED - 1)
-                __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int p = 0; p < 3; ++p) du[p] = DSTAGED ? d0[p] : T::diff(w0 + p, 1);
+    const double isp = fmin(fabs(fma(a, du[0], adv * du[0])), fabs(fma(a, du[1], adv * du[1])));
+    const double ism = fmin(fabs(fma(-a, du[2], adv * du[2])), fabs(fma(-a, du[1], adv * du[1])));
+    const double hs = fma(a * T::kappa, du[1], adv * T::sym(w0, 1));
+    if (wave_all(isp <= 2.0 * delta && ism <= 2.0 * delta) & shortcut) {
+        sel[0] = sel[1] = K - 1;
+        return 0.5 * hs;
     }
+    double gp[W], gm[W];
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-        const int s = fs[i];
-        const double sc = 2.0 * fscale<NC, CH>(s);
-        if (okmask & (1 << s)) {
-            wh[s] = tf.hs[s] * (1.0 / sc);
-            sel[2 * s] = sel[2 * s + 1] = K - 1;
+    for (int t = 0; t < 2 * G; ++t) {
+        const double u = w0[t];
+        const double au = adv * u;
+        if (t < W) gp[t] = fma(a, u, au);
+        if (t >= 1) gm[2 * H + 1 - t] = fma(-a, u, au);
+    }
+    int sp, sm;
+    const double hp = Recon<ORDER>::select(gp, 2.0 * delta, isp, sp);
+    const double hm = Recon<ORDER>::select(gm, 2.0 * delta, ism, sm);
+    sel[0] = sp;
+    sel[1] = sm;
+    return 0.5 * (sp == K - 1 && sm == K - 1 ? hs : hp + hm);
+}
+
+// Roe state of the face whose left node's staged quantities are at nl (quantity stride qs)
+__device__ __forceinline__ RoeState line_roe(const double *nl, int qs, double gm1)
+{
+    return roe_state(nl[5 * qs], nl[6 * qs], 0.0, nl[7 * qs], nl[5 * qs + 1], nl[6 * qs + 1], 0.0, nl[7 * qs + 1], gm1);
+}
+
+// A wave's segment of an Euler line: its staged node quantities and its face fluxes.
+struct LineLds {
+    const double *q;      // staged quantities, stride qs; lane l's face has nodes l .. l + 2H + 1
+    int qs;
+    double *fh;           // fluxes by component (stride fs) and face
+    int fs;
+    unsigned char *list;  // faces that need a selection
+};
+
+// The segment's 64 Euler fluxes where every field takes its top candidate on both sides:
+// the flux is linear in the window (TopStencil; R L = I, so the central part needs no
+// projection), Fhat = S F / 2 + R (kappa alpha L D_1 U) / 2.  One bound tells nearly all
+// such faces: |l.(D F +- alpha D U)| <= |l|_1 max_c(|D F_c| + alpha |D U_c|) with D_1,
+// which both sides share.  Returns the `live` faces that the bound leaves, listed; they
+// are few or, on a coarse line, most of them, and each costs five others.
+// rec(face, i, candidate): a face's selection i (2 field + side); nothing depends on it.
+template <int ORDER, bool CH, class Rec>
+__device__ __forceinline__ unsigned long long line_top(const LineLds &l, const double (&al)[3], double gm1,
+                                                       double delta, bool shortcut, bool live, double (&Fh)[3],
+                                                       const Rec &rec)
+{
+    using T = TopStencil<ORDER>;
+    constexpr int H = ReconTraits<ORDER>::H, NW = 2 * H + 2, K = ReconTraits<ORDER>::K;
+    const int lane = threadIdx.x & 63;
+    const double *w = l.q + lane;
+    double sF[3], dU[3], dF[2];
+    // (two quantities' windows in flight)
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+        double win[NW - 2];
+#pragma unroll
+        for (int t = 0; t < NW - 2; ++t) win[t] = w[m * l.qs + 1 + t];
+        if (m == 1) sF[0] = T::sym1(win, 1);  // F_0 is U_1
+        if (m >= 3) sF[m - 2] = T::sym1(win, 1);
+        if (m < 3) dU[m] = T::diff(win, 1);
+        else dF[m - 3] = T::diff(win, 1);
+        if (m % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    RoeState r{};
+    if constexpr (CH) r = line_roe(w + H, l.qs, gm1);
+    double x[3];
+    to_fields<3, CH>(r, dU, x);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) x[s] *= al[s] * (0.5 * T::kappa / fscale<3, CH>(s));
+    from_fields<3, CH>(r, x, Fh);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) Fh[c] = fma(0.5, sF[c], Fh[c]);
+    // (acoustic rows halved to the window scale of the entropy field)
+    double bound = 1.0;
+    if constexpr (CH) {
+        const double au = 1.0 + fabs(r.u), y = fma(r.b1, au, r.b2);
+        bound = fmax(1.0 + y, 0.5 * fma(r.ic, au, y));
+    }
+    const double a = fmax(al[0], fmax(al[1], al[2]));
+    double node = fma(a, fabs(dU[0]), fabs(dU[1]));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) node = fmax(node, fma(a, fabs(dU[k + 1]), fabs(dF[k])));
+    // (the bound and the indicators differ by rounding; delta = 0 leaves every face)
+    const double thr = delta > 0.0 && shortcut ? 2.0 * delta * (1.0 - 1.0 / 1024.0) : -1.0;
+    const bool ok = bound * node <= thr;
+    const unsigned long long fail = __builtin_amdgcn_ballot_w64(!ok && live);
+    if (live && ok) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rec(lane, i, K - 1);
+    }
+    if ((fail >> lane) & 1)
+        l.list[__builtin_amdgcn_mbcnt_hi((unsigned)(fail >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)fail, 0u))] =
+            (unsigned char)lane;
+    return fail;
+}
+
+// alpha of the three fields (by value: a lane picks one of them)
+struct Alpha3 {
+    double a0, a1, a2;
+};
+
+// The selection of field s on face f of the segment l, both sides: the difference to
+// the top values, zero where the top candidate is chosen after all, goes to the face's
+// place in l.fh.  A lane takes one field of one listed face: where each lane took all
+// fields of its own face, a segment with a shock held its wave for 9500 cycles a stage
+// beside 1200 for the others.  All lanes of the wave call it; `valid` ones count.
+// SERIAL: one side's candidates after the other's (fewer registers, more latency).
+template <int ORDER, bool CH, bool SERIAL, class Rec>
+__device__ __forceinline__ void line_select(const LineLds &l, int f, int s, bool valid, Alpha3 al,
+                                            double gm1, double delta, const Rec &rec)
+{
+    using R = Recon<ORDER>;
+    constexpr int H = R::H, NW = 2 * H + 2, K = R::K;
+    const double *w = l.q + f;
+    const bool ent = s == 1;
+    const double a = !CH || s == 0 ? al.a0 : (s == 1 ? al.a1 : al.a2);
+    double l0 = 0.0, l1 = 0.0, l2 = 0.0;  // the field's row (acoustic rows doubled)
+    if constexpr (CH) {
+        const RoeState r = line_roe(w + H, l.qs, gm1);
+        const double sg = s == 0 ? r.ic : -r.ic, bu = r.b1 * r.u;
+        l0 = ent ? 1.0 - r.b2 : fma(sg, r.u, r.b2);
+        l1 = ent ? bu : -sg - bu;
+        l2 = ent ? -r.b1 : r.b1;
+    }
+    double gp[2 * H + 1], gm[2 * H + 1];
+#pragma unroll
+    for (int t = 0; t < NW; ++t) {
+        const double u0 = w[t], u1 = w[l.qs + t], u2 = w[2 * l.qs + t], f1 = w[3 * l.qs + t], f2 = w[4 * l.qs + t];
+        double pu, pf;
+        if constexpr (CH) {
+            pu = fma(l0, u0, fma(l1, u1, l2 * u2));
+            pf = fma(l0, u1, fma(l1, f1, l2 * f2));
         } else {
-            int sp, sm;
-            const double hp = Recon<ORDER>::select(gp[i], sc * delta, tf.is[s][0], sp);
-            const double hm = Recon<ORDER>::select(gm[i], sc * delta, tf.is[s][1], sm);
-            wh[s] = (sp == K - 1 && sm == K - 1 ? tf.hs[s] : hp + hm) * (1.0 / sc);
-            sel[2 * s] = sp;
-            sel[2 * s + 1] = sm;
+            pu = s == 0 ? u0 : (s == 1 ? u1 : u2);
+            pf = s == 0 ? u1 : (s == 1 ? f1 : f2);
         }
+        if (t <= 2 * H) gp[t] = fma(a, pu, pf);
+        if (t >= 1) gm[2 * H + 1 - t] = fma(-a, pu, pf);
+        if (t % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (two nodes' reads in flight)
+    }
+    const double sd = (CH && !ent ? 4.0 : 2.0) * delta;
+    int cp, cm;
+    double tp, tm;
+    const double hp = R::select_top(gp, sd, cp, tp);
+    if (SERIAL) __builtin_amdgcn_sched_barrier(0);
+    const double hm = R::select_top(gm, sd, cm, tm);
+    if (valid) {
+        rec(f, 2 * s, cp);
+        rec(f, 2 * s + 1, cm);
+        l.fh[s * l.fs + f] = cp == K - 1 && cm == K - 1 ? 0.0 : ((hp - tp) + (hm - tm)) * (CH && !ent ? 0.25 : 0.5);
     }
 }
 
-// Numerical flux of one face from its 2G window nodes (w0: node 0, quantity
-// stride qs, node stride ns; d0/dqs/dns: the staged top differences when
-// DSTAGED, quantities U then F, for advection u only).  shortcut = false: every
-// field takes the full selection (the result is the same).
-template <int EQ, int ORDER, bool DSTAGED, bool CH>
-__device__ __forceinline__ void face_flux(const double *w0, int qs, int ns, const double *d0, int dqs, int dns,
-                                          const double *al, double gm1, double delta, double adv, bool shortcut,
-                                          double (&Fh)[NodeTraits<EQ>::NC], int (&sel)[2 * NodeTraits<EQ>::NC])
+// The listed faces' fluxes, each by its own lane: R times the fields' differences added.
+template <int ORDER, bool CH>
+__device__ __forceinline__ void line_correct(const LineLds &l, bool listed, double gm1, double (&Fh)[3])
 {
-    constexpr int H = ReconTraits<ORDER>::H, G = H + 1, W = 2 * H + 1, K = ReconTraits<ORDER>::K;
-    if constexpr (EQ == ADVECTION) {
-        // f^(+/-) = (a u +/- alpha u)/2, reconstructed as 2 f^(+/-); the
-        // differences and the symmetric stencil of f = a u are a times those of u
-        using T = TopStencil<ORDER>;
-        double du[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) du[p] = DSTAGED ? d0[p * dns] : T::diff(w0 + p * ns, ns);
-        const double a = al[0];
-        const double isp = fmin(fabs(fma(a, du[0], adv * du[0])), fabs(fma(a, du[1], adv * du[1])));
-        const double ism = fmin(fabs(fma(-a, du[2], adv * du[2])), fabs(fma(-a, du[1], adv * du[1])));
-        const double hs = fma(a * T::kappa, du[1], adv * T::sym(w0, ns));
-        if (wave_all(isp <= 2.0 * delta && ism <= 2.0 * delta) & shortcut) {
-            Fh[0] = 0.5 * hs;
-            sel[0] = sel[1] = K - 1;
-            return;
-        }
-        double gp[W], gm[W];
-#pragma unroll
-        for (int t = 0; t < 2 * G; ++t) {
-            const double u = w0[t * ns];
-            const double au = adv * u;
-            if (t < W) gp[t] = fma(a, u, au);
-            if (t >= 1) gm[2 * H + 1 - t] = fma(-a, u, au);
-        }
-        int sp, sm;
-        const double hp = Recon<ORDER>::select(gp, 2.0 * delta, isp, sp);
-        const double hm = Recon<ORDER>::select(gm, 2.0 * delta, ism, sm);
-        Fh[0] = 0.5 * (sp == K - 1 && sm == K - 1 ? hs : hp + hm);
-        sel[0] = sp;
-        sel[1] = sm;
-    } else {
-        constexpr int NC = NodeTraits<EQ>::NC, QR = 2 * NC;
-        const double *nl = w0 + (G - 1) * ns, *nr = w0 + G * ns;
-        RoeState r{};
-        if constexpr (!CH) {
-            // conserved components: no Roe state
-        } else if constexpr (EQ == EULER1D)
-            r = roe_state(nl[QR * qs], nl[(QR + 1) * qs], 0.0, nl[(QR + 2) * qs], nr[QR * qs],
-                          nr[(QR + 1) * qs], 0.0, nr[(QR + 2) * qs], gm1);
-        else
-            r = roe_state(nl[QR * qs], nl[(QR + 1) * qs], nl[(QR + 2) * qs], nl[(QR + 3) * qs], nr[QR * qs],
-                          nr[(QR + 1) * qs], nr[(QR + 2) * qs], nr[(QR + 3) * qs], gm1);
-        double wh[NC];
-        int okmask = 0;  // fields whose top candidate is within delta on every lane
-        TopForm<NC> tf;
-        top_form<NC, ORDER, DSTAGED, CH>(w0, qs, ns, d0, dqs, dns, r, al, delta, tf);
-#pragma unroll
-        for (int s = 0; s < NC; ++s)
-            if (top_wave_ok<NC, CH>(tf, s, delta, shortcut)) okmask |= 1 << s;
-        if (okmask == (1 << NC) - 1) {
-#pragma unroll
-            for (int s = 0; s < NC; ++s) {
-                wh[s] = tf.hs[s] * (1.0 / (2.0 * fscale<NC, CH>(s)));
-                sel[2 * s] = sel[2 * s + 1] = K - 1;
-            }
-        } else if constexpr (NC == 4) {
-            field_pass<4, ORDER, 0, 3, CH>(w0, qs, ns, r, al, delta, okmask, tf, wh, sel);
-            field_pass<4, ORDER, 1, 2, CH>(w0, qs, ns, r, al, delta, okmask, tf, wh, sel);
-        } else {
-            field_pass<3, ORDER, 0, 2, CH>(w0, qs, ns, r, al, delta, okmask, tf, wh, sel);
-            field_pass<3, ORDER, 1, -1, CH>(w0, qs, ns, r, al, delta, okmask, tf, wh, sel);
-        }
-        from_fields<NC, CH>(r, wh, Fh);
-    }
-}
-
-// Staged top differences of two consecutive nodes i and i+1: D_0 of every
-// staged quantity (U then F; advection: u) from nodes i .. i+2H, which the two
-// share (one lane reads 2H+1 nodes for both instead of 2H for each).  x: node
-// i, quantity stride qs, node stride ns; out: quantity stride oqs, node stride
-// ons.  With two == false only node i's difference is formed, from nodes
-// i .. i+2H-1 (node i+2H is not read).
-template <int EQ, int ORDER>
-__device__ __forceinline__ void stage_diff2(const double *x, int qs, int ns, double *out, int oqs, int ons, bool two)
-{
-    constexpr int ND = EQ == ADVECTION ? 1 : 2 * NodeTraits<EQ>::NC;
     constexpr int H = ReconTraits<ORDER>::H;
+    const int lane = threadIdx.x & 63;
+    if (!listed) return;
+    double e[3], d[3];
 #pragma unroll
-    for (int m = 0; m < ND; ++m) {
-        double w[2 * H + 1];
+    for (int s = 0; s < 3; ++s) e[s] = l.fh[s * l.fs + lane];
+    RoeState r{};
+    if constexpr (CH) r = line_roe(l.q + lane + H, l.qs, gm1);
+    from_fields<3, CH>(r, e, d);
 #pragma unroll
-        for (int t = 0; t < 2 * H; ++t) w[t] = x[m * qs + t * ns];
-        w[2 * H] = two ? x[m * qs + 2 * H * ns] : 0.0;
-        out[m * oqs] = TopStencil<ORDER>::diff(w, 1);
-        if (two) out[m * oqs + ons] = TopStencil<ORDER>::diff(w + 1, 1);
+    for (int c = 0; c < 3; ++c) Fh[c] += d[c];
+}
+
+// The selections of a wave's own listed faces (`fail`), and their fluxes.
+template <int ORDER, bool CH, bool SERIAL, class Rec>
+__device__ __forceinline__ void line_selections(const LineLds &l, unsigned long long fail, Alpha3 al,
+                                                double gm1, double delta, double (&Fh)[3], const Rec &rec)
+{
+    if (__builtin_expect(fail == 0, 1)) return;
+    const int lane = threadIdx.x & 63, nf = __popcll(fail);
+    wave_sync();
+#pragma unroll 1
+    for (int at = 0; at < 3 * nf; at += 64) {
+        const int k = min(at + lane, 3 * nf - 1), s = (k >= nf) + (k >= 2 * nf);
+        line_select<ORDER, CH, SERIAL>(l, l.list[k - s * nf], s, at + lane < 3 * nf, al, gm1, delta, rec);
     }
+    wave_sync();
+    line_correct<ORDER, CH>(l, (fail >> lane) & 1, gm1, Fh);
+}
+
+// Staged top differences D_0 of two consecutive advection nodes i and i+1, from nodes
+// i .. i+2H, which the two share (one lane reads 2H+1 nodes for both instead of 2H for
+// each).  x: node i; out: its difference.
+template <int ORDER> __device__ __forceinline__ void stage_diff2(const double *x, double *out)
+{
+    constexpr int H = ReconTraits<ORDER>::H;
+    double w[2 * H + 1];
+#pragma unroll
+    for (int t = 0; t < 2 * H + 1; ++t) w[t] = x[t];
+    out[0] = TopStencil<ORDER>::diff(w, 1);
+    out[1] = TopStencil<ORDER>::diff(w + 1, 1);
 }
 
 // Per-instance values of one sweep launch.  A workgroup walks a contiguous
@@ -360,9 +333,11 @@ __device__ __forceinline__ View<EQ, MODE> load_view(const KParams &P, int n_inst
 // continues the previous one along its line reuses its last 2G staged nodes).
 // Tiles are software-pipelined: the global operands of tile t+1 are loaded into
 // registers while tile t is reconstructed, so the memory latency hides behind
-// the face arithmetic.  Waves per SIMD the register allocation must allow
-// (measured: three, the LDS fits three workgroups per CU, except order 7, which
-// spills at three).
+// the face arithmetic.  Waves per SIMD the register allocation must allow: three at
+// order 5 (four spill, and a 2.2e6-node stage takes 40.4 us against 39.4), two at
+// order 7 (three spill).  With the linear flux and the listed selections of line_top a
+// stage of 2.2e6 nodes takes 42 us where forming the indicators of all fields at every
+// face took 55 (order 7: 48 against 59).
 #ifndef ENOAO_X_WAVES_PER_EU
 #define ENOAO_X_WAVES_PER_EU 3
 #endif
@@ -447,11 +422,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 
     constexpr int H = ReconTraits<ORDER>::H, G = H + 1;
     constexpr int NN = XW_FACES + 2 * G - 1;  // nodes staged per segment
     constexpr int NNP = NN + 1;
-    constexpr int ND = EQ == ADVECTION ? 1 : 2 * NC;  // staged top differences per node
-    constexpr int NDN = XW_FACES + 2;                  // nodes with a staged difference
+    constexpr int NDN = XW_FACES + 2;                  // advection: nodes with a staged difference
     constexpr bool FULL = MODE != M_RHS;  // a stage: combine + maxima here
     __shared__ double lds[NQ * XW_SEGS * NNP];
-    __shared__ double dif[ND * XW_SEGS * NDN];
+    __shared__ double dif[EQ == ADVECTION ? XW_SEGS * NDN : 1];
+    __shared__ unsigned char list[EQ == ADVECTION ? 1 : XW_SEGS * 64];
     __shared__ double fh[NC * XW_SEGS * XW_FACES];
     __shared__ double red[(BLOCK / 64) * 8];
 
@@ -529,29 +504,37 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(ORDER == 
             const bool cont_n = cn.segx != 0;
             if (k + 1 < T) x_prefetch<EQ, MODE, G>(v, cn, cont_n, lane, pre);
             wave_sync();
-            // top differences of the nodes that start one (faces 0..63 read
-            // 0..65), two consecutive nodes per lane
-            static_assert(NDN % 2 == 0 && NDN / 2 <= 64, "one pair of nodes per lane");
-            if (ok && lane < NDN / 2)
-                stage_diff2<EQ, ORDER>(L + 2 * lane, XW_SEGS * NNP, 1, Dl + 2 * lane, XW_SEGS * NDN, 1, true);
-            wave_sync();
+            if constexpr (EQ == ADVECTION) {
+                // top differences of the nodes that start one (faces 0..63 read
+                // 0..65), two consecutive nodes per lane
+                static_assert(NDN % 2 == 0 && NDN / 2 <= 64, "one pair of nodes per lane");
+                if (ok && lane < NDN / 2) stage_diff2<ORDER>(L + 2 * lane, Dl + 2 * lane);
+                wave_sync();
+            }
 
             const int f = sx + lane;  // face index along the line
             if (ok) {
-                double Fh[NC];
-                int sel[2 * NC];
-                face_flux<EQ, ORDER, true, CH>(L + lane, XW_SEGS * NNP, 1, Dl + lane, XW_SEGS * NDN, 1, v.al, P.gm1,
-                                           P.delta, v.adv, (P.flags & KF_FULL_SELECTION) == 0, Fh, sel);
-#pragma unroll
-                for (int q = 0; q < NC; ++q) fh[(q * XW_SEGS + wseg) * XW_FACES + lane] = Fh[q];
-                if (REC && v.sel && f <= nx) {
-                    const long long xblock = (long long)v.ny * (nx + 1);
-#pragma unroll
-                    for (int s = 0; s < NC; ++s) {
-                        const long long o = (long long)(2 * s) * xblock + (long long)c.row * (nx + 1) + f;
-                        v.sel[o] = (uint8_t)sel[2 * s];
-                        v.sel[o + xblock] = (uint8_t)sel[2 * s + 1];
+                auto rec = [&](int l, int i, int candidate) {
+                    if (REC && v.sel)
+                        v.sel[(long long)i * v.ny * (nx + 1) + (long long)c.row * (nx + 1) + sx + l] = (uint8_t)candidate;
+                };
+                const bool shortcut = (P.flags & KF_FULL_SELECTION) == 0;
+                double *Fl = fh + wseg * XW_FACES;
+                if constexpr (EQ == ADVECTION) {
+                    int sel[2];
+                    Fl[lane] = advection_flux<ORDER, true>(L + lane, Dl + lane, v.al[0], v.adv, P.delta, shortcut, sel);
+                    if (f <= nx) {
+                        rec(lane, 0, sel[0]);
+                        rec(lane, 1, sel[1]);
                     }
+                } else {
+                    const LineLds l{L, XW_SEGS * NNP, Fl, XW_SEGS * XW_FACES, list + 64 * wseg};
+                    double Fh[3];
+                    const unsigned long long fail =
+                        line_top<ORDER, CH>(l, v.al, P.gm1, P.delta, shortcut, f <= nx, Fh, rec);
+                    line_selections<ORDER, CH, true>(l, fail, Alpha3{v.al[0], v.al[1], v.al[2]}, P.gm1, P.delta, Fh, rec);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) Fl[q * XW_SEGS * XW_FACES + lane] = Fh[q];
                 }
             }
             wave_sync();
@@ -724,26 +707,23 @@ __global__ void step_control(KParams P)
 // touched only to load the state and store it back.  Within a stage each wave
 // owns 64-face line segments (63 cells each, taken round-robin) and works like
 // a wave of the streaming x-sweep: it stages the segment's node quantities in
-// its own LDS, computes the 64 face fluxes (top differences formed per face, as
-// the y-sweep does: staging them costs a pass and two synchronisations more,
-// and measured 15% slower here) and updates the 63 cells, synchronising only
-// with itself.  The stages write distinct arrays
+// its own LDS, computes the 64 face fluxes and updates the 63 cells.  TEAM: the
+// workgroup's waves share the selections of a round of segments (line_stage);
+// otherwise a wave synchronises only with itself.  The stages write distinct arrays
 // (u^n -> w1 -> w2 -> u^n; stage 3 reads u^n only at the cell it writes), so
 // no wave overwrites what another still reads, and one workgroup barrier per
-// stage (which also publishes the per-wave maxima) is the only one.  Every
-// arithmetic step is the streaming path's (same node quantities, staged top
-// differences, face flux, flux difference, stage combine, maxima and step
-// control), so a member's result is bitwise the one of the streaming kernels.
-// A step of a member takes a fixed latency plus its segments over the waves
-// (measured alone: 13 us at 128 nodes, 41 us at 1700), so a batch step lasts
-// about as long as its largest member's.
+// stage (which also publishes the per-wave maxima) ends it.  Every arithmetic step is
+// the streaming path's, so a member's result is bitwise the one of the streaming
+// kernels.  A step of a member takes a fixed latency plus its segments over the waves
+// (measured alone: 13 us at 128 nodes, 40 us at 1700), so a batch step lasts about as
+// long as its largest member's.
 
-// per-wave LDS of a resident workgroup: staged nodes, face fluxes
+// per-wave LDS of a resident workgroup: staged nodes, face fluxes, listed faces
 template <int EQ, int ORDER> struct ResWave {
     static constexpr int NQ = NodeTraits<EQ>::NQ, NC = NodeTraits<EQ>::NC;
     static constexpr int G = ReconTraits<ORDER>::H + 1;
     static constexpr int NN = XW_FACES + 2 * G - 1, NNP = NN + 1;
-    static constexpr int DOUBLES = NQ * NNP + NC * XW_FACES;
+    static constexpr int DOUBLES = NQ * NNP + NC * XW_FACES + (EQ == ADVECTION ? 0 : 8);
 };
 
 // all threads: the maxima of the waves of stage `par` (every thread reads every
@@ -771,15 +751,8 @@ __device__ __forceinline__ void resident_wave_maxima(Maxima<EQ> &mx, double *red
     constexpr int NV = Maxima<EQ>::NV;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double x = mx.v[i];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-        mx.v[i] = x;
-    }
-    int b = mx.bad;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) b |= __shfl_xor(b, o, 64);
+    for (int i = 0; i < NV; ++i) mx.v[i] = wave_max(mx.v[i]);
+    const int b = __builtin_amdgcn_ballot_w64(mx.bad != 0) != 0;
     if (lane == 0) {
         double *r = red + (par * NW + wv) * 8;
 #pragma unroll
@@ -788,20 +761,23 @@ __device__ __forceinline__ void resident_wave_maxima(Maxima<EQ> &mx, double *red
     }
 }
 
-// One stage over a 1D line for the waves of a resident or cooperative launch:
-// segments first, first + stride, ... (63 cells each).  Each wave stages a
-// segment's node quantities in its own LDS (wl), computes the segment's 64 face
-// fluxes and updates its cells from `in` (and `base`: u^n) into `out`; alpha
-// comes from cm, the maxima of the stage input, and the output's maxima
-// accumulate in mx.
-template <int EQ, int ORDER, int MODE, bool CH>
+// One stage over a 1D line for the NW waves of a workgroup of a resident or
+// cooperative launch: segments first .. first + NW - 1 (63 cells each, one a wave),
+// then those `stride` further, ...  Each wave stages a segment's node quantities in its
+// own LDS (wls: the first wave's), computes the segment's 64 face fluxes and updates its
+// cells from `in` (and `base`: u^n) into `out`; alpha comes from cm, the maxima of the
+// stage input, and the output's maxima accumulate in mx.  The Euler faces that need a
+// selection lie in one or two of the segments, so the workgroup's waves share them.
+// fails: 2 NW words of LDS (two rounds' counts: without a face to select a round has one
+// barrier, and a wave may be a round ahead of one that still reads).
+template <int EQ, int ORDER, int MODE, bool CH, int NW, bool TEAM>
 __device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int n, const double *in,
-                                           const double *base, double *out, double *wl, const double (&cm)[8],
+                                           const double *base, double *out, double *wls, int *fails, const double (&cm)[8],
                                            double dt, int first, int stride, Maxima<EQ> &mx)
 {
     using RW = ResWave<EQ, ORDER>;
     constexpr int NC = RW::NC, NQ = RW::NQ, G = RW::G, NN = RW::NN, NNP = RW::NNP;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double al[NC];
     if constexpr (EQ == ADVECTION) {
         al[0] = fabs(I.adv);
@@ -814,16 +790,21 @@ __device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int 
 #pragma unroll
         for (int c = 0; c < NC; ++c) al[c] = a;
     }
-    double *q = wl, *fh = wl + NQ * NNP;
+    double *wl = wls + wv * RW::DOUBLES, *q = wl, *fh = wl + NQ * NNP;
+    auto lds = [&](int w) {
+        double *p = wls + w * RW::DOUBLES, *f = p + NQ * NNP;
+        return LineLds{p, NNP, f, XW_FACES, (unsigned char *)(f + NC * XW_FACES)};
+    };
     const double idx = 1.0 / I.dx, idy = 1.0 / I.dy;
     const int nseg = (n + XW_CELLS - 1) / XW_CELLS;
-    for (int seg = first; seg < nseg; seg += stride) {
-        const int sx = seg * XW_CELLS;
+    for (int seg0 = first, par = 0; seg0 < nseg; seg0 += stride, par ^= NW) {
+        const int sx = (seg0 + wv) * XW_CELLS;
+        const bool mine = sx < n;  // (the last of them may be fewer than the waves)
         // node quantities of nodes sx - G .. sx + 63 + G - 1
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int i = lane + 64 * j;
-            if (i < NN) {
+            if (mine && i < NN) {
                 const int x = bc_map(sx - G + i, n, I.bcx);
                 double U[NC], qq[NQ];
 #pragma unroll
@@ -834,13 +815,51 @@ __device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int 
             }
         }
         wave_sync();
-        double Fh[NC];
-        int sel[2 * NC];
-        face_flux<EQ, ORDER, false, CH>(q + lane, NNP, 1, nullptr, 0, 0, al, P.gm1, P.delta, I.adv,
-                                        (P.flags & KF_FULL_SELECTION) == 0, Fh, sel);
+        const bool shortcut = (P.flags & KF_FULL_SELECTION) == 0;
+        if constexpr (EQ == ADVECTION) {
+            int sel[2];
+            if (mine) fh[lane] = advection_flux<ORDER, false>(q + lane, nullptr, al[0], I.adv, P.delta, shortcut, sel);
+            wave_sync();
+        } else {
+            auto rec = [](int, int, int) {};
+            const LineLds own = lds(wv);
+            const Alpha3 a3{al[0], al[1], al[2]};
+            double Fh[3] = {0.0, 0.0, 0.0};
+            unsigned long long fail = 0;
+            if (mine) fail = line_top<ORDER, CH>(own, al, P.gm1, P.delta, shortcut, sx + lane <= n, Fh, rec);
+            if constexpr (TEAM) {
+                if (lane == 0) fails[par + wv] = __popcll(fail);
+                __syncthreads();
+                // the waves' listed faces, one wave's after the other's
+                int upto[NW];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) fh[c * XW_FACES + lane] = Fh[c];
-        wave_sync();
+                for (int w = 0; w < NW; ++w) upto[w] = (w ? upto[w - 1] : 0) + __builtin_amdgcn_readfirstlane(fails[par + w]);
+                const int nf = upto[NW - 1];
+                if (nf) {
+#pragma unroll 1
+                    for (int at = 64 * wv; at < 3 * nf; at += 64 * NW) {
+                        const int i = min(at + lane, 3 * nf - 1), s = (i >= nf) + (i >= 2 * nf), k = i - s * nf;
+                        int w = 0, before = 0;
+#pragma unroll
+                        for (int j = 0; j + 1 < NW; ++j) {
+                            w += k >= upto[j];
+                            before = k >= upto[j] ? upto[j] : before;
+                        }
+                        const LineLds l = lds(w);
+                        line_select<ORDER, CH, false>(l, l.list[k - before], s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
+                    }
+                    __syncthreads();
+                    line_correct<ORDER, CH>(own, (fail >> lane) & 1, P.gm1, Fh);
+                }
+            } else {
+                line_selections<ORDER, CH, false>(own, fail, a3, P.gm1, P.delta, Fh, rec);
+            }
+            if (mine) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) fh[c * XW_FACES + lane] = Fh[c];
+            }
+            wave_sync();
+        }
         const int x = sx + lane;
         if (lane < XW_CELLS && x < n) {
             double Un[NC];
@@ -854,18 +873,18 @@ __device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int 
             mx.add(Un, P.gamma, idx, idy);
         }
         wave_sync();  // the next segment overwrites the staged nodes and fluxes
+        // (every wave is past the selection, or there was none)
     }
 }
 
-template <int EQ, int ORDER, int MODE, bool CH, int NW>
+template <int EQ, int ORDER, int MODE, bool CH, int NW, bool TEAM>
 __device__ __forceinline__ void resident_stage(const KParams &P, const Inst &I, int n, const double *in,
-                                               const double *base, double *out, double *wl, double *red, int par,
+                                               const double *base, double *out, double *wls, int *fails, double *red, int par,
                                                double (&cm)[8], Ctrl &C, double dt)
 {
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Maxima<EQ> mx;
     mx.reset();
-    line_stage<EQ, ORDER, MODE, CH>(P, I, n, in, base, out, wl, cm, dt, wv, NW, mx);
+    line_stage<EQ, ORDER, MODE, CH, NW, TEAM>(P, I, n, in, base, out, wls, fails, cm, dt, 0, NW, mx);
     resident_wave_maxima<EQ, NW>(mx, red, par);
     __syncthreads();  // the stage output and every wave's maxima are complete
     resident_maxima<EQ, NW>(red, par, cm, C);
@@ -873,7 +892,7 @@ __device__ __forceinline__ void resident_stage(const KParams &P, const Inst &I, 
 
 // one launch covers members res_order[res_first .. res_first + gridDim.x) (the
 // members of one LDS size class, largest first), one workgroup of NW waves each
-template <int EQ, int ORDER, bool CH, int NW>
+template <int EQ, int ORDER, bool CH, int NW, bool TEAM>
 __global__ __launch_bounds__(64 * NW) void resident_1d(KParams P, int nsteps)
 {
     using RW = ResWave<EQ, ORDER>;
@@ -882,11 +901,11 @@ __global__ __launch_bounds__(64 * NW) void resident_1d(KParams P, int nsteps)
     const int slot = P.res_first + (int)blockIdx.x;
     const Inst &I = P.inst[P.res_order ? P.res_order[slot] : slot];
     const int n = I.nx, pitch = I.pitch, tid = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ int fails[2 * NW];
     double *un = sm;
     double *w1 = un + NC * n;
     double *w2 = w1 + NC * n;
-    double *wl = w2 + NC * n + wv * RW::DOUBLES;
+    double *wls = w2 + NC * n;
     double *red = w2 + NC * n + NW * RW::DOUBLES;  // two parities of NW x 8 values
     GMEM double *ug = gmem(I.u);
 #pragma unroll
@@ -916,9 +935,9 @@ __global__ __launch_bounds__(64 * NW) void resident_1d(KParams P, int nsteps)
         // first stage after the initial maxima's parity 1), so a wave that runs
         // ahead never overwrites values another wave has yet to read
         const int par = (3 * step) & 1;
-        resident_stage<EQ, ORDER, M_S1, CH, NW>(P, I, n, un, un, w1, wl, red, par, cm, C, dt);
-        resident_stage<EQ, ORDER, M_S2, CH, NW>(P, I, n, w1, un, w2, wl, red, par ^ 1, cm, C, dt);
-        resident_stage<EQ, ORDER, M_S3, CH, NW>(P, I, n, w2, un, un, wl, red, par, cm, C, dt);
+        resident_stage<EQ, ORDER, M_S1, CH, NW, TEAM>(P, I, n, un, un, w1, wls, fails, red, par, cm, C, dt);
+        resident_stage<EQ, ORDER, M_S2, CH, NW, TEAM>(P, I, n, w1, un, w2, wls, fails, red, par ^ 1, cm, C, dt);
+        resident_stage<EQ, ORDER, M_S3, CH, NW, TEAM>(P, I, n, w2, un, un, wls, fails, red, par, cm, C, dt);
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c)
@@ -999,17 +1018,16 @@ __device__ __forceinline__ void coop_read(GMEM unsigned long long *am, int slot,
 
 template <int EQ, int ORDER, int MODE, bool CH>
 __device__ __forceinline__ bool coop_stage(const KParams &P, const Inst &I, const double *in, const double *base,
-                                           double *out, double *wl, double *red, GMEM unsigned long long *am,
+                                           double *out, double *wls, int *fails, double *red, GMEM unsigned long long *am,
                                            GMEM unsigned *bar, unsigned &nb, int s, double (&cm)[8], Ctrl &C,
                                            double dt)
 {
     constexpr int NW = RES_BLOCK / 64;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int slot = s % 3;  // stage s writes slot s mod 3 and clears the next one
     if (blockIdx.x == 0 && threadIdx.x < AMAX_VALS) am[((s + 1) % 3) * AMAX_VALS + threadIdx.x] = 0ull;
     Maxima<EQ> mx;
     mx.reset();
-    line_stage<EQ, ORDER, MODE, CH>(P, I, I.nx, in, base, out, wl, cm, dt, (int)blockIdx.x * NW + wv,
+    line_stage<EQ, ORDER, MODE, CH, NW, true>(P, I, I.nx, in, base, out, wls, fails, cm, dt, (int)blockIdx.x * NW,
                                     (int)gridDim.x * NW, mx);
     coop_publish<EQ, NW>(mx, red, am, slot);
     if (!grid_barrier(bar, ++nb * gridDim.x)) return false;
@@ -1027,8 +1045,7 @@ __global__ __launch_bounds__(RES_BLOCK) void coop_1d(KParams P, int nsteps, unsi
     __shared__ double red[NW * 8];
     const Inst &I = P.inst[0];
     const int n = I.nx, tid = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    double *wl = wls + wv * RW::DOUBLES;
+    __shared__ int fails[2 * NW];
     // global memory, so that the stage's loads and stores compile to global instructions
     double *un = (double *)gmem(I.u), *w1 = (double *)gmem(I.w1), *w2 = (double *)gmem(I.w2);
     GMEM unsigned long long *am = gmem(I.amax);
@@ -1055,9 +1072,9 @@ __global__ __launch_bounds__(RES_BLOCK) void coop_1d(KParams P, int nsteps, unsi
     for (int step = 0; ok && step < nsteps; ++step) {
         if (!control_update<EQ>(C, cm[0], cm[2], cm[6], I.dx, I.adv)) break;  // the same in every thread
         const double dt = C.dt;
-        ok = coop_stage<EQ, ORDER, M_S1, CH>(P, I, un, un, w1, wl, red, am, bar, nb, 1, cm, C, dt) &&
-             coop_stage<EQ, ORDER, M_S2, CH>(P, I, w1, un, w2, wl, red, am, bar, nb, 2, cm, C, dt) &&
-             coop_stage<EQ, ORDER, M_S3, CH>(P, I, w2, un, un, wl, red, am, bar, nb, 3, cm, C, dt);
+        ok = coop_stage<EQ, ORDER, M_S1, CH>(P, I, un, un, w1, wls, fails, red, am, bar, nb, 1, cm, C, dt) &&
+             coop_stage<EQ, ORDER, M_S2, CH>(P, I, w1, un, w2, wls, fails, red, am, bar, nb, 2, cm, C, dt) &&
+             coop_stage<EQ, ORDER, M_S3, CH>(P, I, w2, un, un, wls, fails, red, am, bar, nb, 3, cm, C, dt);
     }
     if (blockIdx.x == 0 && tid == 0) {
         if (!ok) C.status |= 2;
@@ -1198,20 +1215,26 @@ hipError_t launch_copy_pitched(const double *src, long long sp, double *dst, lon
 
 using KFn2c = void (*)(KParams, int, unsigned *);
 
-template <int NW> static KFn2 pick_resident_w(int eq, int order, bool ch)
+template <bool TEAM> static KFn2 pick_resident_team(int order, bool ch)
 {
-    if (eq == ADVECTION) return order == 7 ? resident_1d<ADVECTION, 7, true, NW> : resident_1d<ADVECTION, 5, true, NW>;
-    if (ch) return order == 7 ? resident_1d<EULER1D, 7, true, NW> : resident_1d<EULER1D, 5, true, NW>;
-    return order == 7 ? resident_1d<EULER1D, 7, false, NW> : resident_1d<EULER1D, 5, false, NW>;
+    constexpr int NW = RES_BLOCK / 64;
+    if (ch) return order == 7 ? resident_1d<EULER1D, 7, true, NW, TEAM> : resident_1d<EULER1D, 5, true, NW, TEAM>;
+    return order == 7 ? resident_1d<EULER1D, 7, false, NW, TEAM> : resident_1d<EULER1D, 5, false, NW, TEAM>;
 }
 
-static KFn2 pick_resident(int eq, int order, bool ch) { return pick_resident_w<RES_BLOCK / 64>(eq, order, ch); }
+static KFn2 pick_resident(int eq, int order, bool ch, bool team)
+{
+    constexpr int NW = RES_BLOCK / 64;
+    if (eq == ADVECTION)
+        return order == 7 ? resident_1d<ADVECTION, 7, true, NW, false> : resident_1d<ADVECTION, 5, true, NW, false>;
+    return team ? pick_resident_team<true>(order, ch) : pick_resident_team<false>(order, ch);
+}
 
-hipError_t launch_resident(int eq, int order, bool ch, int block, const KParams &p, int n_inst, int nsteps,
+hipError_t launch_resident(int eq, int order, bool ch, bool team, int block, const KParams &p, int n_inst, int nsteps,
                            size_t lds, hipStream_t s)
 {
     if (eq == EULER2D || block != RES_BLOCK) return hipErrorInvalidValue;
-    const KFn2 fn = pick_resident(eq, order, ch);
+    const KFn2 fn = pick_resident(eq, order, ch, team);
     // dynamic LDS beyond the default limit must be allowed per kernel
     const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -1268,7 +1291,7 @@ int resident_groups_per_cu(int eq, int order, bool ch)
 {
     int n = 0;
     if (eq == EULER2D ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)pick_resident(eq, order, ch), RES_BLOCK, 0) !=
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)pick_resident(eq, order, ch, false), RES_BLOCK, 0) !=
             hipSuccess)
         return 0;
     return n;

@@ -68,8 +68,9 @@ hipError_t launch_copy_pitched(const double *src, long long sp, double *dst, lon
                                long long rows, hipStream_t s);
 // nsteps controlled steps of every member (all 1D, all fitting the LDS), one
 // workgroup per member; lds = dynamic LDS bytes per workgroup
-// block: RES_BLOCK threads per workgroup; n_inst members from p.res_order[p.res_first]
-hipError_t launch_resident(int eq, int order, bool ch, int block, const KParams &p, int n_inst, int nsteps,
+// block: RES_BLOCK threads per workgroup; n_inst members from p.res_order[p.res_first];
+// team: a workgroup's waves share the selections of its Euler faces
+hipError_t launch_resident(int eq, int order, bool ch, bool team, int block, const KParams &p, int n_inst, int nsteps,
                            size_t lds, hipStream_t s);
 // largest dynamic LDS a resident workgroup may use on this device (0: none)
 size_t resident_lds_limit();
