@@ -8,6 +8,7 @@ there is no fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from dataclasses import dataclass
@@ -167,6 +168,23 @@ def _dev_ptr(t, shape=None, what="state"):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _dev_ptrs(states, shapes):
+    """Device addresses of a batch's states, each checked as _dev_ptr does.  Attribute by
+    attribute over all of them, the loops in C: 512 states one after the other took 0.35 ms,
+    as long as ten steps of small members; this way 0.1 ms."""
+    import torch
+    T = torch.Tensor
+    try:
+        if (len(states) == len(shapes) and all(isinstance(t, T) for t in states)
+                and all(map(T.is_cuda.__get__, states)) and set(map(T.dtype.__get__, states)) <= {torch.float64}
+                and all(map(T.is_contiguous, states)) and list(map(T.shape.__get__, states)) == shapes):
+            return (ctypes.c_void_p * len(shapes)).from_buffer(array.array("Q", map(T.data_ptr, states)))
+    except (TypeError, RuntimeError):
+        pass
+    # one of them is refused: find it
+    return (ctypes.c_void_p * len(states))(*[_dev_ptr(u, shape).value for u, shape in zip(states, shapes)])
+
+
 def enoao_status_string(status) -> str:
     return lib().enoao_status_string(int(status)).decode()
 
@@ -189,6 +207,7 @@ class Batch:
     def __init__(self, handle, problems):
         self.handle = handle
         self.problems = problems
+        self.shapes = [p.shape for p in problems]
 
     def __del__(self):
         if getattr(self, "handle", None):
@@ -279,7 +298,7 @@ def enoao_batch_destroy(batch: Batch):
 
 
 def enoao_batch_step(batch: Batch, states, nsteps, cfl, t_final=None, stream=None):
-    ptrs = (ctypes.c_void_p * len(states))(*[_dev_ptr(u, p.shape).value for u, p in zip(states, batch.problems)])
+    ptrs = _dev_ptrs(states, batch.shapes)
     tf = None
     if t_final is not None:
         tf = (ctypes.c_double * len(states))(*[float(x) for x in t_final])
