@@ -212,7 +212,7 @@ enoao_status enoao_batch_reset(enoao_batch *batch, void *stream);
 /* Synchronises stream; copies each member's time and step count (either
  * pointer may be NULL) and returns ENOAO_ENONPHYSICAL if a member failed a
  * device-side check (member_status[i] != 0 marks it; may be NULL; bit 1 of it
- * marks a failed grid barrier of the cooperative solver, see enoao_set_coop). */
+ * marks a failed exchange of the cooperative solver, see enoao_set_coop). */
 enoao_status enoao_batch_query(enoao_batch *batch, double *t, int64_t *steps, int32_t *member_status,
                                void *stream);
 
@@ -346,12 +346,13 @@ enoao_status enoao_set_resident(int32_t enable);
  * advection: 20; there this path measured faster), runs the time-step-
  * controlled steps of enoao_solve and enoao_batch_step in one cooperative
  * launch (hipLaunchCooperativeKernel: every workgroup resident) of many steps:
- * the stage states stay in the plan's HBM buffers, a grid barrier replaces the
- * kernel boundary after each stage, and every workgroup takes the same
- * time-step decision from the maxima the workgroups fold together.  On such a
- * line a kernel boundary costs about as much as a stage's work.  The
+ * each workgroup keeps its cells in LDS and registers, and after each stage the
+ * workgroups exchange their maxima and the cells at the ends of their ranges
+ * through words in the plan's workspace, so every workgroup takes the same
+ * time-step decision.  On such a line a kernel boundary costs about as much as
+ * a stage's work.  The
  * arithmetic is the streaming kernels' (Sections 2 to 4 as above), so results
- * are bitwise the same.  A barrier wait is bounded (the bound is never meant to
+ * are bitwise the same.  A wait for a word is bounded (the bound is never meant to
  * be reached): past it the launch stops stepping, the member's status gets
  * bit 1 (value 2) and enoao_solve returns ENOAO_EDEVICE.  Cooperative
  * launches do not overlap one another: callers that solve many such plans at

@@ -165,14 +165,15 @@ struct Runtime {
     // wave of one workgroup per CU: the cooperative solver (coop_groups workgroups)
     bool coop = false;
     int coop_groups = 0;
-    unsigned *d_bar = nullptr;  // its grid barrier words
+    unsigned *d_bar = nullptr;  // its words for a failed exchange
     bool use_coop() const { return coop && g_coop != 0; }
     // A member that also fits the resident solver takes the cooperative one when
     // its line has more segments than this: a resident stage takes its segments
     // four at a time (one per wave), a cooperative one all at once but pays its
-    // barrier and the HBM round trips (measured alone, Euler: 13.4 us per step
-    // resident at 250 nodes, 20 cooperative; 25 against 20 at 630 nodes, 41
-    // against 20 at 1700; advection: 7.8 against 9.9 at 800, 13 against 11 at 1600)
+    // exchange (measured alone, a stage, resident and cooperative: Euler 7.6 and 4.5 us at
+    // 600 nodes, 11.9 and 4.7 at 1300; advection 2.6 and 2.2 at 1000, 3.5 and 2.3 at
+    // 1300).  A few segments fewer would still gain alone (Euler 6.2 and 4.6 us at 400),
+    // but cooperative launches on several streams run one after the other.
     int coop_over_resident_segs() const { return eq == ADVECTION ? 20 : 9; }
     bool coop_first = false;
     int kflags = g_shortcut ? 0 : KF_FULL_SELECTION;  // taken when the plan or batch is created
@@ -713,7 +714,7 @@ struct Runtime {
             bool refused = false;
             HIP_TRY(prof_begin(PROF_COOP, s, slot));
             const hipError_t e =
-                launch_coop(eq, order, ch, coop_groups, params(0, -1, -1), k, h_inst[0].amax, d_bar, s, &refused);
+                launch_coop(eq, order, ch, coop_groups, params(0, -1, -1), k, (unsigned long long *)h_inst[0].w1, d_bar, s, &refused);
             if (e == hipSuccess) {
                 HIP_TRY(prof_end(slot, s));
                 return ENOAO_OK;
@@ -721,9 +722,9 @@ struct Runtime {
             if (!refused) return ENOAO_EDEVICE;
             // The runtime turned the cooperative launch down (it does while another
             // process that has made cooperative launches holds the device): clear the
-            // error and leave the object to the other solvers from now on.  The zeroing
-            // already enqueued cleared the maxima ring, so the maxima of the state at
-            // this step boundary are taken again.
+            // error and leave the object to the other solvers from now on.  The
+            // cooperative solver takes the maxima of the state itself, so they are
+            // taken here for the others.
             (void)hipGetLastError();
             prof_cancel(slot);
             coop = false;
@@ -1226,7 +1227,7 @@ enoao_status enoao_solve(enoao_plan *plan, double *u, double t_final, double cfl
         if (enoao_status e = rt.read_ctrl(s)) return e;
         const Ctrl &h = rt.h_ctrl[0];
         taken = h.steps;
-        if (h.status) {  // bit 1: a grid barrier of the cooperative solver failed (it never should)
+        if (h.status) {  // bit 1: an exchange of the cooperative solver failed (it never should)
             st = (h.status & 2) ? ENOAO_EDEVICE : ENOAO_ENONPHYSICAL;
             break;
         }

@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "enoao_common.hpp"
 #include "enoao_device.hpp"
 #include "enoao_kernels.hpp"
@@ -761,26 +763,13 @@ __device__ __forceinline__ void resident_wave_maxima(Maxima<EQ> &mx, double *red
     }
 }
 
-// One stage over a 1D line for the NW waves of a workgroup of a resident or
-// cooperative launch: segments first .. first + NW - 1 (63 cells each, one a wave),
-// then those `stride` further, ...  Each wave stages a segment's node quantities in its
-// own LDS (wls: the first wave's), computes the segment's 64 face fluxes and updates its
-// cells from `in` (and `base`: u^n) into `out`; alpha comes from cm, the maxima of the
-// stage input, and the output's maxima accumulate in mx.  The Euler faces that need a
-// selection lie in one or two of the segments, so the workgroup's waves share them.
-// fails: 2 NW words of LDS (two rounds' counts: without a face to select a round has one
-// barrier, and a wave may be a round ahead of one that still reads).
-template <int EQ, int ORDER, int MODE, bool CH, int NW, bool TEAM>
-__device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int n, const double *in,
-                                           const double *base, double *out, double *wls, int *fails, const double (&cm)[8],
-                                           double dt, int first, int stride, Maxima<EQ> &mx)
+// alpha of the fields from the maxima of a stage input
+template <int EQ, bool CH>
+__device__ __forceinline__ void line_alpha(const double (&cm)[8], double adv, double (&al)[NodeTraits<EQ>::NC])
 {
-    using RW = ResWave<EQ, ORDER>;
-    constexpr int NC = RW::NC, NQ = RW::NQ, G = RW::G, NN = RW::NN, NNP = RW::NNP;
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double al[NC];
+    constexpr int NC = NodeTraits<EQ>::NC;
     if constexpr (EQ == ADVECTION) {
-        al[0] = fabs(I.adv);
+        al[0] = fabs(adv);
     } else if constexpr (CH) {
         al[0] = cm[0];
         al[1] = cm[1];
@@ -790,14 +779,93 @@ __device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int 
 #pragma unroll
         for (int c = 0; c < NC; ++c) al[c] = a;
     }
+}
+
+// wave w's LDS of a workgroup's (wls: the first's)
+template <int EQ, int ORDER> __device__ __forceinline__ LineLds line_lds(double *wls, int w)
+{
+    using RW = ResWave<EQ, ORDER>;
+    double *q = wls + w * RW::DOUBLES, *fh = q + RW::NQ * RW::NNP;
+    return LineLds{q, RW::NNP, fh, XW_FACES, (unsigned char *)(fh + RW::NC * XW_FACES)};
+}
+
+// The fluxes of the staged segments of a workgroup's NW waves, one each, into their LDS;
+// faces: the number of this wave's that count (0: it has no segment).  TEAM: the Euler
+// faces that need a selection lie in one or two of the segments, so the waves share them;
+// counts: NW words of LDS that no wave reads or writes again before another barrier.
+template <int EQ, int ORDER, bool CH, int NW, bool TEAM>
+__device__ __forceinline__ void line_round(const KParams &P, double adv, double *wls, int *counts, int faces,
+                                           const double (&al)[NodeTraits<EQ>::NC])
+{
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const LineLds own = line_lds<EQ, ORDER>(wls, wv);
+            const bool shortcut = (P.flags & KF_FULL_SELECTION) == 0;
+            if constexpr (EQ == ADVECTION) {
+                int sel[2];
+                if (faces > 0) own.fh[lane] = advection_flux<ORDER, false>(own.q + lane, nullptr, al[0], adv, P.delta, shortcut, sel);
+                wave_sync();
+            } else {
+                auto rec = [](int, int, int) {};
+                                const Alpha3 a3{al[0], al[1], al[2]};
+                double Fh[3] = {0.0, 0.0, 0.0};
+                unsigned long long fail = 0;
+                if (faces > 0) fail = line_top<ORDER, CH>(own, al, P.gm1, P.delta, shortcut, lane < faces, Fh, rec);
+                if constexpr (TEAM) {
+                    if (lane == 0) counts[wv] = __popcll(fail);
+                    __syncthreads();
+                    // the waves' listed faces, one wave's after the other's
+                    int upto[NW];
+    #pragma unroll
+                    for (int w = 0; w < NW; ++w) upto[w] = (w ? upto[w - 1] : 0) + __builtin_amdgcn_readfirstlane(counts[w]);
+                    const int nf = upto[NW - 1];
+                    if (nf) {
+    #pragma unroll 1
+                        for (int at = 64 * wv; at < 3 * nf; at += 64 * NW) {
+                            const int i = min(at + lane, 3 * nf - 1), s = (i >= nf) + (i >= 2 * nf), k = i - s * nf;
+                            int w = 0, before = 0;
+    #pragma unroll
+                            for (int j = 0; j + 1 < NW; ++j) {
+                                w += k >= upto[j];
+                                before = k >= upto[j] ? upto[j] : before;
+                            }
+                            const LineLds l = line_lds<EQ, ORDER>(wls, w);
+                            line_select<ORDER, CH, false>(l, l.list[k - before], s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
+                        }
+                        __syncthreads();
+                        line_correct<ORDER, CH>(own, (fail >> lane) & 1, P.gm1, Fh);
+                    }
+                } else {
+                    line_selections<ORDER, CH, false>(own, fail, a3, P.gm1, P.delta, Fh, rec);
+                }
+                if (faces > 0) {
+    #pragma unroll
+                    for (int c = 0; c < 3; ++c) own.fh[c * XW_FACES + lane] = Fh[c];
+                }
+                wave_sync();
+            }
+}
+
+// One stage over a 1D line for the NW waves of a resident workgroup: segments 0 .. NW - 1
+// (63 cells each, one a wave), then the next NW, ...  Each wave stages a segment's node quantities in its
+// own LDS (wls: the first wave's), computes the segment's 64 face fluxes and updates its
+// cells from `in` (and `base`: u^n) into `out`; alpha comes from cm, the maxima of the
+// stage input, and the output's maxima accumulate in mx.
+// fails: 2 NW words of LDS (two rounds' counts: without a face to select a round has one
+// barrier, and a wave may be a round ahead of one that still reads).
+template <int EQ, int ORDER, int MODE, bool CH, int NW, bool TEAM>
+__device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int n, const double *in,
+                                           const double *base, double *out, double *wls, int *fails, const double (&cm)[8],
+                                           double dt, Maxima<EQ> &mx)
+{
+    using RW = ResWave<EQ, ORDER>;
+    constexpr int NC = RW::NC, NQ = RW::NQ, G = RW::G, NN = RW::NN, NNP = RW::NNP;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double al[NC];
+    line_alpha<EQ, CH>(cm, I.adv, al);
     double *wl = wls + wv * RW::DOUBLES, *q = wl, *fh = wl + NQ * NNP;
-    auto lds = [&](int w) {
-        double *p = wls + w * RW::DOUBLES, *f = p + NQ * NNP;
-        return LineLds{p, NNP, f, XW_FACES, (unsigned char *)(f + NC * XW_FACES)};
-    };
     const double idx = 1.0 / I.dx, idy = 1.0 / I.dy;
     const int nseg = (n + XW_CELLS - 1) / XW_CELLS;
-    for (int seg0 = first, par = 0; seg0 < nseg; seg0 += stride, par ^= NW) {
+    for (int seg0 = 0, par = 0; seg0 < nseg; seg0 += NW, par ^= NW) {
         const int sx = (seg0 + wv) * XW_CELLS;
         const bool mine = sx < n;  // (the last of them may be fewer than the waves)
         // node quantities of nodes sx - G .. sx + 63 + G - 1
@@ -815,51 +883,7 @@ __device__ __forceinline__ void line_stage(const KParams &P, const Inst &I, int 
             }
         }
         wave_sync();
-        const bool shortcut = (P.flags & KF_FULL_SELECTION) == 0;
-        if constexpr (EQ == ADVECTION) {
-            int sel[2];
-            if (mine) fh[lane] = advection_flux<ORDER, false>(q + lane, nullptr, al[0], I.adv, P.delta, shortcut, sel);
-            wave_sync();
-        } else {
-            auto rec = [](int, int, int) {};
-            const LineLds own = lds(wv);
-            const Alpha3 a3{al[0], al[1], al[2]};
-            double Fh[3] = {0.0, 0.0, 0.0};
-            unsigned long long fail = 0;
-            if (mine) fail = line_top<ORDER, CH>(own, al, P.gm1, P.delta, shortcut, sx + lane <= n, Fh, rec);
-            if constexpr (TEAM) {
-                if (lane == 0) fails[par + wv] = __popcll(fail);
-                __syncthreads();
-                // the waves' listed faces, one wave's after the other's
-                int upto[NW];
-#pragma unroll
-                for (int w = 0; w < NW; ++w) upto[w] = (w ? upto[w - 1] : 0) + __builtin_amdgcn_readfirstlane(fails[par + w]);
-                const int nf = upto[NW - 1];
-                if (nf) {
-#pragma unroll 1
-                    for (int at = 64 * wv; at < 3 * nf; at += 64 * NW) {
-                        const int i = min(at + lane, 3 * nf - 1), s = (i >= nf) + (i >= 2 * nf), k = i - s * nf;
-                        int w = 0, before = 0;
-#pragma unroll
-                        for (int j = 0; j + 1 < NW; ++j) {
-                            w += k >= upto[j];
-                            before = k >= upto[j] ? upto[j] : before;
-                        }
-                        const LineLds l = lds(w);
-                        line_select<ORDER, CH, false>(l, l.list[k - before], s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
-                    }
-                    __syncthreads();
-                    line_correct<ORDER, CH>(own, (fail >> lane) & 1, P.gm1, Fh);
-                }
-            } else {
-                line_selections<ORDER, CH, false>(own, fail, a3, P.gm1, P.delta, Fh, rec);
-            }
-            if (mine) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) fh[c * XW_FACES + lane] = Fh[c];
-            }
-            wave_sync();
-        }
+        line_round<EQ, ORDER, CH, NW, TEAM>(P, I.adv, wls, fails + par, mine ? n - sx + 1 : 0, al);
         const int x = sx + lane;
         if (lane < XW_CELLS && x < n) {
             double Un[NC];
@@ -884,7 +908,7 @@ __device__ __forceinline__ void resident_stage(const KParams &P, const Inst &I, 
 {
     Maxima<EQ> mx;
     mx.reset();
-    line_stage<EQ, ORDER, MODE, CH, NW, TEAM>(P, I, n, in, base, out, wls, fails, cm, dt, 0, NW, mx);
+    line_stage<EQ, ORDER, MODE, CH, NW, TEAM>(P, I, n, in, base, out, wls, fails, cm, dt, mx);
     resident_wave_maxima<EQ, NW>(mx, red, par);
     __syncthreads();  // the stage output and every wave's maxima are complete
     resident_maxima<EQ, NW>(red, par, cm, C);
@@ -950,131 +974,259 @@ __global__ __launch_bounds__(64 * NW) void resident_1d(KParams P, int nsteps)
 // LDS, short enough for one segment per wave of at most one workgroup per CU).
 // A kernel boundary between stages costs several microseconds, about a stage's
 // work on such a line; here one cooperative launch (every workgroup resident)
-// runs every controlled step of a call, the stage states in the plan's HBM
-// buffers, with a grid barrier after each stage.  Each wave takes its segments
-// like a wave of the resident solver (line_stage: the same arithmetic, so a
-// result is bitwise the streaming kernels'), each workgroup folds its maxima
-// into the member's three-slot ring with one atomic max per value, and after
-// the barrier every thread reads them and takes the same time-step decision.
+// runs every controlled step of a call.  A workgroup keeps its cells in LDS and
+// registers from the first stage to the last (HBM is touched to load the state and to
+// store it), and the arithmetic is the resident solver's (line_round), so a result is
+// bitwise the streaming kernels'.
+//
+// Between stages the workgroups exchange their maxima and the G cells at either end of
+// their range, one word at a time: a word is empty (a signalling NaN, which arithmetic
+// never gives) until its writer has stored it, so a reader that finds a value needs no
+// barrier, no counter and no cache operation; it waits for what it needs alone, all words
+// in flight together.  With the stage states in HBM, a counting barrier between a release
+// and an acquire of the caches, and the maxima and the states read after it, this part of
+// a stage took 8800 cycles, 3.7 us, of 6 us at 2000 nodes.
+//
+// Stage s uses words of slot s mod 3 and empties the next slot's.  Nobody reads those any
+// more: they held stage s - 2, and every workgroup has published stage s - 1, which it
+// does after it has read stage s - 2.  And a workgroup publishes its maxima of stage s
+// only after its emptying stores have completed, while a reader turns to slot s + 1 only
+// when it has found all workgroups' maxima of stage s.
 
-constexpr unsigned COOP_SPIN_LIMIT = 1u << 19;  // polls of one barrier wait (about 0.5 s; never reached)
+constexpr unsigned COOP_SPIN_LIMIT = 1u << 19;  // polls of one wait (about 0.5 s; never reached)
+constexpr unsigned long long COOP_EMPTY = 0xfff7ffffffffffffull;
+constexpr int COOP_CELLS = RES_BLOCK / 64 * XW_CELLS;  // cells of a workgroup
 
-// Grid barrier: bar[0] counts arrivals (monotonic; the n-th barrier waits for
-// n x grid), bar[1] is set when a wait outlasts its bound.  Every thread's
-// stores before it are visible to every thread after it.  Returns false once
-// a wait has failed (then it no longer waits).
-__device__ __forceinline__ bool grid_barrier(GMEM unsigned *bar, unsigned target)
+// words of a slot: maxima by value and workgroup, then cells by workgroup, end, place and component
+constexpr int coop_slot_words(int nc, int g, int groups) { return groups * (3 + 2 * g * nc); }
+static int coop_exchange_words(int eq, int order, int groups)
 {
-    __shared__ int ok;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(&bar[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int good = 1;
-        for (unsigned spin = 0;; ++spin) {
-            if (__hip_atomic_load(&bar[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) break;
-            if (__hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
-                spin >= COOP_SPIN_LIMIT) {
-                __hip_atomic_store(&bar[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                good = 0;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        ok = good;
+    // (from two workgroups on, 253 nodes, a stage state's buffer holds them: at most 99
+    // words a workgroup against 756)
+    return groups > 1 ? 3 * coop_slot_words(eq == ADVECTION ? 1 : 3, order == 7 ? 5 : 4, groups) : 0;
+}
+
+__device__ __forceinline__ void coop_store(GMEM unsigned long long *p, unsigned long long x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the value of an exchange word once it is there; false after COOP_SPIN_LIMIT polls, or
+// once another wait has failed (bar[1])
+__device__ __forceinline__ bool coop_wait(GMEM unsigned long long *p, GMEM unsigned *bar, unsigned long long &x)
+{
+    for (unsigned spin = 0; spin < COOP_SPIN_LIMIT; ++spin) {
+        x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (x != COOP_EMPTY) return true;
+        if (spin % 64 == 63 && __hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) break;
     }
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    return ok != 0;
+    __hip_atomic_store(&bar[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    x = 0;
+    return false;
 }
 
-// a workgroup's maxima into slot `slot` of the member: one atomic max per value,
-// the non-physical flag as value 7
-template <int EQ, int NW>
-__device__ __forceinline__ void coop_publish(Maxima<EQ> &mx, double *red, GMEM unsigned long long *am, int slot)
-{
-    resident_wave_maxima<EQ, NW>(mx, red, 0);
-    __syncthreads();
-    const int t = threadIdx.x;
-    if (t < Maxima<EQ>::NV || t == 7) {
-        double x = red[t];
-        for (int w = 1; w < NW; ++w) x = fmax(x, red[w * 8 + t]);
-        __hip_atomic_fetch_max(&am[slot * AMAX_VALS + t], as_bits(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
+// A workgroup's part of the line: cell x0 + i of the stage input at win[c][G + i], the
+// halo of G nodes on either side of its `cells`.
+template <int EQ, int ORDER> struct CoopLine {
+    static constexpr int NC = NodeTraits<EQ>::NC, G = ReconTraits<ORDER>::H + 1, PITCH = COOP_CELLS + 2 * G;
+    static constexpr int NV = Maxima<EQ>::NV, NW = RES_BLOCK / 64;
+    double win[NC][PITCH];
+    double red[NW][4];       // a wave's maxima and its non-physical flag
+    double all[3];           // the line's maxima
+    int counts[2 * NW];      // listed faces (line_round), by stage parity
+    int bad, failed;
 
-// every thread: the maxima of slot `slot` (after the barrier that completes them)
-template <int EQ>
-__device__ __forceinline__ void coop_read(GMEM unsigned long long *am, int slot, double (&cm)[8], Ctrl &C)
-{
-#pragma unroll
-    for (int i = 0; i < 8; ++i) cm[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < Maxima<EQ>::NV; ++i)
-        cm[i] = as_double(__hip_atomic_load(&am[slot * AMAX_VALS + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (__hip_atomic_load(&am[slot * AMAX_VALS + 7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0ull)
-        C.status |= 1;
-}
-
-template <int EQ, int ORDER, int MODE, bool CH>
-__device__ __forceinline__ bool coop_stage(const KParams &P, const Inst &I, const double *in, const double *base,
-                                           double *out, double *wls, int *fails, double *red, GMEM unsigned long long *am,
-                                           GMEM unsigned *bar, unsigned &nb, int s, double (&cm)[8], Ctrl &C,
-                                           double dt)
-{
-    constexpr int NW = RES_BLOCK / 64;
-    const int slot = s % 3;  // stage s writes slot s mod 3 and clears the next one
-    if (blockIdx.x == 0 && threadIdx.x < AMAX_VALS) am[((s + 1) % 3) * AMAX_VALS + threadIdx.x] = 0ull;
-    Maxima<EQ> mx;
-    mx.reset();
-    line_stage<EQ, ORDER, MODE, CH, NW, true>(P, I, I.nx, in, base, out, wls, fails, cm, dt, (int)blockIdx.x * NW,
-                                    (int)gridDim.x * NW, mx);
-    coop_publish<EQ, NW>(mx, red, am, slot);
-    if (!grid_barrier(bar, ++nb * gridDim.x)) return false;
-    coop_read<EQ>(am, slot, cm, C);
-    return true;
-}
-
-// bar: the plan's barrier words; the member's maxima slots and bar are zero at launch
-template <int EQ, int ORDER, bool CH>
-__global__ __launch_bounds__(RES_BLOCK) void coop_1d(KParams P, int nsteps, unsigned *bar_)
-{
-    constexpr int NW = RES_BLOCK / 64, NC = NodeTraits<EQ>::NC;
-    using RW = ResWave<EQ, ORDER>;
-    __shared__ double wls[NW * RW::DOUBLES];
-    __shared__ double red[NW * 8];
-    const Inst &I = P.inst[0];
-    const int n = I.nx, tid = threadIdx.x;
-    __shared__ int fails[2 * NW];
-    // global memory, so that the stage's loads and stores compile to global instructions
-    double *un = (double *)gmem(I.u), *w1 = (double *)gmem(I.w1), *w2 = (double *)gmem(I.w2);
-    GMEM unsigned long long *am = gmem(I.amax);
-    GMEM unsigned *bar = gmem(bar_);
-    Ctrl C = *I.ctrl;
-    unsigned nb = 0;  // barriers passed
-    double cm[8];
-    bool ok;
+    // place of node x0 - G + i (i < G) or x0 + cells + i - G of the halo in a slot; -1: own cell `own`
+    __device__ __forceinline__ int halo_word(int i, int c, int x0, int cells, int n, int bc, int groups, int &own) const
     {
-        // maxima of u^n into slot 0
-        const double idx = 1.0 / I.dx, idy = 1.0 / I.dy;
+        const int x = bc_map(i < G ? x0 - G + i : x0 + cells + i - G, n, bc);
+        const int o = x / COOP_CELLS;
+        own = x - x0;
+        if (o == (int)blockIdx.x) return -1;
+        const int k = x - o * COOP_CELLS, oc = min(COOP_CELLS, n - o * COOP_CELLS);
+        const int place = k < G ? k : G + k - (oc - G);  // from its start, or up to its end
+        return 3 * groups + (o * 2 * G + place) * NC + c;
+    }
+};
+
+template <int EQ, int ORDER, bool CH>
+__global__ __launch_bounds__(RES_BLOCK) void coop_1d(KParams P, int nsteps, unsigned long long *exchange,
+                                                    unsigned *bar_)
+{
+    using RW = ResWave<EQ, ORDER>;
+    using CL = CoopLine<EQ, ORDER>;
+    constexpr int NW = RES_BLOCK / 64, NC = RW::NC, G = RW::G, NQ = RW::NQ, NN = RW::NN, NNP = RW::NNP, NV = CL::NV;
+    __shared__ double wls[NW * RW::DOUBLES];
+    __shared__ CL S;
+    const Inst &I = P.inst[0];
+    const int n = I.nx, bc = I.bcx, tid = threadIdx.x, lane = tid & 63, groups = (int)gridDim.x;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int x0 = (int)blockIdx.x * COOP_CELLS, cells = min(COOP_CELLS, n - x0);
+    const int sx = wv * XW_CELLS;                  // the wave's segment, from x0
+    const int at = sx + lane;                      // the lane's cell, from x0
+    const bool cell = lane < XW_CELLS && at < cells;
+    const double idx = 1.0 / I.dx, idy = 1.0 / I.dy, adv = I.adv;
+    GMEM double *un = gmem(I.u);
+    GMEM unsigned long long *ex = gmem(exchange);
+    GMEM unsigned *bar = gmem(bar_);
+    const int slot_words = coop_slot_words(NC, G, groups);
+    Ctrl C = *I.ctrl;
+    double U[NC], base[NC];  // the lane's cell: stage input, u^n
+    double cm[8];
+    if (tid == 0) S.failed = 0;
+
+    // the new stage input U: to the neighbours and into win, the line's maxima into cm
+    auto exchange_stage = [&](int s) {
+        GMEM unsigned long long *now = ex + (s % 3) * slot_words, *next = ex + ((s + 1) % 3) * slot_words;
         Maxima<EQ> mx;
         mx.reset();
-        for (int j = (int)blockIdx.x * RES_BLOCK + tid; j < n; j += (int)gridDim.x * RES_BLOCK) {
-            double U[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) U[c] = un[c * n + j];
+        if (cell) {
             mx.add(U, P.gamma, idx, idy);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) S.win[c][G + at] = U[c];
         }
-        coop_publish<EQ, NW>(mx, red, am, 0);
-        ok = grid_barrier(bar, ++nb * gridDim.x);
-        if (ok) coop_read<EQ>(am, 0, cm, C);
-    }
+        if (groups > 1 && cell) {
+            const int mine = 3 * groups + (int)blockIdx.x * 2 * G * NC;
+#pragma unroll
+            for (int end = 0; end < 2; ++end) {
+                const int k = end == 0 ? at : G + at - (cells - G);
+                if (end == 0 ? at < G : at >= cells - G) {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        coop_store(&now[mine + k * NC + c], as_bits(U[c]));
+                        coop_store(&next[mine + k * NC + c], COOP_EMPTY);
+                    }
+                }
+            }
+        }
+        if (groups > 1 && tid < 3) coop_store(&next[tid * groups + (int)blockIdx.x], COOP_EMPTY);
+        const bool wbad = __builtin_amdgcn_ballot_w64(mx.bad != 0) != 0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const double x = wave_max(mx.v[i]);
+            if (lane == 0) S.red[wv][i] = x;
+        }
+        if (lane == 0) S.red[wv][3] = wbad ? 1.0 : 0.0;
+        if (tid == 0) S.bad = 0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's emptying stores are done
+        __syncthreads();
+        double own = 0.0, bad = 0.0;  // (thread i < 3: value i of the workgroup)
+        if (tid < 3) {
+            if (tid < NV)
+                for (int w = 0; w < NW; ++w) own = fmax(own, S.red[w][tid]);
+            for (int w = 0; w < NW; ++w) bad = fmax(bad, S.red[w][3]);
+        }
+        if (groups == 1) {
+            if (tid < 3) S.all[tid] = own;
+            if (tid == 0 && bad != 0.0) S.bad = 1;
+            if (tid < 2 * G * NC) {
+                int o;
+                (void)S.halo_word(tid / NC, tid % NC, x0, cells, n, bc, groups, o);
+                S.win[tid % NC][tid / NC < G ? tid / NC : cells + tid / NC] = S.win[tid % NC][G + o];
+            }
+        } else {
+            // (the flag is the sign of value 0)
+            if (tid < 3) {
+                unsigned long long w = as_bits(own);
+                if (tid == 0 && bad != 0.0) w |= 1ull << 63;
+                coop_store(&now[tid * groups + (int)blockIdx.x], w);
+            }
+            bool good = true;
+            if (wv < 3 && (wv == 0 || wv < NV)) {
+                // wave i: value i of all workgroups (advection has none: the flags alone)
+                double m = 0.0;
+                bool b = false;
+                for (int g = lane; g < groups; g += 64) {
+                    unsigned long long w;
+                    good = coop_wait(&now[wv * groups + g], bar, w) && good;
+                    b = b || (w >> 63) != 0;
+                    m = fmax(m, as_double(w & ~(1ull << 63)));
+                }
+                m = wave_max(m);
+                b = __builtin_amdgcn_ballot_w64(b) != 0;
+                if (lane == 0) {
+                    S.all[wv] = m;
+                    if (b) S.bad = 1;
+                }
+            } else if (wv == 3) {
+                // the halo
+                static_assert(2 * CL::G * CL::NC <= 64, "a lane per word of the halo");
+                if (lane < 2 * G * NC) {
+                    const int i = lane / NC, c = lane - i * NC;
+                    int o;
+                    const int k = S.halo_word(i, c, x0, cells, n, bc, groups, o);
+                    double x;
+                    if (k < 0) {
+                        x = S.win[c][G + o];
+                    } else {
+                        unsigned long long w;
+                        good = coop_wait(&now[k], bar, w);
+                        x = as_double(w);
+                    }
+                    S.win[c][i < G ? i : cells + i] = x;
+                }
+            }
+            if (!good) S.failed = 1;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) cm[i] = i < 3 && i < NV ? S.all[i] : 0.0;
+        if (S.bad) C.status |= 1;
+        return S.failed == 0;
+    };
+    // one stage: U from win
+    auto stage = [&](auto mode, int s, double dt) {
+        constexpr int MODE = decltype(mode)::value;
+        double al[NC];
+        line_alpha<EQ, CH>(cm, adv, al);
+        double *q = wls + wv * RW::DOUBLES;
+        const bool mine = sx < cells;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = lane + 64 * j;
+            if (mine && i < NN) {
+                // (nodes past the halo of a last, short segment: no face that counts has them)
+                const int k = min(sx + i, cells + 2 * G - 1);
+                double V[NC], qq[NQ];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) V[c] = S.win[c][k];
+                node_quantities<EQ>(V, P.gm1, qq);
+#pragma unroll
+                for (int m = 0; m < NQ; ++m) q[m * NNP + i] = qq[m];
+            }
+        }
+        wave_sync();
+        line_round<EQ, ORDER, CH, NW, true>(P, adv, wls, S.counts + NW * (s & 1), mine ? cells - sx + 1 : 0, al);
+        if (cell) {
+            const double *fh = q + NQ * NNP;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const double Lc = -(fh[c * XW_FACES + lane + 1] - fh[c * XW_FACES + lane]) * idx;
+                U[c] = rk_combine<MODE>(q[c * NNP + lane + G], base[c], dt, Lc);
+            }
+        }
+        // (Euler: a barrier of line_round is behind every wave's reads of win)
+        if (EQ == ADVECTION) __syncthreads();
+        return exchange_stage(s);
+    };
+
+#pragma unroll
+    for (int c = 0; c < NC; ++c) U[c] = base[c] = cell ? un[c * n + x0 + at] : 0.0;
+    bool ok = exchange_stage(0);
+    int taken = 0;
     for (int step = 0; ok && step < nsteps; ++step) {
         if (!control_update<EQ>(C, cm[0], cm[2], cm[6], I.dx, I.adv)) break;  // the same in every thread
         const double dt = C.dt;
-        ok = coop_stage<EQ, ORDER, M_S1, CH>(P, I, un, un, w1, wls, fails, red, am, bar, nb, 1, cm, C, dt) &&
-             coop_stage<EQ, ORDER, M_S2, CH>(P, I, w1, un, w2, wls, fails, red, am, bar, nb, 2, cm, C, dt) &&
-             coop_stage<EQ, ORDER, M_S3, CH>(P, I, w2, un, un, wls, fails, red, am, bar, nb, 3, cm, C, dt);
+        ok = stage(std::integral_constant<int, M_S1>{}, 1, dt) && stage(std::integral_constant<int, M_S2>{}, 2, dt) &&
+             stage(std::integral_constant<int, M_S3>{}, 3, dt);
+        if (!ok) break;
+        ++taken;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) base[c] = U[c];
+    }
+    if (taken && cell) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) un[c * n + x0 + at] = base[c];
     }
     if (blockIdx.x == 0 && tid == 0) {
         if (!ok) C.status |= 2;
@@ -1082,11 +1234,11 @@ __global__ __launch_bounds__(RES_BLOCK) void coop_1d(KParams P, int nsteps, unsi
     }
 }
 
-// zero the member's maxima slots and the barrier words before a cooperative launch
-__global__ void coop_reset(unsigned long long *amax, unsigned *bar)
+// empty exchange words and a clear failure flag before a cooperative launch
+__global__ void coop_reset(unsigned long long *exchange, int words, unsigned *bar)
 {
-    const int t = threadIdx.x;
-    if (t < AMAX_SLOTS * AMAX_VALS) amax[t] = 0ull;
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < words) exchange[t] = COOP_EMPTY;
     if (t < 2) bar[t] = 0u;
 }
 
@@ -1213,7 +1365,7 @@ hipError_t launch_copy_pitched(const double *src, long long sp, double *dst, lon
     return hipLaunchKernel((const void *)copy_pitched, grid, dim3(256), args, 0, s);
 }
 
-using KFn2c = void (*)(KParams, int, unsigned *);
+using KFn2c = void (*)(KParams, int, unsigned long long *, unsigned *);
 
 template <bool TEAM> static KFn2 pick_resident_team(int order, bool ch)
 {
@@ -1263,15 +1415,16 @@ int coop_max_groups(int eq, int order, bool ch)
 }
 
 hipError_t launch_coop(int eq, int order, bool ch, int groups, const KParams &p, int nsteps,
-                       unsigned long long *amax, unsigned *bar, hipStream_t s, bool *refused)
+                       unsigned long long *exchange, unsigned *bar, hipStream_t s, bool *refused)
 {
     *refused = false;
     if (eq == EULER2D || groups < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(coop_reset, dim3(1), dim3(64), 0, s, amax, bar);
+    const int words = coop_exchange_words(eq, order, groups);
+    hipLaunchKernelGGL(coop_reset, dim3(words / BLOCK + 1), dim3(BLOCK), 0, s, exchange, words, bar);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     KParams copy = p;
-    void *args[] = {&copy, &nsteps, &bar};
+    void *args[] = {&copy, &nsteps, &exchange, &bar};
     const hipError_t ce = hipLaunchCooperativeKernel((const void *)pick_coop(eq, order, ch), dim3(groups),
                                                      dim3(RES_BLOCK), args, 0, s);
     *refused = ce != hipSuccess;

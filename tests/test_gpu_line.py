@@ -62,3 +62,33 @@ def test_line_fluxes_at_segment_edges(n, rough, order, recon):
             E.enoao_set_coop(True)
     for name, v in got.items():
         assert np.array_equal(v, got["streaming"]), name
+
+
+@pytest.mark.parametrize("eq,bc", [("euler1d", "periodic"), ("euler1d", "transmissive"), ("advection", "periodic")])
+@pytest.mark.parametrize("order", [5, 7])
+@pytest.mark.parametrize("n", [252, 253, 757, 1263, 2020, 20163])
+def test_cooperative_halos(n, order, eq, bc):
+    """Workgroups of 252 cells whose last one holds fewer than a halo (1, 3, 4 or 3 cells: a
+    halo then spans two workgroups, or wraps), one workgroup alone, and more than a wave of
+    them: bit for bit the streaming kernels' result."""
+    torch = PT.torch_cuda()
+    from paper_2108_12742_amd import enoao as E
+    print(f"[coop] {eq} {n} order {order} {bc}", flush=True)
+    u0 = _state(n, True) if eq == "euler1d" else 1.0 + np.random.default_rng(n).uniform(-0.5, 0.5, (1, 1, n))
+    ep = E.make_problem(eq, n, 1, order, x_lo=0.0, x_hi=1.0, bc_x=bc)
+    got = []
+    for coop in (False, True):
+        E.enoao_set_resident(False)
+        E.enoao_set_coop(coop)
+        try:
+            v = PT.to_dev(torch, u0)
+            plan = E.enoao_plan_create(ep)
+            E.enoao_profile(plan, True)
+            t, steps = E.enoao_solve(plan, v, 1e300, cfl=0.2, max_steps=7)
+            torch.cuda.synchronize()
+            assert ("coop" in {k for k, (_, c) in E.enoao_profile_read(plan).items() if c}) == coop
+            got.append((v.cpu().numpy(), t, steps))
+        finally:
+            E.enoao_set_resident(True)
+            E.enoao_set_coop(True)
+    assert np.array_equal(got[0][0], got[1][0]) and got[0][1:] == got[1][1:]
