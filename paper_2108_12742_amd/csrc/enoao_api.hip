@@ -80,10 +80,8 @@ constexpr size_t BUF_STAGGER = 544;
 inline double *member_buffer(double *m, size_t cells, int i) { return m + (size_t)i * (cells + BUF_STAGGER); }
 
 // Row pitch of the states a pool owns: rows padded to a multiple of 16 doubles
-// (128 bytes), so every row starts on a cache line.  A y-sweep wave reads 8-column
-// strips of 8 rows; with rows at arbitrary 8-byte offsets those straddle two lines
-// about half the time (batches of 2D members with nx = ny = 511 or 625 ran 19-20%
-// below nx = ny = 512 or 624).  Caller-owned states (plans, batches) keep pitch nx.
+// (128 bytes), so every row starts on a cache line (a wave's row of a strip
+// then touches no line more than it must).  Caller-owned states (plans, batches) keep pitch nx.
 inline int padded_pitch(int nx) { return (nx + 15) / 16 * 16; }
 
 // most bytes of a member's list of row segments (2D)
@@ -145,7 +143,7 @@ struct Runtime {
     // pools: the fewest workgroups that share a tile list (the kernel's occupancy)
     int gmin_x[4] = {0, 0, 0, 0}, gmin_m = 0;
     int wg_per_cu = 0;  // resident workgroups per CU of the persistent sweeps (0: occupancy)
-    // per kernel kind (x-sweep stages 1..3, y-sweep stages 1..3): workgroups per
+    // per kernel kind (1D stages 1..3, 2D stages 1..3): workgroups per
     // CU of that launch (0: wg_per_cu)
     int wg_kind[6] = {0, 0, 0, 0, 0, 0};
     bool short_units = false;  // 2D: half as many rows per unit (enoao_plan_set_tiles with 4)

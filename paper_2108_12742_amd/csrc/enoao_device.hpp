@@ -247,7 +247,7 @@ __device__ __forceinline__ double Recon<ORDER>::select_top(const double (&f)[Rec
 //   advection: u
 //   Euler 1D : rho, m, E | F1, F2 | sqrt(rho), u, H   (F0 = m)
 //   Euler 2D : rho, m, n, E | F0..F3 | sqrt(rho), u, v, H
-// (for a y-sweep the two momentum components arrive exchanged, so the same
+// (along y the two momentum components arrive exchanged, so the same
 //  x-direction formulas give the y-flux in exchanged order).
 // 1/x for positive normal x: hardware reciprocal refined by two Newton steps
 // (within an ulp or so; the kernels' reciprocals and quotients are rounding-level

@@ -91,7 +91,7 @@ __device__ __forceinline__ GridView grid_view(const KParams &P, int n_inst, long
     GridView v;
     // (a lone member's control block and maxima are kernel arguments, so their loads do
     // not wait for the descriptor's)
-    v.k = P.lone_ctrl ? 0 : uniform(find_inst<false>(P.inst, n_inst, unit));
+    v.k = P.lone_ctrl ? 0 : uniform(find_last(n_inst, unit, [&](int i) { return P.inst[i].unit0; }));
     const Inst &I = P.inst[v.k];
     v.ctrl = gmem(P.lone_ctrl ? P.lone_ctrl : uniform(I.ctrl));
     v.amax = gmem(P.lone_ctrl ? P.lone_amax : uniform(I.amax));
@@ -285,7 +285,7 @@ __device__ __forceinline__ unsigned fix_range_units(long long units)
 // first entry of the list of the units from `unit` on: every strip row before it has its places
 __device__ __forceinline__ long long fix_list_start(const KParams &P, int n_inst, long long unit)
 {
-    const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst<false>(P.inst, n_inst, unit)];
+    const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst(P.inst, n_inst, unit)];
     const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
     const unsigned low = (unsigned)I.ny / (unsigned)I.row_blocks, extra = (unsigned)I.ny - low * (unsigned)I.row_blocks;
     const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);

@@ -56,14 +56,13 @@ template <typename T> __device__ __forceinline__ T uniform(T x)
 __device__ __forceinline__ double as_double(unsigned long long b) { return __longlong_as_double((long long)b); }
 __device__ __forceinline__ unsigned long long as_bits(double d) { return (unsigned long long)__double_as_longlong(d); }
 
-template <bool X>
-__device__ __forceinline__ int find_inst(const Inst *inst, int n, long long tile)
+// the member that holds a unit (2D), by each lane for itself
+__device__ __forceinline__ int find_inst(const Inst *inst, int n, long long unit)
 {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        const long long t0 = X ? inst[mid].xtile0 : inst[mid].unit0;
-        if (t0 <= tile) lo = mid;
+        if (inst[mid].unit0 <= unit) lo = mid;
         else hi = mid - 1;
     }
     return lo;
@@ -108,6 +107,23 @@ __device__ __forceinline__ double wave_max(double x)
     x = fmax(x, dpp_move<0x142>(x));  // row_bcast:15 into the next row
     x = fmax(x, dpp_move<0x143>(x));  // row_bcast:31 into rows 2 and 3
     return lane_value(x, 63);
+}
+
+// The last of n >= 1 members whose key is at most x (the first's is), searched by a whole
+// wave 64 keys at a time: one load's latency for up to 64 members and two for 4096, where
+// halving the range takes one per bit (512 members: nine, 4 us before a kernel's first load).
+template <class Key> __device__ __forceinline__ int find_last(int n, long long x, const Key &key)
+{
+    const int lane = threadIdx.x & 63;
+    int lo = 0;
+    for (int len = n; len > 1;) {
+        const int step = (len + 63) / 64, k = lo + lane * step;
+        const bool le = lane * step < len && key(k) <= x;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(le)) - 1;
+        lo += c * step;
+        len = min(step, len - c * step);
+    }
+    return lo;
 }
 
 // ---------------------------------------------------------------------------

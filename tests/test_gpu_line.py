@@ -92,3 +92,30 @@ def test_cooperative_halos(n, order, eq, bc):
             E.enoao_set_resident(True)
             E.enoao_set_coop(True)
     assert np.array_equal(got[0][0], got[1][0]) and got[0][1:] == got[1][1:]
+
+
+@pytest.mark.parametrize("members", [2, 63, 65, 200])
+def test_streaming_batch_chunks(members):
+    """Chunks of a streaming batch of uneven members (counts around a wave's width): every
+    member as on its own, bit for bit."""
+    torch = PT.torch_cuda()
+    from paper_2108_12742_amd import enoao as E
+    print(f"[batch] {members}", flush=True)
+    rng = np.random.default_rng(members)
+    sizes = [int(n) for n in np.exp(rng.uniform(np.log(1), np.log(3000), members))]
+    kw = dict(x_lo=0.0, x_hi=1.0, bc_x="transmissive")
+    probs = [E.make_problem("euler1d", n, 1, 5, **kw) for n in sizes]
+    u0 = [_state(n, k % 2 == 0) for k, n in enumerate(sizes)]
+    E.enoao_set_resident(False)
+    E.enoao_set_coop(False)
+    try:
+        states = [PT.to_dev(torch, u) for u in u0]
+        E.enoao_batch_step(E.enoao_batch_create(probs), states, 3, 0.2)
+        for k in {0, members // 2, members - 1, int(np.argmax(sizes)), int(np.argmin(sizes))}:
+            v = PT.to_dev(torch, u0[k])
+            E.enoao_solve(E.enoao_plan_create(probs[k]), v, 1e300, cfl=0.2, max_steps=3)
+            torch.cuda.synchronize()
+            assert torch.equal(v, states[k]), (k, sizes[k])
+    finally:
+        E.enoao_set_resident(True)
+        E.enoao_set_coop(True)
