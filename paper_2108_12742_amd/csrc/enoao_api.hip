@@ -500,9 +500,12 @@ struct Runtime {
         if (eq != EULER2D) return;
         if (ut == 0) list_places = 0;
         I.strips = strips_of(I.nx);
-        I.row_blocks = (I.ny + rows - 1) / rows;
+        const int blocks = (I.ny + rows - 1) / rows;
+        I.low_rows = I.ny / blocks;
+        I.extra_rows = I.ny % blocks;
+        I.inv_strips = 1.0 / I.strips;
         I.unit0 = ut;
-        I.units = (long long)I.strips * I.row_blocks;
+        I.units = (long long)I.strips * blocks;
         ut += I.units;
         I.list0 = list_places;
         list_places += (long long)I.strips * I.ny * fix_places(I.nx);

@@ -78,7 +78,8 @@ struct Inst {
     double adv;                 // advection speed
     int segs_per_row;           // ceil(nx / XW_CELLS)
     int strips;                 // 2D: ceil(nx / strip_cells(order))
-    int row_blocks;             // 2D: blocks of rows per strip
+    int low_rows, extra_rows;   // 2D: rows of a unit, one more in the first extra_rows blocks of rows
+    double inv_strips;          // 1 / strips
     int pitch;                  // row pitch of every state buffer, elements (>= nx; planes pitch * ny apart)
     long long xtile0, unit0;    // first x tile / 2D unit of this instance in the batch lists
     long long xtiles, units;    // number of x tiles / 2D units

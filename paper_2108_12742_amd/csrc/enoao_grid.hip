@@ -71,7 +71,9 @@ __device__ __forceinline__ unsigned long long lane_bits(unsigned long long x, in
 // a launch's values of one member
 struct GridView {
     long long u0, u1;  // its units in the list
-    int k, nx, ny, pitch, bcx, bcy, strips, blocks;
+    int k, nx, ny, pitch, bcx, bcy, strips;
+    unsigned low, extra;  // rows of a unit: low, one more in the first `extra` blocks
+    double inv_strips;
     int active;
     const GMEM double *in;
     GMEM double *out;
@@ -108,7 +110,9 @@ __device__ __forceinline__ GridView grid_view(const KParams &P, int n_inst, long
     v.bcx = uniform(I.bcx);
     v.bcy = uniform(I.bcy);
     v.strips = uniform(I.strips);
-    v.blocks = uniform(I.row_blocks);
+    v.low = (unsigned)uniform(I.low_rows);
+    v.extra = (unsigned)uniform(I.extra_rows);
+    v.inv_strips = uniform(I.inv_strips);
     v.active = uniform(done) == 0;
     v.dt = uniform(dt);
     v.in = gmem(uniform(P.mode == M_S2 ? I.w1 : (P.mode == M_S3 ? I.w2 : I.u)));
@@ -169,12 +173,13 @@ struct UnitBox {
 };
 __device__ __forceinline__ UnitBox unit_box(const GridView &v, long long unit, int cells)
 {
-    const unsigned lu = (unsigned)(unit - v.u0), b = lu / (unsigned)v.strips;
+    // (lu + 1/2) / strips lies at least 1 / (2 strips) from a whole number, its rounding
+    // error far below that: exact, and a tenth of a division's instructions
+    const unsigned lu = (unsigned)(unit - v.u0), b = uniform((unsigned)((lu + 0.5) * v.inv_strips));
     UnitBox u;
     u.x0 = (int)(lu - b * (unsigned)v.strips) * cells;
-    const unsigned low = (unsigned)v.ny / (unsigned)v.blocks, extra = (unsigned)v.ny - low * (unsigned)v.blocks;
-    u.y0 = (int)(b * low + min(b, extra));
-    u.y1 = u.y0 + (int)(low + (b < extra ? 1u : 0u));
+    u.y0 = (int)(b * v.low + min(b, v.extra));
+    u.y1 = u.y0 + (int)(v.low + (b < v.extra ? 1u : 0u));
     return u;
 }
 
@@ -287,7 +292,7 @@ __device__ __forceinline__ long long fix_list_start(const KParams &P, int n_inst
 {
     const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst(P.inst, n_inst, unit)];
     const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
-    const unsigned low = (unsigned)I.ny / (unsigned)I.row_blocks, extra = (unsigned)I.ny - low * (unsigned)I.row_blocks;
+    const unsigned low = (unsigned)I.low_rows, extra = (unsigned)I.extra_rows;
     const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);
     return I.list0 + fix_places(I.nx) * ((long long)I.strips * y0 + (long long)s * rows);
 }
@@ -582,10 +587,12 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
 
 // Scratch of a wave of fix_2d (LDS).  A row segment has at most 57 x-faces and 56
 // y-faces on either side.
+using WaveMost = unsigned long long[7][4];
 template <int NW> struct FixScratch {
     double dF[3][4][58];       // flux corrections by set (x, below, above) and lane from H on
     double exchange[NW][64];   // window values by node and (face, field)
     unsigned char face[176];   // set << 6 | lane of each face
+    WaveMost most;             // the wave's maxima, in four parts
 };
 
 // A face's line along x or y: window node t is pos + t on it
@@ -657,17 +664,27 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     };
     const RkWeights rk = rk_weights(P.mode);
     unsigned long long bad = 0, next = load_entry(at);
-    double mine = 0.0;  // lane i: the wave's maximum of value i
+    WaveMost &M = scratch[wv].most;
+    if (STEP && lane < 28) M[lane >> 2][lane & 3] = 0ull;
     const int ld = min(max(lane - H, 0), 57);  // (lanes outside repeat the first and last)
     GridView v;
     v.u0 = 0;
     v.u1 = -1;
     auto flush = [&]() {
+        wave_sync();
+        unsigned long long mine = 0ull;
+        if (lane < 7) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                mine = max(mine, M[lane][i]);
+                M[lane][i] = 0ull;
+            }
+        }
+        wave_sync();
         if (lane < 7)
             __hip_atomic_fetch_max(&v.amax[P.r_out * amax_slot_words(EULER2D) + blockIdx.x % amax_copies(EULER2D) * AMAX_VALS + lane],
-                                   as_bits(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                   mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (bad && lane == 0) __hip_atomic_fetch_or(&v.ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        mine = 0.0;
         bad = 0;
     };
     while (at < count) {
@@ -835,8 +852,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                 bad |= __builtin_amdgcn_ballot_w64(b);
 #pragma unroll
                 for (int i = 0; i < 7; ++i) {
-                    const double x = wave_max(m.v[i]);
-                    if (lane == i) mine = fmax(mine, x);
+                    // a quad's maximum (a whole wave's over DPP would take twice as long)
+                    double x = fmax(m.v[i], dpp_move<0xb1>(m.v[i]));
+                    x = fmax(x, dpp_move<0x4e>(x));
+                    if ((lane & 3) == 0)
+                        __hip_atomic_fetch_max(&M[i][(lane >> 2) & 3], as_bits(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 }
             }
             sync();
