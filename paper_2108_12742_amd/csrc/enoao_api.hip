@@ -548,7 +548,7 @@ struct Runtime {
         if (eq == EULER2D) {
             // a workgroup per listed row at most (a pool's rows change between steps)
             long long most = 0;
-            for (const Inst &I : h_inst) most += (long long)I.strips * I.ny;
+            for (const Inst &I : h_inst) most += 4ll * I.strips * I.ny;  // (two pieces of two halves a row)
             if (dynamic || h_inst.empty()) most = 1ll << 30;
             grid_fix = (int)std::min<long long>(most, (long long)cus * occupancy_fix_2d(order, M_S2, false, ch));
         }

@@ -517,13 +517,17 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
                         if (lane == 0) pending[wv][npend] = FixEntry{where | (unsigned)(lo << 6 | hi), x, b, t};
                         ++npend;
                     };
-                    if (__popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t) <= FIX_FACES) {
+                    const int faces = __popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t);
+                    if (faces <= FIX_FACES) {
                         push(G, 63 - G, fail_x, fail_b, fail_t);
                     } else {
+                        // (a row coarse along x alone has 57 faces and some: two pieces of two
+                        // passes, where four would be of two as well)
+                        const int width = faces > 3 * FIX_FACES / 2 ? FIX_SPLIT : 2 * FIX_SPLIT;
 #pragma unroll 1
-                        for (int lo = G; lo < min(64 - G, nx - x0 + G); lo += FIX_SPLIT) {  // (pieces with cells: the list's places)
-                            const unsigned long long m = ((1ull << FIX_SPLIT) - 1) << lo;
-                            push(lo, min(lo + FIX_SPLIT, 64 - G) - 1, fail_x & (m | m >> 1), fail_b & m, fail_t & m);
+                        for (int lo = G; lo < min(64 - G, nx - x0 + G); lo += width) {  // (pieces with cells: the list's places)
+                            const unsigned long long m = ((1ull << width) - 1) << lo;
+                            push(lo, min(lo + width, 64 - G) - 1, fail_x & (m | m >> 1), fail_b & m, fail_t & m);
                         }
                     }
                     if (npend > PENDING - 4) flush_pending(unit);
@@ -644,10 +648,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
         const unsigned x = __shfl_up(upto, o, 64);
         upto += lane >= o ? x : 0u;
     }
-    const unsigned count = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1);
-    if (count == 0) return;
+    const unsigned entries = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1);
+    if (entries == 0) return;
     const long long list_skew = list0 - (long long)(upto - mine_n);  // entry i of all is at i + list_skew
-    const bool team = count <= gridDim.x;
+    // Few entries leave waves idle: workgroups share an entry, or halves of entries go to
+    // different workgroups or waves.  (30 x 30, six steps: 513 us without the halves; more
+    // and smaller pieces from the start cost a full machine 5 to 12%.)
+    const unsigned waves = gridDim.x * NWV;
+    const bool team = entries <= gridDim.x;
+    const unsigned halves = 2 * entries <= (team ? gridDim.x : waves) ? 1u : 0u;
+    const unsigned count = entries << halves;
     const unsigned stride = team ? gridDim.x : gridDim.x * NWV;
     unsigned at = team ? blockIdx.x : blockIdx.x * NWV + wv, next_at = at + stride;
     FixScratch<NW> &S = scratch[team ? 0 : wv];
@@ -658,8 +668,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     };
     auto load_entry = [&](unsigned i) {
         if (i >= count) return 0ull;
-        const int c = __popcll(__builtin_amdgcn_ballot_w64(lane < FIX_RANGES && upto <= i));
-        const long long e = i + (long long)lane_bits((unsigned long long)list_skew, c);
+        const unsigned en = i >> halves;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(lane < FIX_RANGES && upto <= en));
+        const long long e = en + (long long)lane_bits((unsigned long long)list_skew, c);
         return lane < 4 ? gmem(P.fix_list)[4 * e + lane] : 0ull;
     };
     const RkWeights rk = rk_weights(P.mode);
@@ -689,11 +700,26 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     };
     while (at < count) {
         {
-            const unsigned long long where = lane_bits(next, 0), fx = lane_bits(next, 1), fb = lane_bits(next, 2),
-                                     ft = lane_bits(next, 3);
+            const unsigned long long where = lane_bits(next, 0);
+            unsigned long long fx = lane_bits(next, 1), fb = lane_bits(next, 2), ft = lane_bits(next, 3);
+            const unsigned half = at & halves;
             next = load_entry(next_at);  // on its way while this one is worked on
             const long long unit = (long long)(where >> 28);
-            const int lo = (int)(where >> 6) & 63, hi = (int)where & 63;  // lanes of its cells
+            int lo = (int)(where >> 6) & 63, hi = (int)where & 63;  // lanes of its cells
+            if (halves) {
+                const int mid = (lo + hi + 1) >> 1;
+                lo = half ? mid : lo;
+                hi = half ? hi : mid - 1;
+                const unsigned long long m = (2ull << hi) - (1ull << lo);
+                fx &= m | m >> 1;
+                fb &= m;
+                ft &= m;
+                if (!(fx | fb | ft)) {
+                    at = next_at;
+                    next_at = at + stride;
+                    continue;
+                }
+            }
             if (unit < v.u0 || unit >= v.u1) {
                 if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();
                 v = grid_view<ORDER, CH>(P, n_inst, unit);
