@@ -26,18 +26,26 @@ import time
 import numpy as np
 
 METRIC = "cell-updates/s + % HBM/FP64 roofline; batched vs plain; p50/p99 latency"
-# y-sweep strip width the library takes by default for each order (the same
-# launch as enoao_plan_set_tiles with 0)
-DEFAULT_STRIP_COLUMNS = {5: 8, 7: 4}
+# 2D tile setting the library takes by default for each order (the same launch as
+# enoao_plan_set_tiles with 0)
+DEFAULT_STRIP_COLUMNS = {5: 8, 7: 8}
 
 
-def kernel_symbol(kind, order, y_strip_columns):
-    """Kernel symbol as rocprofv3 prints it for a profile kind ("sweep_x_s2", ...) of a
-    2D plan without selection record."""
-    stage = int(kind[-1])
-    if kind.startswith("sweep_x"):
-        return f"enoao::sweep_x<2, {order}, {stage}, false, true>"
-    return f"enoao::sweep_y<{order}, {stage}, false, {y_strip_columns}, true>"
+def kernel_symbol(kind, order):
+    """Kernel symbol as rocprofv3 prints it for a 2D profile kind ("sweep_y_s2", ...: a
+    whole stage, both its kernels) of a plan without selection record.  The three stages
+    share one instantiation; fix_2d, launched after it, has the same arguments."""
+    return f"enoao::stage_2d<{order}, true, false, true>"
+
+
+def stage_symbols(symbol):
+    """the kernels whose launches a profile entry of `symbol` covers"""
+    return (symbol, symbol.replace("stage_2d", "fix_2d")) if "stage_2d" in symbol else (symbol,)
+
+
+def _per_launch(workload, field, symbol):
+    v = [_counters(workload).get(field, {}).get(k) for k in stage_symbols(symbol)]
+    return None if None in v else float(sum(v))
 
 
 def kernel_sources_hash():
@@ -98,15 +106,14 @@ def _counters(workload):
 def measured_traffic(symbol, workload):
     """HBM bytes per launch of `symbol` (FETCH_SIZE + WRITE_SIZE, scaled by a copy of
     known size), or None when the kernels changed since the counters were taken."""
-    v = _counters(workload).get("bytes_per_launch", {}).get(symbol)
+    v = _per_launch(workload, "bytes_per_launch", symbol)
     return None if v is None else round(v)
 
 
 def measured_fp64_flops(symbol, workload):
     """Executed FP64 flops per launch of `symbol` (SQ_INSTS_VALU_FLOPS_FP64 x 64 lanes),
     or None."""
-    v = _counters(workload).get("fp64_flops_per_launch", {}).get(symbol)
-    return None if v is None else float(v)
+    return _per_launch(workload, "fp64_flops_per_launch", symbol)
 
 
 def kernel_roofline(R, equation, kind, stage, cells, ms, symbol, workload, order):
@@ -176,7 +183,7 @@ def cpu_baseline(n_sample=2048, max_threads=16):
             "per_thread_value": cells / (sum(per) / len(per)), "nproc": nproc, "cpu_model": model}
 
 
-def kernel_table(R, prof, cells, order, y_strip_columns, workload, equation="euler2d"):
+def kernel_table(R, prof, cells, order, workload, equation="euler2d"):
     """Per kernel kind: mean duration, launches, symbol and roofline; and the kind with
     the largest total time (the dominant kernel)."""
     kernels, best = {}, None
@@ -186,7 +193,7 @@ def kernel_table(R, prof, cells, order, y_strip_columns, workload, equation="eul
         entry = {"mean_ms": round(ms, 4), "launches": cnt}
         if kind.startswith("sweep"):
             stage = int(kind[-1])
-            entry["symbol"] = kernel_symbol(kind, order, y_strip_columns)
+            entry["symbol"] = kernel_symbol(kind, order)
             entry["roofline"] = kernel_roofline(R, equation, kind, stage, cells, ms, entry["symbol"], workload, order)
             if best is None or ms * cnt > best[1]:
                 best = (kind, ms * cnt)
@@ -563,7 +570,7 @@ def bench_order7(n=2048, steps=30, warmup=2, tune=True):
         E.enoao_plan_set_launch_kinds(plan, kinds)
     el, el_inst, prof = timed_solve(E, plan, u, u0, steps, warmup)
     cells = n * n
-    kernels, best = kernel_table(R, prof, cells, 7, yw, workload)
+    kernels, best = kernel_table(R, prof, cells, 7, workload)
     value = cells * steps / el
     return {"workload": workload, "steps": steps, "value": value,
             "unit": "cell-updates/s", "ms_per_step": el * 1e3 / steps,
@@ -713,7 +720,7 @@ def main():
                     help="main workload at the default launch shape (occupancy; y strips of the "
                          "order's default width, or --y-strip-columns)")
     ap.add_argument("--y-strip-columns", type=int, default=0, choices=(0, 4, 8),
-                    help="with --no-tune: y-sweep strip width (0 = the order's default)")
+                    help="with --no-tune: 2D tile setting (8, or 4: half the rows a wave walks; 0 = the order's default)")
     ap.add_argument("--workgroups-per-cu", type=int, default=0,
                     help="with --no-tune: resident workgroups per CU of the persistent sweeps (0 = occupancy)")
     ap.add_argument("--only-leg", choices=("batched", "batched_small", "served", "c1", "plain8"), default=None,
@@ -791,7 +798,7 @@ def main():
     cells = n * n
     value = cells * K / el
     workload = f"euler2d-quadrants-{n}x{n}-ao{args.order}"
-    kernels, best = kernel_table(R, prof, cells, args.order, launch[1], workload)
+    kernels, best = kernel_table(R, prof, cells, args.order, workload)
     roof = dict(kernels[best]["roofline"])
     roof["step"] = step_roofline(R, "euler2d", value, kernels, cells, K, workload)
     out = {

@@ -278,7 +278,8 @@ enoao_status enoao_pool_usage(const enoao_pool *pool, size_t *arena_used, size_t
  * the stream the kernel runs on.  enoao_profile_read synchronises stream and
  * returns, per kernel kind, the mean duration in ms and the number of
  * launches since profiling was enabled.  Kinds (n_kinds <= 10):
- *   0..2 x-sweep of stage 1..3, 3..5 y-sweep of stage 1..3 (2D only),
+ *   0..2 the sweep of stage 1..3 (1D), 3..5 stage 1..3 (2D: the stage kernel
+ *   and the selections after it, one pair of events around both),
  *   6 time-step control, 7 initial per-field maxima, 8 LDS-resident solver,
  *   9 cooperative solver (8 and 9: one launch per call, all of its controlled
  *   steps). */
@@ -300,23 +301,20 @@ enoao_status enoao_plan_set_launch(enoao_plan *plan, int32_t workgroups_per_cu);
 enoao_status enoao_batch_set_launch(enoao_batch *batch, int32_t workgroups_per_cu);
 
 /* Launch shape per kernel kind: workgroups_per_cu[k] (0..64) for kind k of
- * the stage kernels, k = 0..2 the x-sweep of stage 1..3 and 3..5 the y-sweep
- * of stage 1..3 (the kinds of enoao_profile_read); 0, or k >= n_kinds, keeps
- * the object's uniform setting (enoao_plan_set_launch / enoao_batch_set_launch,
- * which in turn clears these).  The sweeps of one stage can prefer different
- * shapes (on the 2048^2 2D Euler workload: the x-sweep 6 per CU, the first
- * y-sweep 2, the others 3).  ENOAO_EINVAL: n_kinds outside 0..6, a NULL array
+ * the stage kernels, k = 0..2 stage 1..3 in 1D and 3..5 stage 1..3 in 2D (the
+ * kinds of enoao_profile_read); 0, or k >= n_kinds, keeps the object's uniform
+ * setting (enoao_plan_set_launch / enoao_batch_set_launch, which in turn clears
+ * these).  ENOAO_EINVAL: n_kinds outside 0..6, a NULL array
  * with n_kinds > 0, or an entry outside 0..64.  The captured graphs are
  * rebuilt on the next call; results do not depend on the shapes. */
 enoao_status enoao_plan_set_launch_kinds(enoao_plan *plan, const int32_t *workgroups_per_cu, int32_t n_kinds);
 enoao_status enoao_batch_set_launch_kinds(enoao_batch *batch, const int32_t *workgroups_per_cu, int32_t n_kinds);
 
-/* Tile width of the 2D y-sweep: columns per wave strip, 4 or 8 (0 = the
- * default: 8 for order 5, 4 for order 7).  A y tile is 4 strips wide and 64/w cell rows tall; wider
- * strips load longer row segments per wave, narrower ones stage fewer halo
- * rows per face.  The plan's or batch's tile lists are rebuilt (this
- * synchronises stream) and its captured graph is dropped.  1D problems have
- * no y-sweep and ignore the setting.  Results do not depend on it. */
+/* Rows that a wave of the 2D stage kernel walks: 8 (and 0, the default) give
+ * each wave that can be resident one stretch of rows, 4 stretches half as long
+ * (more of them to even out the end, more halo rows).  The plan's or batch's
+ * lists are rebuilt (this synchronises stream) and its captured graph is
+ * dropped.  1D problems ignore the setting.  Results do not depend on it. */
 enoao_status enoao_plan_set_tiles(enoao_plan *plan, int32_t y_strip_columns, void *stream);
 enoao_status enoao_batch_set_tiles(enoao_batch *batch, int32_t y_strip_columns, void *stream);
 

@@ -44,7 +44,7 @@ def kernel_sources_hash() -> str:
 
 def kernel_symbol(name: str) -> str:
     """a profiler's kernel name without return type and argument list:
-    "void enoao::sweep_y<5, 2, false, 8, true>(enoao::KParams)" -> "enoao::sweep_y<5, 2, false, 8, true>" """
+    "void enoao::stage_2d<5, true, false, true>(enoao::KParams)" -> "enoao::stage_2d<5, true, false, true>" """
     name = name.strip()
     if name.startswith("void "):
         name = name[5:]

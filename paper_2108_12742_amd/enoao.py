@@ -381,7 +381,7 @@ def _kinds(workgroups_per_cu):
 
 
 def enoao_plan_set_launch_kinds(plan: Plan, workgroups_per_cu):
-    """Workgroups per CU per kernel kind (x-sweep stages 1..3, y-sweep stages 1..3; 0 = uniform)."""
+    """Workgroups per CU per kernel kind (1D stages 1..3, 2D stages 1..3; 0 = uniform)."""
     arr, n = _kinds(workgroups_per_cu)
     _check(lib().enoao_plan_set_launch_kinds(plan.handle, arr, n), "enoao_plan_set_launch_kinds")
 

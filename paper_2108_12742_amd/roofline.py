@@ -8,19 +8,17 @@ multiply-add = 2; fabs and negation free).  Two layouts of the same arithmetic:
   * window form: every stencil node projected and split, every indicator and
     one candidate flux per side (branch-free selection) -- the full selection,
     which the kernels run only for the fields of a wave that need it;
-  * top form (every sweep and the LDS-resident solver): the top candidate's two
-    indicators and the sum of its one-sided values from conserved-variable
-    differences and a symmetric stencil, seven projected vectors per face.  The
-    full selection that waves with a field off the top candidate add is
-    data-dependent and not counted (the count is a lower bound there).
+  * top form (every face kernel): the flux where every field takes its top
+    candidate, from one conserved-variable difference and a symmetric stencil, and
+    the bound on the indicators that tells such faces, one projected vector per
+    face.  The selections of the faces that the bound leaves are data-dependent and
+    not counted (the count is a lower bound there).
 Bytes: algorithmic HBM traffic of a Runge-Kutta stage, per cell: the stage
 reads its input state once (and u^n in stages 2 and 3) and writes its output
 once -- 2 x, 3 x, 3 x the state's 8 * ncomp bytes, i.e. 64/96/96 = 256 B per 2D
 cell-update, 48/72/72 = 192 B for 1D Euler.  Intermediate arrays of an
-implementation (the x-part of L that the 2D x-sweep writes and the y-sweep
-reads back, second reads of the stage input) are not algorithmic: a stage's
-bytes belong to the kernel that completes the stage (the y-sweep in 2D), and
-the 2D x-sweep carries none of its own.
+implementation are not algorithmic.  In 2D a stage is timed as one entry (kernel
+'y': the stage kernel and the selections after it) that carries all of them.
 
 Peaks (MI355X, published): HBM3E 8.0 TB/s; FP64 vector 78.6 TFLOP/s
 (256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz).
@@ -64,13 +62,11 @@ TOP_SYM = {5: 3 + 2 + 2 * 2, 7: 4 + 3 + 3 * 2}
 
 
 def face_flops_top(equation: str, order: int) -> int:
-    """Top form of one face (common path): node quantities and the top
-    differences of one node (the essential work; a kernel that forms them per
-    face from the window does three nodes' worth), the symmetric stencil of F,
-    the Roe state, seven projections (D_0, D_1, D_2 of U and F, S F), per field
-    both sides' indicators (two fma, a min and a compare each) and the value sum
-    (a multiply and an fma, then the window scaling), the back-projection and
-    the flux difference."""
+    """Top form of one face (common path): node quantities, D_1 of U and F (the flux
+    of the density is a component of U), the symmetric stencil of F, the Roe state,
+    one projection (D_1 U), a multiply per field, the back-projection, the sum with
+    the central part, the bound (its two factors, a compare) and the flux
+    difference.  (Advection: both sides' indicators and the value sum.)"""
     d, sym = TOP_DIFF[order], TOP_SYM[order]
     if equation == "advection":
         # differences and stencil of u; per side two a*D products (mul + fma), min,
@@ -80,9 +76,9 @@ def face_flops_top(equation: str, order: int) -> int:
     node = 15 if nc == 4 else 12
     roe = 23 if nc == 4 else 19
     proj_vec = 15 if nc == 4 else 11
-    fields = nc * (2 * (2 * 2 + 1 + 1) + (1 + 2 + 1))
     back = 16 if nc == 4 else 12
-    return node + 2 * nc * d + nc * sym + roe + 7 * proj_vec + fields + back + 2 * nc
+    bound = 12 + 3 * nc + 2
+    return node + (2 * nc - 1) * d + nc * sym + roe + proj_vec + nc + back + 2 * nc + bound + 2 * nc
 
 
 def combine_flops(nc: int, stage: int) -> int:
@@ -96,8 +92,7 @@ MAXIMA_FLOPS = {"advection": 1, "euler1d": 16, "euler2d": 28}  # per-field wave-
 
 def stage_cell_flops(equation: str, stage: int) -> int:
     """Per-cell work of a stage besides the faces, summed over the stage's kernels:
-    1D: combine + maxima in the x-sweep; 2D: the y-sweep adds L_x and L_y (one add
-    per component), combines and takes the maxima."""
+    1D: combine + maxima; 2D: the sum of L_x and L_y too (one add per component)."""
     nc = {"advection": 1, "euler1d": 3, "euler2d": 4}[equation]
     extra = nc if equation == "euler2d" else 0
     return combine_flops(nc, stage) + MAXIMA_FLOPS[equation] + extra
@@ -111,36 +106,23 @@ def stage_bytes(equation: str, stage: int) -> int:
 
 
 def algorithmic_bytes(equation: str, kernel: str, stage: int) -> int:
-    """The stage's algorithmic bytes attributed to one kernel of it: all of them to
-    the kernel that completes the stage (1D x-sweep, 2D y-sweep), none to the 2D
-    x-sweep."""
+    """The stage's algorithmic bytes by profile entry: 1D all to 'x'; 2D all to 'y',
+    which covers the whole stage."""
     if equation == "euler2d" and kernel == "x":
         return 0
     return stage_bytes(equation, stage)
-
-
-def sweep_bytes(equation: str, kernel: str, stage: int) -> int:
-    """Compulsory HBM bytes per cell of one launch (stage 0: evaluation of L only).
-
-    1D 'x': read the stage input (+ u^n for stages 2, 3), write the stage output.
-    2D 'x': read the stage input, write L_x.
-    2D 'y': read the stage input and L_x (+ u^n for stages 2, 3), write the stage
-    output (rhs: L)."""
-    nc = {"advection": 1, "euler1d": 3, "euler2d": 4}[equation]
-    w = 8 * nc
-    if equation == "euler2d":
-        return 2 * w if kernel == "x" else 3 * w + (w if stage > 1 else 0)
-    return 2 * w + (w if stage > 1 else 0)
 
 
 def sweep_flops(equation: str, order: int, kernel: str, stage: int) -> int:
     """Algorithmic flops per cell of one launch (top form)."""
     nc = {"advection": 1, "euler1d": 3, "euler2d": 4}[equation]
     f = face_flops_top(equation, order)
+    if equation == "euler2d":  # both faces of a cell, and L_x + L_y
+        if kernel == "x":
+            return 0
+        f = 2 * f + nc
     if stage == 0:
         return f
-    if equation == "euler2d":
-        return f if kernel == "x" else f + nc + combine_flops(nc, stage) + MAXIMA_FLOPS[equation]
     return f + combine_flops(nc, stage) + MAXIMA_FLOPS[equation]
 
 
@@ -152,14 +134,6 @@ def cell_update_flops(equation: str, order: int) -> int:
 def cell_update_bytes(equation: str) -> int:
     """Algorithmic HBM bytes of one cell-update (three stages): 256 B in 2D."""
     return sum(stage_bytes(equation, s) for s in (1, 2, 3))
-
-
-def split_sweep_bytes(equation: str) -> int:
-    """Compulsory bytes per cell-update of the split 2D layout (x-part of L written and
-    read back, stage input read by both sweeps): the implementation's own minimum."""
-    if equation == "euler2d":
-        return sum(sweep_bytes(equation, "x", s) + sweep_bytes(equation, "y", s) for s in (1, 2, 3))
-    return sum(sweep_bytes(equation, "x", s) for s in (1, 2, 3))
 
 
 def hbm_entry(nbytes: float, seconds: float, traffic=None):

@@ -2,8 +2,9 @@
 
 The sweeps run as persistent grids of (CUs x W) workgroups; W (workgroups of 4
 waves resident per CU) trades latency hiding against the tail of the last
-tiles.  In 2D the y-sweep tile width is a second knob: wave strips of 4 or 8
-columns (longer row segments per load against fewer staged halo rows).  The
+tiles.  In 2D the rows a wave walks are a second knob: setting 8 gives every
+resident wave one stretch of rows, 4 stretches half as long (an evener end
+against more halo rows).  The
 tuner times a few steps of the caller's batch for each candidate (W, width)
 and keeps the fastest per (equation, order, size bucket) in a JSON cache
 (ENOAO_TUNE_CACHE, default ~/.cache/enoao_tune.json).  tune_kinds then lets
@@ -19,7 +20,7 @@ import os
 import time
 
 CANDIDATES = (0, 1, 2, 3, 4, 6, 8, 12, 16)  # W; 0 = the occupancy the kernels' resources allow
-Y_WIDTHS = (8, 4)                    # columns per wave strip of the y tiles (2D only)
+Y_WIDTHS = (8, 4)                    # tile setting (2D only): long or short stretches of rows
 
 
 def cache_path():
@@ -119,16 +120,16 @@ KINDS = ("sweep_x_s1", "sweep_x_s2", "sweep_x_s3", "sweep_y_s1", "sweep_y_s2", "
 
 def tune_kinds(problems, states, w, yw, steps=30, candidates=(2, 3, 4, 6), cfl=0.3, use_cache=True, rounds=3):
     """Per-kernel launch shapes on top of the uniform (w, yw) from tune_batch, by
-    coordinate descent on whole steps: kernel kind by kind (x-sweep stages 1..3,
-    then in 2D y-sweep stages 1..3), each candidate W for that kind is compared
+    coordinate descent on whole steps: kernel kind by kind (stages 1..3 in 1D,
+    then in 2D stages 1..3 there, whose first three kinds launch nothing), each candidate W for that kind is compared
     with the current shapes on whole captured steps, the two timed in turn (best
     of `rounds` timings of `steps` steps each: long enough that the launch and the
     synchronisation around a timing stay below the differences sought, and taken
     in turn so that drifts of the clock affect both), and kept when it gains more
     than 0.3%.  The result is kept if it beats the uniform shape by more than
     0.5% in a last comparison of the same kind.  (The kernels' durations in a
-    profiled run, with events between the launches, did not rank the shapes of the
-    later y-sweeps as a graph replay does.)  Returns (shapes, info): shapes is a
+    profiled run, with events between the launches, did not rank the shapes as a
+    graph replay does.)  Returns (shapes, info): shapes is a
     tuple of workgroups per CU per kind (0: the uniform w) or None; info has the
     trials (ms per step, current and candidate) and the last comparison."""
     import torch
