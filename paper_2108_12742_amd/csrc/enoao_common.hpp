@@ -24,9 +24,10 @@ constexpr int XW_SEGS = 4;
 // block of one strip.
 constexpr int strip_cells(int order) { return order == 7 ? 54 : 56; }
 // Row segments whose faces need a selection are listed for a second kernel: one entry
-// per strip and row, or one per FIX_SPLIT cells where there are more than
-// FIX_FACES faces to select (a segment along a shock holds up to 169, eleven passes of
-// the wave that takes it, and the launch waited for those).  The units are cut into FIX_RANGES ranges with a list
+// per strip and row, or one per 2 FIX_SPLIT cells where there are more than FIX_FACES
+// faces to select, per FIX_SPLIT cells from half as many again (a segment along a shock
+// holds up to 169, eleven passes of the wave that takes it, and the launch waited for
+// those).  The units are cut into FIX_RANGES ranges with a list
 // and a counter each, the counters a cache line apart: the waves that end a launch
 // together take their places at once, and an atomic on one line takes 20 ns.  Four
 // sets of counters, three used in turn by the stages of a step, the fourth by an
