@@ -111,12 +111,27 @@ template <int ORDER> struct Recon {
     //     h6 = h5 + e1/60, h7 = h5 + e2/60, h8 = h6 + g1/105,
     // (a, b, c, ... the 1st, 2nd, 3rd ... undivided differences, index = first
     // node).
+    __device__ __forceinline__ static double select(const double (&f)[W], double delta, double is_top, int &sel)
+    {
+        return select_from(f, f[H], delta, is_top, sel);
+    }
     // The same with the top candidate's indicator taken from the window itself;
     // top: the top candidate's value.
-    __device__ __forceinline__ static double select_top(const double (&f)[W], double delta, int &sel, double &top);
+    __device__ __forceinline__ static double select_top(const double (&f)[W], double delta, int &sel, double &top)
+    {
+        return select_from(f, f[H], delta, window_is_top(f), sel, &top);
+    }
+    // The chosen candidate's value less f_j, formed without f_j.
+    __device__ __forceinline__ static double select_step(const double (&f)[W], double delta, int &sel)
+    {
+        return select_from(f, 0.0, delta, window_is_top(f), sel);
+    }
 
-    __device__ __forceinline__ static double select(const double (&f)[W], double delta, double is_top, int &sel,
-                                                    double *top = nullptr)
+    __device__ __forceinline__ static double window_is_top(const double (&f)[W]);
+
+    // h0: f_j, or 0 for the values less f_j
+    __device__ __forceinline__ static double select_from(const double (&f)[W], double h0, double delta, double is_top,
+                                                         int &sel, double *top = nullptr)
     {
         if constexpr (ORDER == 5) {
             const double a0 = f[1] - f[0], a1 = f[2] - f[1], a2 = f[3] - f[2];
@@ -125,7 +140,7 @@ template <int ORDER> struct Recon {
             const double c0 = b1 - (a1 - a0), c1 = b2 - b1, c2 = b3 - b2, c3 = (a5 - a4) - b3;
             const double d0 = c1 - c0, d1 = c2 - c1, d2 = c3 - c2;
             double h[6];
-            h[0] = f[3];
+            h[0] = h0;
             h[1] = fma(0.5, a3, h[0]);
             h[2] = fma(-1.0 / 6.0, b2, h[1]);
             h[3] = fma(-1.0 / 12.0, c1, h[2]);
@@ -156,7 +171,7 @@ template <int ORDER> struct Recon {
 #pragma unroll
             for (int i = 0; i < 3; ++i) g[i] = e[i + 1] - e[i];
             double h[9];
-            h[0] = f[4];
+            h[0] = h0;
             h[1] = fma(0.5, a[4], h[0]);
             h[2] = fma(-1.0 / 6.0, b[3], h[1]);
             h[3] = fma(-1.0 / 12.0, c[2], h[2]);
@@ -233,12 +248,9 @@ template <int ORDER> struct TopStencil {
     }
 };
 
-template <int ORDER>
-__device__ __forceinline__ double Recon<ORDER>::select_top(const double (&f)[Recon<ORDER>::W], double delta, int &sel,
-                                                           double &top)
+template <int ORDER> __device__ __forceinline__ double Recon<ORDER>::window_is_top(const double (&f)[Recon<ORDER>::W])
 {
-    const double is_top = fmin(fabs(TopStencil<ORDER>::diff(f, 1)), fabs(TopStencil<ORDER>::diff(f + 1, 1)));
-    return select(f, delta, is_top, sel, &top);
+    return fmin(fabs(TopStencil<ORDER>::diff(f, 1)), fabs(TopStencil<ORDER>::diff(f + 1, 1)));
 }
 
 // ---------------------------------------------------------------------------

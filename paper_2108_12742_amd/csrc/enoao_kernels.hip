@@ -77,8 +77,15 @@ struct LineLds {
     int qs;
     double *fh;           // fluxes by component (stride fs) and face
     int fs;
-    unsigned char *list;  // faces that need a selection
+    unsigned char *list;  // faces that need a selection (LINE_CHOSEN: its flux is the selected one)
 };
+constexpr unsigned LINE_FACE = 0x3f, LINE_CHOSEN = 0x80;
+
+// a lane's place among the lanes of a mask
+__device__ __forceinline__ unsigned mask_place(unsigned long long m)
+{
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
 
 // The segment's 64 Euler fluxes where every field takes its top candidate on both sides:
 // the flux is linear in the window (TopStencil; R L = I, so the central part needs no
@@ -136,9 +143,7 @@ __device__ __forceinline__ unsigned long long line_top(const LineLds &l, const d
 #pragma unroll
         for (int i = 0; i < 6; ++i) rec(lane, i, K - 1);
     }
-    if ((fail >> lane) & 1)
-        l.list[__builtin_amdgcn_mbcnt_hi((unsigned)(fail >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)fail, 0u))] =
-            (unsigned char)lane;
+    if ((fail >> lane) & 1) l.list[mask_place(fail)] = (unsigned char)lane;
     return fail;
 }
 
@@ -147,18 +152,23 @@ struct Alpha3 {
     double a0, a1, a2;
 };
 
-// The selection of field s on face f of the segment l, both sides: the difference to
-// the top values, zero where the top candidate is chosen after all, goes to the face's
-// place in l.fh.  A lane takes one field of one listed face: where each lane took all
+// The selection of field s on the face at place `at` of the list of segment l, both sides.
+// The field of the chosen flux less (F_j + F_j+1) / 2 goes to the face's place in l.fh,
+// formed from the chosen candidates' own differences: the top candidate, rejected where
+// its window crosses a jump, is as large as the jump's far side, and a flux formed as a
+// distance from it kept that side's rounding (4e-9 of the largest L at a pressure ratio
+// of 1e8).  A face with a field that does not take the top candidate is marked in the
+// list.  A lane takes one field of one listed face: where each lane took all
 // fields of its own face, a segment with a shock held its wave for 9500 cycles a stage
 // beside 1200 for the others.  All lanes of the wave call it; `valid` ones count.
 // SERIAL: one side's candidates after the other's (fewer registers, more latency).
 template <int ORDER, bool CH, bool SERIAL, class Rec>
-__device__ __forceinline__ void line_select(const LineLds &l, int f, int s, bool valid, Alpha3 al,
+__device__ __forceinline__ void line_select(const LineLds &l, int at, int s, bool valid, Alpha3 al,
                                             double gm1, double delta, const Rec &rec)
 {
     using R = Recon<ORDER>;
     constexpr int H = R::H, NW = 2 * H + 2, K = R::K;
+    const int f = (int)(l.list[at] & LINE_FACE);
     const double *w = l.q + f;
     const bool ent = s == 1;
     const double a = !CH || s == 0 ? al.a0 : (s == 1 ? al.a1 : al.a2);
@@ -170,7 +180,7 @@ __device__ __forceinline__ void line_select(const LineLds &l, int f, int s, bool
         l1 = ent ? bu : -sg - bu;
         l2 = ent ? -r.b1 : r.b1;
     }
-    double gp[2 * H + 1], gm[2 * H + 1];
+    double gp[2 * H + 1], gm[2 * H + 1], du = 0.0;  // du: U_j - U_j+1 on the field
 #pragma unroll
     for (int t = 0; t < NW; ++t) {
         const double u0 = w[t], u1 = w[l.qs + t], u2 = w[2 * l.qs + t], f1 = w[3 * l.qs + t], f2 = w[4 * l.qs + t];
@@ -182,38 +192,46 @@ __device__ __forceinline__ void line_select(const LineLds &l, int f, int s, bool
             pu = s == 0 ? u0 : (s == 1 ? u1 : u2);
             pf = s == 0 ? u1 : (s == 1 ? f1 : f2);
         }
+        if (t == H) du = pu;
+        if (t == H + 1) du -= pu;
         if (t <= 2 * H) gp[t] = fma(a, pu, pf);
         if (t >= 1) gm[2 * H + 1 - t] = fma(-a, pu, pf);
         if (t % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (two nodes' reads in flight)
     }
     const double sd = (CH && !ent ? 4.0 : 2.0) * delta;
     int cp, cm;
-    double tp, tm;
-    const double hp = R::select_top(gp, sd, cp, tp);
+    const double hp = R::select_step(gp, sd, cp);
     if (SERIAL) __builtin_amdgcn_sched_barrier(0);
-    const double hm = R::select_top(gm, sd, cm, tm);
+    const double hm = R::select_step(gm, sd, cm);
     if (valid) {
         rec(f, 2 * s, cp);
         rec(f, 2 * s + 1, cm);
-        l.fh[s * l.fs + f] = cp == K - 1 && cm == K - 1 ? 0.0 : ((hp - tp) + (hm - tm)) * (CH && !ent ? 0.25 : 0.5);
+        l.fh[s * l.fs + f] = fma(a, du, hp + hm) * (CH && !ent ? 0.25 : 0.5);
+        if (cp != K - 1 || cm != K - 1) l.list[at] = (unsigned char)(f | LINE_CHOSEN);
     }
 }
 
-// The listed faces' fluxes, each by its own lane: R times the fields' differences added.
+// The fluxes of the listed faces (`fail`), each by its own lane: (F_j + F_j+1) / 2 and R
+// times what the selections left.  A face where every field takes the top candidate after
+// all keeps line_top's flux, so no result depends on what the bound leaves.
 template <int ORDER, bool CH>
-__device__ __forceinline__ void line_correct(const LineLds &l, bool listed, double gm1, double (&Fh)[3])
+__device__ __forceinline__ void line_correct(const LineLds &l, unsigned long long fail, double gm1, double (&Fh)[3])
 {
     constexpr int H = ReconTraits<ORDER>::H;
     const int lane = threadIdx.x & 63;
-    if (!listed) return;
+    if (!((fail >> lane) & 1) || !(l.list[mask_place(fail)] & LINE_CHOSEN)) return;
+    const double *w = l.q + lane + H;
     double e[3], d[3];
 #pragma unroll
     for (int s = 0; s < 3; ++s) e[s] = l.fh[s * l.fs + lane];
     RoeState r{};
-    if constexpr (CH) r = line_roe(l.q + lane + H, l.qs, gm1);
+    if constexpr (CH) r = line_roe(w, l.qs, gm1);
     from_fields<3, CH>(r, e, d);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) Fh[c] += d[c];
+    for (int c = 0; c < 3; ++c) {
+        const double *F = w + (c + (c ? 2 : 1)) * l.qs;  // F_0 is U_1
+        Fh[c] = fma(0.5, F[0] + F[1], d[c]);
+    }
 }
 
 // The selections of a wave's own listed faces (`fail`), and their fluxes.
@@ -227,10 +245,10 @@ __device__ __forceinline__ void line_selections(const LineLds &l, unsigned long 
 #pragma unroll 1
     for (int at = 0; at < 3 * nf; at += 64) {
         const int k = min(at + lane, 3 * nf - 1), s = (k >= nf) + (k >= 2 * nf);
-        line_select<ORDER, CH, SERIAL>(l, l.list[k - s * nf], s, at + lane < 3 * nf, al, gm1, delta, rec);
+        line_select<ORDER, CH, SERIAL>(l, k - s * nf, s, at + lane < 3 * nf, al, gm1, delta, rec);
     }
     wave_sync();
-    line_correct<ORDER, CH>(l, (fail >> lane) & 1, gm1, Fh);
+    line_correct<ORDER, CH>(l, fail, gm1, Fh);
 }
 
 // Staged top differences D_0 of two consecutive advection nodes i and i+1, from nodes
@@ -841,10 +859,10 @@ __device__ __forceinline__ void line_round(const KParams &P, double adv, double 
                                 before = k >= upto[j] ? upto[j] : before;
                             }
                             const LineLds l = line_lds<EQ, ORDER>(wls, w);
-                            line_select<ORDER, CH, false>(l, l.list[k - before], s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
+                            line_select<ORDER, CH, false>(l, k - before, s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
                         }
                         __syncthreads();
-                        line_correct<ORDER, CH>(own, (fail >> lane) & 1, P.gm1, Fh);
+                        line_correct<ORDER, CH>(own, fail, P.gm1, Fh);
                     }
                 } else {
                     line_selections<ORDER, CH, false>(own, fail, a3, P.gm1, P.delta, Fh, rec);
