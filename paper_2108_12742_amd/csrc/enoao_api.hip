@@ -517,6 +517,7 @@ struct Runtime {
     // again, about one row's time; a second round of units would wait for the first).
     int rows = 1;
     bool wide = false;  // a plane of 4 GiB or more: the recording kernels' 64-bit offsets
+    bool general_2d() const { return wide || (kflags & KF_FULL_SELECTION) != 0; }
     void choose_rows(const enoao_problem *ps, int count)
     {
         if (eq != EULER2D) return;
@@ -683,7 +684,7 @@ struct Runtime {
         KParams p = params(r_in, r_out, r_zero, s - 1);
         // stage s counts its lists with set s mod 3 and zeroes the next stage's
         set_list(p, s % 3, (s + 1) % 3);
-        if (eq == EULER2D) HIP_TRY(launch_stage_2d(order, mode, record || wide, ch, p, grid_2d[mode], grid_fix, st));
+        if (eq == EULER2D) HIP_TRY(launch_stage_2d(order, mode, record || general_2d(), ch, p, grid_2d[mode], grid_fix, st));
         else HIP_TRY(launch_sweep_x(eq, order, mode, record, ch, chunked(p, gmin_x[mode]), grid_x[mode], st));
         HIP_TRY(prof_end(slot, st));
         if (record) last_sel = s - 1;
@@ -702,7 +703,7 @@ struct Runtime {
     {
         KParams p = params(0, -1, -1);
         set_list(p, 3, -1);  // (zeroed with the maxima before it)
-        if (eq == EULER2D) HIP_TRY(launch_stage_2d(order, M_RHS, rec || wide, ch, p, grid_2d[M_RHS], grid_fix, s));
+        if (eq == EULER2D) HIP_TRY(launch_stage_2d(order, M_RHS, rec || general_2d(), ch, p, grid_2d[M_RHS], grid_fix, s));
         else HIP_TRY(launch_sweep_x(eq, order, M_RHS, rec, ch, chunked(p, gmin_x[M_RHS]), grid_x[M_RHS], s));
         last_sel = 0;
         return ENOAO_OK;

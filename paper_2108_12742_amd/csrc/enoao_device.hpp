@@ -115,13 +115,12 @@ template <int ORDER> struct Recon {
     {
         return select_from(f, f[H], delta, is_top, sel);
     }
-    // The same with the top candidate's indicator taken from the window itself;
-    // top: the top candidate's value.
-    __device__ __forceinline__ static double select_top(const double (&f)[W], double delta, int &sel, double &top)
+    // The chosen candidate's value less f_j, formed without f_j, the top candidate's
+    // indicator taken from the window itself; top: the top candidate's value less f_j.
+    __device__ __forceinline__ static double select_step(const double (&f)[W], double delta, int &sel, double &top)
     {
-        return select_from(f, f[H], delta, window_is_top(f), sel, &top);
+        return select_from(f, 0.0, delta, window_is_top(f), sel, &top);
     }
-    // The chosen candidate's value less f_j, formed without f_j.
     __device__ __forceinline__ static double select_step(const double (&f)[W], double delta, int &sel)
     {
         return select_from(f, 0.0, delta, window_is_top(f), sel);

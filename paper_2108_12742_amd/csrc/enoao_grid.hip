@@ -26,10 +26,13 @@
 // several times as long as its neighbours: selecting inside stage_2d took 0.10 ms
 // of a 0.23 ms stage for 15% more instructions, and the selection's registers
 // spilled the row loop's.  stage_2d therefore lists the row segments that hold such
-// faces and gives every cell the top flux; fix_2d spreads the listed rows over the
-// machine, selects, one lane per face and field, and adds the difference to the
-// cells: U += c dt dL, with dL zero where the top candidate is chosen after all, so
-// no result depends on what the bound leaves.
+// faces and gives those faces the mean (F_j + F_j+1) / 2 of their own two nodes; fix_2d
+// spreads the listed rows over the machine, selects, one lane per face and field, and
+// adds what the chosen candidates have beyond the mean to the cells: U += c dt dL.  The
+// mean, and not the top flux: the top candidate was left out because its window crosses
+// a jump, it is as large as the jump's far side, and the cells of the near side kept
+// that side's rounding (1e-9 of the largest L at a pressure ratio of 1e5).  The bound
+// alone tells which form a face takes, also where every face is selected.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -42,17 +45,16 @@
 
 namespace enoao {
 
-// Waves per SIMD of stage_2d.  Order 5 fits two (243 registers).  Order 7 holds a third
-// more rows: at two it spills 38 registers in stages 2 and 3 (0.217 ms on a smooth
-// 2048^2 grid against 0.174 at one; stage 1 0.142 against 0.156).
-constexpr int stage_waves(int order) { return order == 7 ? 1 : 2; }
+// Waves per SIMD of stage_2d: 255 registers at either order (order 7 spills two).
+constexpr int STAGE_WAVES = 2;
 // Waves per SIMD of fix_2d: as many as its LDS lets a CU hold (39 KB a workgroup at
 // order 5, 43 KB at order 7).
 constexpr int fix_waves(int order) { return order == 7 ? 3 : 4; }
 
 // p at a byte offset.  Offsets within a plane below 4 GiB take one 32-bit register
 // (unsigned) beside a wave-uniform address; larger planes take 64-bit offsets, in the
-// recording instantiations, which also serve members that large without a record.
+// recording instantiations, which also serve members that large without a record, and
+// runs that list every face.
 template <class Off> __device__ __forceinline__ double row_load(const GMEM double *p, Off off)
 {
     return *(const GMEM double *)((const GMEM char *)p + off);
@@ -299,7 +301,9 @@ __device__ __forceinline__ long long fix_list_start(const KParams &P, int n_inst
 
 // A listed row segment: unit << 28 | row within the unit << 12 | first lane of its
 // cells << 6 | last, and the lanes whose faces need a selection: right of the lane's
-// column, below and above the row.
+// column, below and above the row.  Where every face is listed a segment has FIX_SPLIT
+// cells, and the lanes that hold a top flux are marked once more, half a turn on.
+__device__ __forceinline__ unsigned long long half_turn(unsigned long long m) { return m << 32 | m >> 32; }
 struct FixEntry {
     unsigned long long where, x, below, above;
 };
@@ -307,7 +311,7 @@ static_assert(sizeof(FixEntry) == FIX_ENTRY_BYTES, "list sizes");
 
 template <int ORDER, bool STEP, bool REC, bool CH>
 __global__ __launch_bounds__(BLOCK)
-__attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P)
+__attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
 {
     using T = TopStencil<ORDER>;
     using Off = std::conditional_t<REC, long long, unsigned>;
@@ -316,6 +320,11 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
     constexpr int CELLS = strip_cells(ORDER);  // columns a wave updates
     constexpr int ROW = 64 + 2 * G;            // row buffer: lane l's node at l + H
     static_assert(CELLS == 64 - 2 * G, "a lane per column, halo included");
+    // The mean flux of the faces that the bound leaves: by a select in every row, or under a
+    // branch.  The branch lets order 7 run two waves per SIMD (2048^2, four steps: 2.57 ms
+    // against 3.25 with selects, at one wave); at order 5, where both fit, it takes the
+    // schedule more (eight steps: 4.45 ms against 4.32).
+    constexpr bool MEAN_SELECT = ORDER == 5;
     constexpr int NWV = BLOCK / 64, PENDING = 16;
     __shared__ double rows[NWV][7][ROW];
     __shared__ WaveMax maxima[STEP ? NWV : 1];
@@ -334,7 +343,8 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
     const long long stride = (long long)g * NWV;
     // threshold of the bound (it and the indicators differ by rounding); delta = 0
     // leaves every face to the selection
-    const double thr = P.delta > 0.0 && !(P.flags & KF_FULL_SELECTION) ? 2.0 * P.delta * (1.0 - 1.0 / 1024.0) : -1.0;
+    const double thr = P.delta > 0.0 ? 2.0 * P.delta * (1.0 - 1.0 / 1024.0) : -1.0;
+    const bool full = REC && (P.flags & KF_FULL_SELECTION) != 0;  // every face is listed
 
     const RkWeights rk = rk_weights(P.mode);
     WaveMax &M = maxima[STEP ? wv : 0];
@@ -391,7 +401,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
         double pre[4];
         NodePrim pl;                      // row r - H
         double Gm[4];                     // y-flux below row r - H
-        unsigned long long fail_b = 0;    // its faces that need a selection
+        unsigned long long fail_b = 0;    // its faces that the bound leaves
         auto load_row = [&](int r) {
             const int y = r < 0 || r >= ny ? bc_map(r, ny, v.bcy) : r;
             const GMEM double *p = v.in + (long long)y * v.pitch;
@@ -464,8 +474,15 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
                 top_flux<CH>(ro, sF, dU, v.ay, Fy);
                 const bool ok = row_bound<CH>(ro) * node_bound(dU, dF, v.my) <= thr;
                 fail_t = __builtin_amdgcn_ballot_w64(!ok && cell);
+                if (MEAN_SELECT || fail_t) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int q = c == 0 ? 1 : 3 + c;
+                        Fy[c] = ok ? Fy[c] : 0.5 * (w[q][H - 1] + w[q][H]);
+                    }
+                }
             }
-            if (REC && v.sel && cell && !((fail_t >> lane) & 1)) {
+            if (REC && v.sel && !full && cell && !((fail_t >> lane) & 1)) {
                 const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
@@ -481,14 +498,16 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
                 }
                 // x-faces of row j: lane l's face is between columns l and l + 1
                 wave_sync();
-                double sx[4], dx[4], df[3];
+                double sx[4], dx[4], df[3], mean[4];
 #pragma unroll
                 for (int i = 0; i < 7; ++i) {
                     double win[NS];
 #pragma unroll
                     for (int t = 0; t < NS; ++t) win[t] = i < 4 && t == H - 1 ? w[i == 1 ? 2 : (i == 2 ? 1 : i)][H - 1] : rb[i][lane + 1 + t];
-                    if (i == 1) sx[0] = T::sym1(win, 1);
-                    if (i >= 4) sx[i - 3] = T::sym1(win, 1);
+                    if (i == 1 || i >= 4) {
+                        sx[i == 1 ? 0 : i - 3] = T::sym1(win, 1);
+                        mean[i == 1 ? 0 : i - 3] = 0.5 * (win[H - 1] + win[H]);
+                    }
                     if (i < 4) dx[i] = T::diff(win, 1);
                     else df[i - 4] = T::diff(win, 1);
                     if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
@@ -502,14 +521,21 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
                 top_flux<CH>(ro, sx, dx, v.ax, Fx);
                 const bool ok = row_bound<CH>(ro) * node_bound(dx, df, v.mx) <= thr;
                 const unsigned long long fail_x = __builtin_amdgcn_ballot_w64(!ok && face);
-                if (REC && v.sel && face && !((fail_x >> lane) & 1)) {
+                if (MEAN_SELECT || fail_x) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const double *f = &rb[c == 0 ? 1 : 3 + c][lane + H];
+                        Fx[c] = ok ? Fx[c] : (MEAN_SELECT ? mean[c] : 0.5 * (f[0] + f[1]));
+                    }
+                }
+                if (REC && v.sel && !full && face && !((fail_x >> lane) & 1)) {
                     const long long xb = (long long)ny * (nx + 1);
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
                         v.sel[i * xb + (long long)j * (nx + 1) + xn + 1] = (uint8_t)(K - 1);
                 }
-                // cells with a face that needs a selection: their maxima are fix_2d's
-                const unsigned long long fixed = fail_x | (fail_x << 1) | fail_b | fail_t;
+                // cells with a listed face: their maxima are fix_2d's
+                const unsigned long long fixed = full ? ~0ull : fail_x | (fail_x << 1) | fail_b | fail_t;
                 if (fixed) {
                     const unsigned long long where = (unsigned long long)unit << 28 | (unsigned)(j - y0) << 12;
                     auto push = [&](int lo, int hi, unsigned long long x, unsigned long long b, unsigned long long t) {
@@ -518,16 +544,25 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
                         ++npend;
                     };
                     const int faces = __popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t);
-                    if (faces <= FIX_FACES) {
+                    if (faces <= FIX_FACES && !full) {
                         push(G, 63 - G, fail_x, fail_b, fail_t);
                     } else {
                         // (a row coarse along x alone has 57 faces and some: two pieces of two
                         // passes, where four would be of two as well)
-                        const int width = faces > 3 * FIX_FACES / 2 ? FIX_SPLIT : 2 * FIX_SPLIT;
+                        const int width = faces > 3 * FIX_FACES / 2 || full ? FIX_SPLIT : 2 * FIX_SPLIT;
 #pragma unroll 1
                         for (int lo = G; lo < min(64 - G, nx - x0 + G); lo += width) {  // (pieces with cells: the list's places)
-                            const unsigned long long m = ((1ull << width) - 1) << lo;
-                            push(lo, min(lo + width, 64 - G) - 1, fail_x & (m | m >> 1), fail_b & m, fail_t & m);
+                            const unsigned long long m = ((1ull << width) - 1) << lo, mx = m | m >> 1;
+                            unsigned long long x = fail_x & mx, b = fail_b & m, t = fail_t & m;
+                            if (full) {
+                                // every face; those with a top flux twice
+                                const unsigned long long fs = __builtin_amdgcn_ballot_w64(face) & mx;
+                                const unsigned long long cs = __builtin_amdgcn_ballot_w64(cell) & m;
+                                x = fs | half_turn(fs & ~x);
+                                b = cs | half_turn(cs & ~b);
+                                t = cs | half_turn(cs & ~t);
+                            }
+                            push(lo, min(lo + width, 64 - G) - 1, x, b, t);
                         }
                     }
                     if (npend > PENDING - 4) flush_pending(unit);
@@ -593,7 +628,7 @@ __attribute__((amdgpu_waves_per_eu(stage_waves(ORDER)))) void stage_2d(KParams P
 // y-faces on either side.
 using WaveMost = unsigned long long[7][4];
 template <int NW> struct FixScratch {
-    double dF[3][4][58];       // flux corrections by set (x, below, above) and lane from H on
+    double dF[3][4][58];       // what the faces' fluxes have beyond the mean, by set (x, below, above) and lane from H on
     double exchange[NW][64];   // window values by node and (face, field)
     unsigned char face[176];   // set << 6 | lane of each face
     WaveMost most;             // the wave's maxima, in four parts
@@ -625,15 +660,16 @@ template <class Off> struct FixLine {
 // longer than the imbalance it removed, 20 ns each); where the list is short, the four
 // waves of a workgroup share a segment, and halves of segments go to different ones.
 // Four lanes per face, one per field, for the selection, one lane per cell for the
-// update.  stage_2d gave the fields' top values; a field that chooses another candidate
-// on either side contributes the difference.  Bound by its instructions (VALU issue 0.86
+// update.  stage_2d gave the mean of the fluxes of the face's two nodes; a field
+// contributes alpha l.(U_j - U_j+1) / 2 and what its chosen candidates have beyond the
+// two nodes.  Bound by its instructions (VALU issue 0.86
 // of the cycles at 2048^2): about 450 a pass of sixteen faces and 300 an entry.
 template <int ORDER, bool STEP, bool REC, bool CH>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves(ORDER)))) void fix_2d(KParams P)
 {
     using R = Recon<ORDER>;
     using Off = std::conditional_t<REC, long long, unsigned>;
-    constexpr int H = R::H, G = H + 1, NW = 2 * H + 2, K = R::K, CELLS = strip_cells(ORDER), NWV = BLOCK / 64;
+    constexpr int H = R::H, G = H + 1, NW = 2 * H + 2, CELLS = strip_cells(ORDER), NWV = BLOCK / 64;
     __shared__ FixScratch<NW> scratch[NWV];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -675,6 +711,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
         return lane < 4 ? gmem(P.fix_list)[4 * e + lane] : 0ull;
     };
     const RkWeights rk = rk_weights(P.mode);
+    const bool full = REC && (P.flags & KF_FULL_SELECTION) != 0;
     unsigned long long bad = 0, next = load_entry(at);
     WaveMost &M = scratch[wv].most;
     if (STEP && lane < 28) M[lane >> 2][lane & 3] = 0ull;
@@ -704,9 +741,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             const unsigned long long where = lane_bits(next, 0);
             unsigned long long fx = lane_bits(next, 1), fb = lane_bits(next, 2), ft = lane_bits(next, 3);
             const unsigned half = at & halves;
+            unsigned long long tx = 0, tb = 0, tt = 0;  // faces with a top flux (full)
             next = load_entry(next_at);  // on its way while this one is worked on
             const long long unit = (long long)(where >> 28);
             int lo = (int)(where >> 6) & 63, hi = (int)where & 63;  // lanes of its cells
+            if (full) {
+                const unsigned long long m = (2ull << hi) - (1ull << lo), mx = m | m >> 1;
+                tx = half_turn(fx) & mx;
+                tb = half_turn(fb) & m;
+                tt = half_turn(ft) & m;
+                fx &= mx;
+                fb &= m;
+                ft &= m;
+            }
             if (halves) {
                 const int mid = (lo + hi + 1) >> 1;
                 lo = half ? mid : lo;
@@ -836,9 +883,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             const double sd = (acoustic ? 4.0 : 2.0) * P.delta;
             int sp, sm;
             double tp, tm;
-            const double hp = R::select_top(gp, sd, sp, tp);
+            const double hp = R::select_step(gp, sd, sp, tp);
             __builtin_amdgcn_sched_barrier(0);
-            const double hm = R::select_top(gm, sd, sm, tm);
+            const double hm = R::select_step(gm, sd, sm, tm);
             if (REC && v.sel && valid) {
                 const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
                 const long long o = l.x ? 2 * s * xb + (long long)l.row * (nx + 1) + l.col + 1
@@ -847,7 +894,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                 v.sel[o + (l.x ? xb : yb)] = (uint8_t)sm;
             }
             // R de, summed over the face's four lanes; lane s stores component s
-            const double es = sp == K - 1 && sm == K - 1 ? 0.0 : ((hp - tp) + (hm - tm)) * (acoustic ? 0.25 : 0.5);
+            double es = fma(a, pu[H] - pu[H + 1], hp + hm);
+            if (full && (((set == 0u ? tx : (set == 1u ? tb : tt)) >> (f & 63u)) & 1)) es = (hp - tp) + (hm - tm);  // (zero)
+            es *= acoustic ? 0.25 : 0.5;
             double d = es;
             if constexpr (CH) {
                 const double e[4] = {s == 0 ? es : 0.0, s == 1 ? es : 0.0, s == 2 ? es : 0.0, s == 3 ? es : 0.0};

@@ -74,3 +74,35 @@ def test_line_jump(at, ratio, order, recon):
                 E.enoao_set_coop(True)
         for v in ends:
             assert np.array_equal(v, got)
+
+
+@pytest.mark.parametrize("order,recon", METHODS)
+@pytest.mark.parametrize("ratio", RATIOS)
+@pytest.mark.parametrize("shape", ["x", "y", "corner"])
+def test_grid_jump(shape, ratio, order, recon):
+    torch = PT.torch_cuda()
+    from paper_2108_12742_amd import enoao as E
+    print(f"[jump] grid {shape} ratio {ratio:.0e} order {order} {recon}", flush=True)
+    nx, ny = 130, 40
+    x, y = np.meshgrid(np.arange(nx), np.arange(ny))
+    one = np.ones((ny, nx))
+    kw = dict(bc_x="transmissive", bc_y="transmissive", recon_vars=recon)
+    ep, ep_rec = (E.make_problem("euler2d", nx, ny, order, record_selection=r, **kw) for r in (False, True))
+    op = PT.oracle_problem(ep)
+    inside = {"x": x <= 55, "y": y <= 17, "corner": (x <= 55) & (y <= 17)}[shape]
+    for p in (np.where(inside, ratio, 1.0), np.where(inside, 1.0, ratio)):
+        u0 = W.conserved_2d(one, 0.1 * one, -0.2 * one, p)
+        plan, L = _evaluate(torch, E, ep_rec, u0)
+        assert recon == "characteristic" or (L[:, _quiet(u0)] == 0.0).all()
+        dt = O.cfl_dt(op, u0, 0.3)
+        got, recs = PT.gpu_step_recorded(torch, E, plan, u0, dt)
+        PT.check_step(op, u0, dt, got, recs)
+        for tiles in (0, 4):  # without a record; then with half the rows a wave walks
+            plan = E.enoao_plan_create(ep)
+            if tiles:
+                E.enoao_plan_set_tiles(plan, tiles)
+            u = PT.to_dev(torch, u0)
+            E.enoao_step(plan, u, dt)
+            torch.cuda.synchronize()
+            E.enoao_plan_check(plan)
+            assert np.array_equal(u.cpu().numpy(), got)
