@@ -250,22 +250,24 @@ __device__ __forceinline__ NodePrim node_prim(double rho, double m, double n, do
 
 // Bound of the left eigenvectors' scaled row sums of a face (acoustic rows halved
 // to the window scale of the others), so that every indicator of the face is at
-// most this times the node bound.  Component-wise variables: 1.
+// most this times the node bound.  Component-wise variables: 1.  (NaN for a state whose
+// eigenvectors do not exist: fmax would drop it.)
 template <bool CH> __device__ __forceinline__ double row_bound(const RoeState &r)
 {
     if constexpr (!CH) return 1.0;
     const double au = 1.0 + fabs(r.u), av = fabs(r.v);
     const double x = fma(r.b1, au + av, r.b2);
-    return fmax(fmax(1.0 + x, 0.5 * fma(r.ic, au, x)), 1.0 + av);
+    return fmax(fmax(1.0 + x, 0.5 * fma(r.ic, au, x)), fma(0.0, x, 1.0 + av));
 }
 
-// Node bound max_c(|D F_c| + alpha |D U_c|); F_0 is U_1.
+// Node bound max_c(|D F_c| + alpha |D U_c|); F_0 is U_1.  dF[0] holds the pressure, so it
+// tells a NaN in any component of a node, which fmax drops.
 __device__ __forceinline__ double node_bound(const double (&dU)[4], const double (&dF)[3], double amax)
 {
     double b = fma(amax, fabs(dU[0]), fabs(dU[1]));
 #pragma unroll
     for (int k = 0; k < 3; ++k) b = fmax(b, fma(amax, fabs(dU[k + 1]), fabs(dF[k])));
-    return b;
+    return fma(0.0, dF[0], b);
 }
 
 // Flux of a face whose fields all take the top candidate on both sides:

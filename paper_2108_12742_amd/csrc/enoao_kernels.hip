@@ -135,6 +135,7 @@ __device__ __forceinline__ unsigned long long line_top(const LineLds &l, const d
     double node = fma(a, fabs(dU[0]), fabs(dU[1]));
 #pragma unroll
     for (int k = 0; k < 2; ++k) node = fmax(node, fma(a, fabs(dU[k + 1]), fabs(dF[k])));
+    node = fma(0.0, dF[0], node);  // (dF[0] holds the pressure: a NaN of any component, which fmax drops)
     // (the bound and the indicators differ by rounding; delta = 0 leaves every face)
     const double thr = delta > 0.0 && shortcut ? 2.0 * delta * (1.0 - 1.0 / 1024.0) : -1.0;
     const bool ok = bound * node <= thr;
