@@ -388,8 +388,10 @@ struct Runtime {
     // member the largest one's and hold the CUs at the occupancy of the largest.
     // Members (largest first) are grouped by how many of their workgroups one CU
     // holds: as many as fit its LDS (4, 3, 2 or 1), at most as many as the kernel's
-    // registers allow (two for Euler: more LDS classes would not raise occupancy,
-    // only add launches).  Each class is one launch, and the classes run
+    // registers allow, and at most two for Euler (its registers allow three, but a third
+    // launch starts 20 us after the second and the members that share a CU by threes
+    // take longer: 503 us against 469 on 512 members of 128 to 1700 nodes, ten steps).
+    // Each class is one launch, and the classes run
     // concurrently on streams of their own (forked from and joined to the caller's
     // stream): every class needs a hardware queue of its own, since two classes
     // sharing one run one after the other (HIP spreads streams over few queues).
@@ -405,10 +407,11 @@ struct Runtime {
             per_cu = (int)limit;
         int by_regs = resident_groups_per_cu(eq, order, ch);
         by_regs = by_regs < 1 ? 4 : by_regs;
+        by_regs = std::min(by_regs, eq == ADVECTION ? 4 : 2);
         auto cls = [&](long long nx, int &block, size_t &lds) {
             block = RES_BLOCK;
             lds = resident_lds_bytes(nc, nq, g, nx, RES_BLOCK);
-            for (int k = by_regs < 4 ? by_regs : 4; k >= 2; --k)
+            for (int k = by_regs; k >= 2; --k)
                 if (lds + 1024 <= (size_t)per_cu / k) return k;  // 1 KiB for each workgroup's static LDS
             return lds <= limit ? 1 : 0;
         };
