@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__(64 * NW) void resident_1d(KParams P, int nsteps)
 //
 // Between stages the workgroups exchange their maxima and the G cells at either end of
 // their range, one word at a time: a word is empty (a signalling NaN, which arithmetic
-// never gives) until its writer has stored it, so a reader that finds a value needs no
+// never gives, and which coop_load takes out of the caller's state) until its writer has stored it, so a reader that finds a value needs no
 // barrier, no counter and no cache operation; it waits for what it needs alone, all words
 // in flight together.  With the stage states in HBM, a counting barrier between a release
 // and an acquire of the caches, and the maxima and the states read after it, this part of
@@ -1040,6 +1040,14 @@ static int coop_exchange_words(int eq, int order, int groups)
 __device__ __forceinline__ void coop_store(GMEM unsigned long long *p, unsigned long long x)
 {
     __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// a value of the caller's state; a NaN with the bits of an empty word, which a reader
+// would wait for in vain, as the quiet NaN that arithmetic makes of it
+__device__ __forceinline__ double coop_load(GMEM const double *p)
+{
+    const unsigned long long x = as_bits(*p);
+    return as_double(x == COOP_EMPTY ? x | 1ull << 51 : x);
 }
 
 // the value of an exchange word once it is there; false after COOP_SPIN_LIMIT polls, or
@@ -1242,7 +1250,7 @@ __global__ __launch_bounds__(RES_BLOCK) void coop_1d(KParams P, int nsteps, unsi
     };
 
 #pragma unroll
-    for (int c = 0; c < NC; ++c) U[c] = base[c] = cell ? un[c * n + x0 + at] : 0.0;
+    for (int c = 0; c < NC; ++c) U[c] = base[c] = cell ? coop_load(&un[c * n + x0 + at]) : 0.0;
     bool ok = exchange_stage(0);
     int taken = 0;
     for (int step = 0; ok && step < nsteps; ++step) {

@@ -40,3 +40,29 @@ def test_nan_in_one_node(components, ny, order, recon):
     # fluxes of size 4 at most, over dx = 1 / 130 (dy = 1 / 30): their rounding
     assert np.isnan(L[:, ~far]).any()
     assert (np.abs(L[:, far]) <= PT.RTOL * 4 * nx).all(), np.argwhere(~(np.abs(L).max(0) <= PT.RTOL * 4 * nx) & far)
+
+
+@pytest.mark.parametrize("eq", ["euler1d", "advection"])
+def test_cooperative_solver_takes_any_nan(eq):
+    """The cooperative solver's workgroups tell an empty word by the bits of a signalling NaN.
+    A caller's state may hold those bits, at a workgroup's end, where they are sent to its
+    neighbour: a non-physical state like any other."""
+    torch = PT.torch_cuda()
+    from paper_2108_12742_amd import enoao as E
+    n = 1000
+    ep = E.make_problem(eq, n, 1, 5, x_lo=0.0, x_hi=1.0)
+    u = np.ones((1, 1, n)) if eq == "advection" else W.conserved_1d(*(np.full(n, x) for x in (1.0, 0.3, 1.0)))[:, None, :]
+    u = np.ascontiguousarray(u)
+    u.view(np.uint64)[-1, 0, 251:253] = 0xFFF7FFFFFFFFFFFF
+    for coop in (False, True):
+        E.enoao_set_resident(False)
+        E.enoao_set_coop(coop)
+        try:
+            print(f"[nan] cooperative {coop} {eq}", flush=True)
+            plan, v = E.enoao_plan_create(ep), PT.to_dev(torch, u)
+            with pytest.raises(E.EnoaoError, match="non-physical"):
+                E.enoao_solve(plan, v, 1e300, cfl=0.3, max_steps=5)
+            assert np.array_equal(v.cpu().numpy().view(np.uint64), u.view(np.uint64))
+        finally:
+            E.enoao_set_resident(True)
+            E.enoao_set_coop(True)
