@@ -171,9 +171,12 @@ def _dev_ptr(t, shape=None, what="state"):
 def _dev_ptrs(states, shapes):
     """Device addresses of a batch's states, each checked as _dev_ptr does.  Attribute by
     attribute over all of them, the loops in C: 512 states one after the other took 0.35 ms,
-    as long as ten steps of small members; this way 0.1 ms."""
+    as long as ten steps of small members; this way 0.1 ms.  (States past the last member are
+    ignored; the library reads an address for every member, so fewer are refused.)"""
     import torch
     T = torch.Tensor
+    if len(states) < len(shapes):
+        raise ValueError(f"{len(states)} states for a batch of {len(shapes)} members")
     try:
         if (len(states) == len(shapes) and all(isinstance(t, T) for t in states)
                 and all(map(T.is_cuda.__get__, states)) and set(map(T.dtype.__get__, states)) <= {torch.float64}
@@ -181,7 +184,7 @@ def _dev_ptrs(states, shapes):
             return (ctypes.c_void_p * len(shapes)).from_buffer(array.array("Q", map(T.data_ptr, states)))
     except (TypeError, RuntimeError):
         pass
-    # one of them is refused: find it
+    # one of them is refused, or there are more: one by one
     return (ctypes.c_void_p * len(states))(*[_dev_ptr(u, shape).value for u, shape in zip(states, shapes)])
 
 

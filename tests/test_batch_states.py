@@ -22,6 +22,21 @@ def test_host_states_are_refused():
             E._dev_ptrs([bad], [(3, 1, 8)])
 
 
+def test_fewer_states_than_members_are_refused():
+    from paper_2108_12742_amd import enoao as E
+    with pytest.raises(ValueError):
+        E._dev_ptrs([], [(3, 1, 8)])
+    with pytest.raises(ValueError):
+        E._dev_ptrs([torch.zeros((3, 1, 8), dtype=torch.float64)], [(3, 1, 8)] * 2)
+
+
+@pytest.mark.gpu
+def test_more_states_than_members():
+    from paper_2108_12742_amd import enoao as E
+    states = [torch.zeros((3, 1, 8), dtype=torch.float64, device="cuda") for _ in range(3)]
+    assert list(E._dev_ptrs(states, [(3, 1, 8)] * 2))[:2] == [u.data_ptr() for u in states[:2]]
+
+
 @pytest.mark.gpu
 def test_refused_states_and_addresses():
     from paper_2108_12742_amd import enoao as E
