@@ -71,7 +71,7 @@ size_t selection_count(const enoao_problem *p)
 
 // A member's state-sized buffers are laid out one after another with a gap of
 // BUF_STAGGER doubles (4352 bytes) between them: buffers that a kernel streams
-// together (stage input, x-part, stage output) then do not start at offsets
+// together (the stage input, u^n, the stage output) then do not start at offsets
 // that are multiples of a large power of two, which made their lines contend
 // for the same cache sets and memory channels.
 constexpr size_t BUF_STAGGER = 544;
@@ -84,25 +84,49 @@ inline double *member_buffer(double *m, size_t cells, int i) { return m + (size_
 // then touches no line more than it must).  Caller-owned states (plans, batches) keep pitch nx.
 inline int padded_pitch(int nx) { return (nx + 15) / 16 * 16; }
 
-// most bytes of a member's list of row segments (2D)
-size_t fix_list_bytes(const enoao_problem *p)
-{
-    const size_t c = strip_cells(p->order);
-    return p->equation == EULER2D ? (p->nx + c - 1) / c * p->ny * fix_places(p->nx) * FIX_ENTRY_BYTES : 0;
-}
-
-// device bytes of one member: w1, w2 (+ Lx for 2D) and the selection record
+// bytes of a member's stage states w1 and w2 and of its selection record
 size_t member_bytes(const enoao_problem *p)
 {
     const size_t n = (size_t)ncomp_of(p->equation) * p->nx * p->ny;
-    const int bufs = p->equation == EULER2D ? 3 : 2;
-    size_t b = bufs * (n + BUF_STAGGER) * sizeof(double);
+    size_t b = 2 * (n + BUF_STAGGER) * sizeof(double);
     // three records: one per Runge-Kutta stage of a step (enoao_rhs uses the first)
     if (p->flags & ENOAO_F_RECORD_SELECTION) b += (3 * selection_count(p) + 255) / 256 * 256;
     return b;
 }
 
-size_t member_fixed_bytes() { return sizeof(Inst) + sizeof(Ctrl) + AMAX_SLOTS * amax_slot_words(EULER2D) * 8 + 256; }
+// bytes for a member's lists of row segments (2D): a third state's room, a place per cell,
+// which a grid one column wide fills
+size_t list_bytes(const enoao_problem *p)
+{
+    const size_t n = (size_t)ncomp_of(p->equation) * p->nx * p->ny;
+    static_assert(FIX_ENTRY_BYTES == 4 * sizeof(double), "a place per cell");
+    return p->equation == EULER2D ? (n + BUF_STAGGER) * sizeof(double) : 0;
+}
+
+// Offsets in the one device allocation of a batch (a plan is a batch of one).
+struct Layout {
+    size_t total = 0, hdr, inst, ctrl, amax, order, bar, counters, lists;
+    std::vector<size_t> member;
+    Layout(const enoao_problem *ps, int count)
+    {
+        auto take = [&](size_t bytes) {
+            const size_t o = total;
+            total += (bytes + 255) / 256 * 256;
+            return o;
+        };
+        hdr = take(sizeof(BatchHdr));
+        inst = take(sizeof(Inst) * count);
+        ctrl = take(sizeof(Ctrl) * count);
+        amax = take(8ull * AMAX_SLOTS * amax_slot_words(ps[0].equation) * count);
+        order = take(sizeof(int) * count);
+        bar = take(2 * sizeof(unsigned));
+        counters = take(ps[0].equation == EULER2D ? FIX_SETS * FIX_SET_WORDS * sizeof(unsigned) : 0);
+        size_t list = 0;
+        for (int i = 0; i < count; ++i) list += list_bytes(&ps[i]);
+        lists = take(list);
+        for (int i = 0; i < count; ++i) member.push_back(take(member_bytes(&ps[i])));
+    }
+};
 
 #define HIP_TRY(x)                                    \
     do {                                              \
@@ -293,39 +317,21 @@ struct Runtime {
         HIP_TRY(hipGetDevice(&device));
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
 
-        // layout of the single device allocation
-        size_t off = 0;
-        auto take = [&](size_t bytes) {
-            const size_t o = off;
-            off += (bytes + 255) / 256 * 256;
-            return o;
-        };
-        const size_t o_hdr = take(sizeof(BatchHdr));
-        const size_t o_inst = take(sizeof(Inst) * count);
-        const size_t o_ctrl = take(sizeof(Ctrl) * count);
-        const size_t o_amax = take(8ull * amax_words() * count);
-        const size_t o_order = take(sizeof(int) * count);
-        const size_t o_bar = take(2 * sizeof(unsigned));
-        const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * sizeof(unsigned));
-        size_t fix_bytes = 0;
-        for (int i = 0; i < count; ++i) fix_bytes += fix_list_bytes(&ps[i]);
-        const size_t o_fix = take(fix_bytes);
-        std::vector<size_t> o_mem(count);
-        for (int i = 0; i < count; ++i) o_mem[i] = take(member_bytes(&ps[i]));
-        if (hipMalloc(&d_block, off) != hipSuccess) {
+        const Layout at(ps, count);
+        if (hipMalloc(&d_block, at.total) != hipSuccess) {
             d_block = nullptr;
             return ENOAO_ENOMEM;
         }
         char *base = (char *)d_block;
-        d_hdr = (BatchHdr *)(base + o_hdr);
-        d_inst = (Inst *)(base + o_inst);
-        d_ctrl = (Ctrl *)(base + o_ctrl);
-        d_amax = (unsigned long long *)(base + o_amax);
-        d_res_order = (int *)(base + o_order);
-        d_bar = (unsigned *)(base + o_bar);
+        d_hdr = (BatchHdr *)(base + at.hdr);
+        d_inst = (Inst *)(base + at.inst);
+        d_ctrl = (Ctrl *)(base + at.ctrl);
+        d_amax = (unsigned long long *)(base + at.amax);
+        d_res_order = (int *)(base + at.order);
+        d_bar = (unsigned *)(base + at.bar);
         if (eq == EULER2D) {
-            d_fix_count = (unsigned *)(base + o_fixc);
-            d_fix_list = (unsigned long long *)(base + o_fix);
+            d_fix_count = (unsigned *)(base + at.counters);
+            d_fix_list = (unsigned long long *)(base + at.lists);
         }
         if (hipHostMalloc((void **)&h_ctrl, sizeof(Ctrl) * count, hipHostMallocDefault) != hipSuccess) {
             h_ctrl = nullptr;
@@ -337,11 +343,10 @@ struct Runtime {
         choose_rows(ps, count);
         long long xt = 0, ut = 0;
         for (int i = 0; i < count; ++i) {
-            double *m = (double *)(base + o_mem[i]);
+            double *m = (double *)(base + at.member[i]);
             const size_t cells = (size_t)nc * ps[i].nx * ps[i].ny;
             fill_inst(h_inst[i], ps[i], nullptr, member_buffer(m, cells, 0), member_buffer(m, cells, 1),
-                      eq == EULER2D ? member_buffer(m, cells, 2) : nullptr,
-                      rec ? (uint8_t *)member_buffer(m, cells, eq == EULER2D ? 3 : 2) : nullptr,
+                      rec ? (uint8_t *)member_buffer(m, cells, 2) : nullptr,
                       d_amax + (size_t)i * amax_words(), d_ctrl + i, xt, ut);
         }
         h_hdr.n_inst = count;
@@ -470,14 +475,13 @@ struct Runtime {
     }
 
     // descriptor of one member; advances the running tile offsets
-    void fill_inst(Inst &I, const enoao_problem &p, double *u, double *w1, double *w2, double *lx, uint8_t *sel,
+    void fill_inst(Inst &I, const enoao_problem &p, double *u, double *w1, double *w2, uint8_t *sel,
                    unsigned long long *amax, Ctrl *ctrl, long long &xt, long long &ut, int pitch = 0)
     {
         std::memset(&I, 0, sizeof(I));
         I.u = u;
         I.w1 = w1;
         I.w2 = w2;
-        I.lx = lx;
         I.sel = sel;
         I.amax = amax;
         I.ctrl = ctrl;
@@ -962,8 +966,7 @@ struct enoao_pool {
             const int pitch = padded_pitch(p.nx);
             const size_t cells = (size_t)r.nc * pitch * p.ny;
             Inst I;
-            r.fill_inst(I, p, member_buffer(m, cells, 0), member_buffer(m, cells, 1), member_buffer(m, cells, 2),
-                        r.eq == EULER2D ? member_buffer(m, cells, 3) : nullptr, nullptr,
+            r.fill_inst(I, p, member_buffer(m, cells, 0), member_buffer(m, cells, 1), member_buffer(m, cells, 2), nullptr,
                         r.d_amax + (size_t)k * r.amax_words(), r.d_ctrl + k, xt, ut, pitch);
             r.h_inst.push_back(I);
         }
@@ -1054,7 +1057,7 @@ const char *enoao_status_string(enoao_status s)
 size_t enoao_workspace_bytes(const enoao_problem *prob)
 {
     if (check_problem(prob)) return 0;
-    return sizeof(BatchHdr) + member_fixed_bytes() + member_bytes(prob);
+    return Layout(prob, 1).total;
 }
 
 enoao_status enoao_set_launch(int32_t workgroups_per_cu, int32_t reserved)
@@ -1275,7 +1278,7 @@ enoao_status enoao_step_noalloc(const enoao_problem *prob, double *u, double dt,
     rt.d_amax = (unsigned long long *)(base + NA_AMAX);
     rt.d_res_order = nullptr;
     if (rt.eq == EULER2D) {
-        // the third state buffer holds the lists (at most a place per cell)
+        // the lists in place of a third state (list_bytes)
         rt.d_fix_count = (unsigned *)(base + NA_FIX);
         rt.d_fix_list = (unsigned long long *)member_buffer((double *)(base + NA_MEM),
                                                             (size_t)rt.nc * prob->nx * prob->ny, 2);
@@ -1286,8 +1289,7 @@ enoao_status enoao_step_noalloc(const enoao_problem *prob, double *u, double dt,
     rt.wg_per_cu = g_wg_per_cu;
     rt.choose_rows(prob, 1);
     long long xt = 0, ut = 0;
-    rt.fill_inst(I, *prob, u, member_buffer(m, cells, 0), member_buffer(m, cells, 1),
-                 rt.eq == EULER2D ? member_buffer(m, cells, 2) : nullptr, nullptr, rt.d_amax, rt.d_ctrl, xt, ut);
+    rt.fill_inst(I, *prob, u, member_buffer(m, cells, 0), member_buffer(m, cells, 1), nullptr, rt.d_amax, rt.d_ctrl, xt, ut);
     rt.h_hdr.n_inst = 1;
     rt.h_hdr.xtiles_total = xt;
     rt.h_hdr.units_total = ut;

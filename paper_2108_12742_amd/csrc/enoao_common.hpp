@@ -69,7 +69,7 @@ struct Ctrl {
 struct Inst {
     double *u;                  // u^n: caller state, updated in place by stage 3
     double *w1, *w2;            // stage-1 and stage-2 states
-    double *lx;                 // 2D: x-part of L; rhs: the L output
+    double *lx;                 // rhs: the L output
     unsigned long long *amax;   // AMAX_SLOTS x amax_copies x AMAX_VALS
     Ctrl *ctrl;
     uint8_t *sel;               // selection record or nullptr

@@ -276,7 +276,7 @@ template <int EQ, int MODE> struct View {
     const GMEM double *in;    // stage input
     GMEM double *out;         // stage output
     const GMEM double *base;  // u^n (stages 2 and 3)
-    GMEM double *lx;          // x-part of L (2D) / L (rhs)
+    GMEM double *lx;          // rhs: L
     GMEM uint8_t *sel;
     GMEM unsigned long long *amax;
     GMEM Ctrl *ctrl;
