@@ -224,7 +224,9 @@ enoao_status enoao_batch_query(enoao_batch *batch, double *t, int64_t *steps, in
  * Intended for serving loops: admit requests as memory frees up, step, poll,
  * retire finished ones.
  *
- * enoao_pool_member_bytes: arena bytes a member needs (0 if invalid).  The
+ * enoao_pool_member_bytes: arena bytes a member needs (0 if invalid; four
+ *   states in 2D, of which the device holds three and the lists of selected
+ *   faces: a pool never allocates more than its arena and control data).  The
  *   pool keeps its members' states with rows padded to 128-byte multiples;
  *   admit and retire take and give the dense [ncomp][ny][nx] layout.
  * enoao_pool_admit: copies the initial state u0 (host memory if u0_on_host,

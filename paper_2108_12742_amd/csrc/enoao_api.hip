@@ -920,6 +920,13 @@ struct enoao_pool {
 
     static size_t align(size_t b) { return (b + 255) / 256 * 256; }
 
+    // A 2D member is charged for four states and holds three (its own, w1 and w2), packed:
+    // charges and so offsets are multiples of 1 KiB.  The lists take less than the rest
+    // of the charge, so a pool allocates no more than its arena.
+    static size_t held(const Runtime &r, size_t charged) { return r.eq == EULER2D ? charged / 4 * 3 : charged; }
+    double *place(size_t off) const { return (double *)(arena + held(rt, off)); }
+    double *member(int slot) const { return place(slots[slot].off); }
+
     bool arena_alloc(size_t bytes, size_t &off)
     {
         for (size_t i = 0; i < free_list.size(); ++i) {
@@ -962,7 +969,7 @@ struct enoao_pool {
         for (int k = 0; k < max_members; ++k) {
             if (!slots[k].used) continue;
             const enoao_problem &p = slots[k].prob;
-            double *m = (double *)(arena + slots[k].off);
+            double *m = member(k);
             const int pitch = padded_pitch(p.nx);
             const size_t cells = (size_t)r.nc * pitch * p.ny;
             Inst I;
@@ -1013,7 +1020,7 @@ struct enoao_pool {
             // member's w1 buffer: the member no longer steps)
             const int pitch = padded_pitch(p.nx);
             const long long rows = (long long)r.nc * p.ny;
-            double *mem = (double *)(arena + slots[slot].off);
+            double *mem = member(slot);
             const size_t cells = (size_t)r.nc * pitch * p.ny;
             double *dst = u_out_on_host ? member_buffer(mem, cells, 1) : u_out;
             HIP_TRY(launch_copy_pitched(member_buffer(mem, cells, 0), pitch, dst, p.nx, p.nx, rows, s));
@@ -1547,10 +1554,10 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     const size_t o_ctrl = take(sizeof(Ctrl) * max_members);
     const size_t o_amax = take(8ull * r.amax_words() * max_members);
     const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * sizeof(unsigned));
-    // (a member of ny rows and s strips holds at least 128 ny max(16, 54 (s - 1)) bytes of
-    // the arena, and its list at most 128 s ny)
+    // (a member of ny rows and s strips is charged at least 128 ny max(16, 54 (s - 1)) bytes
+    // of the arena, and its list takes at most 128 s ny)
     const size_t o_fix = take(r.eq == EULER2D ? arena_bytes / 16 + 256 : 0);
-    const size_t o_arena = take(arena_bytes);
+    const size_t o_arena = take(enoao_pool::held(r, arena_bytes));
     if (hipMalloc(&r.d_block, off) != hipSuccess) {
         r.d_block = nullptr;
         return fail(ENOAO_ENOMEM);
@@ -1636,7 +1643,7 @@ enoao_status enoao_pool_admit(enoao_pool *pool, const enoao_problem *prob, const
     // through the member's w1 buffer, unused until its first step)
     const int pitch = padded_pitch(prob->nx);
     const long long rows = (long long)r.nc * prob->ny;
-    double *mem = (double *)(pool->arena + off);
+    double *mem = pool->place(off);
     const size_t cells = (size_t)r.nc * pitch * prob->ny;
     const double *src = u0;
     if (u0_on_host) {

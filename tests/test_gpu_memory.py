@@ -1,4 +1,5 @@
-"""Device memory: a plan takes what enoao_workspace_bytes says."""
+"""Device memory: a plan takes what enoao_workspace_bytes says, and a pool no more than its
+arena (beside its control data)."""
 import pytest
 
 from tests import parity as PT
@@ -27,3 +28,15 @@ def test_workspace_bytes(eq, nx, ny, record):
     E.enoao_plan_create(ep)  # (what the runtime keeps from the first on)
     taken, plan = _taken(torch, lambda: E.enoao_plan_create(ep))
     assert abs(taken - E.enoao_workspace_bytes(ep)) <= SLACK
+
+
+@pytest.mark.parametrize("eq,n", [("euler1d", 1000), ("euler2d", 128)])
+def test_pool_stays_within_its_arena(eq, n):
+    torch = PT.torch_cuda()
+    from paper_2108_12742_amd import enoao as E
+    like, arena = E.make_problem(eq, n, n if eq == "euler2d" else 1), 4 << 30
+    print(f"[memory] pool {eq}", flush=True)
+    E.enoao_pool_create(like, 16, 1 << 20)
+    taken, pool = _taken(torch, lambda: E.enoao_pool_create(like, 16, arena))
+    assert taken <= arena + SLACK
+    assert E.enoao_pool_usage(pool)[1] == arena
