@@ -295,9 +295,10 @@ enoao_status enoao_batch_profile_read(enoao_batch *batch, double *avg_ms, int64_
  * (1..64; 0 = the occupancy the compiler's register and LDS use allow).
  * enoao_set_launch sets the default for plans and batches created afterwards
  * (reserved must be 0); the per-object calls change an existing plan or batch
- * (its captured graph is rebuilt on the next call).  Results do not depend on
- * the launch shape: every tile is computed the same way whichever workgroup
- * runs it. */
+ * (its captured graph is rebuilt on the next call).  The stretches of rows that
+ * 2D waves walk do not depend on it (enoao_plan_set_tiles).  Results do not
+ * depend on the launch shape: every tile is computed the same way whichever
+ * workgroup runs it. */
 enoao_status enoao_set_launch(int32_t workgroups_per_cu, int32_t reserved);
 enoao_status enoao_plan_set_launch(enoao_plan *plan, int32_t workgroups_per_cu);
 enoao_status enoao_batch_set_launch(enoao_batch *batch, int32_t workgroups_per_cu);

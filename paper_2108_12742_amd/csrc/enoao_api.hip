@@ -519,17 +519,17 @@ struct Runtime {
     }
     int strips_of(int nx) const { return (nx + strip_cells(order) - 1) / strip_cells(order); }
 
-    // Rows per unit: as many units as the launch has waves resident, so every wave
-    // takes one (the rows above a unit's first face are read and their fluxes formed
-    // again, about one row's time; a second round of units would wait for the first).
+    // Rows per unit: as many units as the device holds waves of the stage kernel, so every
+    // wave takes one (the rows above a unit's first face are read and their fluxes formed
+    // again, about one row's time; a second round of units would wait for the first).  The
+    // launch shape (wg_per_cu) does not enter: it may be set before or after, per kernel.
     int rows = 1;
     bool wide = false;  // a plane of 4 GiB or more: the recording kernels' 64-bit offsets
     bool general_2d() const { return wide || (kflags & KF_FULL_SELECTION) != 0; }
     void choose_rows(const enoao_problem *ps, int count)
     {
         if (eq != EULER2D) return;
-        const int per_cu = wg_per_cu > 0 ? wg_per_cu : occupancy_2d(order, M_S2, false, ch);
-        const long long waves = (long long)cus * per_cu * (BLOCK / 64);
+        const long long waves = (long long)cus * occupancy_2d(order, M_S2, false, ch) * (BLOCK / 64);
         long long total = 0;
         int most = 1;
         if (!dynamic) wide = false;  // (a pool's captured graphs outlive its members)
