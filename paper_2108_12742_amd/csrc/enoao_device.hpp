@@ -48,14 +48,12 @@
 
 namespace enoao {
 
-// Wave-uniform shortcut: when every lane of the wave has IS <= delta for the
-// top candidate on both sides of a field, that candidate is every lane's choice
-// (first principle) and the field's value is the top candidate's alone;
-// otherwise the field takes the full selection.  A lane's result does not
-// depend on the path: the full selection uses the same top indicator and, when
-// it picks the top candidate on both sides, the same value.  The kernels take
-// a flag that turns the shortcut off (every face takes the full selection), so
-// that property can be checked.
+// Shortcut: a face whose top candidate is within delta on both sides of every field
+// takes it (first principle), and its flux is linear in the window.  Advection asks the
+// indicators themselves, a wave at a time; the Euler faces a bound on them, each for
+// itself.  A face's result does not depend on the path: the full selection of a face that
+// the shortcut would take finds the top candidates and leaves the same flux.  The kernels
+// take a flag that sends every face to the full selection, so that property can be checked.
 
 // true when the predicate holds on every active lane of the wave (one ballot)
 __device__ __forceinline__ bool wave_all(bool p) { return __builtin_amdgcn_ballot_w64(!p) == 0; }
@@ -257,9 +255,6 @@ template <int ORDER> __device__ __forceinline__ double Recon<ORDER>::window_is_t
 // loads it; faces read them from LDS).
 //   advection: u
 //   Euler 1D : rho, m, E | F1, F2 | sqrt(rho), u, H   (F0 = m)
-//   Euler 2D : rho, m, n, E | F0..F3 | sqrt(rho), u, v, H
-// (along y the two momentum components arrive exchanged, so the same
-//  x-direction formulas give the y-flux in exchanged order).
 // 1/x for positive normal x: hardware reciprocal refined by two Newton steps
 // (within an ulp or so; the kernels' reciprocals and quotients are rounding-level
 // different from IEEE division).
@@ -314,7 +309,7 @@ __device__ __forceinline__ void sqrt_rcp_nr(double x, double &root, double &inv)
 template <int EQ> struct NodeTraits;
 template <> struct NodeTraits<ADVECTION> { static constexpr int NC = 1, NQ = 1; };
 template <> struct NodeTraits<EULER1D> { static constexpr int NC = 3, NQ = 8; };
-template <> struct NodeTraits<EULER2D> { static constexpr int NC = 4, NQ = 12; };
+template <> struct NodeTraits<EULER2D> { static constexpr int NC = 4; };
 
 // Returns false for a non-physical node (rho <= 0, p <= 0 or NaN).
 template <int EQ>
@@ -324,7 +319,7 @@ __device__ __forceinline__ bool node_quantities(const double (&U)[NodeTraits<EQ>
     if constexpr (EQ == ADVECTION) {
         q[0] = U[0];
         return U[0] == U[0];
-    } else if constexpr (EQ == EULER1D) {
+    } else {
         const double rho = U[0], m = U[1], E = U[2];
         const double ir = rcp_nr(rho);
         const double u = m * ir;
@@ -332,15 +327,6 @@ __device__ __forceinline__ bool node_quantities(const double (&U)[NodeTraits<EQ>
         q[0] = rho; q[1] = m; q[2] = E;
         q[3] = fma(m, u, p); q[4] = (E + p) * u;  // (F_0 is m)
         q[5] = sqrt_nr(rho); q[6] = u; q[7] = (E + p) * ir;
-        return rho > 0.0 && p > 0.0;
-    } else {
-        const double rho = U[0], m = U[1], n = U[2], E = U[3];
-        const double ir = rcp_nr(rho);
-        const double u = m * ir, v = n * ir;
-        const double p = gm1 * fma(-0.5 * rho, fma(u, u, v * v), E);
-        q[0] = rho; q[1] = m; q[2] = n; q[3] = E;
-        q[4] = m; q[5] = fma(m, u, p); q[6] = m * v; q[7] = (E + p) * u;
-        q[8] = sqrt_nr(rho); q[9] = u; q[10] = v; q[11] = (E + p) * ir;
         return rho > 0.0 && p > 0.0;
     }
 }

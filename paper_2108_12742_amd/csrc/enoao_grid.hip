@@ -630,7 +630,7 @@ __attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
 // y-faces on either side.
 using WaveMost = unsigned long long[7][4];
 template <int NW> struct FixScratch {
-    double dF[3][4][58];       // what the faces' fluxes have beyond the mean, by set (x, below, above) and lane from H on
+    double dF[3][4][58];       // fluxes beyond the mean by set (x, below, above) and lane from H on
     double exchange[NW][64];   // window values by node and (face, field)
     unsigned char face[176];   // set << 6 | lane of each face
     WaveMost most;             // the wave's maxima, in four parts
@@ -691,8 +691,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     if (entries == 0) return;
     const long long list_skew = list0 - (long long)(upto - mine_n);  // entry i of all is at i + list_skew
     // Few entries leave waves idle: workgroups share an entry, or halves of entries go to
-    // different workgroups or waves.  (30 x 30, six steps: 513 us without the halves; more
-    // and smaller pieces from the start cost a full machine 5 to 12%.)
+    // different workgroups or waves.  (128^2, a step: 94 us against 96 without the halves,
+    // 511 x 257, ten steps: 1040 against 1031; more and smaller pieces from the start cost a
+    // full machine 5 to 12%.)
     const unsigned waves = gridDim.x * NWV;
     const bool team = entries <= gridDim.x;
     const unsigned halves = 2 * entries <= (team ? gridDim.x : waves) ? 1u : 0u;
@@ -813,102 +814,102 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             };
 #pragma unroll 1
             for (int k0 = start; k0 < 4 * nf; k0 += step) {
-            const bool valid = k0 + lane < 4 * nf;
-            const int k = min(k0 + lane, 4 * nf - 1), s = k & 3;
-            const unsigned f = S.face[k >> 2], set = f >> 6;
-            const bool acoustic = CH && (s == 0 || s == 3);
-            const FixLine<Off> l = line(f);
-            const double a = alpha(l.x, s);
-            // The four lanes of a face share its window: each loads a quarter of the nodes
-            // and projects them on all fields, and takes its field of the others' from LDS
-            // (every lane loading the whole window took twice as long, half of it in the
-            // loads).
-            constexpr int NPL = (NW + 3) / 4;
-            double Q[NPL][4];
-            l.template load<NW, NPL>(v, plane, s * NPL, Q);
-            double U[NPL][4], F[NPL][4], hh[NPL];
-#pragma unroll
-            for (int i = 0; i < NPL; ++i) {
-                const double rho = Q[i][0], m = l.x ? Q[i][1] : Q[i][2], n = l.x ? Q[i][2] : Q[i][1], E = Q[i][3];
-                const double ir = rcp_nr(rho), u = m * ir, w = n * ir;
-                const double p = node_pressure(rho, u, w, E, P.gm1);
-                U[i][0] = rho;
-                U[i][1] = m;
-                U[i][2] = n;
-                U[i][3] = E;
-                F[i][0] = m;
-                F[i][1] = fma(m, u, p);
-                F[i][2] = m * w;
-                F[i][3] = (E + p) * u;
-                hh[i] = (E + p) * ir;
-                Q[i][1] = u;
-                Q[i][2] = w;
-            }
-            RoeState ro{};
-            if constexpr (CH) {
-                // nodes H and H + 1 from the lanes that hold them
-                constexpr int iL = H % NPL, iR = (H + 1) % NPL;
-                constexpr int fromL = 0x55 * (H / NPL), fromR = 0x55 * ((H + 1) / NPL);  // quad_perm broadcasts
-                ro = roe_state(sqrt_nr(dpp_move<fromL>(Q[iL][0])), dpp_move<fromL>(Q[iL][1]), dpp_move<fromL>(Q[iL][2]),
-                               dpp_move<fromL>(hh[iL]), sqrt_nr(dpp_move<fromR>(Q[iR][0])), dpp_move<fromR>(Q[iR][1]),
-                               dpp_move<fromR>(Q[iR][2]), dpp_move<fromR>(hh[iR]), P.gm1);
-            }
-            // windows g+ and g- = P F +- a P U; a lane's columns are rotated by its place in
-            // the quad, so the four writes of an instruction fall in different banks
-            double pu[NW], gp[2 * H + 1], gm[2 * H + 1];
-            double(&X)[NW][64] = scratch[wv].exchange;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
+                const bool valid = k0 + lane < 4 * nf;
+                const int k = min(k0 + lane, 4 * nf - 1), s = k & 3;
+                const unsigned f = S.face[k >> 2], set = f >> 6;
+                const bool acoustic = CH && (s == 0 || s == 3);
+                const FixLine<Off> l = line(f);
+                const double a = alpha(l.x, s);
+                // The four lanes of a face share its window: each loads a quarter of the nodes
+                // and projects them on all fields, and takes its field of the others' from LDS
+                // (every lane loading the whole window took twice as long, half of it in the
+                // loads).
+                constexpr int NPL = (NW + 3) / 4;
+                double Q[NPL][4];
+                l.template load<NW, NPL>(v, plane, s * NPL, Q);
+                double U[NPL][4], F[NPL][4], hh[NPL];
 #pragma unroll
                 for (int i = 0; i < NPL; ++i) {
-                    double w[4];
-                    to_fields<4, CH>(ro, h == 0 ? U[i] : F[i], w);
-                    const int t = s * NPL + i;
-                    if (4 * NPL == NW || t < NW) {
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) X[t][(lane & 60) + ((c + s) & 3)] = w[c];
-                    }
+                    const double rho = Q[i][0], m = l.x ? Q[i][1] : Q[i][2], n = l.x ? Q[i][2] : Q[i][1], E = Q[i][3];
+                    const double ir = rcp_nr(rho), u = m * ir, w = n * ir;
+                    const double p = node_pressure(rho, u, w, E, P.gm1);
+                    U[i][0] = rho;
+                    U[i][1] = m;
+                    U[i][2] = n;
+                    U[i][3] = E;
+                    F[i][0] = m;
+                    F[i][1] = fma(m, u, p);
+                    F[i][2] = m * w;
+                    F[i][3] = (E + p) * u;
+                    hh[i] = (E + p) * ir;
+                    Q[i][1] = u;
+                    Q[i][2] = w;
                 }
-                wave_sync();
-#pragma unroll
-                for (int t = 0; t < NW; ++t) {
-                    const double x = X[t][(lane & 60) + ((s + t / NPL) & 3)];
-                    if (h == 0) {
-                        pu[t] = x;
-                    } else {
-                        if (t <= 2 * H) gp[t] = fma(a, pu[t], x);
-                        if (t >= 1) gm[2 * H + 1 - t] = fma(-a, pu[t], x);
-                    }
+                RoeState ro{};
+                if constexpr (CH) {
+                    // nodes H and H + 1 from the lanes that hold them
+                    constexpr int iL = H % NPL, iR = (H + 1) % NPL;
+                    constexpr int fromL = 0x55 * (H / NPL), fromR = 0x55 * ((H + 1) / NPL);  // quad_perm broadcasts
+                    ro = roe_state(sqrt_nr(dpp_move<fromL>(Q[iL][0])), dpp_move<fromL>(Q[iL][1]), dpp_move<fromL>(Q[iL][2]),
+                                   dpp_move<fromL>(hh[iL]), sqrt_nr(dpp_move<fromR>(Q[iR][0])), dpp_move<fromR>(Q[iR][1]),
+                                   dpp_move<fromR>(Q[iR][2]), dpp_move<fromR>(hh[iR]), P.gm1);
                 }
-                wave_sync();
+                // windows g+ and g- = P F +- a P U; a lane's columns are rotated by its place in
+                // the quad, so the four writes of an instruction fall in different banks
+                double pu[NW], gp[2 * H + 1], gm[2 * H + 1];
+                double(&X)[NW][64] = scratch[wv].exchange;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int i = 0; i < NPL; ++i) {
+                        double w[4];
+                        to_fields<4, CH>(ro, h == 0 ? U[i] : F[i], w);
+                        const int t = s * NPL + i;
+                        if (4 * NPL == NW || t < NW) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) X[t][(lane & 60) + ((c + s) & 3)] = w[c];
+                        }
+                    }
+                    wave_sync();
+#pragma unroll
+                    for (int t = 0; t < NW; ++t) {
+                        const double x = X[t][(lane & 60) + ((s + t / NPL) & 3)];
+                        if (h == 0) {
+                            pu[t] = x;
+                        } else {
+                            if (t <= 2 * H) gp[t] = fma(a, pu[t], x);
+                            if (t >= 1) gm[2 * H + 1 - t] = fma(-a, pu[t], x);
+                        }
+                    }
+                    wave_sync();
+                }
+                const double sd = (acoustic ? 4.0 : 2.0) * P.delta;
+                int sp, sm;
+                double tp, tm;
+                const double hp = R::select_step(gp, sd, sp, tp);
+                __builtin_amdgcn_sched_barrier(0);
+                const double hm = R::select_step(gm, sd, sm, tm);
+                if (REC && v.sel && valid) {
+                    const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
+                    const long long o = l.x ? 2 * s * xb + (long long)l.row * (nx + 1) + l.col + 1
+                                            : 8 * xb + 2 * s * yb + (long long)(set == 1u ? l.row : l.row + 1) * nx + l.col;
+                    v.sel[o] = (uint8_t)sp;
+                    v.sel[o + (l.x ? xb : yb)] = (uint8_t)sm;
+                }
+                // R de, summed over the face's four lanes; lane s stores component s
+                double es = fma(a, pu[H] - pu[H + 1], hp + hm);
+                if (full && (((set == 0u ? tx : (set == 1u ? tb : tt)) >> (f & 63u)) & 1)) es = (hp - tp) + (hm - tm);  // (zero)
+                es *= acoustic ? 0.25 : 0.5;
+                double d = es;
+                if constexpr (CH) {
+                    const double e[4] = {s == 0 ? es : 0.0, s == 1 ? es : 0.0, s == 2 ? es : 0.0, s == 3 ? es : 0.0};
+                    double r[4];
+                    back_project<4>(ro, e, r);
+                    const double d0 = quad_sum(r[0]), d1 = quad_sum(r[1]), d2 = quad_sum(r[2]), d3 = quad_sum(r[3]);
+                    d = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
+                }
+                if (valid) S.dF[set][s][(f & 63u) - H] = d;
             }
-            const double sd = (acoustic ? 4.0 : 2.0) * P.delta;
-            int sp, sm;
-            double tp, tm;
-            const double hp = R::select_step(gp, sd, sp, tp);
-            __builtin_amdgcn_sched_barrier(0);
-            const double hm = R::select_step(gm, sd, sm, tm);
-            if (REC && v.sel && valid) {
-                const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
-                const long long o = l.x ? 2 * s * xb + (long long)l.row * (nx + 1) + l.col + 1
-                                        : 8 * xb + 2 * s * yb + (long long)(set == 1u ? l.row : l.row + 1) * nx + l.col;
-                v.sel[o] = (uint8_t)sp;
-                v.sel[o + (l.x ? xb : yb)] = (uint8_t)sm;
-            }
-            // R de, summed over the face's four lanes; lane s stores component s
-            double es = fma(a, pu[H] - pu[H + 1], hp + hm);
-            if (full && (((set == 0u ? tx : (set == 1u ? tb : tt)) >> (f & 63u)) & 1)) es = (hp - tp) + (hm - tm);  // (zero)
-            es *= acoustic ? 0.25 : 0.5;
-            double d = es;
-            if constexpr (CH) {
-                const double e[4] = {s == 0 ? es : 0.0, s == 1 ? es : 0.0, s == 2 ? es : 0.0, s == 3 ? es : 0.0};
-                double r[4];
-                back_project<4>(ro, e, r);
-                const double d0 = quad_sum(r[0]), d1 = quad_sum(r[1]), d2 = quad_sum(r[2]), d3 = quad_sum(r[3]);
-                d = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
-            }
-            if (valid) S.dF[set][s][(f & 63u) - H] = d;
-        }
             sync();
             bool b = false;
             Maxima<EULER2D> m;

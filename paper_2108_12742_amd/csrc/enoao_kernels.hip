@@ -334,8 +334,7 @@ __device__ __forceinline__ View<EQ, MODE> load_view(const KParams &P, int n_inst
         if constexpr (CH) {
             v.al[0] = m0;
             v.al[1] = m1;
-            if (NC == 4) v.al[2] = m1;
-            v.al[NC - 1] = m2;
+            v.al[2] = m2;
         } else {
             // one alpha for all components: max(|u| + c) = max(max|u - c|, max|u + c|)
             const double a = fmax(m0, m2);
@@ -830,50 +829,50 @@ __device__ __forceinline__ void line_round(const KParams &P, double adv, double 
 {
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LineLds own = line_lds<EQ, ORDER>(wls, wv);
-            const bool shortcut = (P.flags & KF_FULL_SELECTION) == 0;
-            if constexpr (EQ == ADVECTION) {
-                int sel[2];
-                if (faces > 0) own.fh[lane] = advection_flux<ORDER, false>(own.q + lane, nullptr, al[0], adv, P.delta, shortcut, sel);
-                wave_sync();
-            } else {
-                auto rec = [](int, int, int) {};
-                                const Alpha3 a3{al[0], al[1], al[2]};
-                double Fh[3] = {0.0, 0.0, 0.0};
-                unsigned long long fail = 0;
-                if (faces > 0) fail = line_top<ORDER, CH>(own, al, P.gm1, P.delta, shortcut, lane < faces, Fh, rec);
-                if constexpr (TEAM) {
-                    if (lane == 0) counts[wv] = __popcll(fail);
-                    __syncthreads();
-                    // the waves' listed faces, one wave's after the other's
-                    int upto[NW];
-    #pragma unroll
-                    for (int w = 0; w < NW; ++w) upto[w] = (w ? upto[w - 1] : 0) + __builtin_amdgcn_readfirstlane(counts[w]);
-                    const int nf = upto[NW - 1];
-                    if (nf) {
-    #pragma unroll 1
-                        for (int at = 64 * wv; at < 3 * nf; at += 64 * NW) {
-                            const int i = min(at + lane, 3 * nf - 1), s = (i >= nf) + (i >= 2 * nf), k = i - s * nf;
-                            int w = 0, before = 0;
-    #pragma unroll
-                            for (int j = 0; j + 1 < NW; ++j) {
-                                w += k >= upto[j];
-                                before = k >= upto[j] ? upto[j] : before;
-                            }
-                            const LineLds l = line_lds<EQ, ORDER>(wls, w);
-                            line_select<ORDER, CH, false>(l, k - before, s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
-                        }
-                        __syncthreads();
-                        line_correct<ORDER, CH>(own, fail, P.gm1, Fh);
+    const bool shortcut = (P.flags & KF_FULL_SELECTION) == 0;
+    if constexpr (EQ == ADVECTION) {
+        int sel[2];
+        if (faces > 0) own.fh[lane] = advection_flux<ORDER, false>(own.q + lane, nullptr, al[0], adv, P.delta, shortcut, sel);
+        wave_sync();
+    } else {
+        auto rec = [](int, int, int) {};
+        const Alpha3 a3{al[0], al[1], al[2]};
+        double Fh[3] = {0.0, 0.0, 0.0};
+        unsigned long long fail = 0;
+        if (faces > 0) fail = line_top<ORDER, CH>(own, al, P.gm1, P.delta, shortcut, lane < faces, Fh, rec);
+        if constexpr (TEAM) {
+            if (lane == 0) counts[wv] = __popcll(fail);
+            __syncthreads();
+            // the waves' listed faces, one wave's after the other's
+            int upto[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) upto[w] = (w ? upto[w - 1] : 0) + __builtin_amdgcn_readfirstlane(counts[w]);
+            const int nf = upto[NW - 1];
+            if (nf) {
+#pragma unroll 1
+                for (int at = 64 * wv; at < 3 * nf; at += 64 * NW) {
+                    const int i = min(at + lane, 3 * nf - 1), s = (i >= nf) + (i >= 2 * nf), k = i - s * nf;
+                    int w = 0, before = 0;
+#pragma unroll
+                    for (int j = 0; j + 1 < NW; ++j) {
+                        w += k >= upto[j];
+                        before = k >= upto[j] ? upto[j] : before;
                     }
-                } else {
-                    line_selections<ORDER, CH, false>(own, fail, a3, P.gm1, P.delta, Fh, rec);
+                    const LineLds l = line_lds<EQ, ORDER>(wls, w);
+                    line_select<ORDER, CH, false>(l, k - before, s, at + lane < 3 * nf, a3, P.gm1, P.delta, rec);
                 }
-                if (faces > 0) {
-    #pragma unroll
-                    for (int c = 0; c < 3; ++c) own.fh[c * XW_FACES + lane] = Fh[c];
-                }
-                wave_sync();
+                __syncthreads();
+                line_correct<ORDER, CH>(own, fail, P.gm1, Fh);
             }
+        } else {
+            line_selections<ORDER, CH, false>(own, fail, a3, P.gm1, P.delta, Fh, rec);
+        }
+        if (faces > 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) own.fh[c * XW_FACES + lane] = Fh[c];
+        }
+        wave_sync();
+    }
 }
 
 // One stage over a 1D line for the NW waves of a resident workgroup: segments 0 .. NW - 1

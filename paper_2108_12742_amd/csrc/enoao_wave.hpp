@@ -16,7 +16,7 @@ namespace enoao {
 // P.grid_min, at most the grid).  A pool's grid covers the machine several
 // times over; many small chunks let the workgroups that finish early take
 // more of them, which evens out members of uneven cost, while a pool holding
-// few tiles keeps chunks long enough for the y walks' row reuse.
+// few tiles keeps chunks long enough to pay for their first loads.
 __device__ __forceinline__ long long chunk_groups(const KParams &P, long long T)
 {
     const long long g = gridDim.x;
