@@ -120,7 +120,7 @@ struct Layout {
         amax = take(8ull * AMAX_SLOTS * amax_slot_words(ps[0].equation) * count);
         order = take(sizeof(int) * count);
         bar = take(2 * sizeof(unsigned));
-        counters = take(ps[0].equation == EULER2D ? FIX_SETS * FIX_SET_WORDS * sizeof(unsigned) : 0);
+        counters = take(ps[0].equation == EULER2D ? FIX_SETS * FIX_SET_WORDS * 8 : 0);
         size_t list = 0;
         for (int i = 0; i < count; ++i) list += list_bytes(&ps[i]);
         lists = take(list);
@@ -153,7 +153,7 @@ struct Runtime {
     Inst *d_inst = nullptr;
     Ctrl *d_ctrl = nullptr;
     unsigned long long *d_amax = nullptr;
-    unsigned *d_fix_count = nullptr;           // 2D: list counters (FIX_SETS sets)
+    unsigned long long *d_fix_count = nullptr; // 2D: list counters (FIX_SETS sets)
     unsigned long long *d_fix_list = nullptr;  // 2D: lists of row segments that need a selection
     int *d_res_order = nullptr;  // LDS-resident launches: members by decreasing size
     Ctrl *h_ctrl = nullptr;    // pinned mirror
@@ -330,7 +330,7 @@ struct Runtime {
         d_res_order = (int *)(base + at.order);
         d_bar = (unsigned *)(base + at.bar);
         if (eq == EULER2D) {
-            d_fix_count = (unsigned *)(base + at.counters);
+            d_fix_count = (unsigned long long *)(base + at.counters);
             d_fix_list = (unsigned long long *)(base + at.lists);
         }
         if (hipHostMalloc((void **)&h_ctrl, sizeof(Ctrl) * count, hipHostMallocDefault) != hipSuccess) {
@@ -831,7 +831,7 @@ struct enoao_plan {
 namespace {
 
 // (the list counters and the maxima ring follow the stated bytes)
-constexpr size_t NA_FIX = ENOAO_NOALLOC_SCRATCH_BYTES, NA_AMAX = NA_FIX + FIX_SETS * FIX_SET_WORDS * sizeof(unsigned);
+constexpr size_t NA_FIX = ENOAO_NOALLOC_SCRATCH_BYTES, NA_AMAX = NA_FIX + FIX_SETS * FIX_SET_WORDS * 8;
 constexpr size_t NA_END = NA_AMAX + AMAX_SLOTS * amax_slot_words(EULER2D) * 8;
 __device__ __align__(256) unsigned char scratch[NA_END];
 
@@ -1286,7 +1286,7 @@ enoao_status enoao_step_noalloc(const enoao_problem *prob, double *u, double dt,
     rt.d_res_order = nullptr;
     if (rt.eq == EULER2D) {
         // the lists in place of a third state (list_bytes)
-        rt.d_fix_count = (unsigned *)(base + NA_FIX);
+        rt.d_fix_count = (unsigned long long *)(base + NA_FIX);
         rt.d_fix_list = (unsigned long long *)member_buffer((double *)(base + NA_MEM),
                                                             (size_t)rt.nc * prob->nx * prob->ny, 2);
     }
@@ -1553,7 +1553,7 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     const size_t o_inst = take(sizeof(Inst) * max_members);
     const size_t o_ctrl = take(sizeof(Ctrl) * max_members);
     const size_t o_amax = take(8ull * r.amax_words() * max_members);
-    const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * sizeof(unsigned));
+    const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * 8);
     // (a member of ny rows and s strips is charged at least 128 ny max(16, 54 (s - 1)) bytes
     // of the arena, and its list takes at most 128 s ny)
     const size_t o_fix = take(r.eq == EULER2D ? arena_bytes / 16 + 256 : 0);
@@ -1568,7 +1568,7 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     r.d_ctrl = (Ctrl *)(base + o_ctrl);
     r.d_amax = (unsigned long long *)(base + o_amax);
     if (r.eq == EULER2D) {
-        r.d_fix_count = (unsigned *)(base + o_fixc);
+        r.d_fix_count = (unsigned long long *)(base + o_fixc);
         r.d_fix_list = (unsigned long long *)(base + o_fix);
     }
     pl->arena = base + o_arena;

@@ -23,18 +23,20 @@ constexpr int XW_SEGS = 4;
 // rows are cut into blocks of equal height to within one; a unit of work is one
 // block of one strip.
 constexpr int strip_cells(int order) { return order == 7 ? 54 : 56; }
-// Row segments whose faces need a selection are listed for a second kernel: one entry
-// per strip and row, or one per 2 FIX_SPLIT cells where there are more than FIX_FACES
-// faces to select, per FIX_SPLIT cells from half as many again (a segment along a shock
-// holds up to 169, eleven passes of the wave that takes it, and the launch waited for
-// those).  The units are cut into FIX_RANGES ranges with a list
+// Row segments whose faces need a selection are listed for a second kernel: pieces of a
+// strip's row of at most FIX_FACES faces, two passes of the wave that takes one, as far as
+// the places of a row allow (FIX_SPLIT cells a place; a row along a shock holds up to 169
+// faces).  The pieces of two passes are dealt before those of one, so that every wave has
+// about the same to do.  The units are cut into FIX_RANGES ranges with a list
 // and a counter each, the counters a cache line apart: the waves that end a launch
-// together take their places at once, and an atomic on one line takes 20 ns.  Four
+// together take their places at once, and an atomic on one line takes 20 ns.  A list is
+// filled from both ends, a counter holds both numbers: its low half the pieces of two
+// passes, from the list's start on, its high half those of one, from the end back.  Four
 // sets of counters, three used in turn by the stages of a step, the fourth by an
 // evaluation of L.
-constexpr int FIX_SPLIT = 14, FIX_FACES = 48;
+constexpr int FIX_SPLIT = 14, FIX_FACES = 32, FIX_PASS = 16;
 constexpr int fix_places(int nx) { return nx > 3 * FIX_SPLIT ? 4 : (nx + FIX_SPLIT - 1) / FIX_SPLIT; }  // per strip and row
-constexpr int FIX_ENTRY_BYTES = 32, FIX_RANGES = 32, FIX_COUNTER_STRIDE = 16;
+constexpr int FIX_ENTRY_BYTES = 32, FIX_RANGES = 32, FIX_COUNTER_STRIDE = 8;
 constexpr int FIX_SET_WORDS = FIX_RANGES * FIX_COUNTER_STRIDE, FIX_SETS = 4;
 constexpr int BLOCK = 256;
 

@@ -285,26 +285,13 @@ __device__ __forceinline__ void top_flux(const RoeState &r, const double (&sF)[4
     for (int c = 0; c < 4; ++c) Fh[c] = fma(0.5, sF[c], Fh[c]);
 }
 
-// units per range of the lists (a launch has fewer than 2^32)
-__device__ __forceinline__ unsigned fix_range_units(long long units)
-{
-    return max(1u, ((unsigned)units + FIX_RANGES - 1) / FIX_RANGES);
-}
-
-// first entry of the list of the units from `unit` on: every strip row before it has its places
-__device__ __forceinline__ long long fix_list_start(const KParams &P, int n_inst, long long unit)
-{
-    const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst(P.inst, n_inst, unit)];
-    const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
-    const unsigned low = (unsigned)I.low_rows, extra = (unsigned)I.extra_rows;
-    const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);
-    return I.list0 + fix_places(I.nx) * ((long long)I.strips * y0 + (long long)s * rows);
-}
-
-// A listed row segment: unit << 28 | row within the unit << 12 | first lane of its
-// cells << 6 | last, and the lanes whose faces need a selection: right of the lane's
-// column, below and above the row.  Where every face is listed a segment has FIX_SPLIT
+// A listed piece of a row: unit << 28 | row within the unit << 12 | FIX_LAST for the row's
+// last piece | its number << 6 | faces a piece (0: the whole row), and the lanes of the
+// row whose faces need a selection: right of the lane's column, below and above the row.
+// A piece has the cells with as many of these faces before them as its number and that
+// size say; fix_2d cuts it out.  Where every face is listed a piece has FIX_SPLIT
 // cells, and the lanes that hold a top flux are marked once more, half a turn on.
+constexpr unsigned FIX_LAST = 1u << 8;
 __device__ __forceinline__ unsigned long long half_turn(unsigned long long m) { return m << 32 | m >> 32; }
 struct FixEntry {
     unsigned long long where, x, below, above;
@@ -337,7 +324,6 @@ __attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
     double(&rb)[7][ROW] = rows[wv];
     const int n_inst = P.hdr->n_inst;
     const long long units = P.hdr->units_total;
-    if (P.fix_zero && blockIdx.x == 0 && threadIdx.x < FIX_RANGES) gmem(P.fix_zero)[FIX_COUNTER_STRIDE * threadIdx.x] = 0u;
     // Consecutive units (neighbouring strips of the same rows, which share their halo
     // columns) go to one XCD's L2: workgroups are dealt to the eight XCDs in turn.
     const unsigned g = gridDim.x;
@@ -355,36 +341,41 @@ __attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
 #pragma unroll
         for (int i = 0; i < 7; ++i) M.v[i][lane] = 0ull;
     }
-    // the pending entries of a unit to its range's list
-    unsigned npend = 0;
+    // the pending entries of a unit to its range's list: those of two passes are in the
+    // first n_two places of `pending`, those of one in the last n_one
+    unsigned n_two = 0, n_one = 0;
     const unsigned per_range = fix_range_units(units);
     auto flush_pending = [&](long long unit) {
-        if (npend == 0) return;
+        if (n_two + n_one == 0) return;
         wave_sync();
         const unsigned range = (unsigned)unit / per_range;
-        unsigned at = 0;
+        unsigned long long at = 0;
         if (lane == 0)
-            at = __hip_atomic_fetch_add(gmem(P.fix_count) + range * FIX_COUNTER_STRIDE, npend, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-        const long long base = fix_list_start(P, n_inst, (long long)range * per_range);
-        if ((unsigned)lane < 4 * npend) {
+            at = __hip_atomic_fetch_add(gmem(P.fix_count) + range * FIX_COUNTER_STRIDE,
+                                        (unsigned long long)(0u - n_one) << 32 | n_two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        at = lane_bits(at, 0);
+        const unsigned e = lane >> 2;
+        const bool two = e < n_two;
+        if (two || e >= PENDING - n_one) {
             const unsigned long long *src = &pending[wv][0].where;
-            gmem(P.fix_list)[4 * (base + uniform(at)) + lane] = src[lane];
+            const unsigned to = two ? (unsigned)at + e : (unsigned)(at >> 32) + e - PENDING;
+            gmem(P.fix_list)[4ull * to + (lane & 3)] = src[lane];
         }
         wave_sync();
-        npend = 0;
+        n_two = n_one = 0;
     };
     GridView v;
     v.u0 = 0;
     v.u1 = -1;
     bool have = false;
+    if (P.lone_ctrl) v = grid_view<ORDER, CH>(P, n_inst, 0);  // (its loads beside the header's)
     for (long long unit = (long long)blk * NWV + wv; unit < units; unit += stride) {
         if (unit >= v.u1) {
             if (STEP && have) wave_flush(&M, 1, bad, v.amax, v.ctrl, P.r_out);
             bad = 0;
             v = grid_view<ORDER, CH>(P, n_inst, unit);
-            have = v.active != 0;
         }
+        have = v.active != 0;
         if (!have) continue;
         static_assert(amax_slot_words(EULER2D) == 64, "a lane per word of a slot");
         if (STEP && P.r_zero >= 0 && unit == v.u0) v.amax[P.r_zero * 64 + lane] = 0ull;
@@ -540,34 +531,34 @@ __attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
                 const unsigned long long fixed = full ? ~0ull : fail_x | (fail_x << 1) | fail_b | fail_t;
                 if (fixed) {
                     const unsigned long long where = (unsigned long long)unit << 28 | (unsigned)(j - y0) << 12;
-                    auto push = [&](int lo, int hi, unsigned long long x, unsigned long long b, unsigned long long t) {
-                        if (!(x | b | t)) return;
-                        if (lane == 0) pending[wv][npend] = FixEntry{where | (unsigned)(lo << 6 | hi), x, b, t};
-                        ++npend;
-                    };
-                    const int faces = __popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t);
-                    if (faces <= FIX_FACES && !full) {
-                        push(G, 63 - G, fail_x, fail_b, fail_t);
-                    } else {
-                        // (a row coarse along x alone has 57 faces and some: two pieces of two
-                        // passes, where four would be of two as well)
-                        const int width = faces > 3 * FIX_FACES / 2 || full ? FIX_SPLIT : 2 * FIX_SPLIT;
-#pragma unroll 1
-                        for (int lo = G; lo < min(64 - G, nx - x0 + G); lo += width) {  // (pieces with cells: the list's places)
-                            const unsigned long long m = ((1ull << width) - 1) << lo, mx = m | m >> 1;
-                            unsigned long long x = fail_x & mx, b = fail_b & m, t = fail_t & m;
-                            if (full) {
-                                // every face; those with a top flux twice
-                                const unsigned long long fs = __builtin_amdgcn_ballot_w64(face) & mx;
-                                const unsigned long long cs = __builtin_amdgcn_ballot_w64(cell) & m;
-                                x = fs | half_turn(fs & ~x);
-                                b = cs | half_turn(cs & ~b);
-                                t = cs | half_turn(cs & ~t);
-                            }
-                            push(lo, min(lo + width, 64 - G) - 1, x, b, t);
-                        }
+                    const int faces = __popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t), places = fix_places(nx);
+                    // pieces of `most` faces, a cell's three more and the one on its left again
+                    constexpr int MOST = FIX_FACES - 3;
+                    int pieces = min(places, 1 + (faces > FIX_FACES) + (faces > 2 * MOST) + (faces > 3 * MOST));
+                    int most = max(MOST, pieces == 4 ? (faces + 3) >> 2 : (pieces == 3 ? (faces + 2) / 3 : (faces + 1) >> 1));
+                    int rest = faces - (pieces - 1) * most;  // (about: the last one's)
+                    unsigned long long x = fail_x, b = fail_b, t = fail_t;
+                    if (full) {
+                        // every face; those with a top flux twice (lane k: those of piece k)
+                        const unsigned long long m = ((1ull << FIX_SPLIT) - 1) << ((G + FIX_SPLIT * lane) & 63);
+                        const unsigned long long fs = __builtin_amdgcn_ballot_w64(face) & (m | m >> 1);
+                        const unsigned long long cs = __builtin_amdgcn_ballot_w64(cell) & m;
+                        x = fs | half_turn(fs & ~x);
+                        b = cs | half_turn(cs & ~b);
+                        t = cs | half_turn(cs & ~t);
+                        pieces = min(places, (nx - x0 + FIX_SPLIT - 1) / FIX_SPLIT);  // (those with cells)
+                        most = rest = FIX_FACES;
                     }
-                    if (npend > PENDING - 4) flush_pending(unit);
+                    if (pieces == 1 && !full) most = 0;
+                    const unsigned one = rest <= FIX_PASS ? 1u : 0u;
+                    if (lane < pieces) {
+                        const bool last = lane == pieces - 1;
+                        pending[wv][last && one ? PENDING - 1 - n_one : n_two + lane] =
+                            FixEntry{where | (last ? FIX_LAST : 0u) | (unsigned)(lane << 6 | most), x, b, t};
+                    }
+                    n_two += pieces - one;
+                    n_one += one;
+                    if (n_two + n_one > PENDING - 4) flush_pending(unit);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 const int perm[4] = {0, 2, 1, 3};
@@ -632,31 +623,21 @@ using WaveMost = unsigned long long[7][4];
 template <int NW> struct FixScratch {
     double dF[3][4][58];       // fluxes beyond the mean by set (x, below, above) and lane from H on
     double exchange[NW][64];   // window values by node and (face, field)
+    double member[12];         // the member's alpha along x and along y by field, 1/dx, 1/dy, the weight of dL
     unsigned char face[176];   // set << 6 | lane of each face
     WaveMost most;             // the wave's maxima, in four parts
 };
 
-// A face's line along x or y: window node t is pos + t on it
-template <class Off> struct FixLine {
-    bool x;
-    int pos, row, col;
-    // nodes t0 .. t0 + N - 1 (the last node for those past it) of a window of NW
-    template <int NW, int N>
-    __device__ __forceinline__ void load(const GridView &v, long long plane, int t0, double (&U)[N][4]) const
-    {
-        const int n = x ? v.nx : v.ny;
-        const bool off = pos < 0 || pos + NW > n;  // the window crosses the boundary
-        const bool any = __builtin_amdgcn_ballot_w64(off) != 0;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            int k = pos + min(t0 + i, NW - 1);
-            if (any) k = k < 0 || k >= n ? bc_map(k, n, x ? v.bcx : v.bcy) : k;
-            const Off o = 8 * (x ? (Off)row * v.pitch + k : (Off)k * v.pitch + col);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) U[i][c] = row_load(v.in + c * plane, o);
-        }
-    }
-};
+// node k of n on a line, k at most a window beyond either end (small: n may be less than that)
+__device__ __forceinline__ int line_node(int k, int n, bool periodic, bool small)
+{
+    if (small) return bc_map(k, n, periodic ? BC_PERIODIC : BC_TRANSMISSIVE);
+    const int wrapped = k + (k < 0 ? n : (k >= n ? -n : 0));
+    return periodic ? wrapped : min(max(k, 0), n - 1);
+}
+
+// alpha of field s from those of u-c, u, u+c
+__device__ __forceinline__ double field_alpha(const double (&r)[3], int s) { return s == 0 ? r[0] : (s == 3 ? r[2] : r[1]); }
 
 // A wave takes one listed row segment at a time (handing them out from a counter took
 // longer than the imbalance it removed, 20 ns each); where the list is short, the four
@@ -676,20 +657,36 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_inst = P.hdr->n_inst;
-    // lane c: list c's first entry, and the entries of the lists up to it
+    GridView v;
+    v.u0 = 0;
+    v.u1 = -1;
+    auto enter = [&](long long unit) {
+        v = grid_view<ORDER, CH>(P, n_inst, unit);
+        // (in LDS: the loops below run out of scalar registers)
+        double x = lane < 4 ? field_alpha(v.rx, lane) : field_alpha(v.ry, lane & 3);
+        x = lane < 8 ? x : (lane == 8 ? v.idx : (lane == 9 ? v.idy : rk_weights(P.mode).y * v.dt));
+        if (lane < 11) scratch[wv].member[lane] = x;
+    };
+    // lane c: list c's pieces of two passes, lane FIX_RANGES + c: those of one; upto: the
+    // entries up to them.  Entry i of all is at skew + i, counted back among those of one.
+    static_assert(2 * FIX_RANGES == 64, "a lane per list and end");
     const long long units = P.hdr->units_total;
-    const unsigned per_range = fix_range_units(units);
-    unsigned upto = lane < FIX_RANGES ? gmem(P.fix_count)[lane * FIX_COUNTER_STRIDE] : 0u;
+    const bool two = lane < FIX_RANGES;
+    const unsigned long long counted = gmem(P.fix_count)[lane % FIX_RANGES * FIX_COUNTER_STRIDE];
+    if (P.lone_ctrl) enter(0);  // (beside the counters' loads: 2 us of a short launch)
+    const unsigned long long empty = fix_empty(P, n_inst, units, lane % FIX_RANGES);
+    if (P.fix_zero && blockIdx.x == gridDim.x - 1 && wv == 0 && two) gmem(P.fix_zero)[FIX_COUNTER_STRIDE * lane] = empty;
+    const unsigned list_end = two ? (unsigned)empty : (unsigned)(empty >> 32);
+    unsigned upto = two ? (unsigned)counted - list_end : list_end - (unsigned)(counted >> 32);
     const unsigned mine_n = upto;
-    const long long list0 = upto ? fix_list_start(P, n_inst, (long long)lane * per_range) : 0ll;
 #pragma unroll
-    for (int o = 1; o < FIX_RANGES; o *= 2) {
+    for (int o = 1; o < 64; o *= 2) {
         const unsigned x = __shfl_up(upto, o, 64);
         upto += lane >= o ? x : 0u;
     }
-    const unsigned entries = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1);
+    const unsigned entries = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
     if (entries == 0) return;
-    const long long list_skew = list0 - (long long)(upto - mine_n);  // entry i of all is at i + list_skew
+    const unsigned skew = two ? list_end - (upto - mine_n) : list_end - 1 + (upto - mine_n);
     // Few entries leave waves idle: workgroups share an entry, or halves of entries go to
     // different workgroups or waves.  (128^2, a step: 94 us against 96 without the halves,
     // 511 x 257, ten steps: 1040 against 1031; more and smaller pieces from the start cost a
@@ -698,8 +695,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     const bool team = entries <= gridDim.x;
     const unsigned halves = 2 * entries <= (team ? gridDim.x : waves) ? 1u : 0u;
     const unsigned count = entries << halves;
-    const unsigned stride = team ? gridDim.x : gridDim.x * NWV;
-    unsigned at = team ? blockIdx.x : blockIdx.x * NWV + wv, next_at = at + stride;
+    // There and back: who has the longest of one round has the shortest of the next.
+    const unsigned stride = team ? gridDim.x : waves, first = team ? blockIdx.x : blockIdx.x * NWV + wv;
+    const unsigned turn = 2 * stride - 1 - 2 * first;  // from a round's entry to the next round's, and 2 stride - turn
+    unsigned at = first, next_at = at + turn, leap = 2 * stride - turn;
     FixScratch<NW> &S = scratch[team ? 0 : wv];
     const int start = team ? 64 * wv : 0, step = team ? BLOCK : 64;
     auto sync = [&]() {
@@ -709,19 +708,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     auto load_entry = [&](unsigned i) {
         if (i >= count) return 0ull;
         const unsigned en = i >> halves;
-        const int c = __popcll(__builtin_amdgcn_ballot_w64(lane < FIX_RANGES && upto <= en));
-        const long long e = en + (long long)lane_bits((unsigned long long)list_skew, c);
-        return lane < 4 ? gmem(P.fix_list)[4 * e + lane] : 0ull;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(upto <= en));
+        const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)skew, c) + (c < FIX_RANGES ? en : 0u - en);
+        return lane < 4 ? gmem(P.fix_list)[4ull * e + lane] : 0ull;
     };
-    const RkWeights rk = rk_weights(P.mode);
     const bool full = REC && (P.flags & KF_FULL_SELECTION) != 0;
     unsigned long long bad = 0, next = load_entry(at);
     WaveMost &M = scratch[wv].most;
     if (STEP && lane < 28) M[lane >> 2][lane & 3] = 0ull;
     const int ld = min(max(lane - H, 0), 57);  // (lanes outside repeat the first and last)
-    GridView v;
-    v.u0 = 0;
-    v.u1 = -1;
     auto flush = [&]() {
         wave_sync();
         unsigned long long mine = 0ull;
@@ -747,33 +742,36 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             unsigned long long tx = 0, tb = 0, tt = 0;  // faces with a top flux (full)
             next = load_entry(next_at);  // on its way while this one is worked on
             const long long unit = (long long)(where >> 28);
-            int lo = (int)(where >> 6) & 63, hi = (int)where & 63;  // lanes of its cells
+            const unsigned most = (unsigned)where & 63u, piece = (unsigned)(where >> 6) & 3u;
+            unsigned long long own = ((1ull << CELLS) - 1) << G;  // lanes of its cells
             if (full) {
-                const unsigned long long m = (2ull << hi) - (1ull << lo), mx = m | m >> 1;
-                tx = half_turn(fx) & mx;
-                tb = half_turn(fb) & m;
-                tt = half_turn(ft) & m;
-                fx &= mx;
-                fb &= m;
-                ft &= m;
+                own &= ((1ull << FIX_SPLIT) - 1) << (G + FIX_SPLIT * piece);
+                tx = half_turn(fx) & (own | own >> 1);
+                tb = half_turn(fb) & own;
+                tt = half_turn(ft) & own;
+            } else if (most) {
+                const unsigned before = mask_place(fx) + mask_place(fb) + mask_place(ft);
+                own &= __builtin_amdgcn_ballot_w64(before >= piece * most && ((where & FIX_LAST) || before < (piece + 1) * most));
             }
+            int lo = own ? (int)__builtin_ctzll(own) : 0, hi = own ? 63 - (int)__builtin_clzll(own) : 0;
             if (halves) {
                 const int mid = (lo + hi + 1) >> 1;
+                own &= half ? ~0ull << mid : ~(~0ull << mid);
                 lo = half ? mid : lo;
                 hi = half ? hi : mid - 1;
-                const unsigned long long m = (2ull << hi) - (1ull << lo);
-                fx &= m | m >> 1;
-                fb &= m;
-                ft &= m;
-                if (!(fx | fb | ft)) {
-                    at = next_at;
-                    next_at = at + stride;
-                    continue;
-                }
+            }
+            fx &= own | own >> 1;
+            fb &= own;
+            ft &= own;
+            if (!(fx | fb | ft)) {
+                at = next_at;
+                next_at = at + leap;
+                leap = 2 * stride - leap;
+                continue;
             }
             if (unit < v.u0 || unit >= v.u1) {
                 if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();
-                v = grid_view<ORDER, CH>(P, n_inst, unit);
+                enter(unit);
             }
             const int nx = v.nx, ny = v.ny;
             const long long plane = (long long)v.pitch * ny;
@@ -788,15 +786,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
 #pragma unroll
                     for (int c = 0; c < 4; ++c) S.dF[k][c][ld] = 0.0;
                     if ((m >> lane) & 1)
-                        S.face[nf + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] =
-                            (unsigned char)(k << 6 | lane);
+                        S.face[nf + mask_place(m)] = (unsigned char)(k << 6 | lane);
                 }
                 nf += __popcll(m);
             }
             // the cells, their top values on the way while the faces are selected
             const unsigned long long fixed = fx | (fx << 1) | fb | ft;
             const int xn = x0 - G + lane;
-            const bool cell = (!team || wv == 0) && ((fixed >> lane) & 1) && lane >= lo && lane <= hi && xn < nx;
+            const bool cell = (!team || wv == 0) && ((fixed & own) >> lane & 1) && xn < nx;
             GMEM double *out = v.out + (long long)j * v.pitch + xn;
             double Uc[4] = {0.0, 0.0, 0.0, 0.0};
             if (cell) {
@@ -804,33 +801,38 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                 for (int c = 0; c < 4; ++c) Uc[c] = out[c * plane];
             }
             sync();
-            auto line = [&](unsigned f) {
-                const int col = x0 - G + (int)(f & 63u);
-                return FixLine<Off>{f < 64u, f < 64u ? col - H : (f < 128u ? j - 1 : j) - H, j, col};
-            };
-            auto alpha = [&](bool x, int s) {
-                const double a0 = x ? v.rx[0] : v.ry[0], a1 = x ? v.rx[1] : v.ry[1], a2 = x ? v.rx[2] : v.ry[2];
-                return s == 0 ? a0 : (s == 3 ? a2 : a1);
-            };
+            // a window of the entry may cross the boundary
+            const bool edge = x0 - G + lo - G < 0 || x0 - G + hi + G >= nx || j - G < 0 || j + G >= ny;
+            const bool small = nx < NW || ny < NW;
+            const double *mem = scratch[wv].member;
 #pragma unroll 1
             for (int k0 = start; k0 < 4 * nf; k0 += step) {
                 const bool valid = k0 + lane < 4 * nf;
                 const int k = min(k0 + lane, 4 * nf - 1), s = k & 3;
                 const unsigned f = S.face[k >> 2], set = f >> 6;
                 const bool acoustic = CH && (s == 0 || s == 3);
-                const FixLine<Off> l = line(f);
-                const double a = alpha(l.x, s);
+                const bool ax = f < 64u;  // an x-face
+                const int col = x0 - G + (int)(f & 63u);
+                const int pos = (ax ? col : (f < 128u ? j - 1 : j)) - H;  // window node t is pos + t on the face's line
+                const double a = mem[(ax ? 0 : 4) + s];
                 // The four lanes of a face share its window: each loads a quarter of the nodes
                 // and projects them on all fields, and takes its field of the others' from LDS
                 // (every lane loading the whole window took twice as long, half of it in the
                 // loads).
                 constexpr int NPL = (NW + 3) / 4;
                 double Q[NPL][4];
-                l.template load<NW, NPL>(v, plane, s * NPL, Q);
+#pragma unroll
+                for (int i = 0; i < NPL; ++i) {
+                    int n = pos + min(s * NPL + i, NW - 1);
+                    if (edge) n = line_node(n, ax ? nx : ny, (ax ? v.bcx : v.bcy) == BC_PERIODIC, small);
+                    const Off o = 8 * ((Off)(ax ? j : n) * v.pitch + (ax ? n : col));
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) Q[i][c] = row_load(v.in + c * plane, o);
+                }
                 double U[NPL][4], F[NPL][4], hh[NPL];
 #pragma unroll
                 for (int i = 0; i < NPL; ++i) {
-                    const double rho = Q[i][0], m = l.x ? Q[i][1] : Q[i][2], n = l.x ? Q[i][2] : Q[i][1], E = Q[i][3];
+                    const double rho = Q[i][0], m = ax ? Q[i][1] : Q[i][2], n = ax ? Q[i][2] : Q[i][1], E = Q[i][3];
                     const double ir = rcp_nr(rho), u = m * ir, w = n * ir;
                     const double p = node_pressure(rho, u, w, E, P.gm1);
                     U[i][0] = rho;
@@ -850,9 +852,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                     // nodes H and H + 1 from the lanes that hold them
                     constexpr int iL = H % NPL, iR = (H + 1) % NPL;
                     constexpr int fromL = 0x55 * (H / NPL), fromR = 0x55 * ((H + 1) / NPL);  // quad_perm broadcasts
-                    ro = roe_state(sqrt_nr(dpp_move<fromL>(Q[iL][0])), dpp_move<fromL>(Q[iL][1]), dpp_move<fromL>(Q[iL][2]),
-                                   dpp_move<fromL>(hh[iL]), sqrt_nr(dpp_move<fromR>(Q[iR][0])), dpp_move<fromR>(Q[iR][1]),
-                                   dpp_move<fromR>(Q[iR][2]), dpp_move<fromR>(hh[iR]), P.gm1);
+                    double sL, sR;
+                    if constexpr (fromL != fromR) {  // (one root in every lane, of the node it has)
+                        const double root = sqrt_nr(s <= H / NPL ? Q[iL][0] : Q[iR][0]);
+                        sL = quad_move<fromL>(root);
+                        sR = quad_move<fromR>(root);
+                    } else {
+                        sL = sqrt_nr(quad_move<fromL>(Q[iL][0]));
+                        sR = sqrt_nr(quad_move<fromR>(Q[iR][0]));
+                    }
+                    ro = roe_state(sL, quad_move<fromL>(Q[iL][1]), quad_move<fromL>(Q[iL][2]), quad_move<fromL>(hh[iL]), sR,
+                                   quad_move<fromR>(Q[iR][1]), quad_move<fromR>(Q[iR][2]), quad_move<fromR>(hh[iR]), P.gm1);
                 }
                 // windows g+ and g- = P F +- a P U; a lane's columns are rotated by its place in
                 // the quad, so the four writes of an instruction fall in different banks
@@ -891,22 +901,21 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                 const double hm = R::select_step(gm, sd, sm, tm);
                 if (REC && v.sel && valid) {
                     const long long xb = (long long)ny * (nx + 1), yb = (long long)(ny + 1) * nx;
-                    const long long o = l.x ? 2 * s * xb + (long long)l.row * (nx + 1) + l.col + 1
-                                            : 8 * xb + 2 * s * yb + (long long)(set == 1u ? l.row : l.row + 1) * nx + l.col;
+                    const long long o = ax ? 2 * s * xb + (long long)j * (nx + 1) + col + 1
+                                            : 8 * xb + 2 * s * yb + (long long)(set == 1u ? j : j + 1) * nx + col;
                     v.sel[o] = (uint8_t)sp;
-                    v.sel[o + (l.x ? xb : yb)] = (uint8_t)sm;
+                    v.sel[o + (ax ? xb : yb)] = (uint8_t)sm;
                 }
-                // R de, summed over the face's four lanes; lane s stores component s
+                // R times the four lanes' fields; lane s stores component s
                 double es = fma(a, pu[H] - pu[H + 1], hp + hm);
                 if (full && (((set == 0u ? tx : (set == 1u ? tb : tt)) >> (f & 63u)) & 1)) es = (hp - tp) + (hm - tm);  // (zero)
                 es *= acoustic ? 0.25 : 0.5;
                 double d = es;
                 if constexpr (CH) {
-                    const double e[4] = {s == 0 ? es : 0.0, s == 1 ? es : 0.0, s == 2 ? es : 0.0, s == 3 ? es : 0.0};
+                    const double e[4] = {quad_move<0x00>(es), quad_move<0x55>(es), quad_move<0xaa>(es), quad_move<0xff>(es)};
                     double r[4];
                     back_project<4>(ro, e, r);
-                    const double d0 = quad_sum(r[0]), d1 = quad_sum(r[1]), d2 = quad_sum(r[2]), d3 = quad_sum(r[3]);
-                    d = s == 0 ? d0 : (s == 1 ? d1 : (s == 2 ? d2 : d3));
+                    d = s == 0 ? r[0] : (s == 1 ? r[1] : (s == 2 ? r[2] : r[3]));
                 }
                 if (valid) S.dF[set][s][(f & 63u) - H] = d;
             }
@@ -916,15 +925,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             m.reset();
             if (cell) {
                 const int perm[4] = {0, 2, 1, 3};
+                const double idx = mem[8], idy = mem[9], c = mem[10];
                 double U[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const double lx = -(S.dF[0][c][ld] - S.dF[0][c][ld - 1]) * v.idx;
-                    const double dL = lx - (S.dF[2][perm[c]][ld] - S.dF[1][perm[c]][ld]) * v.idy;
-                    U[c] = STEP ? fma(rk.y * v.dt, dL, Uc[c]) : Uc[c] + dL;
-                    out[c * plane] = U[c];
+                for (int q = 0; q < 4; ++q) {
+                    const double lx = -(S.dF[0][q][ld] - S.dF[0][q][ld - 1]) * idx;
+                    const double dL = lx - (S.dF[2][perm[q]][ld] - S.dF[1][perm[q]][ld]) * idy;
+                    U[q] = STEP ? fma(c, dL, Uc[q]) : Uc[q] + dL;
+                    out[q * plane] = U[q];
                 }
-                if (STEP) m.add(U, P.gamma, v.idx, v.idy);
+                if (STEP) m.add(U, P.gamma, idx, idy);
                 b = m.bad != 0;
             }
             if (STEP && (!team || wv == 0)) {
@@ -932,15 +942,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
 #pragma unroll
                 for (int i = 0; i < 7; ++i) {
                     // a quad's maximum (a whole wave's over DPP would take twice as long)
-                    double x = fmax(m.v[i], dpp_move<0xb1>(m.v[i]));
-                    x = fmax(x, dpp_move<0x4e>(x));
+                    double x = fmax(m.v[i], quad_move<0xb1>(m.v[i]));
+                    x = fmax(x, quad_move<0x4e>(x));
                     if ((lane & 3) == 0)
                         __hip_atomic_fetch_max(&M[i][(lane >> 2) & 3], as_bits(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 }
             }
             sync();
             at = next_at;
-            next_at = at + stride;
+            next_at = at + leap;
+            leap = 2 * stride - leap;
         }
     }
     if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();

@@ -81,12 +81,6 @@ struct LineLds {
 };
 constexpr unsigned LINE_FACE = 0x3f, LINE_CHOSEN = 0x80;
 
-// a lane's place among the lanes of a mask
-__device__ __forceinline__ unsigned mask_place(unsigned long long m)
-{
-    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-}
-
 // The segment's 64 Euler fluxes where every field takes its top candidate on both sides:
 // the flux is linear in the window (TopStencil; R L = I, so the central part needs no
 // projection), Fhat = S F / 2 + R (kappa alpha L D_1 U) / 2.  One bound tells nearly all
@@ -659,7 +653,8 @@ __global__ void reset_maxima(KParams P, int words)
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n * words; k += gridDim.x * blockDim.x)
         gmem(P.inst[k / words].amax)[k % words] = 0ull;
     if (P.fix_count && blockIdx.x == 0)
-        for (int k = threadIdx.x; k < FIX_SETS * FIX_RANGES; k += blockDim.x) gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = 0u;
+        for (int k = threadIdx.x; k < FIX_SETS * FIX_RANGES; k += blockDim.x)
+            gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = fix_empty(P, n, P.hdr->units_total, k % FIX_RANGES);
 }
 
 // What precedes the maxima of a lone member's state, in one launch: the caller's
@@ -682,7 +677,8 @@ __global__ void begin_lone(KParams P, Inst *inst, const double *u, double *lx, C
     }
     for (int k = t; k < words; k += blockDim.x) gmem(P.lone_amax)[k] = 0ull;
     if (P.fix_count)
-        for (int k = t; k < FIX_SETS * FIX_RANGES; k += blockDim.x) gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = 0u;
+        for (int k = t; k < FIX_SETS * FIX_RANGES; k += blockDim.x)
+            gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = fix_empty(P, 1, P.hdr->units_total, k % FIX_RANGES);
 }
 
 // Time-step control of one instance: CFL (or fixed) step from the maxima m of

@@ -37,10 +37,10 @@ struct KParams {
     // a lone member's control block and maxima (null: per descriptor)
     Ctrl *lone_ctrl;
     unsigned long long *lone_amax;
-    // 2D stages: the lists of row segments that need a selection, their counters (zero
-    // at launch) and the set zeroed for a later launch (null: none)
+    // 2D stages: the lists of row segments that need a selection, their counters (fix_empty
+    // at launch) and the set that is emptied for the next stage (null: none)
     unsigned long long *fix_list;
-    unsigned *fix_count, *fix_zero;
+    unsigned long long *fix_count, *fix_zero;
 };
 
 // every face takes the full selection (no wave-uniform shortcut); results are

@@ -68,6 +68,31 @@ __device__ __forceinline__ int find_inst(const Inst *inst, int n, long long unit
     return lo;
 }
 
+// units per range of the lists (a launch has fewer than 2^32)
+__device__ __forceinline__ unsigned fix_range_units(long long units)
+{
+    return max(1u, ((unsigned)units + FIX_RANGES - 1) / FIX_RANGES);
+}
+
+// first place of the list of the units from `unit` on (their number: the end of the last
+// list): every strip row before it has its places
+__device__ __forceinline__ unsigned fix_list_start(const KParams &P, int n_inst, long long unit)
+{
+    const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst(P.inst, n_inst, unit)];
+    const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
+    const unsigned low = (unsigned)I.low_rows, extra = (unsigned)I.extra_rows;
+    const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);
+    return (unsigned)(I.list0 + fix_places(I.nx) * ((long long)I.strips * y0 + (long long)s * rows));
+}
+
+// a range's counter while its list is empty: the list's start and end
+__device__ __forceinline__ unsigned long long fix_empty(const KParams &P, int n_inst, long long units, unsigned range)
+{
+    const unsigned per = fix_range_units(units);
+    const unsigned from = fix_list_start(P, n_inst, min(units, (long long)range * per));
+    return (unsigned long long)fix_list_start(P, n_inst, min(units, (long long)(range + 1) * per)) << 32 | from;
+}
+
 // value of the neighbouring lane (lane 0 / 63 keep their own)
 template <int CTRL> __device__ __forceinline__ double dpp_move(double x)
 {
@@ -80,11 +105,20 @@ template <int CTRL> __device__ __forceinline__ double dpp_move(double x)
 __device__ __forceinline__ double lane_prev(double x) { return dpp_move<0x138>(x); }  // wave_shr:1
 __device__ __forceinline__ double lane_next(double x) { return dpp_move<0x130>(x); }  // wave_shl:1
 
-// sum over the four lanes of a quad, the same in each
-__device__ __forceinline__ double quad_sum(double x)
+// value of another lane of the quad (every lane has one: no old value to keep)
+template <int PERM> __device__ __forceinline__ double quad_move(double x)
 {
-    const double y = x + dpp_move<0xb1>(x);  // quad_perm 1, 0, 3, 2
-    return y + dpp_move<0x4e>(y);            // quad_perm 2, 3, 0, 1
+    union { double d; int w[2]; } a, b;
+    a.d = x;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) b.w[i] = __builtin_amdgcn_mov_dpp(a.w[i], PERM, 0xf, 0xf, false);
+    return b.d;
+}
+
+// a lane's place among the lanes of a mask
+__device__ __forceinline__ unsigned mask_place(unsigned long long m)
+{
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
 // lane i's value, in scalar registers
