@@ -556,7 +556,7 @@ struct Runtime {
         if (eq == EULER2D) {
             // a workgroup per listed row at most (a pool's rows change between steps)
             long long most = 0;
-            for (const Inst &I : h_inst) most += 4ll * I.strips * I.ny;  // (two pieces of two halves a row)
+            for (const Inst &I : h_inst) most += 2ll * fix_places(I.nx) * I.strips * I.ny;  // (pieces of two halves)
             if (dynamic || h_inst.empty()) most = 1ll << 30;
             grid_fix = (int)std::min<long long>(most, (long long)cus * occupancy_fix_2d(order, M_S2, false, ch));
         }
@@ -1554,8 +1554,9 @@ enoao_status enoao_pool_create(const enoao_problem *like, int32_t max_members, s
     const size_t o_ctrl = take(sizeof(Ctrl) * max_members);
     const size_t o_amax = take(8ull * r.amax_words() * max_members);
     const size_t o_fixc = take(FIX_SETS * FIX_SET_WORDS * 8);
-    // (a member of ny rows and s strips is charged at least 128 ny max(16, 54 (s - 1)) bytes
-    // of the arena, and its list takes at most 128 s ny)
+    // (a member of ny rows is charged 128 bytes of the arena for each column of its pitch and
+    // row, and its list takes 32 for each place: one for ten columns of a strip or fewer, six
+    // for each strip of 54 or more)
     const size_t o_fix = take(r.eq == EULER2D ? arena_bytes / 16 + 256 : 0);
     const size_t o_arena = take(enoao_pool::held(r, arena_bytes));
     if (hipMalloc(&r.d_block, off) != hipSuccess) {

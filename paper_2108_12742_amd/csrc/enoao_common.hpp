@@ -34,8 +34,8 @@ constexpr int strip_cells(int order) { return order == 7 ? 54 : 56; }
 // passes, from the list's start on, its high half those of one, from the end back.  Four
 // sets of counters, three used in turn by the stages of a step, the fourth by an
 // evaluation of L.
-constexpr int FIX_SPLIT = 14, FIX_FACES = 32, FIX_PASS = 16;
-constexpr int fix_places(int nx) { return nx > 3 * FIX_SPLIT ? 4 : (nx + FIX_SPLIT - 1) / FIX_SPLIT; }  // per strip and row
+constexpr int FIX_SPLIT = 10, FIX_FACES = 32, FIX_PASS = 16;
+constexpr int fix_places(int nx) { return nx > 5 * FIX_SPLIT ? 6 : (nx + FIX_SPLIT - 1) / FIX_SPLIT; }  // per strip and row
 constexpr int FIX_ENTRY_BYTES = 32, FIX_RANGES = 32, FIX_COUNTER_STRIDE = 8;
 constexpr int FIX_SET_WORDS = FIX_RANGES * FIX_COUNTER_STRIDE, FIX_SETS = 4;
 constexpr int BLOCK = 256;

@@ -291,7 +291,7 @@ __device__ __forceinline__ void top_flux(const RoeState &r, const double (&sF)[4
 // A piece has the cells with as many of these faces before them as its number and that
 // size say; fix_2d cuts it out.  Where every face is listed a piece has FIX_SPLIT
 // cells, and the lanes that hold a top flux are marked once more, half a turn on.
-constexpr unsigned FIX_LAST = 1u << 8;
+constexpr unsigned FIX_LAST = 1u << 9;
 __device__ __forceinline__ unsigned long long half_turn(unsigned long long m) { return m << 32 | m >> 32; }
 struct FixEntry {
     unsigned long long where, x, below, above;
@@ -534,8 +534,11 @@ __attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
                     const int faces = __popcll(fail_x) + __popcll(fail_b) + __popcll(fail_t), places = fix_places(nx);
                     // pieces of `most` faces, a cell's three more and the one on its left again
                     constexpr int MOST = FIX_FACES - 3;
-                    int pieces = min(places, 1 + (faces > FIX_FACES) + (faces > 2 * MOST) + (faces > 3 * MOST));
-                    int most = max(MOST, pieces == 4 ? (faces + 3) >> 2 : (pieces == 3 ? (faces + 2) / 3 : (faces + 1) >> 1));
+                    int pieces = min(places, 1 + (faces > FIX_FACES) + (faces > 2 * MOST) + (faces > 3 * MOST) +
+                                                 (faces > 4 * MOST) + (faces > 5 * MOST));
+                    // (a narrow grid's row of n cells has 3 n + 1 faces at most)
+                    static_assert(6 * MOST >= 3 * CELLS + 1 && FIX_SPLIT == 10, "places of a row");
+                    int most = faces > MOST * pieces ? MOST + 2 : MOST;
                     int rest = faces - (pieces - 1) * most;  // (about: the last one's)
                     unsigned long long x = fail_x, b = fail_b, t = fail_t;
                     if (full) {
@@ -558,7 +561,7 @@ __attribute__((amdgpu_waves_per_eu(STAGE_WAVES))) void stage_2d(KParams P)
                     }
                     n_two += pieces - one;
                     n_one += one;
-                    if (n_two + n_one > PENDING - 4) flush_pending(unit);
+                    if (n_two + n_one > PENDING - 6) flush_pending(unit);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 const int perm[4] = {0, 2, 1, 3};
@@ -660,12 +663,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     GridView v;
     v.u0 = 0;
     v.u1 = -1;
+    unsigned long long seen = 0ull;  // lane: value lane % AMAX_VALS of copy lane / AMAX_VALS
     auto enter = [&](long long unit) {
         v = grid_view<ORDER, CH>(P, n_inst, unit);
         // (in LDS: the loops below run out of scalar registers)
         double x = lane < 4 ? field_alpha(v.rx, lane) : field_alpha(v.ry, lane & 3);
         x = lane < 8 ? x : (lane == 8 ? v.idx : (lane == 9 ? v.idy : rk_weights(P.mode).y * v.dt));
         if (lane < 11) scratch[wv].member[lane] = x;
+        // what stage_2d has left in the maxima already: most waves have no more to add
+        // (thousands of atomics on a few lines at a launch's end, 20 ns each)
+        if (STEP) seen = v.amax[P.r_out * amax_slot_words(EULER2D) + lane];
     };
     // lane c: list c's pieces of two passes, lane FIX_RANGES + c: those of one; upto: the
     // entries up to them.  Entry i of all is at skew + i, counted back among those of one.
@@ -679,11 +686,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     const unsigned list_end = two ? (unsigned)empty : (unsigned)(empty >> 32);
     unsigned upto = two ? (unsigned)counted - list_end : list_end - (unsigned)(counted >> 32);
     const unsigned mine_n = upto;
-#pragma unroll
-    for (int o = 1; o < 64; o *= 2) {
-        const unsigned x = __shfl_up(upto, o, 64);
-        upto += lane >= o ? x : 0u;
-    }
+    upto = wave_scan(upto);
     const unsigned entries = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
     if (entries == 0) return;
     const unsigned skew = two ? list_end - (upto - mine_n) : list_end - 1 + (upto - mine_n);
@@ -717,20 +720,28 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     WaveMost &M = scratch[wv].most;
     if (STEP && lane < 28) M[lane >> 2][lane & 3] = 0ull;
     const int ld = min(max(lane - H, 0), 57);  // (lanes outside repeat the first and last)
-    auto flush = [&]() {
+    // the maxima of the waves w0 .. w1 - 1 into the member's
+    auto flush = [&](int w0, int w1) {
         wave_sync();
         unsigned long long mine = 0ull;
         if (lane < 7) {
+            for (int w = w0; w < w1; ++w) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                mine = max(mine, M[lane][i]);
-                M[lane][i] = 0ull;
+                for (int i = 0; i < 4; ++i) {
+                    mine = max(mine, scratch[w].most[lane][i]);
+                    scratch[w].most[lane][i] = 0ull;
+                }
             }
         }
         wave_sync();
-        if (lane < 7)
+        double most = as_double(seen);
+#pragma unroll
+        for (int o = AMAX_VALS; o < 64; o *= 2) most = fmax(most, __shfl_xor(most, o, 64));
+        if (lane < 7 && mine > as_bits(most))
             __hip_atomic_fetch_max(&v.amax[P.r_out * amax_slot_words(EULER2D) + blockIdx.x % amax_copies(EULER2D) * AMAX_VALS + lane],
                                    mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto flag = [&]() {
         if (bad && lane == 0) __hip_atomic_fetch_or(&v.ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bad = 0;
     };
@@ -742,7 +753,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             unsigned long long tx = 0, tb = 0, tt = 0;  // faces with a top flux (full)
             next = load_entry(next_at);  // on its way while this one is worked on
             const long long unit = (long long)(where >> 28);
-            const unsigned most = (unsigned)where & 63u, piece = (unsigned)(where >> 6) & 3u;
+            const unsigned most = (unsigned)where & 63u, piece = (unsigned)(where >> 6) & 7u;
             unsigned long long own = ((1ull << CELLS) - 1) << G;  // lanes of its cells
             if (full) {
                 own &= ((1ull << FIX_SPLIT) - 1) << (G + FIX_SPLIT * piece);
@@ -770,7 +781,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                 continue;
             }
             if (unit < v.u0 || unit >= v.u1) {
-                if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();
+                if (STEP && v.u1 >= 0 && (!team || wv == 0)) {
+                    flush(wv, wv + 1);
+                    flag();
+                }
                 enter(unit);
             }
             const int nx = v.nx, ny = v.ny;
@@ -954,7 +968,21 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             leap = 2 * stride - leap;
         }
     }
-    if (STEP && v.u1 >= 0 && (!team || wv == 0)) flush();
+    if constexpr (STEP) {
+        // (together where the waves end in one member, as in stage_2d)
+        __shared__ int ended[NWV];
+        if (lane == 0) ended[wv] = v.u1 >= 0 ? v.k : -1;
+        flag();
+        __syncthreads();
+        int first = NWV;
+        bool same = true;
+#pragma unroll
+        for (int w = NWV - 1; w >= 0; --w) {
+            same = same && (ended[w] == v.k || ended[w] < 0);
+            first = ended[w] >= 0 ? w : first;
+        }
+        if (v.u1 >= 0 && (same ? wv == first : true)) flush(same ? 0 : wv, same ? NWV : wv + 1);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -74,11 +74,10 @@ __device__ __forceinline__ unsigned fix_range_units(long long units)
     return max(1u, ((unsigned)units + FIX_RANGES - 1) / FIX_RANGES);
 }
 
-// first place of the list of the units from `unit` on (their number: the end of the last
-// list): every strip row before it has its places
-__device__ __forceinline__ unsigned fix_list_start(const KParams &P, int n_inst, long long unit)
+// first place of the list of a member's units from `unit` on (the end of the last: the
+// member's end): every strip row before it has its places
+__device__ __forceinline__ unsigned fix_list_start(const Inst &I, long long unit)
 {
-    const Inst &I = P.inst[P.lone_ctrl ? 0 : find_inst(P.inst, n_inst, unit)];
     const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
     const unsigned low = (unsigned)I.low_rows, extra = (unsigned)I.extra_rows;
     const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);
@@ -89,8 +88,16 @@ __device__ __forceinline__ unsigned fix_list_start(const KParams &P, int n_inst,
 __device__ __forceinline__ unsigned long long fix_empty(const KParams &P, int n_inst, long long units, unsigned range)
 {
     const unsigned per = fix_range_units(units);
-    const unsigned from = fix_list_start(P, n_inst, min(units, (long long)range * per));
-    return (unsigned long long)fix_list_start(P, n_inst, min(units, (long long)(range + 1) * per)) << 32 | from;
+    const long long u0 = min(units, (long long)range * per), u1 = min(units, (long long)(range + 1) * per);
+    unsigned from, to;
+    if (P.lone_ctrl) {
+        from = fix_list_start(P.inst[0], u0);
+        to = fix_list_start(P.inst[0], u1);
+    } else {
+        from = fix_list_start(P.inst[find_inst(P.inst, n_inst, u0)], u0);
+        to = fix_list_start(P.inst[find_inst(P.inst, n_inst, u1)], u1);
+    }
+    return (unsigned long long)to << 32 | from;
 }
 
 // value of the neighbouring lane (lane 0 / 63 keep their own)
@@ -113,6 +120,18 @@ template <int PERM> __device__ __forceinline__ double quad_move(double x)
 #pragma unroll
     for (int i = 0; i < 2; ++i) b.w[i] = __builtin_amdgcn_mov_dpp(a.w[i], PERM, 0xf, 0xf, false);
     return b.d;
+}
+
+// sum of the lanes up to each
+__device__ __forceinline__ unsigned wave_scan(unsigned x)
+{
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return x;
 }
 
 // a lane's place among the lanes of a mask
