@@ -25,9 +25,9 @@
 // others, and they lie along shocks, so a wave that met them in its strip worked
 // several times as long as its neighbours: selecting inside stage_2d took 0.10 ms
 // of a 0.23 ms stage for 15% more instructions, and the selection's registers
-// spilled the row loop's.  stage_2d therefore lists the row segments that hold such
+// spilled the row loop's.  stage_2d therefore lists the rows of a strip that hold such
 // faces and gives those faces the mean (F_j + F_j+1) / 2 of their own two nodes; fix_2d
-// spreads the listed rows over the machine, selects, one lane per face and field, and
+// spreads pieces of the listed rows over the machine, selects, one lane per face and field, and
 // adds what the chosen candidates have beyond the mean to the cells: U += c dt dL.  The
 // mean, and not the top flux: the top candidate was left out because its window crosses
 // a jump, it is as large as the jump's far side, and the cells of the near side kept
@@ -127,8 +127,7 @@ __device__ __forceinline__ GridView grid_view(const KParams &P, int n_inst, long
     }
     v.idx = uniform(1.0 / I.dx);
     v.idy = uniform(1.0 / I.dy);
-#pragma unroll
-    for (int o = AMAX_VALS; o < 64; o *= 2) am = fmax(am, __shfl_xor(am, o, 64));
+    am = copies_max(am);
     double ax[3], ay[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -626,7 +625,8 @@ using WaveMost = unsigned long long[7][4];
 template <int NW> struct FixScratch {
     double dF[3][4][58];       // fluxes beyond the mean by set (x, below, above) and lane from H on
     double exchange[NW][64];   // window values by node and (face, field)
-    double member[12];         // the member's alpha along x and along y by field, 1/dx, 1/dy, the weight of dL
+    double member[20];         // the member's alpha along x and along y by field, 1/dx, 1/dy, the weight of dL; the
+                               // maxima of its new state so far, from 12 on
     unsigned char face[176];   // set << 6 | lane of each face
     WaveMost most;             // the wave's maxima, in four parts
 };
@@ -642,14 +642,21 @@ __device__ __forceinline__ int line_node(int k, int n, bool periodic, bool small
 // alpha of field s from those of u-c, u, u+c
 __device__ __forceinline__ double field_alpha(const double (&r)[3], int s) { return s == 0 ? r[0] : (s == 3 ? r[2] : r[1]); }
 
-// A wave takes one listed row segment at a time (handing them out from a counter took
+// A wave takes one listed piece of a row at a time (handing them out from a counter took
 // longer than the imbalance it removed, 20 ns each); where the list is short, the four
-// waves of a workgroup share a segment, and halves of segments go to different ones.
+// waves of a workgroup share a piece, and halves of pieces go to different ones.
 // Four lanes per face, one per field, for the selection, one lane per cell for the
 // update.  stage_2d gave the mean of the fluxes of the face's two nodes; a field
 // contributes alpha l.(U_j - U_j+1) / 2 and what its chosen candidates have beyond the
-// two nodes.  Bound by its instructions (VALU issue 0.86
-// of the cycles at 2048^2): about 450 a pass of sixteen faces and 300 an entry.
+// two nodes.
+// A pass of sixteen faces takes a SIMD about 1 us however many waves are on it, so the
+// launch lasts as long as its fullest SIMD: pieces of whole rows of one to eleven passes
+// left 14 on one beside 9.4 on average (56 x 1532); pieces of one or two, those of two
+// dealt first, leave 9.  The member's values come beside the lists' counters, and a wave
+// adds to the member's maxima only what exceeds stage_2d's.  With that, and 430 VALU
+// instructions a pass instead of 570, before and now (us, same card): 1000 x 60, six
+// steps, 611 and 520; order 7 on 60 x 1200 829 and 754; 511 x 257, ten, 1060 and 904;
+// 2048^2, eight, 4100 and 3930; a pool of 16 4610 and 4140.
 template <int ORDER, bool STEP, bool REC, bool CH>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves(ORDER)))) void fix_2d(KParams P)
 {
@@ -663,7 +670,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     GridView v;
     v.u0 = 0;
     v.u1 = -1;
-    unsigned long long seen = 0ull;  // lane: value lane % AMAX_VALS of copy lane / AMAX_VALS
     auto enter = [&](long long unit) {
         v = grid_view<ORDER, CH>(P, n_inst, unit);
         // (in LDS: the loops below run out of scalar registers)
@@ -672,7 +678,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
         if (lane < 11) scratch[wv].member[lane] = x;
         // what stage_2d has left in the maxima already: most waves have no more to add
         // (thousands of atomics on a few lines at a launch's end, 20 ns each)
-        if (STEP) seen = v.amax[P.r_out * amax_slot_words(EULER2D) + lane];
+        if (STEP) {
+            const double seen = copies_max(as_double(v.amax[P.r_out * amax_slot_words(EULER2D) + lane]));
+            if (lane < AMAX_VALS) scratch[wv].member[12 + lane] = seen;
+        }
     };
     // lane c: list c's pieces of two passes, lane FIX_RANGES + c: those of one; upto: the
     // entries up to them.  Entry i of all is at skew + i, counted back among those of one.
@@ -698,10 +707,40 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     const bool team = entries <= gridDim.x;
     const unsigned halves = 2 * entries <= (team ? gridDim.x : waves) ? 1u : 0u;
     const unsigned count = entries << halves;
-    // There and back: who has the longest of one round has the shortest of the next.
-    const unsigned stride = team ? gridDim.x : waves, first = team ? blockIdx.x : blockIdx.x * NWV + wv;
-    const unsigned turn = 2 * stride - 1 - 2 * first;  // from a round's entry to the next round's, and 2 stride - turn
-    unsigned at = first, next_at = at + turn, leap = 2 * stride - turn;
+    // A lone member's entries go round by round, there and back: who has the longest of one
+    // round has the shortest of the next.  Several members': each wave (or workgroup) takes
+    // neighbouring entries, mostly of one member, whose values take 2 us to load (a served
+    // run: 4.65e9 cell-updates/s round by round, 5.1e9 so); as many of two passes as any
+    // other to within one, entries of one pass first in their stead where there is one
+    // fewer, then as many as any other.
+    const unsigned sharers = team ? gridDim.x : waves, mine = team ? blockIdx.x : blockIdx.x * NWV + wv;
+    unsigned at, to = 0, jump, end = 0;  // the entry; lone: jump, the way to the next; else: its last of two passes
+                                         // but one is jump, the first and the last but one of one pass
+    if (P.lone_ctrl) {
+        at = mine;
+        jump = 2 * sharers - 1 - 2 * mine;
+    } else {
+        const unsigned n_two = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1) << halves, n_one = count - n_two;
+        const unsigned each = n_two / sharers, more = n_two - each * sharers, fewer = sharers - more;
+        const bool few = n_one <= 2 * fewer;  // one-pass entries: all in the stead of others
+        const unsigned d = few ? fewer : sharers, rest = few ? n_one : n_one - 2 * fewer, k = few ? mine - more : sharers - 1 - mine;
+        const unsigned each1 = rest / d, more1 = rest - each1 * d;
+        const unsigned twos = each + (mine < more ? 1u : 0u);
+        const unsigned ones = few && mine < more ? 0u : each1 + (k < more1 ? 1u : 0u) + (few || mine < more ? 0u : 2u);
+        jump = mine * each + min(mine, more) + twos;
+        to = ones ? n_two + k * each1 + min(k, more1) + (few ? 0u : 2 * min(k, fewer)) : count;
+        end = to + ones;
+        at = twos ? jump - twos : to;
+    }
+    auto advance = [&]() {
+        if (P.lone_ctrl) {
+            at += jump;
+            jump = 2 * sharers - jump;
+        } else {
+            ++at;
+            at = at == jump ? to : (at == end ? count : at);
+        }
+    };
     FixScratch<NW> &S = scratch[team ? 0 : wv];
     const int start = team ? 64 * wv : 0, step = team ? BLOCK : 64;
     auto sync = [&]() {
@@ -723,23 +762,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     // the maxima of the waves w0 .. w1 - 1 into the member's
     auto flush = [&](int w0, int w1) {
         wave_sync();
-        unsigned long long mine = 0ull;
+        unsigned long long most = 0ull;
         if (lane < 7) {
             for (int w = w0; w < w1; ++w) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    mine = max(mine, scratch[w].most[lane][i]);
+                    most = max(most, scratch[w].most[lane][i]);
                     scratch[w].most[lane][i] = 0ull;
                 }
             }
         }
         wave_sync();
-        double most = as_double(seen);
-#pragma unroll
-        for (int o = AMAX_VALS; o < 64; o *= 2) most = fmax(most, __shfl_xor(most, o, 64));
-        if (lane < 7 && mine > as_bits(most))
+        if (lane < 7 && most > as_bits(scratch[wv].member[12 + lane]))
             __hip_atomic_fetch_max(&v.amax[P.r_out * amax_slot_words(EULER2D) + blockIdx.x % amax_copies(EULER2D) * AMAX_VALS + lane],
-                                   mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                   most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     auto flag = [&]() {
         if (bad && lane == 0) __hip_atomic_fetch_or(&v.ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -751,7 +787,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             unsigned long long fx = lane_bits(next, 1), fb = lane_bits(next, 2), ft = lane_bits(next, 3);
             const unsigned half = at & halves;
             unsigned long long tx = 0, tb = 0, tt = 0;  // faces with a top flux (full)
-            next = load_entry(next_at);  // on its way while this one is worked on
+            advance();
+            next = load_entry(at);  // on its way while this one is worked on
             const long long unit = (long long)(where >> 28);
             const unsigned most = (unsigned)where & 63u, piece = (unsigned)(where >> 6) & 7u;
             unsigned long long own = ((1ull << CELLS) - 1) << G;  // lanes of its cells
@@ -774,12 +811,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             fx &= own | own >> 1;
             fb &= own;
             ft &= own;
-            if (!(fx | fb | ft)) {
-                at = next_at;
-                next_at = at + leap;
-                leap = 2 * stride - leap;
-                continue;
-            }
+            if (!(fx | fb | ft)) continue;
             if (unit < v.u0 || unit >= v.u1) {
                 if (STEP && v.u1 >= 0 && (!team || wv == 0)) {
                     flush(wv, wv + 1);
@@ -963,9 +995,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
                 }
             }
             sync();
-            at = next_at;
-            next_at = at + leap;
-            leap = 2 * stride - leap;
         }
     }
     if constexpr (STEP) {

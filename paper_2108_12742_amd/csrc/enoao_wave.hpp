@@ -122,6 +122,29 @@ template <int PERM> __device__ __forceinline__ double quad_move(double x)
     return b.d;
 }
 
+// maximum over the lanes whose numbers agree in the last three bits (the copies of a maxima slot)
+__device__ __forceinline__ double copies_max(double x)
+{
+    static_assert(AMAX_VALS == 8, "a lane's value is its number's last three bits");
+    x = fmax(x, dpp_move<0x128>(x));  // row_ror:8
+    union { double d; unsigned w[2]; } a, lo, hi;
+    a.d = x;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a.w[i], a.w[i], false, false);  // even rows, odd rows
+        lo.w[i] = r[0];
+        hi.w[i] = r[1];
+    }
+    a.d = fmax(lo.d, hi.d);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a.w[i], a.w[i], false, false);  // the halves
+        lo.w[i] = r[0];
+        hi.w[i] = r[1];
+    }
+    return fmax(lo.d, hi.d);
+}
+
 // sum of the lanes up to each
 __device__ __forceinline__ unsigned wave_scan(unsigned x)
 {
