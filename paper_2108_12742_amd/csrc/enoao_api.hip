@@ -556,7 +556,7 @@ struct Runtime {
         if (eq == EULER2D) {
             // a workgroup per listed row at most (a pool's rows change between steps)
             long long most = 0;
-            for (const Inst &I : h_inst) most += 2ll * fix_places(I.nx) * I.strips * I.ny;  // (pieces of two halves)
+            for (const Inst &I : h_inst) most += 2ll * fix_places(I.nx) * I.strips * I.ny;  // (two for each piece: a team's rule)
             if (dynamic || h_inst.empty()) most = 1ll << 30;
             grid_fix = (int)std::min<long long>(most, (long long)cus * occupancy_fix_2d(order, M_S2, false, ch));
         }

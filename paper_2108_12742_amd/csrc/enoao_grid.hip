@@ -45,10 +45,10 @@
 
 namespace enoao {
 
-// Waves per SIMD of stage_2d: 255 registers at either order (order 7 spills two).
+// Waves per SIMD of stage_2d: 247 to 256 registers.
 constexpr int STAGE_WAVES = 2;
-// Waves per SIMD of fix_2d: as many as its LDS lets a CU hold (39 KB a workgroup at
-// order 5, 43 KB at order 7).
+// Waves per SIMD of fix_2d: as many as its LDS lets a CU hold (40 KB a workgroup at
+// order 5, 44 KB at order 7).
 constexpr int fix_waves(int order) { return order == 7 ? 3 : 4; }
 
 // p at a byte offset.  Offsets within a plane below 4 GiB take one 32-bit register
@@ -644,19 +644,19 @@ __device__ __forceinline__ double field_alpha(const double (&r)[3], int s) { ret
 
 // A wave takes one listed piece of a row at a time (handing them out from a counter took
 // longer than the imbalance it removed, 20 ns each); where the list is short, the four
-// waves of a workgroup share a piece, and halves of pieces go to different ones.
+// waves of a workgroup share a piece.
 // Four lanes per face, one per field, for the selection, one lane per cell for the
 // update.  stage_2d gave the mean of the fluxes of the face's two nodes; a field
 // contributes alpha l.(U_j - U_j+1) / 2 and what its chosen candidates have beyond the
 // two nodes.
 // A pass of sixteen faces takes a SIMD about 1 us however many waves are on it, so the
-// launch lasts as long as its fullest SIMD: pieces of whole rows of one to eleven passes
-// left 14 on one beside 9.4 on average (56 x 1532); pieces of one or two, those of two
-// dealt first, leave 9.  The member's values come beside the lists' counters, and a wave
-// adds to the member's maxima only what exceeds stage_2d's.  With that, and 430 VALU
-// instructions a pass instead of 570, before and now (us, same card): 1000 x 60, six
-// steps, 611 and 520; order 7 on 60 x 1200 829 and 754; 511 x 257, ten, 1060 and 904;
-// 2048^2, eight, 4100 and 3930; a pool of 16 4610 and 4140.
+// launch lasts as long as its fullest SIMD: pieces of one to five passes left 14 on one
+// beside 9.4 on average (56 x 1532); pieces of one or two, those of two dealt first, leave
+// 9.  The member's values come beside the lists' counters, and a wave adds to the member's
+// maxima only what exceeds stage_2d's.  With that, and 430 VALU instructions a pass instead
+// of 570, before and now (us, same card): 1000 x 60, six steps, 611 and 512; order 7 on
+// 60 x 1200 829 and 756; 511 x 257, ten, 1060 and 897; 2048^2, eight, 4100 and 3940; a pool
+// of 16 4610 and 4095.
 template <int ORDER, bool STEP, bool REC, bool CH>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves(ORDER)))) void fix_2d(KParams P)
 {
@@ -699,14 +699,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     const unsigned entries = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
     if (entries == 0) return;
     const unsigned skew = two ? list_end - (upto - mine_n) : list_end - 1 + (upto - mine_n);
-    // Few entries leave waves idle: workgroups share an entry, or halves of entries go to
-    // different workgroups or waves.  (128^2, a step: 94 us against 96 without the halves,
-    // 511 x 257, ten steps: 1040 against 1031; more and smaller pieces from the start cost a
-    // full machine 5 to 12%.)
+    // Few entries leave waves idle: the four waves of a workgroup share one, which pays up to
+    // an entry for two workgroups, at order 7, whose passes are longer, up to one for each
+    // (six steps, us with and without: 64^2 365 and 380, 100^2 391 and 381; order 7 64^2 392
+    // and 420, 100^2 406 and 415, 128^2, where there are more than workgroups, 427).
     const unsigned waves = gridDim.x * NWV;
-    const bool team = entries <= gridDim.x;
-    const unsigned halves = 2 * entries <= (team ? gridDim.x : waves) ? 1u : 0u;
-    const unsigned count = entries << halves;
+    const bool team = (ORDER == 7 ? 1 : 2) * entries <= gridDim.x;
     // A lone member's entries go round by round, there and back: who has the longest of one
     // round has the shortest of the next.  Several members': each wave (or workgroup) takes
     // neighbouring entries, mostly of one member, whose values take 2 us to load (a served
@@ -714,13 +712,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     // other to within one, entries of one pass first in their stead where there is one
     // fewer, then as many as any other.
     const unsigned sharers = team ? gridDim.x : waves, mine = team ? blockIdx.x : blockIdx.x * NWV + wv;
-    unsigned at, to = 0, jump, end = 0;  // the entry; lone: jump, the way to the next; else: its last of two passes
-                                         // but one is jump, the first and the last but one of one pass
+    unsigned at, jump;         // the entry; a lone member's: the way to the next
+    unsigned to = 0, end = 0;  // several members': at `jump` go on to `to`, where those of one pass begin, up to `end`
     if (P.lone_ctrl) {
         at = mine;
         jump = 2 * sharers - 1 - 2 * mine;
     } else {
-        const unsigned n_two = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1) << halves, n_one = count - n_two;
+        const unsigned n_two = (unsigned)__builtin_amdgcn_readlane((int)upto, FIX_RANGES - 1), n_one = entries - n_two;
         const unsigned each = n_two / sharers, more = n_two - each * sharers, fewer = sharers - more;
         const bool few = n_one <= 2 * fewer;  // one-pass entries: all in the stead of others
         const unsigned d = few ? fewer : sharers, rest = few ? n_one : n_one - 2 * fewer, k = few ? mine - more : sharers - 1 - mine;
@@ -728,7 +726,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
         const unsigned twos = each + (mine < more ? 1u : 0u);
         const unsigned ones = few && mine < more ? 0u : each1 + (k < more1 ? 1u : 0u) + (few || mine < more ? 0u : 2u);
         jump = mine * each + min(mine, more) + twos;
-        to = ones ? n_two + k * each1 + min(k, more1) + (few ? 0u : 2 * min(k, fewer)) : count;
+        to = ones ? n_two + k * each1 + min(k, more1) + (few ? 0u : 2 * min(k, fewer)) : entries;
         end = to + ones;
         at = twos ? jump - twos : to;
     }
@@ -738,7 +736,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             jump = 2 * sharers - jump;
         } else {
             ++at;
-            at = at == jump ? to : (at == end ? count : at);
+            at = at == jump ? to : (at == end ? entries : at);
         }
     };
     FixScratch<NW> &S = scratch[team ? 0 : wv];
@@ -748,10 +746,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
         else wave_sync();
     };
     auto load_entry = [&](unsigned i) {
-        if (i >= count) return 0ull;
-        const unsigned en = i >> halves;
-        const int c = __popcll(__builtin_amdgcn_ballot_w64(upto <= en));
-        const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)skew, c) + (c < FIX_RANGES ? en : 0u - en);
+        if (i >= entries) return 0ull;
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(upto <= i));
+        const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)skew, c) + (c < FIX_RANGES ? i : 0u - i);
         return lane < 4 ? gmem(P.fix_list)[4ull * e + lane] : 0ull;
     };
     const bool full = REC && (P.flags & KF_FULL_SELECTION) != 0;
@@ -781,11 +778,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
         if (bad && lane == 0) __hip_atomic_fetch_or(&v.ctrl->status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bad = 0;
     };
-    while (at < count) {
+    while (at < entries) {
         {
             const unsigned long long where = lane_bits(next, 0);
             unsigned long long fx = lane_bits(next, 1), fb = lane_bits(next, 2), ft = lane_bits(next, 3);
-            const unsigned half = at & halves;
             unsigned long long tx = 0, tb = 0, tt = 0;  // faces with a top flux (full)
             advance();
             next = load_entry(at);  // on its way while this one is worked on
@@ -800,13 +796,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             } else if (most) {
                 const unsigned before = mask_place(fx) + mask_place(fb) + mask_place(ft);
                 own &= __builtin_amdgcn_ballot_w64(before >= piece * most && ((where & FIX_LAST) || before < (piece + 1) * most));
-            }
-            int lo = own ? (int)__builtin_ctzll(own) : 0, hi = own ? 63 - (int)__builtin_clzll(own) : 0;
-            if (halves) {
-                const int mid = (lo + hi + 1) >> 1;
-                own &= half ? ~0ull << mid : ~(~0ull << mid);
-                lo = half ? mid : lo;
-                hi = half ? hi : mid - 1;
             }
             fx &= own | own >> 1;
             fb &= own;
@@ -848,6 +837,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
             }
             sync();
             // a window of the entry may cross the boundary
+            const int lo = (int)__builtin_ctzll(own), hi = 63 - (int)__builtin_clzll(own);
             const bool edge = x0 - G + lo - G < 0 || x0 - G + hi + G >= nx || j - G < 0 || j + G >= ny;
             const bool small = nx < NW || ny < NW;
             const double *mem = scratch[wv].member;
