@@ -393,10 +393,13 @@ __device__ __forceinline__ XCur x_next(XCur c, int per_row)
 // meets, before any tile (its values, the first loads, its maxima), as much as for
 // MEMBER_TILES tiles, so the list is cut evenly with that much added to every member.
 // (512 lines of 128 to 16384 nodes, a stage: 53 us uncharged, 41.3 at 2, 40.9 at 4, 46 at 8.)
+// With a workgroup for each tile there is nothing to even out, and the charge left workgroups
+// without a tile beside others with two (64 lines of 128 to 2500 nodes, ten steps: 521 us
+// charged, 382 not; from there to twice as many tiles it goes either way).
 constexpr int MEMBER_TILES = 4;
 __device__ __forceinline__ long long chunk_start(const Inst *inst, int n_inst, long long tiles, long long b, long long ng)
 {
-    if (n_inst == 1 || b == ng) return b * tiles / ng;
+    if (n_inst == 1 || b == ng || tiles <= ng) return b * tiles / ng;
     const long long x = b * (tiles + (long long)MEMBER_TILES * n_inst) / ng;
     const int lo = uniform(find_last(n_inst, x, [&](int k) { return inst[k].xtile0 + (long long)MEMBER_TILES * k; }));
     const long long t = inst[lo].xtile0;
