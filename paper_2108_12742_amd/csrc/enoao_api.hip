@@ -178,6 +178,7 @@ struct Runtime {
         int first, count;  // members res_order[first .. first + count)
         int block;         // threads per workgroup
         size_t lds;        // dynamic LDS bytes per workgroup
+        bool team;         // a workgroup's waves share the selections (rounds_shared)
     };
     std::vector<ResClass> res_classes;
     std::vector<hipStream_t> res_streams;  // classes after the first run on these, concurrently
@@ -432,7 +433,7 @@ struct Runtime {
                 return ENOAO_OK;
             }
             if (k != prev_k) {
-                res_classes.push_back({i, 0, block, lds});  // the first member of a class is its largest
+                res_classes.push_back({i, 0, block, lds, rounds_shared(ps[sorted[i]].nx)});  // the first member of a class is its largest
                 prev_k = k;
             }
             res_classes.back().count++;
@@ -451,6 +452,20 @@ struct Runtime {
         return ENOAO_OK;
     }
 
+    // Whether the waves of a resident workgroup share the selections of their segments, four
+    // a round (nx: the largest member's).  With a CU to each member its latency counts and
+    // sharing pays in a single round (100 steps, us shared and not: 126 nodes 1143 and 1545,
+    // 252 1097 and 1302; 100 lines to 250 nodes, ten steps, 240 and 260).  Each round ends
+    // with every wave's, so several cost more than they save (16 lines of 300 to 1500 nodes
+    // 434 and 367), but for a lone line whose last round is not a single segment's (300
+    // nodes 1792 and 1373, 400 1877 and 2032, 500 1878 and 2121, 567 2487 and 1964).  With
+    // more members than CUs the barriers cost more than they save (512: 537 and 479).
+    bool rounds_shared(long long nx) const
+    {
+        const long long segs = (nx + XW_CELLS - 1) / XW_CELLS, round = RES_BLOCK / 64;
+        return n <= cus && (segs <= round || (n == 1 && segs % round != 1));
+    }
+
     // k controlled steps of every member on the resident solver
     enoao_status resident_steps(int k, hipStream_t s)
     {
@@ -463,10 +478,7 @@ struct Runtime {
             if (c > 0) HIP_TRY(hipStreamWaitEvent(st, res_events[0], 0));
             KParams p = params(0, -1, -1);
             p.res_first = rc.first;
-            // with a CU to each member its latency counts, and the waves share the selections
-            // (128 nodes: 5.1 us a stage alone, 4.5 shared); with more, the barriers of the
-            // sharing cost more than it saves (512 members: 479 us alone, 537 shared)
-            HIP_TRY(launch_resident(eq, order, ch, n <= cus, rc.block, p, rc.count, k, rc.lds, st));
+            HIP_TRY(launch_resident(eq, order, ch, rc.team, rc.block, p, rc.count, k, rc.lds, st));
             if (c > 0) HIP_TRY(hipEventRecord(res_events[c], st));
         }
         for (size_t c = 1; c < res_classes.size(); ++c) HIP_TRY(hipStreamWaitEvent(s, res_events[c], 0));
