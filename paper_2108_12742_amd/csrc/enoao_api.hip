@@ -353,6 +353,7 @@ struct Runtime {
         h_hdr.n_inst = count;
         h_hdr.xtiles_total = xt;
         h_hdr.units_total = ut;
+        set_lists(h_inst, h_hdr);
         HIP_TRY(hipMemcpyAsync(d_hdr, &h_hdr, sizeof(BatchHdr), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipMemcpyAsync(d_inst, h_inst.data(), sizeof(Inst) * count, hipMemcpyHostToDevice, stream));
         std::vector<Ctrl> c0(count);
@@ -529,6 +530,21 @@ struct Runtime {
         I.list0 = list_places;
         list_places += (long long)I.strips * I.ny * fix_places(I.nx);
     }
+    // the ranges' lists: every strip row before a unit has its places
+    void set_lists(const std::vector<Inst> &members, BatchHdr &hdr) const
+    {
+        if (eq != EULER2D || members.empty()) return;
+        const long long per = fix_range_units(hdr.units_total);
+        size_t k = 0;
+        for (int r = 0; r <= FIX_RANGES; ++r) {
+            const long long unit = std::min(hdr.units_total, r * per);
+            while (k + 1 < members.size() && members[k + 1].unit0 <= unit) ++k;
+            const Inst &I = members[k];
+            const long long lu = unit - I.unit0, b = lu / I.strips, s = lu % I.strips;
+            const long long y0 = b * I.low_rows + std::min<long long>(b, I.extra_rows);
+            hdr.lists[r] = (unsigned)(I.list0 + fix_places(I.nx) * (I.strips * y0 + s * (I.low_rows + (b < I.extra_rows))));
+        }
+    }
     int strips_of(int nx) const { return (nx + strip_cells(order) - 1) / strip_cells(order); }
 
     // Rows per unit: as many units as the device holds waves of the stage kernel, so every
@@ -637,6 +653,7 @@ struct Runtime {
         long long ut = 0;
         for (int i = 0; i < n; ++i) set_units(h_inst[i], ut);
         h_hdr.units_total = ut;
+        set_lists(h_inst, h_hdr);
         HIP_TRY(hipMemcpyAsync(d_inst, h_inst.data(), sizeof(Inst) * n, hipMemcpyHostToDevice, s));
         HIP_TRY(hipMemcpyAsync(d_hdr, &h_hdr, sizeof(BatchHdr), hipMemcpyHostToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));  // the host copies are reused
@@ -993,6 +1010,7 @@ struct enoao_pool {
         r.h_hdr.n_inst = r.n;
         r.h_hdr.xtiles_total = xt;
         r.h_hdr.units_total = ut;
+        r.set_lists(r.h_inst, r.h_hdr);
         pin_cur ^= 1;
         HIP_TRY(hipEventSynchronize(ev_pin[pin_cur]));  // this buffer's previous upload
         char *h = h_pin[pin_cur];
@@ -1312,6 +1330,7 @@ enoao_status enoao_step_noalloc(const enoao_problem *prob, double *u, double dt,
     rt.h_hdr.n_inst = 1;
     rt.h_hdr.xtiles_total = xt;
     rt.h_hdr.units_total = ut;
+    rt.set_lists({I}, rt.h_hdr);
     rt.set_grids();
     Ctrl c;
     std::memset(&c, 0, sizeof(Ctrl));

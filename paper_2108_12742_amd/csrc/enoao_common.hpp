@@ -111,6 +111,13 @@ struct BatchHdr {
     int n_inst;
     int pad;
     long long xtiles_total, units_total;
+    unsigned lists[FIX_RANGES + 1];  // 2D: where each range's list starts, and the last one's end
 };
+
+// units per range of the lists (a launch has fewer than 2^32)
+constexpr unsigned fix_range_units(long long units)
+{
+    return units > FIX_RANGES ? ((unsigned)units + FIX_RANGES - 1) / FIX_RANGES : 1u;
+}
 
 }  // namespace enoao

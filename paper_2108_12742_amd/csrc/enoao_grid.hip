@@ -34,6 +34,7 @@
 // that side's rounding (1e-9 of the largest L at a pressure ratio of 1e5).  The bound
 // alone tells which form a face takes, also where every face is selected.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -89,44 +90,58 @@ struct GridView {
     double rx[3], ry[3];  // alpha of the fields u-c, u, u+c (component-wise: one for all)
 };
 
+// a value of a descriptor whose 8-byte words the lanes hold
+template <class T> __device__ __forceinline__ T inst_value(unsigned long long words, unsigned offset)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "a word or half of one");
+    const unsigned long long w = lane_bits(words, (int)offset / 8) >> (offset % 8 * 8);
+    union { unsigned long long w; T v; } a;
+    a.w = w;
+    return a.v;
+}
+#define INST_VALUE(name) inst_value<decltype(Inst::name)>(words, offsetof(Inst, name))
+
 template <int ORDER, bool CH>
 __device__ __forceinline__ GridView grid_view(const KParams &P, int n_inst, long long unit)
 {
     GridView v;
     // (a lone member's control block and maxima are kernel arguments, so their loads do
-    // not wait for the descriptor's)
+    // not wait for the descriptor's, which is read at once, a word a lane: value by value it
+    // took six loads one after the other)
     v.k = P.lone_ctrl ? 0 : uniform(find_last(n_inst, unit, [&](int i) { return P.inst[i].unit0; }));
-    const Inst &I = P.inst[v.k];
-    v.ctrl = gmem(P.lone_ctrl ? P.lone_ctrl : uniform(I.ctrl));
-    v.amax = gmem(P.lone_ctrl ? P.lone_amax : uniform(I.amax));
-    // one lane per value and copy of the stage input's maxima
     const int lane = threadIdx.x & 63;
+    static_assert(sizeof(Inst) % 8 == 0 && sizeof(Inst) <= 512, "a lane per word of a descriptor");
+    const unsigned long long words = gmem((const unsigned long long *)(P.inst + v.k))[min(lane, (int)sizeof(Inst) / 8 - 1)];
+    v.ctrl = gmem(P.lone_ctrl ? P.lone_ctrl : INST_VALUE(ctrl));
+    v.amax = gmem(P.lone_ctrl ? P.lone_amax : INST_VALUE(amax));
+    // one lane per value and copy of the stage input's maxima
     double am = as_double(v.amax[P.r_in * amax_slot_words(EULER2D) + lane]);
     const int done = v.ctrl->done;
     const double dt = v.ctrl->dt;
-    v.u0 = uniform(I.unit0);
-    v.u1 = v.u0 + uniform(I.units);
-    v.nx = uniform(I.nx);
-    v.ny = uniform(I.ny);
-    v.pitch = uniform(I.pitch);
-    v.bcx = uniform(I.bcx);
-    v.bcy = uniform(I.bcy);
-    v.strips = uniform(I.strips);
-    v.low = (unsigned)uniform(I.low_rows);
-    v.extra = (unsigned)uniform(I.extra_rows);
-    v.inv_strips = uniform(I.inv_strips);
+    v.u0 = INST_VALUE(unit0);
+    v.u1 = v.u0 + INST_VALUE(units);
+    v.nx = INST_VALUE(nx);
+    v.ny = INST_VALUE(ny);
+    v.pitch = INST_VALUE(pitch);
+    v.bcx = INST_VALUE(bcx);
+    v.bcy = INST_VALUE(bcy);
+    v.strips = INST_VALUE(strips);
+    v.low = (unsigned)INST_VALUE(low_rows);
+    v.extra = (unsigned)INST_VALUE(extra_rows);
+    v.inv_strips = INST_VALUE(inv_strips);
     v.active = uniform(done) == 0;
     v.dt = uniform(dt);
-    v.in = gmem(uniform(P.mode == M_S2 ? I.w1 : (P.mode == M_S3 ? I.w2 : I.u)));
-    v.out = gmem(uniform(P.mode == M_RHS ? I.lx : (P.mode == M_S1 ? I.w1 : (P.mode == M_S2 ? I.w2 : I.u))));
-    v.base = gmem(uniform(I.u));
-    v.sel = gmem(uniform(I.sel));
+    double *const u = INST_VALUE(u), *const w1 = INST_VALUE(w1), *const w2 = INST_VALUE(w2);
+    v.in = gmem(P.mode == M_S2 ? w1 : (P.mode == M_S3 ? w2 : u));
+    v.out = gmem(P.mode == M_RHS ? INST_VALUE(lx) : (P.mode == M_S1 ? w1 : (P.mode == M_S2 ? w2 : u)));
+    v.base = gmem(u);
+    v.sel = gmem(INST_VALUE(sel));
     if (v.sel && P.sel_slot > 0) {
         // records of one evaluation: x block [4][2][ny][nx+1], then the y block [4][2][ny+1][nx]
         v.sel += (long long)P.sel_slot * 8ll * ((long long)v.ny * (v.nx + 1) + (long long)(v.ny + 1) * v.nx);
     }
-    v.idx = uniform(1.0 / I.dx);
-    v.idy = uniform(1.0 / I.dy);
+    v.idx = uniform(1.0 / INST_VALUE(dx));
+    v.idy = uniform(1.0 / INST_VALUE(dy));
     am = copies_max(am);
     double ax[3], ay[3];
 #pragma unroll
@@ -656,7 +671,7 @@ __device__ __forceinline__ double field_alpha(const double (&r)[3], int s) { ret
 // maxima only what exceeds stage_2d's.  With that, and 430 VALU instructions a pass instead
 // of 570, before and now (us, same card): 1000 x 60, six steps, 611 and 512; order 7 on
 // 60 x 1200 829 and 756; 511 x 257, ten, 1060 and 897; 2048^2, eight, 4100 and 3940; a pool
-// of 16 4610 and 4095.
+// of 16 4610 and 4010.
 template <int ORDER, bool STEP, bool REC, bool CH>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves(ORDER)))) void fix_2d(KParams P)
 {
@@ -686,11 +701,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fix_waves
     // lane c: list c's pieces of two passes, lane FIX_RANGES + c: those of one; upto: the
     // entries up to them.  Entry i of all is at skew + i, counted back among those of one.
     static_assert(2 * FIX_RANGES == 64, "a lane per list and end");
-    const long long units = P.hdr->units_total;
     const bool two = lane < FIX_RANGES;
     const unsigned long long counted = gmem(P.fix_count)[lane % FIX_RANGES * FIX_COUNTER_STRIDE];
+    const unsigned long long empty = fix_empty(P, lane % FIX_RANGES);
     if (P.lone_ctrl) enter(0);  // (beside the counters' loads: 2 us of a short launch)
-    const unsigned long long empty = fix_empty(P, n_inst, units, lane % FIX_RANGES);
     if (P.fix_zero && blockIdx.x == gridDim.x - 1 && wv == 0 && two) gmem(P.fix_zero)[FIX_COUNTER_STRIDE * lane] = empty;
     const unsigned list_end = two ? (unsigned)empty : (unsigned)(empty >> 32);
     unsigned upto = two ? (unsigned)counted - list_end : list_end - (unsigned)(counted >> 32);

@@ -657,7 +657,7 @@ __global__ void reset_maxima(KParams P, int words)
         gmem(P.inst[k / words].amax)[k % words] = 0ull;
     if (P.fix_count && blockIdx.x == 0)
         for (int k = threadIdx.x; k < FIX_SETS * FIX_RANGES; k += blockDim.x)
-            gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = fix_empty(P, n, P.hdr->units_total, k % FIX_RANGES);
+            gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = fix_empty(P, k % FIX_RANGES);
 }
 
 // What precedes the maxima of a lone member's state, in one launch: the caller's
@@ -681,7 +681,7 @@ __global__ void begin_lone(KParams P, Inst *inst, const double *u, double *lx, C
     for (int k = t; k < words; k += blockDim.x) gmem(P.lone_amax)[k] = 0ull;
     if (P.fix_count)
         for (int k = t; k < FIX_SETS * FIX_RANGES; k += blockDim.x)
-            gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = fix_empty(P, 1, P.hdr->units_total, k % FIX_RANGES);
+            gmem(P.fix_count)[k * FIX_COUNTER_STRIDE] = fix_empty(P, k % FIX_RANGES);
 }
 
 // Time-step control of one instance: CFL (or fixed) step from the maxima m of

@@ -56,48 +56,10 @@ template <typename T> __device__ __forceinline__ T uniform(T x)
 __device__ __forceinline__ double as_double(unsigned long long b) { return __longlong_as_double((long long)b); }
 __device__ __forceinline__ unsigned long long as_bits(double d) { return (unsigned long long)__double_as_longlong(d); }
 
-// the member that holds a unit (2D), by each lane for itself
-__device__ __forceinline__ int find_inst(const Inst *inst, int n, long long unit)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (inst[mid].unit0 <= unit) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// units per range of the lists (a launch has fewer than 2^32)
-__device__ __forceinline__ unsigned fix_range_units(long long units)
-{
-    return max(1u, ((unsigned)units + FIX_RANGES - 1) / FIX_RANGES);
-}
-
-// first place of the list of a member's units from `unit` on (the end of the last: the
-// member's end): every strip row before it has its places
-__device__ __forceinline__ unsigned fix_list_start(const Inst &I, long long unit)
-{
-    const unsigned lu = (unsigned)(unit - I.unit0), b = lu / (unsigned)I.strips, s = lu - b * (unsigned)I.strips;
-    const unsigned low = (unsigned)I.low_rows, extra = (unsigned)I.extra_rows;
-    const unsigned y0 = b * low + min(b, extra), rows = low + (b < extra ? 1u : 0u);
-    return (unsigned)(I.list0 + fix_places(I.nx) * ((long long)I.strips * y0 + (long long)s * rows));
-}
-
 // a range's counter while its list is empty: the list's start and end
-__device__ __forceinline__ unsigned long long fix_empty(const KParams &P, int n_inst, long long units, unsigned range)
+__device__ __forceinline__ unsigned long long fix_empty(const KParams &P, unsigned range)
 {
-    const unsigned per = fix_range_units(units);
-    const long long u0 = min(units, (long long)range * per), u1 = min(units, (long long)(range + 1) * per);
-    unsigned from, to;
-    if (P.lone_ctrl) {
-        from = fix_list_start(P.inst[0], u0);
-        to = fix_list_start(P.inst[0], u1);
-    } else {
-        from = fix_list_start(P.inst[find_inst(P.inst, n_inst, u0)], u0);
-        to = fix_list_start(P.inst[find_inst(P.inst, n_inst, u1)], u1);
-    }
-    return (unsigned long long)to << 32 | from;
+    return (unsigned long long)P.hdr->lists[range + 1] << 32 | P.hdr->lists[range];
 }
 
 // value of the neighbouring lane (lane 0 / 63 keep their own)
